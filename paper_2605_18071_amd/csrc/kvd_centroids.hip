@@ -27,42 +27,119 @@ __device__ __forceinline__ double widen_kv(uint16_t raw) {
   return (double)(BF16 ? as_f32((u32)raw << 16) : (float)__builtin_bit_cast(_Float16, raw));
 }
 
+// What the assignment screens with, per 16 centroids: [2 parts][4 chunks of 32 dims][64 lanes][8 elements], lane i + 16 g of
+// chunk c holding dims 32c + 8g .. +7 of centroid i, which is the A operand of a 16x16x32 MFMA as a wave loads it (1 KiB
+// contiguous per chunk).  Part 0 is the centroid rounded to the KV dtype, part 1 the rest rounded once more.
+constexpr int kScreenTile = 2 * 4 * kWave * 8;            // elements
+struct ScreenArgs {
+  uint16_t* frag;       // [U][tiles][kScreenTile]
+  float* neg_half;      // [U][16 * tiles] minus half the squared norm; minus infinity beyond the last centroid
+  int tiles;            // ceil(Nc / 16)
+};
+
+// One wave, centroid c of unit u, lane l holding dims 2l and 2l + 1.
+template <bool BF16>
+__device__ __forceinline__ void store_screen(const ScreenArgs& sa, int u, int c, double x0, double x1) {
+  const int lane = threadIdx.x & (kWave - 1);
+  const u32 h0 = f64_to_kv<BF16>(x0), h1 = f64_to_kv<BF16>(x1);
+  const u32 l0 = f64_to_kv<BF16>(x0 - widen_kv<BF16>((uint16_t)h0)), l1 = f64_to_kv<BF16>(x1 - widen_kv<BF16>((uint16_t)h1));
+  const int d = 2 * lane, at = ((d >> 5) * kWave + ((d & 31) >> 3) * 16 + (c & 15)) * 8 + (d & 7);
+  uint16_t* tile = sa.frag + ((size_t)u * sa.tiles + (c >> 4)) * kScreenTile;
+  *reinterpret_cast<u32*>(tile + at) = h0 | (h1 << 16);
+  *reinterpret_cast<u32*>(tile + kScreenTile / 2 + at) = l0 | (l1 << 16);
+  double n = x0 * x0 + x1 * x1;
+#pragma unroll
+  for (int m = 32; m >= 1; m >>= 1) n += __shfl_xor(n, m, kWave);
+  if (lane == 0) sa.neg_half[(size_t)u * sa.tiles * 16 + c] = (float)(-0.5 * n);
+}
+
+constexpr int kCentroidWaves = 4;     // centroids per block of the kernels that write them
+
 // cent64 [U][Nc][D] <- summaries of the pages floor((c + 1/2) * n_valid / Nc)
 template <bool BF16>
-__global__ __launch_bounds__(kHeadDim) void kmeans_init_kernel(const uint16_t* __restrict__ summ, double* __restrict__ cent64,
-                                                              const int32_t* __restrict__ seq_len, int NP, int Nc, int P,
-                                                              int Hkv) {
-  const int c = blockIdx.x, u = blockIdx.y, d = threadIdx.x;
+__global__ __launch_bounds__(kCentroidWaves* kWave) void kmeans_init_kernel(const uint16_t* __restrict__ summ,
+                                                                           double* __restrict__ cent64, ScreenArgs sa,
+                                                                           const int32_t* __restrict__ seq_len, int NP, int Nc,
+                                                                           int P, int Hkv) {
+  const int c = blockIdx.x * kCentroidWaves + threadIdx.x / kWave, u = blockIdx.y, lane = threadIdx.x & (kWave - 1);
+  if (c >= sa.tiles * 16) return;
+  if (c >= Nc) {                                            // the last tile's empty places
+    if (lane == 0) sa.neg_half[(size_t)u * sa.tiles * 16 + c] = -INFINITY;
+    uint16_t* tile = sa.frag + ((size_t)u * sa.tiles + (c >> 4)) * kScreenTile;
+    for (int k = lane; k < kScreenTile / 16; k += kWave) tile[((k >> 3) * 16 + (c & 15)) * 8 + (k & 7)] = 0;
+    return;
+  }
   int n_valid = (seq_len[u / Hkv] + P - 1) / P;
   n_valid = n_valid < NP ? n_valid : NP;
   const int page = (int)(((double)c + 0.5) * (double)n_valid / (double)Nc);
-  cent64[((size_t)u * Nc + c) * kHeadDim + d] = widen_kv<BF16>(summ[((size_t)u * NP + page) * kHeadDim + d]);
+  const u32 raw = *reinterpret_cast<const u32*>(summ + ((size_t)u * NP + page) * kHeadDim + 2 * lane);
+  const double x0 = widen_kv<BF16>((uint16_t)raw), x1 = widen_kv<BF16>((uint16_t)(raw >> 16));
+  *reinterpret_cast<double2*>(cent64 + ((size_t)u * Nc + c) * kHeadDim + 2 * lane) = make_double2(x0, x1);
+  store_screen<BF16>(sa, u, c, x0, x1);
 }
 
-constexpr int kAssignThreads = 256;
-constexpr int kAssignPoints = 16;     // points per block
+// Nearest centroid of every page, exactly as the definition has it: squared distance summed in
+// fp64 in dim order, ties to the lower centroid.  Computing all of them in fp64 is bound by the
+// fp64 rate (8 units of 8192 pages against 4096 centroids: 4.4 ms a round); so
+// the distances are first bounded on the matrix cores, where a round is 137 GFLOP of 16-bit MFMA:
+//   v = x . (c_hi + c_lo) - |c|^2 / 2        (the larger, the nearer)
+// in fp32, each within E of its true value, E = 2^-14 (|x| C + C^2 / 2) + 2^-20 |x| with C the unit's
+// largest centroid norm.  That covers the part of c that two 16-bit parts leave out (2^-18 |x| |c| for
+// bf16; for fp16 2^-24, or 2^-25 per dim among its subnormals), and 256 fp32 roundings of sums no
+// larger than |x| |c| + |c|^2 / 2 (2^-16 of that).  The nearest centroid is among those whose v is
+// within 2 E of the largest: one of them, as a rule, and then it is the answer; several are compared
+// in fp64, in the definition's order of operations; more than kAssignCap (exact ties, or data whose
+// differences the screening cannot see) and the page is compared with every centroid in fp64.
+//
+// Block (x, u): points 256x .. 256x+255 of unit u.  Wave w takes 64 of them (B operands kept in
+// registers) and one half of the centroid tiles, which the block stages through LDS, double
+// buffered: each tile is read once per 256 points and feeds 32 MFMAs per wave.  The tiles are gone
+// through twice, for the largest v of every point and then for the candidates: recomputing v is
+// cheaper than keeping sorted lists, whose length depends on the order of the centroids.
+constexpr int kAssignThreads = 512;
+constexpr int kAssignBlock = 256;     // points per block
+constexpr int kAssignCap = 8;         // candidates per point that are compared one by one
+constexpr int kAssignPoints = 16;     // points at a time that are compared with every centroid
 
-// Block (x, u): points 16x .. 16x+15 of unit u against all centroids.  The points sit in LDS as
-// fp64; thread t takes centroids t, t + 256, ... and keeps, for each of the 16 points, the best
-// (distance, centroid) it has seen; the threads' bests are then reduced per point.
+typedef float f32x4_c __attribute__((ext_vector_type(4)));
 template <bool BF16>
-__global__ __launch_bounds__(kAssignThreads) void kmeans_assign_kernel(const uint16_t* __restrict__ summ,
-                                                                      const double* __restrict__ cent64,
-                                                                      int32_t* __restrict__ assign,   // [U][NP]
-                                                                      const int32_t* __restrict__ seq_len, int NP, int Nc,
-                                                                      int P, int Hkv) {
-  __shared__ double pts[kAssignPoints][kHeadDim];
-  __shared__ double best_d[kAssignPoints][kAssignThreads / kWave];
-  __shared__ int best_c[kAssignPoints][kAssignThreads / kWave];
-  const int u = blockIdx.y, tid = threadIdx.x, lane = tid & (kWave - 1), w = tid / kWave;
-  int n_valid = (seq_len[u / Hkv] + P - 1) / P;
-  n_valid = n_valid < NP ? n_valid : NP;
-  const int p0 = blockIdx.x * kAssignPoints;
-  if (p0 >= n_valid) return;
+__device__ __forceinline__ f32x4_c mfma_16x16x32(const uint4& a, const uint4& b, f32x4_c c) {
+  if (BF16) {
+    typedef __bf16 v8 __attribute__((ext_vector_type(8)));
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8, a), __builtin_bit_cast(v8, b), c, 0, 0, 0);
+  } else {
+    typedef _Float16 v8 __attribute__((ext_vector_type(8)));
+    return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(v8, a), __builtin_bit_cast(v8, b), c, 0, 0, 0);
+  }
+}
+
+struct AssignSmem {
+  union {
+    uint4 tile[2][2][kScreenTile / 8];                      // [buffer][half of the centroids]
+    struct {
+      double pts[kAssignPoints][kHeadDim];
+      double best_d[kAssignPoints][kAssignThreads / kWave];
+      int best_c[kAssignPoints][kAssignThreads / kWave];
+    } all;
+  } a;
+  float best[2][kAssignBlock];                              // largest v of a point in each half
+  float norm[kAssignThreads / kWave];
+  int n_cand[kAssignBlock];
+  uint16_t cand[kAssignBlock][kAssignCap];
+  int hard[kAssignBlock];                                   // points to compare with every centroid
+  int n_hard;
+};
+
+// Points sm.hard[first ..] (at most kAssignPoints of them) against all centroids in fp64.
+template <bool BF16>
+__device__ __forceinline__ void assign_exhaustive(AssignSmem& sm, int first, const uint16_t* __restrict__ summ_u,
+                                                  const double* __restrict__ cent_u, int32_t* __restrict__ assign_u, int p0, int Nc) {
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), w = tid / kWave;
+  const int n = sm.n_hard - first < kAssignPoints ? sm.n_hard - first : kAssignPoints;
+  __syncthreads();                                          // (the staging area is free, the batch before this one is done)
   for (int i = tid; i < kAssignPoints * kHeadDim; i += kAssignThreads) {
     const int pi = i / kHeadDim, d = i % kHeadDim;
-    const int page = (p0 + pi) < n_valid ? (p0 + pi) : (n_valid - 1);
-    pts[pi][d] = widen_kv<BF16>(summ[((size_t)u * NP + page) * kHeadDim + d]);
+    sm.a.all.pts[pi][d] = pi < n ? widen_kv<BF16>(summ_u[(size_t)(p0 + sm.hard[first + pi]) * kHeadDim + d]) : 0.0;
   }
   __syncthreads();
   double bd[kAssignPoints];
@@ -70,7 +147,7 @@ __global__ __launch_bounds__(kAssignThreads) void kmeans_assign_kernel(const uin
 #pragma unroll
   for (int i = 0; i < kAssignPoints; ++i) { bd[i] = INFINITY; bc[i] = 0x7fffffff; }
   for (int c = tid; c < Nc; c += kAssignThreads) {
-    const double* crow = cent64 + ((size_t)u * Nc + c) * kHeadDim;
+    const double* crow = cent_u + (size_t)c * kHeadDim;
     double acc[kAssignPoints];
 #pragma unroll
     for (int i = 0; i < kAssignPoints; ++i) acc[i] = 0.0;
@@ -78,14 +155,14 @@ __global__ __launch_bounds__(kAssignThreads) void kmeans_assign_kernel(const uin
       const double2 cv = *reinterpret_cast<const double2*>(crow + d);
 #pragma unroll
       for (int i = 0; i < kAssignPoints; ++i) {
-        const double e0 = pts[i][d] - cv.x, e1 = pts[i][d + 1] - cv.y;
+        const double e0 = sm.a.all.pts[i][d] - cv.x, e1 = sm.a.all.pts[i][d + 1] - cv.y;
         acc[i] = fma(e0, e0, acc[i]);
         acc[i] = fma(e1, e1, acc[i]);
       }
     }
 #pragma unroll
     for (int i = 0; i < kAssignPoints; ++i)
-      if (acc[i] < bd[i]) { bd[i] = acc[i]; bc[i] = c; }       // centroids come in ascending order per thread
+      if (acc[i] < bd[i]) { bd[i] = acc[i]; bc[i] = c; }    // centroids come in ascending order per thread
   }
   // smallest (distance, centroid) per point over the block
 #pragma unroll
@@ -98,90 +175,274 @@ __global__ __launch_bounds__(kAssignThreads) void kmeans_assign_kernel(const uin
       const int oc = __shfl_xor(c, m, kWave);
       if (od < d || (od == d && oc < c)) { d = od; c = oc; }
     }
-    if (lane == 0) { best_d[i][w] = d; best_c[i][w] = c; }
+    if (lane == 0) { sm.a.all.best_d[i][w] = d; sm.a.all.best_c[i][w] = c; }
   }
   __syncthreads();
-  if (tid < kAssignPoints && p0 + tid < n_valid) {
-    double d = best_d[tid][0];
-    int c = best_c[tid][0];
+  if (tid < n) {
+    double d = sm.a.all.best_d[tid][0];
+    int c = sm.a.all.best_c[tid][0];
     for (int j = 1; j < kAssignThreads / kWave; ++j) {
-      const double od = best_d[tid][j];
-      const int oc = best_c[tid][j];
+      const double od = sm.a.all.best_d[tid][j];
+      const int oc = sm.a.all.best_c[tid][j];
       if (od < d || (od == d && oc < c)) { d = od; c = oc; }
     }
-    assign[(size_t)u * NP + p0 + tid] = c;
+    assign_u[p0 + sm.hard[first + tid]] = c < Nc ? c : 0;   // (no distance is a number: any cluster, within bounds)
   }
+}
+
+template <bool BF16>
+__global__ __launch_bounds__(kAssignThreads, 2) void kmeans_assign_kernel(const uint16_t* __restrict__ summ,
+                                                                         const double* __restrict__ cent64, ScreenArgs sa,
+                                                                         int32_t* __restrict__ assign,   // [U][NP]
+                                                                         const int32_t* __restrict__ seq_len, int NP, int Nc,
+                                                                         int P, int Hkv) {
+  __shared__ AssignSmem sm;
+  const int u = blockIdx.y, tid = threadIdx.x, lane = tid & (kWave - 1), w = tid / kWave;
+  int n_valid = (seq_len[u / Hkv] + P - 1) / P;
+  n_valid = n_valid < NP ? n_valid : NP;
+  const int p0 = blockIdx.x * kAssignBlock;
+  if (p0 >= n_valid) return;
+  const uint16_t* summ_u = summ + (size_t)u * NP * kHeadDim;
+  const double* cent_u = cent64 + (size_t)u * Nc * kHeadDim;
+  int32_t* assign_u = assign + (size_t)u * NP;
+  const float* neg_u = sa.neg_half + (size_t)u * sa.tiles * 16;
+  const int half = w >> 2, pw = (w & 3) * 64, j = lane & 15, g = lane >> 4;
+
+  // B operands: lane (j, g) of group q holds dims 32c + 8g .. +7 of point pw + 16 q + j
+  uint4 x[4][4];
+  float slack[4];                                           // 2 E of the point
+  {
+    float cmax2 = 0.f;                                      // largest squared norm of the unit's centroids
+    for (int c = tid; c < Nc; c += kAssignThreads) cmax2 = fmaxf(cmax2, -2.f * neg_u[c]);
+    cmax2 = wave_allreduce_max(cmax2);
+    if (lane == 0) sm.norm[w] = cmax2;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kAssignThreads / kWave; ++i) cmax2 = fmaxf(cmax2, sm.norm[i]);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int p = p0 + pw + 16 * q + j;
+      const uint16_t* row = summ_u + (size_t)(p < n_valid ? p : n_valid - 1) * kHeadDim + 8 * g;
+      float n = 0.f;
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        x[q][c] = *reinterpret_cast<const uint4*>(row + 32 * c);
+        float f[8];
+        cvt8<BF16>(x[q][c], f);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) n = fmaf(f[e], f[e], n);
+      }
+      n += __shfl_xor(n, 16, kWave);
+      n += __shfl_xor(n, 32, kWave);
+      // (2^-14 instead of the 2^-15.5 that the terms above add up to leaves room for the roundings of E itself)
+      const float xn = sqrtf(n);
+      slack[q] = 2.f * (6.103515625e-5f * (xn * sqrtf(cmax2) + 0.5f * cmax2) + 9.5367431640625e-7f * xn);
+    }
+  }
+  for (int i = tid; i < kAssignBlock; i += kAssignThreads) sm.n_cand[i] = 0;
+  if (tid == 0) sm.n_hard = 0;
+
+  // iteration i stages tile i of the lower half and tile n_half + i of the upper half (the last tile
+  // again where the halves are uneven: the waves of that half then skip it)
+  const int n_half = (sa.tiles + 1) / 2;
+  const uint4* frag_u = reinterpret_cast<const uint4*>(sa.frag) + (size_t)u * sa.tiles * (kScreenTile / 8);
+  uint4 lower, upper;
+  auto fetch = [&](int i) {
+    const int t = n_half + i < sa.tiles ? n_half + i : sa.tiles - 1;
+    lower = frag_u[(size_t)i * (kScreenTile / 8) + tid];
+    upper = frag_u[(size_t)t * (kScreenTile / 8) + tid];
+  };
+  static_assert(kScreenTile / 8 == kAssignThreads, "one 16-byte unit of a tile per thread");
+  // f(t, v): v[q] = the values of rows 4g .. 4g+3 of tile t for this lane's point of group q
+  auto sweep = [&](auto f) {
+    fetch(0);
+    for (int i = 0; i < n_half; ++i) {
+      sm.a.tile[i & 1][0][tid] = lower;
+      sm.a.tile[i & 1][1][tid] = upper;
+      if (i + 1 < n_half) fetch(i + 1);
+      __syncthreads();                                      // (buffer i & 1 is written again two iterations on, after the next barrier)
+      const int t = half * n_half + i;
+      if (t < sa.tiles) {
+        const float4 nh = *reinterpret_cast<const float4*>(neg_u + t * 16 + 4 * g);
+        f32x4_c v[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) v[q] = f32x4_c{nh.x, nh.y, nh.z, nh.w};
+#pragma unroll
+        for (int part = 0; part < 2; ++part)
+#pragma unroll
+          for (int c = 0; c < 4; ++c) {
+            const uint4 a = sm.a.tile[i & 1][half][(part * 4 + c) * kWave + lane];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) v[q] = mfma_16x16x32<BF16>(a, x[q][c], v[q]);
+          }
+        f(t, v);
+      }
+    }
+    __syncthreads();
+  };
+
+  float top[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) top[q] = -INFINITY;
+  sweep([&](int, const f32x4_c (&v)[4]) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) top[q] = fmaxf(fmaxf(top[q], fmaxf(v[q][0], v[q][1])), fmaxf(v[q][2], v[q][3]));
+  });
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    top[q] = fmaxf(top[q], __shfl_xor(top[q], 16, kWave));
+    top[q] = fmaxf(top[q], __shfl_xor(top[q], 32, kWave));
+    if (g == 0) sm.best[half][pw + 16 * q + j] = top[q];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < 4; ++q) top[q] = fmaxf(top[q], sm.best[half ^ 1][pw + 16 * q + j]) - slack[q];
+  sweep([&](int t, const f32x4_c (&v)[4]) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      if (!(fmaxf(fmaxf(v[q][0], v[q][1]), fmaxf(v[q][2], v[q][3])) >= top[q])) continue;
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (v[q][e] >= top[q] && t * 16 + 4 * g + e < Nc) {
+          const int at = atomicAdd(&sm.n_cand[pw + 16 * q + j], 1);
+          if (at < kAssignCap) sm.cand[pw + 16 * q + j][at] = (uint16_t)(t * 16 + 4 * g + e);
+        }
+    }
+  });
+
+  if (tid < kAssignBlock && p0 + tid < n_valid) {
+    const int n = sm.n_cand[tid];
+    if (n < 1 || n > kAssignCap) {
+      sm.hard[atomicAdd(&sm.n_hard, 1)] = tid;
+    } else {
+      int bc = sm.cand[tid][0];
+      if (n > 1) {
+        const uint16_t* row = summ_u + (size_t)(p0 + tid) * kHeadDim;
+        double bd = INFINITY;
+        bc = 0x7fffffff;
+        for (int k = 0; k < n; ++k) {
+          const int c = sm.cand[tid][k];
+          const double* crow = cent_u + (size_t)c * kHeadDim;
+          double acc = 0.0;
+          for (int d = 0; d < kHeadDim; d += 2) {
+            const u32 raw = *reinterpret_cast<const u32*>(row + d);
+            const double2 cv = *reinterpret_cast<const double2*>(crow + d);
+            const double e0 = widen_kv<BF16>((uint16_t)raw) - cv.x, e1 = widen_kv<BF16>((uint16_t)(raw >> 16)) - cv.y;
+            acc = fma(e0, e0, acc);
+            acc = fma(e1, e1, acc);
+          }
+          if (acc < bd || (acc == bd && c < bc)) { bd = acc; bc = c; }
+        }
+      }
+      assign_u[p0 + tid] = bc < Nc ? bc : 0;
+    }
+  }
+  __syncthreads();
+  for (int first = 0; first < sm.n_hard; first += kAssignPoints)
+    assign_exhaustive<BF16>(sm, first, summ_u, cent_u, assign_u, p0, Nc);
 }
 
 constexpr int kCsrThreads = 1024;
 
+constexpr int kRankMost = 128;        // members of a cluster up to which each finds its own place among them
+
 // One block per unit: cluster_start [Nc+1] and cluster_pages [NP] (pages of every cluster in
-// ascending order) from assign.
+// ascending order) from assign; page_cluster [NP], if given, receives the assignment too.  Latency-bound
+// and alone on its CU, so everything happens in LDS: the counts, their scan, the members in arrival
+// order, and each page's place = the number of smaller pages among its cluster's members.  The reads
+// for that grow with the square of a cluster's size, so a cluster of more than kRankMost pages is
+// gone through by one wave instead, in page order.
 __global__ __launch_bounds__(kCsrThreads) void kmeans_csr_kernel(const int32_t* __restrict__ assign,
                                                                 int32_t* __restrict__ cluster_start,   // [U][Nc+1]
                                                                 int32_t* __restrict__ cluster_pages,   // [U][NP]
-                                                                int32_t* __restrict__ cursor,          // [U][Nc] scratch
+                                                                int32_t* __restrict__ page_cluster,    // [U][NP] or null
                                                                 const int32_t* __restrict__ seq_len, int NP, int Nc,
                                                                 int P, int Hkv) {
+  __shared__ uint16_t as[KVD_FAST_MAX_PAGES], members[KVD_FAST_MAX_PAGES];
+  __shared__ int cur[KVD_MAX_CENTROIDS];                    // counts; then the next place of a cluster; in the end its end
   __shared__ int scan_smem[kCsrThreads / kWave + 1];
-  __shared__ int carry;
+  __shared__ int large[KVD_FAST_MAX_PAGES / kRankMost], n_large;
   const int u = blockIdx.x, tid = threadIdx.x;
   int n_valid = (seq_len[u / Hkv] + P - 1) / P;
   n_valid = n_valid < NP ? n_valid : NP;
-  const int32_t* as = assign + (size_t)u * NP;
+  const int32_t* as_u = assign + (size_t)u * NP;
   int32_t* start = cluster_start + (size_t)u * (Nc + 1);
   int32_t* pages = cluster_pages + (size_t)u * NP;
-  int32_t* cur = cursor + (size_t)u * Nc;
+  int32_t* pc = page_cluster != nullptr ? page_cluster + (size_t)u * NP : nullptr;
   for (int c = tid; c < Nc; c += kCsrThreads) cur[c] = 0;
-  for (int p = n_valid + tid; p < NP; p += kCsrThreads) pages[p] = -1;
-  if (tid == 0) carry = 0;
+  if (tid == 0) n_large = 0;
   __syncthreads();
-  for (int p = tid; p < n_valid; p += kCsrThreads) atomicAdd(&cur[as[p]], 1);
+  for (int p = tid; p < NP; p += kCsrThreads) {
+    const int c = p < n_valid ? as_u[p] : -1;
+    if (pc != nullptr) pc[p] = c;
+    if (c < 0) { pages[p] = -1; continue; }
+    as[p] = (uint16_t)c;
+    atomicAdd(&cur[c], 1);
+  }
   __syncthreads();
   // exclusive scan of the counts, 1024 clusters at a time
+  int base = 0;
   for (int c0 = 0; c0 < Nc; c0 += kCsrThreads) {
-    const int c = c0 + tid;
-    const int cnt = c < Nc ? cur[c] : 0;
+    const int c = c0 + tid, cnt = c < Nc ? cur[c] : 0;
     int total;
-    const int ex = block_exclusive_scan<kCsrThreads>(cnt, scan_smem, total);
-    const int base = carry;
-    if (c < Nc) start[c] = base + ex;
-    __syncthreads();
-    if (tid == 0) carry = base + total;
-    __syncthreads();
+    const int at = base + block_exclusive_scan<kCsrThreads>(cnt, scan_smem, total);
+    base += total;
+    if (c < Nc) {
+      start[c] = at;
+      cur[c] = at;
+      if (cnt > kRankMost) large[atomicAdd(&n_large, 1)] = c;
+    }
   }
-  if (tid == 0) start[Nc] = carry;
-  for (int c = tid; c < Nc; c += kCsrThreads) cur[c] = 0;
+  if (tid == 0) start[Nc] = base;
+  __syncthreads();
+  for (int p = tid; p < n_valid; p += kCsrThreads) members[atomicAdd(&cur[as[p]], 1)] = (uint16_t)p;
   __syncthreads();
   for (int p = tid; p < n_valid; p += kCsrThreads) {
-    const int c = as[p];
-    pages[start[c] + atomicAdd(&cur[c], 1)] = p;
+    const int c = as[p], b = c > 0 ? cur[c - 1] : 0, e = cur[c];
+    if (e - b > kRankMost) continue;
+    int before = 0;
+    for (int i = b; i < e; ++i) before += members[i] < p ? 1 : 0;
+    pages[b + before] = p;
   }
-  __syncthreads();
-  // every cluster's list in ascending page order (lists are short: insertion sort by one thread)
-  for (int c = tid; c < Nc; c += kCsrThreads) {
-    const int b = start[c], e = start[c + 1];
-    for (int i = b + 1; i < e; ++i) {
-      const int v = pages[i];
-      int j = i - 1;
-      while (j >= b && pages[j] > v) { pages[j + 1] = pages[j]; --j; }
-      pages[j + 1] = v;
+  const int lane = tid & (kWave - 1);
+  for (int i = tid / kWave; i < n_large; i += kCsrThreads / kWave) {
+    const int c = large[i];
+    int at = c > 0 ? cur[c - 1] : 0;
+    for (int p0 = 0; p0 < n_valid; p0 += kWave) {
+      const int p = p0 + lane;
+      const u64 mine = __ballot(p < n_valid && as[p] == c);
+      if ((mine >> lane) & 1ull) pages[at + __popcll(mine & ((1ull << lane) - 1ull))] = p;
+      at += __popcll(mine);
     }
   }
 }
 
-// Block (c, u), thread d: new centroid = mean of the members' summaries in ascending page order.
+// One wave per centroid, two dims per lane: new centroid = mean of the members' summaries in ascending page order.
 template <bool BF16>
-__global__ __launch_bounds__(kHeadDim) void kmeans_update_kernel(const uint16_t* __restrict__ summ, double* __restrict__ cent64,
-                                                                const int32_t* __restrict__ cluster_start,
-                                                                const int32_t* __restrict__ cluster_pages, int NP, int Nc) {
-  const int c = blockIdx.x, u = blockIdx.y, d = threadIdx.x;
+__global__ __launch_bounds__(kCentroidWaves* kWave) void kmeans_update_kernel(const uint16_t* __restrict__ summ,
+                                                                             double* __restrict__ cent64, ScreenArgs sa,
+                                                                             const int32_t* __restrict__ cluster_start,
+                                                                             const int32_t* __restrict__ cluster_pages, int NP,
+                                                                             int Nc) {
+  const int c = blockIdx.x * kCentroidWaves + threadIdx.x / kWave, u = blockIdx.y, lane = threadIdx.x & (kWave - 1);
+  if (c >= Nc) return;
   const int b = cluster_start[(size_t)u * (Nc + 1) + c], e = cluster_start[(size_t)u * (Nc + 1) + c + 1];
-  if (e == b) return;                                       // an empty cluster keeps its centroid
-  const int32_t* pages = cluster_pages + (size_t)u * NP;
-  double acc = 0.0;
-  for (int i = b; i < e; ++i) acc += widen_kv<BF16>(summ[((size_t)u * NP + pages[i]) * kHeadDim + d]);
-  cent64[((size_t)u * Nc + c) * kHeadDim + d] = acc / (double)(e - b);
+  double2* cent = reinterpret_cast<double2*>(cent64 + ((size_t)u * Nc + c) * kHeadDim) + lane;
+  double2 x;
+  if (e == b) {
+    x = *cent;                                              // an empty cluster keeps its centroid
+  } else {
+    const int32_t* pages = cluster_pages + (size_t)u * NP;
+    double a0 = 0.0, a1 = 0.0;
+    for (int i = b; i < e; ++i) {
+      const u32 raw = *reinterpret_cast<const u32*>(summ + ((size_t)u * NP + pages[i]) * kHeadDim + 2 * lane);
+      a0 += widen_kv<BF16>((uint16_t)raw);
+      a1 += widen_kv<BF16>((uint16_t)(raw >> 16));
+    }
+    x = make_double2(a0 / (double)(e - b), a1 / (double)(e - b));
+    *cent = x;
+  }
+  store_screen<BF16>(sa, u, c, x.x, x.y);
 }
 
 template <bool BF16>
@@ -267,39 +528,45 @@ hipError_t kvd_run_build_centroids(kvd_ctx* c, int layer, int iterations, int32_
   uint16_t* cent = reinterpret_cast<uint16_t*>(c->centroids) + lu * c->Nc * kHeadDim;
   int32_t* cstart = c->cluster_start + lu * (c->Nc + 1);
   int32_t* cpages = c->cluster_pages + lu * c->NP;
-  double* cent64 = nullptr;
-  int32_t* assign = nullptr;
-  int32_t* cursor = nullptr;
-  hipError_t e = hipMalloc(reinterpret_cast<void**>(&cent64), (size_t)c->U * c->Nc * kHeadDim * sizeof(double));
-  if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void**>(&assign), (size_t)c->U * c->NP * sizeof(int32_t));
-  if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void**>(&cursor), (size_t)c->U * c->Nc * sizeof(int32_t));
+  ScreenArgs sa;
+  sa.tiles = (c->Nc + 15) / 16;
+  // one temporary block: fp64 centroids, screening tiles, half norms, assignment
+  const size_t n_cent = (size_t)c->U * c->Nc, n_tiles = (size_t)c->U * sa.tiles, n_points = (size_t)c->U * c->NP;
+  size_t at = 0;
+  auto place = [&](size_t bytes) { const size_t o = at; at += (bytes + 255) & ~(size_t)255; return o; };
+  const size_t o_cent = place(n_cent * kHeadDim * sizeof(double)), o_frag = place(n_tiles * kScreenTile * 2),
+               o_neg = place(n_tiles * 16 * sizeof(float)), o_assign = place(n_points * sizeof(int32_t));
+  char* temp = nullptr;
+  hipError_t e = hipMalloc(reinterpret_cast<void**>(&temp), at);
   if (e == hipSuccess) {
-    const dim3 per_centroid(c->Nc, c->U), per_points((c->NP + kAssignPoints - 1) / kAssignPoints, c->U);
+    double* cent64 = reinterpret_cast<double*>(temp + o_cent);
+    int32_t* assign = reinterpret_cast<int32_t*>(temp + o_assign);
+    sa.frag = reinterpret_cast<uint16_t*>(temp + o_frag);
+    sa.neg_half = reinterpret_cast<float*>(temp + o_neg);
+    const dim3 per_centroid(c->Nc, c->U), per_tile_row((sa.tiles * 16 + kCentroidWaves - 1) / kCentroidWaves, c->U);
+    const dim3 per_points((c->NP + kAssignBlock - 1) / kAssignBlock, c->U), centroid_block(kCentroidWaves * kWave);
 #define KVD_DT(KERNEL, ...)                                                    \
   do {                                                                         \
     if (c->bf16) hipLaunchKernelGGL((KERNEL<true>), __VA_ARGS__);              \
     else hipLaunchKernelGGL((KERNEL<false>), __VA_ARGS__);                     \
   } while (0)
-    KVD_DT(kmeans_init_kernel, per_centroid, dim3(kHeadDim), 0, s, summ, cent64, c->d_seq_len, c->NP, c->Nc, c->P, c->Hkv);
+    KVD_DT(kmeans_init_kernel, per_tile_row, centroid_block, 0, s, summ, cent64, sa, c->d_seq_len, c->NP, c->Nc, c->P, c->Hkv);
     for (int it = 0; it < iterations && e == hipSuccess; ++it) {
-      KVD_DT(kmeans_assign_kernel, per_points, dim3(kAssignThreads), 0, s, summ, cent64, assign, c->d_seq_len, c->NP, c->Nc,
+      KVD_DT(kmeans_assign_kernel, per_points, dim3(kAssignThreads), 0, s, summ, cent64, sa, assign, c->d_seq_len, c->NP, c->Nc,
              c->P, c->Hkv);
       if (assign_trace != nullptr)
         e = hipMemcpyAsync(assign_trace + (size_t)it * c->U * c->NP, assign, (size_t)c->U * c->NP * sizeof(int32_t),
                            hipMemcpyDeviceToDevice, s);
-      hipLaunchKernelGGL(kmeans_csr_kernel, dim3(c->U), dim3(kCsrThreads), 0, s, assign, cstart, cpages, cursor, c->d_seq_len,
-                         c->NP, c->Nc, c->P, c->Hkv);
-      KVD_DT(kmeans_update_kernel, per_centroid, dim3(kHeadDim), 0, s, summ, cent64, cstart, cpages, c->NP, c->Nc);
+      hipLaunchKernelGGL(kmeans_csr_kernel, dim3(c->U), dim3(kCsrThreads), 0, s, assign, cstart, cpages,
+                         it + 1 == iterations ? c->d_page_cluster + lu * c->NP : nullptr, c->d_seq_len, c->NP, c->Nc, c->P, c->Hkv);
+      KVD_DT(kmeans_update_kernel, per_tile_row, centroid_block, 0, s, summ, cent64, sa, cstart, cpages, c->NP, c->Nc);
     }
     KVD_DT(kmeans_store_kernel, per_centroid, dim3(kHeadDim), 0, s, cent64, cent, c->Nc);
 #undef KVD_DT
     if (e == hipSuccess) e = hipGetLastError();
-    if (e == hipSuccess) e = kvd_launch_cluster_inverse(c, layer, s);   // the page -> cluster table of the new lists
     const hipError_t e2 = hipStreamSynchronize(s);
     if (e == hipSuccess) e = e2;
   }
-  if (cent64) (void)hipFree(cent64);
-  if (assign) (void)hipFree(assign);
-  if (cursor) (void)hipFree(cursor);
+  if (temp) (void)hipFree(temp);
   return e;
 }
