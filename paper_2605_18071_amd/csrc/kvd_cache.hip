@@ -225,10 +225,8 @@ __device__ __forceinline__ void copy_page(const char* __restrict__ src, char* __
                                           unsigned page_bytes, uint16_t* vt) {
   const int tid = threadIdx.x;
   if (TILED == kLayoutPacked) {
-    __syncthreads();                                   // previous page's readers are done with vt
-    packed_copy_phase_a(src, P, dst, vt, tid);
-    __syncthreads();
-    packed_copy_phase_b(P, dst, vt, tid);
+    const int w = tid / kWave;
+    for (int tg = w; tg < (P >> 2); tg += kGatherThreads / kWave) packed_copy_group(src, P, tg, dst, vt + w * (4 * kHeadDim));
     return;
   }
   if (!TILED) {
@@ -260,19 +258,28 @@ __global__ __launch_bounds__(kGatherThreads) void gather_kernel(const char* __re
   __shared__ uint16_t vt[kTileTokens * kHeadDim];
   const int u = blockIdx.y + u0;
   const int m = miss_count[u];
-  for (int j = blockIdx.x; j < m; j += gridDim.x) {
+  // where miss j comes from and its slot (nullptr: nothing to copy)
+  auto source = [&](int j, int& slot) -> const char* {
     const int page = miss_list[((size_t)u * k + j) * 2];
-    const int slot = miss_list[((size_t)u * k + j) * 2 + 1];
-    if (slot < 0) continue;
-    const char* src;
-    if (src_offset != nullptr) {
-      const int64_t off = src_offset[(size_t)u * k + j];
-      if (off < 0) continue;
-      src = store + off;
-    } else {
-      src = store + ((size_t)u * NP + page) * page_bytes;
+    slot = miss_list[((size_t)u * k + j) * 2 + 1];
+    if (slot < 0) return nullptr;
+    if (src_offset == nullptr) return store + ((size_t)u * NP + page) * page_bytes;
+    const int64_t off = src_offset[(size_t)u * k + j];
+    return off < 0 ? nullptr : store + off;
+  };
+  int slot;
+  if (TILED == kLayoutPacked) {
+    // four tokens at a time, so that every wave of the block has some whatever the page size
+    const int w = threadIdx.x / kWave, groups = P >> 2;
+    for (int it = blockIdx.x * (kGatherThreads / kWave) + w; it < m * groups; it += gridDim.x * (kGatherThreads / kWave)) {
+      const char* src = source(it / groups, slot);
+      if (src != nullptr) packed_copy_group(src, P, it % groups, pool + ((size_t)u * Cmax + slot) * page_bytes, vt + w * (4 * kHeadDim));
     }
-    copy_page<TILED>(src, pool + ((size_t)u * Cmax + slot) * page_bytes, P, page_bytes, vt);
+    return;
+  }
+  for (int j = blockIdx.x; j < m; j += gridDim.x) {
+    const char* src = source(j, slot);
+    if (src != nullptr) copy_page<TILED>(src, pool + ((size_t)u * Cmax + slot) * page_bytes, P, page_bytes, vt);
   }
 }
 

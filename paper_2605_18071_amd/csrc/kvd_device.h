@@ -44,6 +44,13 @@ __device__ __forceinline__ void wave_drain_memory() {
   __builtin_amdgcn_s_waitcnt(0);
 }
 
+// LDS accesses of this wave before the fence are ordered before those after it, for data that only this
+// wave touches (LDS operations of a wave complete in order; the fence keeps the compiler from reordering).
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
 // Thread 0 polls *flag until it equals `want` (device-scope loads, sleeping between polls) or
 // until `limit` ticks of the 100 MHz wall clock have passed; the verdict is shared through
 // *lds_ok.  Returns false on a time-out.  Contains a barrier: call from all threads.

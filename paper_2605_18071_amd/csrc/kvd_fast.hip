@@ -15,10 +15,18 @@ __global__ __launch_bounds__(kFastThreads) void select_resolve_kernel(FastArgs a
   select_resolve_body<kFastThreads, IPT, DO_SELECT, DO_RESOLVE, false>(a, blockIdx.x + a.u0, sm);
 }
 
+template <bool DO_SELECT, bool DO_RESOLVE>
+__global__ __launch_bounds__(kFastThreads) void select_resolve_big_kernel(FastArgs a) {
+  __shared__ FastSmem<kFastThreads, true> sm;
+  select_resolve_body<kFastThreads, 4, DO_SELECT, DO_RESOLVE, false, ScoresAlreadyThere, false, true>(a, blockIdx.x + a.u0, sm);
+}
+
 template <bool SEL, bool RES>
-static void launch_fast(int ipt, const FastArgs& a, int n_units, hipStream_t s) {
+static void launch_fast(bool big, int ipt, const FastArgs& a, int n_units, hipStream_t s) {
   dim3 grid(n_units), block(kFastThreads);
-  if (ipt <= 4)
+  if (big)
+    hipLaunchKernelGGL((select_resolve_big_kernel<SEL, RES>), grid, block, 0, s, a);
+  else if (ipt <= 4)
     hipLaunchKernelGGL((select_resolve_kernel<4, SEL, RES>), grid, block, 0, s, a);
   else if (ipt <= 8)
     hipLaunchKernelGGL((select_resolve_kernel<8, SEL, RES>), grid, block, 0, s, a);
@@ -29,8 +37,10 @@ static void launch_fast(int ipt, const FastArgs& a, int n_units, hipStream_t s) 
 }  // namespace kvd
 
 bool kvd_fast_path_ok(const kvd_ctx* c) {
-  return !c->generic_select && c->NP <= KVD_FAST_MAX_PAGES && c->Cmax <= KVD_FAST_MAX_CAPACITY;
+  return !c->generic_select && c->NP <= KVD_BIG_MAX_PAGES && c->Cmax <= KVD_BIG_MAX_CAPACITY;
 }
+
+bool kvd_fast_path_big(const kvd_ctx* c) { return c->NP > KVD_FAST_MAX_PAGES || c->Cmax > KVD_FAST_MAX_CAPACITY; }
 
 kvd::FastArgs kvd_fast_args(kvd_ctx* c, int layer, int step, bool do_gather, const float* scores, int32_t* sel_pages,
                             int32_t* sel_slots, int32_t* hit_mask, int32_t* evicted, int32_t* counts, int u0) {
@@ -72,8 +82,9 @@ hipError_t kvd_launch_select_resolve(kvd_ctx* c, int layer, int step, bool do_se
   if (u1 <= u0) return hipSuccess;
   const FastArgs a = kvd_fast_args(c, layer, step, do_gather, scores, sel_pages, sel_slots, hit_mask, evicted, counts, u0);
   const int ipt = (c->NP + kFastThreads - 1) / kFastThreads;
-  if (do_select && do_resolve) launch_fast<true, true>(ipt, a, u1 - u0, s);
-  else if (do_select) launch_fast<true, false>(ipt, a, u1 - u0, s);
-  else launch_fast<false, true>(4, a, u1 - u0, s);
+  const bool big = kvd_fast_path_big(c);
+  if (do_select && do_resolve) launch_fast<true, true>(big, ipt, a, u1 - u0, s);
+  else if (do_select) launch_fast<true, false>(big, ipt, a, u1 - u0, s);
+  else launch_fast<false, true>(big, 4, a, u1 - u0, s);
   return hipGetLastError();
 }

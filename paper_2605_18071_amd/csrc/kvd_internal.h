@@ -10,6 +10,8 @@ constexpr int KVD_MAX_TOPK = 2048;      // k
 constexpr int KVD_MAX_CAPACITY = 65536; // Cmax
 constexpr int KVD_FAST_MAX_PAGES = 16384;    // register-resident selection: 1024 threads x 16 pages
 constexpr int KVD_FAST_MAX_CAPACITY = 4096; // register-resident directory scan: 1024 threads x 4 slots
+constexpr int KVD_BIG_MAX_PAGES = 65536;     // the same kernel reading the scores once per pass: 64 pages of a thread as mask bits
+constexpr int KVD_BIG_MAX_CAPACITY = 16384;  // 16 slots per thread
 constexpr int KVD_MAX_PAGE = 256;       // P
 constexpr int KVD_MAX_MICRO = 16;       // micro-batches per step
 constexpr int KVD_PIPE_STREAMS = 3;      // side streams a step may spread its micro-batches over
@@ -129,6 +131,7 @@ hipError_t kvd_launch_select(kvd_ctx* c, const float* scores, int32_t* sel_pages
 hipError_t kvd_launch_resolve(kvd_ctx* c, int layer, int step, const int32_t* sel_pages, int32_t* sel_slots,
                               int32_t* hit_mask, int32_t* evicted, int32_t* counts, int u0, int u1, hipStream_t s);
 bool kvd_fast_path_ok(const kvd_ctx* c);
+bool kvd_fast_path_big(const kvd_ctx* c);   // ... and beyond the sizes that its registers hold
 hipError_t kvd_launch_select_resolve(kvd_ctx* c, int layer, int step, bool do_select, bool do_resolve, bool do_gather,
                                      const float* scores, int32_t* sel_pages, int32_t* sel_slots, int32_t* hit_mask,
                                      int32_t* evicted, int32_t* counts, int u0, int u1, hipStream_t s);

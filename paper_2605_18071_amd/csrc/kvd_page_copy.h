@@ -53,40 +53,36 @@ __device__ __forceinline__ void tile_copy_phase_b(char* __restrict__ dst_tile, c
   slot_store16<HANDOFF>(dst_tile + kTilePartBytes + gt * 16, outv);
 }
 
-// One page of 4 or 8 tokens from the host store's natural layout into the packed layout, by the
-// first 16 * P threads of a group (gt = thread index in the group), two phases with the caller's
-// barrier between them.  Phase A: thread gt moves K unit gt — (c, g, t) with 4c + g = gt / P,
-// t = gt % P — and parks one 16-byte unit of V in LDS (`vt`, P x 128 elements, natural order).
+// Four tokens (token group tg) of a page in the packed layout, from the host store's natural layout, by one
+// wave: every lane moves one 16-byte unit of K — (c, g, t) with 4c + g = lane / 4, t = 4 tg + lane % 4 —
+// and one of V, which the wave transposes through `vt` (4 x 128 elements of LDS of its own).  A wave
+// waits for nobody: a page is cut into P / 4 such groups, and all waves of a workgroup have loads in flight
+// whatever the page size (a group of 256 threads per page used 64 of them for pages of 4 tokens).
 template <bool HANDOFF = false>
-__device__ __forceinline__ void packed_copy_phase_a(const char* __restrict__ src_page, int P, char* __restrict__ dst_slot,
-                                                    uint16_t* vt, int gt) {
-  if (gt >= 16 * P) return;
-  const int t = gt % P, cg = gt / P;
+__device__ __forceinline__ void packed_copy_group(const char* __restrict__ src_page, int P, int tg, char* __restrict__ dst_slot,
+                                                  uint16_t* vt) {
+  const int lane = threadIdx.x & (kWave - 1);
+  const int t = 4 * tg + (lane & 3), cg = lane >> 2;
+  const int row = lane >> 4, ch = lane & 15;
   const uint4 kq = *reinterpret_cast<const uint4*>(src_page + (size_t)t * kRowBytes + cg * 16);
-  const int row = gt >> 4, ch = gt & 15;
-  const uint4 vq = *reinterpret_cast<const uint4*>(src_page + (size_t)(P + row) * kRowBytes + ch * 16);
-  slot_store16<HANDOFF>(dst_slot + gt * 16, kq);
+  const uint4 vq = *reinterpret_cast<const uint4*>(src_page + (size_t)(P + 4 * tg + row) * kRowBytes + ch * 16);
+  slot_store16<HANDOFF>(dst_slot + (size_t)(cg * P + t) * 16, kq);
+  wave_lds_fence();                                    // (the group before this one has been read)
   *reinterpret_cast<uint4*>(vt + row * kHeadDim + ch * 8) = vq;
-}
-
-// Phase B: thread gt assembles V unit gt = (c * P/4 + tg) * 16 + i: tokens 4tg..4tg+3 of dim
-// 32c + i, then of dim 32c + 16 + i.
-template <bool HANDOFF = false>
-__device__ __forceinline__ void packed_copy_phase_b(int P, char* __restrict__ dst_slot, const uint16_t* vt, int gt) {
-  if (gt >= 16 * P) return;
-  const int i = gt & 15, q = gt >> 4, groups = P >> 2;
-  const int tg = q % groups, c = q / groups;
+  wave_lds_fence();
+  // V unit (c, tg, i): tokens 4tg..4tg+3 of dim 32c + i, then of dim 32c + 16 + i
+  const int c = lane >> 4, i = lane & 15;
   uint16_t e[8];
 #pragma unroll
   for (int hh = 0; hh < 2; ++hh)
 #pragma unroll
-    for (int k = 0; k < 4; ++k) e[hh * 4 + k] = vt[(4 * tg + k) * kHeadDim + 32 * c + 16 * hh + i];
+    for (int k = 0; k < 4; ++k) e[hh * 4 + k] = vt[k * kHeadDim + 32 * c + 16 * hh + i];
   uint4 outv;
   outv.x = (u32)e[0] | ((u32)e[1] << 16);
   outv.y = (u32)e[2] | ((u32)e[3] << 16);
   outv.z = (u32)e[4] | ((u32)e[5] << 16);
   outv.w = (u32)e[6] | ((u32)e[7] << 16);
-  slot_store16<HANDOFF>(dst_slot + (size_t)P * kRowBytes + gt * 16, outv);
+  slot_store16<HANDOFF>(dst_slot + (size_t)P * kRowBytes + (size_t)((c * (P >> 2) + tg) * 16 + i) * 16, outv);
 }
 
 }  // namespace kvd

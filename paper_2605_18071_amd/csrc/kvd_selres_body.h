@@ -13,6 +13,8 @@
 // launch, so a lookup never waits on a dependent global load; every global load the block needs
 // is issued in its first instructions.
 #pragma once
+#include <type_traits>
+
 #include "kvd_device.h"
 #include "kvd_internal.h"
 #include "kvd_page_copy.h"
@@ -69,9 +71,15 @@ __device__ __forceinline__ float victim_score(const FastArgs& a, int u, int page
   return HANDOFF ? load_agent(sc) : *sc;
 }
 
-template <int NT>
+// BIG: units of up to KVD_BIG_MAX_PAGES pages and KVD_BIG_MAX_CAPACITY slots; the map alone is 128 of the
+// CU's 160 KiB, and page numbers no longer leave a 16-bit value free for "none".
+template <int NT, bool BIG = false>
 struct FastSmem {
   static constexpr int NW = NT / kWave;
+  static constexpr int kMaxPages = BIG ? KVD_BIG_MAX_PAGES : KVD_FAST_MAX_PAGES;
+  static constexpr int kMaxCapacity = BIG ? KVD_BIG_MAX_CAPACITY : KVD_FAST_MAX_CAPACITY;
+  typedef std::conditional_t<BIG, u32, uint16_t> page_t;
+  static constexpr page_t kNoPage = (page_t)~(page_t)0;
   static constexpr int kCopyGroups = NT / 256;           // tiles copied at a time
   union {
     struct {
@@ -80,10 +88,10 @@ struct FastSmem {
     } sel;
     uint16_t vt[kCopyGroups][kTileTokens * kHeadDim];    // V tiles in flight during the fetch
   } a;
-  uint16_t p2s[KVD_FAST_MAX_PAGES];                      // page -> slot of this unit, kAbsent = not resident
-  uint16_t sel[KVD_MAX_TOPK];                            // selected pages (kAbsent = padding)
+  uint16_t p2s[kMaxPages];                               // page -> slot of this unit, kAbsent = not resident
+  page_t sel[KVD_MAX_TOPK];                              // selected pages (kNoPage = padding)
   uint16_t assign[KVD_MAX_TOPK];                         // slot handed to the i-th miss
-  u32 hit_bitmap[KVD_FAST_MAX_CAPACITY / 32];
+  u32 hit_bitmap[kMaxCapacity / 32];
   int scan[2][NW];
   float red_min[NW], red_max[NW];
   int red_cnt[NW];
@@ -105,8 +113,8 @@ __device__ __forceinline__ u64 selection_order_key(float s, int page) {
 // Exclusive prefix sum over the block with one barrier: the wave totals alternate between two
 // LDS rows (`flip` is the caller's per-thread call counter), so a call never overwrites totals
 // that slower waves may still be reading from the call before.
-template <int NT>
-__device__ __forceinline__ int fast_scan(int v, FastSmem<NT>& sm, int& flip, int& total) {
+template <int NT, bool BIG>
+__device__ __forceinline__ int fast_scan(int v, FastSmem<NT, BIG>& sm, int& flip, int& total) {
   constexpr int NW = NT / kWave;
   const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
   const int inc = wave_inclusive_scan(v);
@@ -125,22 +133,12 @@ __device__ __forceinline__ int fast_scan(int v, FastSmem<NT>& sm, int& flip, int
   return base + inc - v;
 }
 
-// Items j = 0..IPT-1 of every thread: bkt(j) in [0, 2047], or -1 for "not a candidate"; key(j)
-// distinct; key1 < key2 implies bkt1 <= bkt2.  sm.a.sel.hist must be zero and sm.cand_n zero on
-// entry (with a barrier since).  Returns the need-th smallest key among the candidates
-// (1 <= need <= number of candidates).  `refine(bin, r)` is called by all threads when the
-// decisive bucket holds more than kListCap items and must return the r-th smallest key of that
-// bucket.  Ends with the block synchronised.
-template <int NT, int IPT, class KeyOf, class BktOf, class Refine>
-__device__ __forceinline__ u64 two_level_select(KeyOf key, BktOf bkt, int need, FastSmem<NT>& sm, int& flip,
-                                                Refine refine) {
+// The histogram is filled (no barrier since): sm.bin = the bucket that holds the need-th smallest
+// item, sm.below = the items in the buckets before it.  Ends with the block synchronised.
+template <int NT, bool BIG>
+__device__ __forceinline__ void find_bucket(int need, FastSmem<NT, BIG>& sm, int& flip) {
   const int tid = threadIdx.x;
   u32* hist = sm.a.sel.hist;
-#pragma unroll
-  for (int j = 0; j < IPT; ++j) {
-    const int bj = bkt(j);
-    if (bj >= 0) atomicAdd(&hist[bj], 1u);
-  }
   __syncthreads();
   constexpr int BPT = kRadixBins / NT;
   int local = 0;
@@ -159,15 +157,13 @@ __device__ __forceinline__ u64 two_level_select(KeyOf key, BktOf bkt, int need, 
     sm.below = ex;
   }
   __syncthreads();
-  const int bin = sm.bin;
-  const int r = need - sm.below;
-  const int m = (int)hist[bin];
-  if (m > kListCap) return refine(bin, r);
-#pragma unroll
-  for (int j = 0; j < IPT; ++j)
-    if (bkt(j) == bin) sm.a.sel.cand[atomicAdd(&sm.cand_n, 1)] = key(j);
+}
+
+// The r-th smallest of the m candidates in the list (no barrier since they were put there).
+template <int NT, bool BIG>
+__device__ __forceinline__ u64 rank_candidates(int m, int r, FastSmem<NT, BIG>& sm) {
   __syncthreads();
-  for (int c = tid; c < m; c += NT) {
+  for (int c = threadIdx.x; c < m; c += NT) {
     const u64 mine = sm.a.sel.cand[c];
     int rank = 0;
     for (int x = 0; x < m; ++x) rank += sm.a.sel.cand[x] < mine ? 1 : 0;
@@ -175,6 +171,32 @@ __device__ __forceinline__ u64 two_level_select(KeyOf key, BktOf bkt, int need, 
   }
   __syncthreads();
   return sm.thr;
+}
+
+// Items j = 0..IPT-1 of every thread: bkt(j) in [0, 2047], or -1 for "not a candidate"; key(j)
+// distinct; key1 < key2 implies bkt1 <= bkt2.  sm.a.sel.hist must be zero and sm.cand_n zero on
+// entry (with a barrier since).  Returns the need-th smallest key among the candidates
+// (1 <= need <= number of candidates).  `refine(bin, r)` is called by all threads when the
+// decisive bucket holds more than kListCap items and must return the r-th smallest key of that
+// bucket.  Ends with the block synchronised.
+template <int NT, int IPT, bool BIG, class KeyOf, class BktOf, class Refine>
+__device__ __forceinline__ u64 two_level_select(KeyOf key, BktOf bkt, int need, FastSmem<NT, BIG>& sm, int& flip,
+                                                Refine refine) {
+  constexpr int UNROLL = BIG ? 1 : IPT;               // (BIG: the items are read again from memory, not held in registers)
+#pragma unroll UNROLL
+  for (int j = 0; j < IPT; ++j) {
+    const int bj = bkt(j);
+    if (bj >= 0) atomicAdd(&sm.a.sel.hist[bj], 1u);
+  }
+  find_bucket<NT>(need, sm, flip);
+  const int bin = sm.bin;
+  const int r = need - sm.below;
+  const int m = (int)sm.a.sel.hist[bin];
+  if (m > kListCap) return refine(bin, r);
+#pragma unroll UNROLL
+  for (int j = 0; j < IPT; ++j)
+    if (bkt(j) == bin) sm.a.sel.cand[atomicAdd(&sm.cand_n, 1)] = key(j);
+  return rank_candidates<NT>(m, r, sm);
 }
 
 // Victim key of lookahead eviction: ascending in (score, -page), so that the lowest score leaves
@@ -202,6 +224,148 @@ __device__ __forceinline__ int victim_bucket(long long age, int page, int NP) {
   return (int)(2048 - 32 * age) + (int)(((long long)page * 32) / NP);
 }
 
+// Top-K selection of a unit whose scores do not fit the workgroup's registers (see
+// select_resolve_body for the rules).  The scores are read three times, 16 bytes per lane: for the
+// extremes, for the histogram, and for which pages lie before the decisive bucket and which in it; the
+// later passes find them in the L2.  A wave owns 256 * nq consecutive pages, of which a lane holds
+// two 64-bit masks.  One workgroup per unit, so the passes are bound by what one CU reads from its L2 and
+// by instruction issue.  32 units of 32768 pages and 8192 slots:
+// selection, directory update and fetch of an all-hit step 23 us, against 115 us as the size-agnostic kernels,
+// which refine their keys over global memory pass by pass (select 90, resolve 20, fetch 5).
+template <int NT>
+__device__ __forceinline__ void select_big(const FastArgs& a, int u, int seq, FastSmem<NT, true>& sm, int& flip) {
+  constexpr int NW = NT / kWave;
+  static_assert(KVD_BIG_MAX_PAGES <= NT * 64, "one mask bit per page of a lane");
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), w = tid / kWave, k = a.k;
+  int n_valid = (seq + a.P - 1) / a.P;
+  n_valid = n_valid < a.NP ? n_valid : a.NP;
+  const int k_eff = k < n_valid ? k : n_valid;
+  const int recent_from = n_valid - a.recent;
+  const float* sc = a.scores + (size_t)u * a.NP;
+  const int nq = (n_valid + 4 * NT - 1) / (4 * NT);
+  const int wave_p0 = w * (4 * kWave) * nq;
+  const bool vec = (a.NP & 3) == 0;
+  auto quad = [&](int q, float (&s)[4]) {              // this lane's q-th four pages
+    const int p = wave_p0 + q * (4 * kWave) + 4 * lane;
+    if (vec) {                                         // (NP a multiple of 4: the four pages are all there or none)
+      float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (p < a.NP) v = *reinterpret_cast<const float4*>(sc + p);
+      s[0] = v.x; s[1] = v.y; s[2] = v.z; s[3] = v.w;
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) s[e] = p + e < a.NP ? sc[p + e] : 0.f;
+    }
+  };
+  auto upto = [&](int q, int bound) -> u32 {           // bits of the q-th four pages below `bound`
+    const int n = bound - (wave_p0 + q * (4 * kWave) + 4 * lane);
+    return (1u << (n < 0 ? 0 : (n > 4 ? 4 : n))) - 1u;
+  };
+  auto free_of = [&](int q) -> u32 { return upto(q, recent_from) & ~upto(q, a.sink); };
+  // calls f(q, scores, free bits) for this lane's pages, four quads' loads in flight
+  auto for_quads = [&](auto f) {
+    for (int q0 = 0; q0 < nq; q0 += 4) {
+      float s[4][4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) quad(q0 + i < nq ? q0 + i : q0, s[i]);
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        if (q0 + i < nq) f(q0 + i, s[i], free_of(q0 + i));
+    }
+  };
+  u64 take = 0;                                        // bit 4q + e: the q-th four pages' e-th is selected
+  float fmin = INFINITY, fmax = -INFINITY;
+  int n_forced = 0;
+  for_quads([&](int q, const float (&s)[4], u32 fr) {
+    const u32 forced = upto(q, n_valid) & ~fr;
+    take |= (u64)forced << (4 * q);
+    n_forced += __popc(forced);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      fmin = fminf(fmin, (fr >> e) & 1u ? s[e] : INFINITY);
+      fmax = fmaxf(fmax, (fr >> e) & 1u ? s[e] : -INFINITY);
+    }
+  });
+  fmin = wave_allreduce_min(fmin);
+  fmax = wave_allreduce_max(fmax);
+  n_forced = wave_inclusive_scan(n_forced);
+  if (lane == kWave - 1) { sm.red_min[w] = fmin; sm.red_max[w] = fmax; sm.red_cnt[w] = n_forced; }
+  __syncthreads();
+  n_forced = 0;
+#pragma unroll
+  for (int i = 0; i < NW; ++i) {
+    fmin = fminf(fmin, sm.red_min[i]);
+    fmax = fmaxf(fmax, sm.red_max[i]);
+    n_forced += sm.red_cnt[i];
+  }
+  const int k_free = k_eff - n_forced;
+  if (k_free > 0) {
+    const float range = fmax - fmin;
+    const float inv = range > 0.f ? 2047.0f / range : 0.f;
+    auto bucket_of = [&](float v) -> int { return (int)fminf(fmaxf((fmax - v) * inv, 0.f), 2047.f); };
+    for_quads([&](int, const float (&s)[4], u32 fr) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if ((fr >> e) & 1u) atomicAdd(&sm.a.sel.hist[bucket_of(s[e])], 1u);
+    });
+    find_bucket<NT>(k_free, sm, flip);
+    const int bin = sm.bin, r = k_free - sm.below, m = (int)sm.a.sel.hist[bin];
+    const bool listed = m <= kListCap;
+    u64 tied = 0;                                      // pages of the decisive bucket
+    for_quads([&](int q, const float (&s)[4], u32 fr) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        if (!((fr >> e) & 1u)) continue;
+        const int b = bucket_of(s[e]);
+        if (b < bin) take |= 1ull << (4 * q + e);
+        if (b == bin) {
+          tied |= 1ull << (4 * q + e);
+          if (listed) sm.a.sel.cand[atomicAdd(&sm.cand_n, 1)] = selection_order_key(s[e], wave_p0 + q * (4 * kWave) + 4 * lane + e);
+        }
+      }
+    });
+    u64 thr;
+    if (listed) {
+      thr = rank_candidates<NT>(m, r, sm);
+    } else {
+      auto fn = [&](int i, u64& kk) -> bool {
+        if (i < a.sink || i >= recent_from) return false;
+        const float v = sc[i];
+        if (bucket_of(v) != bin) return false;
+        kk = selection_order_key(v, i);
+        return true;
+      };
+      thr = block_kth_smallest<NT>(fn, n_valid, r, sm.generic, sm.a.sel.hist);
+    }
+    while (tied) {
+      const int bit = __ffsll((unsigned long long)tied) - 1;
+      tied &= tied - 1;
+      const int p = wave_p0 + (bit >> 2) * (4 * kWave) + 4 * lane + (bit & 3);
+      if (selection_order_key(sc[p], p) <= thr) take |= 1ull << bit;
+    }
+  }
+  // output in ascending page order = (wave, quad, lane, element)
+  int total;
+  const int lane_pos = fast_scan<NT>((int)__popcll(take), sm, flip, total);
+  int pos_q = __builtin_amdgcn_readfirstlane(lane_pos);
+  int32_t* out = a.sel_pages + (size_t)u * k;
+  for (int q = 0; q < nq; ++q) {
+    u32 bits = (u32)(take >> (4 * q)) & 15u;
+    const int cnt = __popc(bits), inc = wave_inclusive_scan(cnt);
+    int pos = pos_q + inc - cnt;
+    pos_q += __builtin_amdgcn_readlane(inc, kWave - 1);
+    while (bits) {
+      const int p = wave_p0 + q * (4 * kWave) + 4 * lane + __ffs((int)bits) - 1;
+      bits &= bits - 1;
+      if (pos < k) { sm.sel[pos] = (u32)p; out[pos] = p; }
+      ++pos;
+    }
+  }
+  for (int i = k_eff + tid; i < k; i += NT) {
+    sm.sel[i] = FastSmem<NT, true>::kNoPage;
+    out[i] = -1;
+  }
+}
+
 // All NT threads of a workgroup, for unit u.  DO_SELECT: scores -> sel_pages (Top-K, ties to the
 // lower page, sink/recent pages forced, ascending page order, -1 padding).  DO_RESOLVE: sel_pages
 // -> directory update, slots, hit mask, evicted list, counts, the (page, slot) miss list and,
@@ -215,15 +379,21 @@ __device__ __forceinline__ int victim_bucket(long long age, int page, int NP) {
 // SEL_IN_LDS (with HANDOFF and without DO_SELECT): scores_ready() itself produces the selection —
 // the hierarchical index's cluster selection, by the same workgroup — and leaves it in sm.sel
 // (16-bit pages, kAbsent = padding) and in a.sel_pages; nothing is read back from global memory.
+// BIG: more pages than the registers hold (NP <= KVD_BIG_MAX_PAGES whatever IPT, Cmax <= KVD_BIG_MAX_CAPACITY;
+// without HANDOFF): the unit's scores are read once per pass over the pages instead.
 struct ScoresAlreadyThere { __device__ bool operator()() const { return true; } };
 template <int NT, int IPT, bool DO_SELECT, bool DO_RESOLVE, bool HANDOFF, class ScoresReady = ScoresAlreadyThere,
-          bool SEL_IN_LDS = false>
-__device__ __forceinline__ bool select_resolve_body(const FastArgs& a, int u, FastSmem<NT>& sm,
+          bool SEL_IN_LDS = false, bool BIG = false>
+__device__ __forceinline__ bool select_resolve_body(const FastArgs& a, int u, FastSmem<NT, BIG>& sm,
                                                     ScoresReady scores_ready = ScoresReady()) {
-  constexpr int CPT = KVD_FAST_MAX_CAPACITY / NT;
+  static_assert(!(BIG && HANDOFF), "the big form is a kernel of its own");
+  typedef typename FastSmem<NT, BIG>::page_t page_t;
+  constexpr page_t kNoPage = FastSmem<NT, BIG>::kNoPage;
+  constexpr int CPT = FastSmem<NT, BIG>::kMaxCapacity / NT;
+  constexpr int UNROLL = BIG ? 1 : CPT;                 // (BIG: slots are read again where they are needed, not held in registers)
   constexpr int KPT = KVD_MAX_TOPK / NT;
   constexpr int NW = NT / kWave;
-  constexpr int kCopyGroups = FastSmem<NT>::kCopyGroups;
+  constexpr int kCopyGroups = FastSmem<NT, BIG>::kCopyGroups;
   const int tid = threadIdx.x, lane = tid & (kWave - 1), w = tid / kWave;
   const int b = u / a.Hkv;
   const int k = a.k;
@@ -232,14 +402,17 @@ __device__ __forceinline__ bool select_resolve_body(const FastArgs& a, int u, Fa
   // ---- every global load of the block, issued up front
   int32_t* spage = a.slot_page + (size_t)u * a.Cmax;
   int32_t* sstamp = a.slot_stamp + (size_t)u * a.Cmax;
-  int sp[CPT], ss[CPT];                               // page in slot (-1 free, -2 no such slot), stamp
+  int sp[BIG ? 1 : CPT], ss[BIG ? 1 : CPT];           // page in slot (-1 free, -2 no such slot), stamp (BIG: read again where needed)
   int C = 0, R = 0;
+  const int cpt = BIG ? (a.Cmax + NT - 1) / NT : CPT;  // consecutive slots per thread
   if (DO_RESOLVE) {
+    if constexpr (!BIG) {
 #pragma unroll
-    for (int j = 0; j < CPT; ++j) {
-      const int s = tid * CPT + j;
-      sp[j] = s < a.Cmax ? spage[s] : -2;
-      ss[j] = s < a.Cmax ? sstamp[s] : 0;
+      for (int j = 0; j < CPT; ++j) {
+        const int s = tid * CPT + j;
+        sp[j] = s < a.Cmax ? spage[s] : -2;
+        ss[j] = s < a.Cmax ? sstamp[s] : 0;
+      }
     }
     C = a.capacity[u];
     R = a.resident[u];
@@ -249,7 +422,7 @@ __device__ __forceinline__ bool select_resolve_body(const FastArgs& a, int u, Fa
   static_assert(IPT % 4 == 0, "four consecutive pages per load");
   const int wave_p0 = w * (kWave * IPT);
   auto page_of = [&](int j) -> int { return wave_p0 + (j >> 2) * (4 * kWave) + 4 * lane + (j & 3); };
-  float s[IPT];
+  float s[BIG ? 4 : IPT];
   int seq = 0;
   auto load_scores = [&]() {
     const float* sc = a.scores + (size_t)u * a.NP;
@@ -273,12 +446,12 @@ __device__ __forceinline__ bool select_resolve_body(const FastArgs& a, int u, Fa
     }
   };
   if (DO_SELECT) {
-    if (!HANDOFF) load_scores();                       // (with HANDOFF the scores may not be complete yet)
+    if (!HANDOFF && !BIG) load_scores();                       // (with HANDOFF the scores may not be complete yet)
     seq = a.seq_len[b];
   } else if (!SEL_IN_LDS) {
     for (int i = tid; i < k; i += NT) {
       const int p = a.sel_pages[(size_t)u * k + i];
-      sm.sel[i] = (p >= 0 && p < a.NP) ? (uint16_t)p : kAbsent;
+      sm.sel[i] = (p >= 0 && p < a.NP) ? (page_t)p : kNoPage;
     }
   }
 
@@ -287,13 +460,18 @@ __device__ __forceinline__ bool select_resolve_body(const FastArgs& a, int u, Fa
   if (DO_RESOLVE) {
     u32* p2s32 = reinterpret_cast<u32*>(sm.p2s);
     for (int i = tid; i < (a.NP + 1) / 2; i += NT) p2s32[i] = 0xffffffffu;
-    for (int i = tid; i < KVD_FAST_MAX_CAPACITY / 32; i += NT) sm.hit_bitmap[i] = 0;
+    for (int i = tid; i < FastSmem<NT, BIG>::kMaxCapacity / 32; i += NT) sm.hit_bitmap[i] = 0;
     for (int i = tid; i < k; i += NT) sm.assign[i] = kAbsent;
   }
   if (tid == 0) { sm.cand_n = 0; sm.n_ev = 0; }
   __syncthreads();
-  float vs[CPT];                                       // lookahead eviction: this step's score of the page in each slot
-  if (DO_RESOLVE) {
+  float vs[BIG ? 1 : CPT];                             // lookahead eviction: this step's score of the page in each slot
+  if constexpr (DO_RESOLVE && BIG) {
+    for (int sl = tid; sl < C; sl += NT) {
+      const int p = spage[sl];
+      if (p >= 0) sm.p2s[p] = (uint16_t)sl;
+    }
+  } else if constexpr (DO_RESOLVE) {
 #pragma unroll
     for (int j = 0; j < CPT; ++j) {
       const int sl = tid * CPT + j;
@@ -306,7 +484,7 @@ __device__ __forceinline__ bool select_resolve_body(const FastArgs& a, int u, Fa
     if (!scores_ready()) return false;
     if (DO_SELECT) load_scores();
   }
-  if (DO_RESOLVE) {
+  if constexpr (DO_RESOLVE && !BIG) {
 #pragma unroll
     for (int j = 0; j < CPT; ++j) {
       vs[j] = 0.f;
@@ -315,7 +493,12 @@ __device__ __forceinline__ bool select_resolve_body(const FastArgs& a, int u, Fa
   }
 
   // ---- selection
-  if (DO_SELECT) {
+  if constexpr (DO_SELECT && BIG) {
+    select_big<NT>(a, u, seq, sm, flip);
+    if (!DO_RESOLVE) return true;
+    for (int i = tid; i < kRadixBins; i += NT) sm.a.sel.hist[i] = 0;
+    if (tid == 0) sm.cand_n = 0;
+  } else if (DO_SELECT) {
     int n_valid = (seq + a.P - 1) / a.P;
     n_valid = n_valid < a.NP ? n_valid : a.NP;
     const int k_eff = k < n_valid ? k : n_valid;
@@ -417,7 +600,7 @@ __device__ __forceinline__ bool select_resolve_body(const FastArgs& a, int u, Fa
         if ((take >> j) & 1u) {
           if (pos < k) {
             const int p = page_of(j);
-            sm.sel[pos] = (uint16_t)p;
+            sm.sel[pos] = (page_t)p;
             out[pos] = p;
           }
           ++pos;
@@ -425,7 +608,7 @@ __device__ __forceinline__ bool select_resolve_body(const FastArgs& a, int u, Fa
       }
     }
     for (int i = k_eff + tid; i < k; i += NT) {
-      sm.sel[i] = kAbsent;
+      sm.sel[i] = kNoPage;
       out[i] = -1;
     }
     if (!DO_RESOLVE) return true;
@@ -450,8 +633,9 @@ __device__ __forceinline__ bool select_resolve_body(const FastArgs& a, int u, Fa
     my_slot[j] = -1;
     const int i = i0 + j;
     if (j < per && i < k) {
-      const int p = sm.sel[i];
-      if (p == kAbsent) {                             // padding (or a page the caller made up)
+      const page_t entry_page = sm.sel[i];
+      const int p = (int)entry_page;
+      if (entry_page == kNoPage) {                    // padding (or a page the caller made up)
         sslots[i] = -1;
         if (HANDOFF) store_agent(entry + i, pack_sel_entry(-1, -1));
         hmask[i] = 0;
@@ -491,23 +675,39 @@ __device__ __forceinline__ bool select_resolve_body(const FastArgs& a, int u, Fa
   }
 
   // ---- victims: the e smallest (stamp, page) among resident slots that were not hit
-  auto is_cand = [&](int j) -> bool {
-    const int sl = tid * CPT + j;
-    return sp[j] >= 0 && !((sm.hit_bitmap[sl >> 5] >> (sl & 31)) & 1u);
+  // what this thread's j-th slot holds (the directory is written only after the slots have been handed out)
+  auto page_at = [&](int j) -> int {
+    if constexpr (BIG) return tid * cpt + j < C ? spage[tid * cpt + j] : -2;
+    else return sp[j];
+  };
+  auto stamp_at = [&](int j) -> int {
+    if constexpr (BIG) return sstamp[tid * cpt + j];
+    else return ss[j];
+  };
+  auto score_at = [&](int j, int page) -> float {
+    if constexpr (BIG) return a.lookahead ? victim_score<HANDOFF>(a, u, page) : 0.f;
+    else return vs[j];
   };
   u32 cand_mask = 0;
-#pragma unroll
-  for (int j = 0; j < CPT; ++j) cand_mask |= is_cand(j) ? (1u << j) : 0u;
+#pragma unroll UNROLL
+  for (int j = 0; j < cpt; ++j) {
+    const int sl = tid * cpt + j;
+    const bool cand = page_at(j) >= 0 && !((sm.hit_bitmap[sl >> 5] >> (sl & 31)) & 1u);
+    cand_mask |= cand ? (1u << j) : 0u;
+  }
   // lookahead eviction buckets the candidates' scores linearly between their extremes
   float vmin = 0.f, vinv = 0.f;
   if (a.lookahead && e > 0) {
     float lo = INFINITY, hi = -INFINITY;
-#pragma unroll
-    for (int j = 0; j < CPT; ++j)
-      if (((cand_mask >> j) & 1u) && vs[j] > -INFINITY) {   // (a page of no cluster scores -inf: bucket 0 whatever the range)
-        lo = fminf(lo, vs[j]);
-        hi = fmaxf(hi, vs[j]);
+#pragma unroll UNROLL
+    for (int j = 0; j < cpt; ++j) {
+      if (!((cand_mask >> j) & 1u)) continue;
+      const float v = score_at(j, page_at(j));
+      if (v > -INFINITY) {                             // (a page of no cluster scores -inf: bucket 0 whatever the range)
+        lo = fminf(lo, v);
+        hi = fmaxf(hi, v);
       }
+    }
     lo = wave_allreduce_min(lo);
     hi = wave_allreduce_max(hi);
     if (lane == 0) { sm.red_min[w] = lo; sm.red_max[w] = hi; }
@@ -552,11 +752,13 @@ __device__ __forceinline__ bool select_resolve_body(const FastArgs& a, int u, Fa
     return in_pool(v, page) ? 1024 + (la_bucket(v) >> 1) : (victim_bucket((long long)a.step - (long long)st, page, a.NP) >> 1);
   };
   auto vkey_of = [&](int j) -> u64 {
-    return a.lookahead ? la_key(vs[j], ss[j], sp[j]) : ((u64)((u32)ss[j] ^ 0x80000000u) << 32) | (u32)sp[j];
+    const int st = stamp_at(j), p = page_at(j);
+    return a.lookahead ? la_key(score_at(j, p), st, p) : ((u64)((u32)st ^ 0x80000000u) << 32) | (u32)p;
   };
   auto vbkt_of = [&](int j) -> int {
     if (!((cand_mask >> j) & 1u)) return -1;
-    return a.lookahead ? la_bkt(vs[j], ss[j], sp[j]) : victim_bucket((long long)a.step - (long long)ss[j], sp[j], a.NP);
+    const int st = stamp_at(j), p = page_at(j);
+    return a.lookahead ? la_bkt(score_at(j, p), st, p) : victim_bucket((long long)a.step - (long long)st, p, a.NP);
   };
   u64 vthr = 0;
   if (e > 0) {
@@ -584,24 +786,24 @@ __device__ __forceinline__ bool select_resolve_body(const FastArgs& a, int u, Fa
   // ascending page order
   int avail = 0;
   u32 av_mask = 0, vic_mask = 0;
-#pragma unroll
-  for (int j = 0; j < CPT; ++j) {
+#pragma unroll UNROLL
+  for (int j = 0; j < cpt; ++j) {
     const bool vic = e > 0 && ((cand_mask >> j) & 1u) && vkey_of(j) <= vthr;
-    const bool av = sp[j] == -1 || vic;
+    const bool av = page_at(j) == -1 || vic;
     vic_mask |= vic ? (1u << j) : 0u;
     av_mask |= av ? (1u << j) : 0u;
     avail += av ? 1 : 0;
   }
   int total_avail;
   int rank = fast_scan<NT>(avail, sm, flip, total_avail);
-#pragma unroll
-  for (int j = 0; j < CPT; ++j) {
+#pragma unroll UNROLL
+  for (int j = 0; j < cpt; ++j) {
     if ((av_mask >> j) & 1u) {
       if (rank < m) {
-        sm.assign[rank] = (uint16_t)(tid * CPT + j);
+        sm.assign[rank] = (uint16_t)(tid * cpt + j);
         if ((vic_mask >> j) & 1u) {
           const int at = atomicAdd(&sm.n_ev, 1);
-          if (at < k) evout[at] = sp[j];
+          if (at < k) evout[at] = page_at(j);
         }
       }
       ++rank;
@@ -652,35 +854,30 @@ __device__ __forceinline__ bool select_resolve_body(const FastArgs& a, int u, Fa
     return true;
   }
 
-  // ---- fetch the unit's missed pages: groups of 256 threads, one 16-token tile (or one page in
-  // the natural layout) each per round.  Miss j is (page, sm.assign[j]); the pages are staged in
+  // ---- fetch the unit's missed pages: groups of 256 threads, one 16-token tile (or one or two pages
+  // in the natural layout) each per round; packed pages by waves.  Miss j is (page, sm.assign[j]); the pages are staged in
   // sm.sel[j], each thread writing the misses it found at their ranks.
   __syncthreads();                                     // everyone is done with sm.sel / sm.a.sel
 #pragma unroll
   for (int j = 0; j < KPT; ++j) {
     // my misses keep their rank: miss_rank was advanced once per miss above
     const int p = my_page[KPT - 1 - j];
-    if (p >= 0) sm.sel[--miss_rank] = (uint16_t)p;
+    if (p >= 0) sm.sel[--miss_rank] = (page_t)p;
   }
   __syncthreads();
   const int grp = tid >> 8, gt = tid & 255;
   const char* store_u = a.store + (size_t)u * a.NP * a.page_bytes;
   char* pool_u = a.pool + (size_t)u * a.Cmax * a.page_bytes;
   if (a.tiled == kLayoutPacked) {
-    // pages of 4 or 8 tokens: one page per group and round
-    for (int j0 = 0; j0 < m; j0 += kCopyGroups) {
-      const int jm = j0 + grp;
-      const bool on = jm < m;
-      int page = 0, slot = -1;
-      if (on) {
-        page = sm.sel[jm];
-        slot = sm.assign[jm] == kAbsent ? -1 : sm.assign[jm];
-      }
-      char* dst = pool_u + (size_t)(slot < 0 ? 0 : slot) * a.page_bytes;
-      if (on && slot >= 0) packed_copy_phase_a<HANDOFF>(store_u + (size_t)page * a.page_bytes, a.P, dst, sm.a.vt[grp], gt);
-      __syncthreads();
-      if (on && slot >= 0) packed_copy_phase_b<HANDOFF>(a.P, dst, sm.a.vt[grp], gt);
-      __syncthreads();
+    // one group of four tokens per wave and round
+    const int groups = a.P >> 2, n_items = m * groups;
+    uint16_t* vt = &sm.a.vt[0][0] + w * (4 * kHeadDim);
+    for (int it = w; it < n_items; it += NW) {
+      const int jm = it / groups, tg = it % groups;
+      const int page = (int)sm.sel[jm];
+      const int slot = sm.assign[jm] == kAbsent ? -1 : sm.assign[jm];
+      if (slot >= 0)
+        packed_copy_group<HANDOFF>(store_u + (size_t)page * a.page_bytes, a.P, tg, pool_u + (size_t)slot * a.page_bytes, vt);
     }
   } else if (a.tiled) {
     const int tiles = a.P / kTileTokens;
@@ -692,7 +889,7 @@ __device__ __forceinline__ bool select_resolve_body(const FastArgs& a, int u, Fa
       if (on) {
         const int jm = it / tiles;
         tile = it % tiles;
-        page = sm.sel[jm];
+        page = (int)sm.sel[jm];
         slot = sm.assign[jm] == kAbsent ? -1 : sm.assign[jm];
       }
       char* dst_tile = pool_u + (size_t)(slot < 0 ? 0 : slot) * a.page_bytes + (size_t)tile * kTileBytes;
@@ -703,13 +900,25 @@ __device__ __forceinline__ bool select_resolve_body(const FastArgs& a, int u, Fa
     }
   } else {
     const unsigned units = a.page_bytes / 16;
-    for (int jm = grp; jm < m; jm += kCopyGroups) {
-      const int page = sm.sel[jm];
-      const int slot = sm.assign[jm] == kAbsent ? -1 : sm.assign[jm];
-      if (slot < 0) continue;
-      const uint4* s4 = reinterpret_cast<const uint4*>(store_u + (size_t)page * a.page_bytes);
-      uint4* d4 = reinterpret_cast<uint4*>(pool_u + (size_t)slot * a.page_bytes);
-      for (unsigned o = gt; o < units; o += 256) slot_store16<HANDOFF>(d4 + o, s4[o]);
+    auto ends = [&](int jm, const uint4*& src, uint4*& dst) -> bool {
+      if (jm >= m || sm.assign[jm] == kAbsent) return false;
+      src = reinterpret_cast<const uint4*>(store_u + (size_t)sm.sel[jm] * a.page_bytes);
+      dst = reinterpret_cast<uint4*>(pool_u + (size_t)sm.assign[jm] * a.page_bytes);
+      return true;
+    };
+    // two pages of a group in flight where one does not give each of its threads a load
+    const int pages = units <= 256 ? 2 : 1;
+    for (int jm = grp; jm < m; jm += pages * kCopyGroups) {
+      const uint4 *s0 = nullptr, *s1 = nullptr;
+      uint4 *d0 = nullptr, *d1 = nullptr;
+      const bool on0 = ends(jm, s0, d0), on1 = pages == 2 && ends(jm + kCopyGroups, s1, d1);
+      for (unsigned o = gt; o < units; o += 256) {
+        uint4 v0, v1;
+        if (on0) v0 = s0[o];
+        if (on1) v1 = s1[o];
+        if (on0) slot_store16<HANDOFF>(d0 + o, v0);
+        if (on1) slot_store16<HANDOFF>(d1 + o, v1);
+      }
     }
   }
   publish_misses();

@@ -347,7 +347,7 @@ bool kvd_step_shape_ok(const kvd_ctx* c, const kvd_shape& e) {
 }
 
 bool kvd_single_launch_ok(const kvd_ctx* c) {
-  return kvd_fast_path_ok(c) && c->tiled && c->NP <= kvd::kStepThreadsWide * 16 &&
+  return kvd_fast_path_ok(c) && !kvd_fast_path_big(c) && c->tiled &&
          (c->k + c->S1 - 1) / c->S1 <= kvd::kAttnIdxCap;   // a split's entries are staged in LDS
 }
 
