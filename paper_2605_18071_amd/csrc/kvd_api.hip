@@ -251,23 +251,9 @@ int kvd_create(const kvd_config* cfg, kvd_ctx** out) {
   c->scale = cfg->softmax_scale > 0.f ? cfg->softmax_scale : 1.0f / sqrtf((float)c->D);
   c->page_bytes = (size_t)2 * c->P * c->D * 2;
   int S = cfg->attn_splits;
-  // 16-token tiles of a unit's selection (pages of 4 or 8 tokens share tiles)
-  const int sel_tiles = c->tiled == kvd::kLayoutPacked ? (c->k * c->P + 15) / 16 : c->k * ((c->P + 15) / 16);
-  if (S == 0) {
-    const int tiles = sel_tiles;
-    if (c->tiled) {
-      // the MFMA kernel runs one 512-thread workgroup per CU: about one workgroup per CU in the
-      // grid, every wave keeping at least two tiles of 16 tokens
-      S = (c->n_cus + c->U / 2) / c->U;
-      if (S > tiles / 16) S = tiles / 16;
-    } else {
-      // the VALU kernel: one round of resident 256-thread workgroups, 8 tiles each at least
-      S = (512 + c->U / 2) / c->U;
-      if (S > (tiles + 7) / 8) S = (tiles + 7) / 8;
-    }
-    if (S > KVD_MAX_SPLITS) S = KVD_MAX_SPLITS;
-    if (S < 1) S = 1;
-  }
+  // 16-token tiles of a unit's selection (only pages of a multiple of 16 tokens do not share tiles)
+  const int sel_tiles = (c->k * c->P + 15) / 16;
+  if (S == 0) S = kvd_attn_splits(c->tiled, c->U, c->k, c->P, c->n_cus);
   if (S > c->k) S = c->k;
   c->S = S;
   // The one-launch step runs one workgroup per CU: 512 threads with 256 registers per lane (three

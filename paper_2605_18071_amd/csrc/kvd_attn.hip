@@ -2,13 +2,13 @@
 // Overview: attention runs over the union of resident and newly fetched entries).  See
 // kvd_attn_body.h for the split-K frame.
 //
-// Two kernels share that frame:
-//  * attend_mfma_kernel — pages whose size is a multiple of 16 tokens are kept in the slot pool in
-//    an operand-ready tile layout (see kvd_tile_layout.h), so that every wave load is 1 KiB
-//    contiguous and lands directly in MFMA operand registers: S^T = K Q^T with 16x16x32 MFMAs,
-//    O^T += V^T P^T with 16x16x16 MFMAs whose B operand is the softmaxed C tile of the first.
-//    Pages of 4 or 8 tokens take the same kernel over the packed layout: 16 / P pages per tile.
-//  * attend_valu_kernel — any page size, natural [token][dim] slots, fp32 VALU arithmetic.
+// One kernel, three layouts that differ in how a lane finds its operands:
+//  * pages of a multiple of 16 tokens are kept in the slot pool in an operand-ready tile layout (see
+//    kvd_tile_layout.h), so that every wave load is 1 KiB contiguous and lands directly in MFMA operand
+//    registers: S^T = K Q^T with 16x16x32 MFMAs, O^T += V^T P^T with 16x16x16 MFMAs whose B operand is
+//    the softmaxed C tile of the first;
+//  * pages of 4 or 8 tokens take the same kernel over the packed layout: 16 / P pages per tile;
+//  * pages of any other size keep natural [token][dim] slots, of which a tile takes 16 consecutive tokens.
 #include <math.h>
 
 #include <mutex>
@@ -26,167 +26,33 @@ static __device__ __align__(256) unsigned char scratch[kNoAllocScratchBytes];
 
 namespace kvd {
 
-constexpr int kAttnThreads = 256;
-constexpr int kAttnWaves = kAttnThreads / kWave;
+constexpr int kMergeThreads = 256;
 
 template <int G>
-__global__ __launch_bounds__(kAttnThreads) void combine_kernel(AttnArgs a) {
-  merge_splits<G, kAttnThreads, false>(a, blockIdx.x + a.u0);
+__global__ __launch_bounds__(kMergeThreads) void combine_kernel(AttnArgs a) {
+  merge_splits<G, kMergeThreads, false>(a, blockIdx.x + a.u0);
 }
 
 // 512 threads and up to 256 registers per lane: one workgroup per CU, three tile buffers (24 KiB)
 // in flight per wave; the grid is sized to about one workgroup per CU (see kvd_create).
 constexpr int kAttnMfmaThreads = 512;
-template <bool BF16, int G, bool PACKED>
+template <bool BF16, int G, int LAYOUT>
 __global__ __launch_bounds__(kAttnMfmaThreads, 2) void attend_mfma_kernel(AttnArgs a) {
   __shared__ AttnSmem<G, kAttnMfmaThreads / kWave> sm;
-  attend_mfma_body<BF16, G, kAttnMfmaThreads, false, false, PACKED>(a, sm, blockIdx.y + a.u0, blockIdx.x);
-}
-
-// ---------------------------------------------------------------------------------------------
-// VALU kernel (any page size, natural slots)
-// ---------------------------------------------------------------------------------------------
-// Block (split, u): 4 waves, wave w takes selected entries first + w, first + w + 4, ...
-// A wave load covers 4 token rows: lane (r, c) = (lane / 16, lane % 16) holds dims 8c..8c+7 of
-// token 4j + r of a 16-token tile.  Each 16-lane row keeps its own running (max, sum, acc) for the
-// G query heads, so nothing crosses rows inside the loop; rows and waves are merged at the end.
-template <bool BF16, int G>
-__global__ __launch_bounds__(kAttnThreads) void attend_valu_kernel(AttnArgs a) {
-  __shared__ AttnSmem<G, kAttnWaves> sm;
-  const int split = blockIdx.x, u = blockIdx.y + a.u0;
-  const int b = u / a.Hkv, h = u % a.Hkv;
-  const int tid = threadIdx.x, lane = tid & (kWave - 1), w = tid / kWave;
-  const int r = lane >> 4, c = lane & 15;
-
-  float qf[G][8];
-  {
-    const uint16_t* qrow = a.q + ((size_t)b * a.Hq + (size_t)h * G) * kHeadDim + c * 8;
-#pragma unroll
-    for (int g = 0; g < G; ++g) {
-      const uint4 raw = *reinterpret_cast<const uint4*>(qrow + (size_t)g * kHeadDim);
-      cvt8<BF16>(raw, qf[g]);
-    }
-  }
-  float m[G], l[G], acc[G][8];
-#pragma unroll
-  for (int g = 0; g < G; ++g) {
-    m[g] = -INFINITY;
-    l[g] = 0.f;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) acc[g][e] = 0.f;
-  }
-
-  const int seq = a.seq_len[b];
-  const int first = split * a.per_split;
-  const int last = (first + a.per_split) < a.k ? (first + a.per_split) : a.k;
-  const int32_t* sel = a.sel_pages + (size_t)u * a.k;
-  const int32_t* slots = a.sel_slots + (size_t)u * a.k;
-  const char* pool_u = a.pool + (size_t)u * a.Cmax * a.page_bytes;
-
-  for (int i = first + w; i < last; i += kAttnWaves) {
-    const int page = __builtin_amdgcn_readfirstlane(sel[i]);
-    const int slot = __builtin_amdgcn_readfirstlane(slots[i]);
-    if (page < 0 || slot < 0 || slot >= a.Cmax) continue;
-    int ntok = seq - page * a.P;
-    ntok = ntok < a.P ? ntok : a.P;
-    if (ntok <= 0) continue;
-    const char* kbase = pool_u + (size_t)slot * a.page_bytes + c * 16;
-    const char* vbase = kbase + (size_t)a.P * kRowBytes;
-    for (int t0 = 0; t0 < ntok; t0 += 16) {
-      uint4 kraw[4], vraw[4];
-#pragma unroll
-      for (int jj = 0; jj < 4; ++jj) {
-        int tok = t0 + 4 * jj + r;
-        tok = tok < ntok ? tok : ntok - 1;
-        kraw[jj] = *reinterpret_cast<const uint4*>(kbase + (size_t)tok * kRowBytes);
-        vraw[jj] = *reinterpret_cast<const uint4*>(vbase + (size_t)tok * kRowBytes);
-      }
-      float x[4][G];
-#pragma unroll
-      for (int jj = 0; jj < 4; ++jj) {
-        float kf[8];
-        cvt8<BF16>(kraw[jj], kf);
-        const bool valid = (t0 + 4 * jj + r) < ntok;
-#pragma unroll
-        for (int g = 0; g < G; ++g) {
-          float s = 0.f;
-#pragma unroll
-          for (int e = 0; e < 8; ++e) s = fmaf(qf[g][e], kf[e], s);
-          s = row16_allreduce_sum(s);
-          x[jj][g] = valid ? s * a.scale_log2 : -INFINITY;
-        }
-      }
-      float p[4][G];
-#pragma unroll
-      for (int g = 0; g < G; ++g) {
-        float mx = fmaxf(fmaxf(x[0][g], x[1][g]), fmaxf(x[2][g], x[3][g]));
-        const float m_new = fmaxf(m[g], mx);
-        const float m_safe = m_new == -INFINITY ? 0.f : m_new;
-        const float alpha = exp2f(m[g] - m_safe);
-        float ps = 0.f;
-#pragma unroll
-        for (int jj = 0; jj < 4; ++jj) {
-          p[jj][g] = exp2f(x[jj][g] - m_safe);
-          ps += p[jj][g];
-        }
-        l[g] = l[g] * alpha + ps;
-        m[g] = m_new;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) acc[g][e] *= alpha;
-      }
-#pragma unroll
-      for (int jj = 0; jj < 4; ++jj) {
-        float vf[8];
-        cvt8<BF16>(vraw[jj], vf);
-#pragma unroll
-        for (int g = 0; g < G; ++g)
-#pragma unroll
-          for (int e = 0; e < 8; ++e) acc[g][e] = fmaf(p[jj][g], vf[e], acc[g][e]);
-      }
-    }
-  }
-
-  // merge the 4 rows of the wave (lanes differing in bits 4 and 5)
-#pragma unroll
-  for (int g = 0; g < G; ++g) {
-#pragma unroll
-    for (int mask = 16; mask <= 32; mask <<= 1) {
-      const float mo = __shfl_xor(m[g], mask, kWave);
-      const float lo = __shfl_xor(l[g], mask, kWave);
-      const float mn = fmaxf(m[g], mo);
-      const float ms = mn == -INFINITY ? 0.f : mn;
-      const float sa = exp2f(m[g] - ms), sb = exp2f(mo - ms);
-      l[g] = l[g] * sa + lo * sb;
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const float ao = __shfl_xor(acc[g][e], mask, kWave);
-        acc[g][e] = acc[g][e] * sa + ao * sb;
-      }
-      m[g] = mn;
-    }
-  }
-  if (r == 0) {
-#pragma unroll
-    for (int g = 0; g < G; ++g) {
-#pragma unroll
-      for (int e = 0; e < 8; ++e) sm.acc[w][g][c * 8 + e] = acc[g][e];
-      if (c == 0) { sm.m[w][g] = m[g]; sm.l[w][g] = l[g]; }
-    }
-  }
-  finish_split<G, kAttnThreads>(a, sm, u, split);
+  attend_mfma_body<BF16, G, kAttnMfmaThreads, false, false, LAYOUT>(a, sm, blockIdx.y + a.u0, blockIdx.x);
 }
 
 template <bool BF16, int G>
 static void launch_attend(int layout, const AttnArgs& a, dim3 grid, hipStream_t s, hipEvent_t between) {
   if (layout == kLayoutPacked)
-    hipLaunchKernelGGL((attend_mfma_kernel<BF16, G, true>), grid, dim3(kAttnMfmaThreads), 0, s, a);
+    hipLaunchKernelGGL((attend_mfma_kernel<BF16, G, kLayoutPacked>), grid, dim3(kAttnMfmaThreads), 0, s, a);
   else if (layout == kLayoutTiles)
-    hipLaunchKernelGGL((attend_mfma_kernel<BF16, G, false>), grid, dim3(kAttnMfmaThreads), 0, s, a);
+    hipLaunchKernelGGL((attend_mfma_kernel<BF16, G, kLayoutTiles>), grid, dim3(kAttnMfmaThreads), 0, s, a);
   else
-    hipLaunchKernelGGL((attend_valu_kernel<BF16, G>), grid, dim3(kAttnThreads), 0, s, a);
+    hipLaunchKernelGGL((attend_mfma_kernel<BF16, G, kLayoutNatural>), grid, dim3(kAttnMfmaThreads), 0, s, a);
   if (between != nullptr) (void)hipEventRecord(between, s);   // no kernel follows when the merge is fused
   if (a.S > 1 && !a.fuse_merge)
-    hipLaunchKernelGGL((combine_kernel<G>), dim3(grid.y), dim3(kAttnThreads), 0, s, a);
+    hipLaunchKernelGGL((combine_kernel<G>), dim3(grid.y), dim3(kMergeThreads), 0, s, a);
 }
 
 template <bool BF16>
@@ -205,6 +71,18 @@ static bool dispatch_group(int G, int layout, const AttnArgs& a, dim3 grid, hipS
 }
 
 }  // namespace kvd
+
+// Split-K factor where the caller leaves it open: one 512-thread workgroup runs per CU, so about one workgroup per
+// CU in the grid.  Every wave keeps at least two tiles of 16 tokens; over natural slots, where a tile costs a
+// wave more, one (2 units of 40 pages of 12 tokens: 23.8 us a step with the first rule, 19.8 with the second).
+int kvd_attn_splits(int layout, int U, int k, int P, int cus) {
+  const int tiles = (k * P + 15) / 16;                 // of a unit's selection
+  int S = (cus + U / 2) / U;
+  const int most = layout == kvd::kLayoutNatural ? tiles / 8 : tiles / 16;
+  if (S > most) S = most;
+  if (S > KVD_MAX_SPLITS) S = KVD_MAX_SPLITS;
+  return S < 1 ? 1 : S;
+}
 
 kvd::AttnArgs kvd_attn_args(kvd_ctx* c, int layer, const void* q, const int32_t* sel_pages, const int32_t* sel_slots,
                             float* out, float* lse, int u0) {
@@ -312,21 +190,7 @@ extern "C" int kvd_sparse_decode_attn_noalloc(const void* q, const void* slot_po
   }
   const int U = batch * n_kv_heads;
   const int layout = slot_layout_of(page_size);
-  const bool tiled = layout != kLayoutNatural;
-  // split-K factor: the rule of kvd_create
-  int S = attn_splits;
-  if (S == 0) {
-    const int tiles = layout == kLayoutPacked ? (topk_pages * page_size + 15) / 16 : topk_pages * ((page_size + 15) / 16);
-    if (tiled) {
-      S = (cus + U / 2) / U;
-      if (S > tiles / 16) S = tiles / 16;
-    } else {
-      S = (512 + U / 2) / U;
-      if (S > (tiles + 7) / 8) S = (tiles + 7) / 8;
-    }
-    if (S > KVD_MAX_SPLITS) S = KVD_MAX_SPLITS;
-    if (S < 1) S = 1;
-  }
+  int S = attn_splits == 0 ? kvd_attn_splits(layout, U, topk_pages, page_size, cus) : attn_splits;
   if (S > topk_pages) S = topk_pages;
   // the scratch array, cut into tickets [U], (max, sum) [U][S][G][2] and accumulators [U][S][G][D]
   const size_t rows = (size_t)U * S * G;

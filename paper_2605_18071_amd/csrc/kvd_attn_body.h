@@ -5,6 +5,8 @@
 // log-sum-exp, either by the last workgroup of the unit to finish or by a second kernel.
 // Shared by the stand-alone attention kernels and the single-launch layer-step kernel.
 #pragma once
+#include <type_traits>
+
 #include "kvd_device.h"
 #include "kvd_internal.h"
 #include "kvd_tile_layout.h"
@@ -169,7 +171,7 @@ __device__ __forceinline__ bool finish_split(const AttnArgs& a, AttnSmem<GroupMa
 }
 
 // ---------------------------------------------------------------------------------------------
-// MFMA attention (page size a multiple of 16, tile-layout slots)
+// MFMA attention
 // ---------------------------------------------------------------------------------------------
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -184,6 +186,12 @@ __device__ __forceinline__ f32x4 mfma_qk(const uint4& kfrag, const uint4& qfrag,
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kfrag), __builtin_bit_cast(bf16x8, qfrag), c, 0, 0, 0);
   else
     return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, kfrag), __builtin_bit_cast(f16x8, qfrag), c, 0, 0, 0);
+}
+
+// The same instruction for the P.V product of 16 tokens with P in two parts: c + v0 p0 + v1 p1.
+template <bool BF16>
+__device__ __forceinline__ f32x4 mfma_pv2(const uint2& v0, const uint2& v1, const uint2& p0, const uint2& p1, f32x4 c) {
+  return mfma_qk<BF16>(make_uint4(v0.x, v0.y, v1.x, v1.y), make_uint4(p0.x, p0.y, p1.x, p1.y), c);
 }
 
 template <bool BF16>
@@ -204,17 +212,30 @@ __device__ __forceinline__ f32x4 mfma_pv(const uint2& vfrag, const uint2& pfrag,
 // HANDOFF: the selection was written by another workgroup of the same launch.
 // LEAN: for 128 registers per lane (two workgroups of 8 waves per CU): two tile buffers instead of
 // three and the Q^T fragments re-read from LDS for every tile.
-// PACKED: pages of 4 or 8 tokens in the packed slot layout: a tile is made of 16 / P consecutive
+// LAYOUT kLayoutPacked: pages of 4 or 8 tokens in the packed slot layout: a tile is made of 16 / P consecutive
 // entries of the split, every lane fetching its 16-byte units from the slot of its own page, and
 // every token of the tile is valid or not on its own (a page beyond the selection's end, a made-up
 // page, the ragged last page of a sequence).
+// LAYOUT kLayoutNatural: pages of any other size, K and V rows as the host has them.  A tile is 16
+// consecutive tokens of the split's pages put one after the other, whichever pages they lie in.  What the
+// other layouts prepare in the slot is had here by the choice of rows: row i of the K operand is token
+// 4 (i % 4) + i / 4 of the tile, so that lane (j, g) of the C tile holds the logits of tokens g, 4 + g, 8 + g
+// and 12 + g; lane (i, g) fetches 16 bytes of the V rows of the same four tokens, eight dims of each, and the
+// halves of dim 8i + e, put together in pairs, are its V^T operand of the e-th MFMA (16 byte permutes a
+// tile, no LDS), whose C tile then holds dims 8 (4g + 0..3) + e.  P keeps as many bits as fp32 has, since this
+// layout used to be computed in fp32 throughout: three bf16 parts, or two fp16 parts of P scaled by 2^15, which
+// puts the fp16 subnormals out of the way.  (32 units x 85 pages of 24 tokens, G = 7: 35 us in fp32 VALU
+// arithmetic, 13.6 us so; 128 units x 100 pages of 20 tokens, G = 1 / 4 / 8: steps of 47 / 64 / 119 us became
+// 45 / 46 / 49.)
 // Returns 1 in the workgroup that completed the unit's output, 0 in the others, -1 (from all
 // threads, no output) when a HANDOFF wait ran out.  inputs_ready_tick (one thread passes it)
 // receives the wall clock at which the split's entries were all there.
-template <bool BF16, int GT, int NT, bool HANDOFF, bool LEAN = false, bool PACKED = false>
+template <bool BF16, int GT, int NT, bool HANDOFF, bool LEAN = false, int LAYOUT = kLayoutTiles>
 __device__ __forceinline__ int attend_mfma_body(const AttnArgs& a, AttnSmem<GroupMax<GT>::value, NT / kWave>& sm, int u,
                                                 int split, long long* inputs_ready_tick = nullptr) {
   constexpr int NW = NT / kWave;
+  constexpr bool PACKED = LAYOUT == kLayoutPacked, NATURAL = LAYOUT == kLayoutNatural;
+  constexpr float kPScale = NATURAL && !BF16 ? 32768.f : 1.f;   // of the probabilities that multiply V
   const int G = group_size<GT>(a);
   const int b = u / a.Hkv, h = u % a.Hkv;
   const int tid = threadIdx.x, lane = tid & (kWave - 1), w = tid / kWave;
@@ -246,7 +267,10 @@ __device__ __forceinline__ int attend_mfma_body(const AttnArgs& a, AttnSmem<Grou
   const int pages_per_tile = PACKED ? 16 / a.P : 1;
   const int first = split * a.per_split;
   const int last = (first + a.per_split) < a.k ? (first + a.per_split) : a.k;
-  const int n_tiles = PACKED ? (last - first + pages_per_tile - 1) / pages_per_tile : (last - first) * tiles_per_page;
+  const int n_tiles = PACKED ? (last - first + pages_per_tile - 1) / pages_per_tile
+                      : NATURAL ? ((last - first) * a.P + 15) >> 4 : (last - first) * tiles_per_page;
+  // T / P for a token of the split (below 2^20): the product with the reciprocal rounded up, off by less than T P / 2^32
+  const u32 recip = NATURAL ? 0xffffffffu / (u32)a.P + 1u : 0u;   // (P = 1: 2^32 wraps to 0, handled below)
   const int32_t* sel = a.sel_pages + (size_t)u * a.k;
   const int32_t* slots = a.sel_slots + (size_t)u * a.k;
   const char* pool_u = a.pool + (size_t)u * a.Cmax * a.page_bytes;
@@ -331,6 +355,62 @@ __device__ __forceinline__ int attend_mfma_body(const AttnArgs& a, AttnSmem<Grou
       }
       return;
     }
+    if (NATURAL) {
+      // token d of the tile: row (16 t + d) % P of entry (16 t + d) / P
+      const int t_u = __builtin_amdgcn_readfirstlane(t);
+      const int e0 = (int)((u32)(((u64)(16 * t_u) * recip) >> 32)) + (a.P == 1 ? 16 * t_u : 0), row0 = 16 * t_u - e0 * a.P;
+      auto entry = [&](int e, int& page, int& slot) {
+        page = -1; slot = -1;
+        if (e < n_entries) {
+          if (idx_in_lds) { page = sm.page[e]; slot = sm.slot[e]; }
+          else { page = sel[first + e]; slot = slots[first + e]; }
+        }
+        if (slot >= a.Cmax) slot = -1;
+      };
+      int page0 = -1, slot0 = -1, page1 = -1, slot1 = -1;   // P > 16: the tile lies in entries e0 and e0 + 1
+      if (a.P > 16) {
+        entry(e0, page0, slot0);
+        entry(e0 + 1, page1, slot1);
+        page0 = __builtin_amdgcn_readfirstlane(page0); slot0 = __builtin_amdgcn_readfirstlane(slot0);
+        page1 = __builtin_amdgcn_readfirstlane(page1); slot1 = __builtin_amdgcn_readfirstlane(slot1);
+      }
+      auto place = [&](int d, int& page, int& slot, int& row) {
+        row = row0 + d;
+        if (a.P > 16) {
+          const bool next = row >= a.P;
+          row -= next ? a.P : 0;
+          page = next ? page1 : page0;
+          slot = next ? slot1 : slot0;
+        } else {
+          const int de = a.P == 1 ? row : (int)__umulhi((u32)row, recip);
+          row -= de * a.P;
+          entry(e0 + de, page, slot);
+        }
+      };
+      int page, slot, row;
+      place(4 * (j & 3) + (j >> 2), page, slot, row);
+      const bool kok = page >= 0 && slot >= 0 && page * a.P + row < seq;
+      const u32 valid = (u32)(__ballot(kok) & 0xffffull);   // bit i: the token of row i takes part
+      tl.valid = valid;
+      if (valid == 0) return;
+#pragma unroll
+      for (int c = 0; c < 4; ++c) { tl.k[c] = make_uint4(0u, 0u, 0u, 0u); tl.v[c] = make_uint4(0u, 0u, 0u, 0u); }
+      if (kok) {
+        // (each 128-byte line is the business of two of these loads: no streaming hint)
+        const char* kb = pool_u + (size_t)slot * a.page_bytes + (u32)(row * kRowBytes + g * 16);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) tl.k[c] = *reinterpret_cast<const uint4*>(kb + c * 64);
+      }
+      const u32 mine = (valid >> (4 * g)) & 15u;
+#pragma unroll
+      for (int m = 0; m < 4; ++m) {
+        if ((mine >> m) & 1u) {                        // (a token that takes no part may hold anything: its V stays zero)
+          place(4 * m + g, page, slot, row);
+          tl.v[m] = load_stream16(pool_u + (size_t)slot * a.page_bytes + (u32)((a.P + row) * kRowBytes + j * 16));
+        }
+      }
+      return;
+    }
     const int e = t / tiles_per_page, tile = t % tiles_per_page;
     int page, slot;
     if (idx_in_lds) {
@@ -353,11 +433,12 @@ __device__ __forceinline__ int attend_mfma_body(const AttnArgs& a, AttnSmem<Grou
 #pragma unroll
     for (int c = 0; c < 4; ++c) tl.v[c] = load_stream16(tb + 256 + c * 64);
   };
-  auto compute = [&](Tile& tl) {
+  // careful: see below
+  auto compute = [&](Tile& tl, auto careful) {
     const u32 valid = tl.valid;
     if (valid == 0) return;
     const u32 mine = (valid >> (4 * g)) & 15u;          // this lane's four tokens 4g..4g+3
-    if (valid != 0xffffu) {
+    if (!NATURAL && valid != 0xffffu) {
       // a tile with tokens that take no part (the ragged end of a sequence, whose slot holds whatever
       // the store had there since a page is copied whole; with PACKED also a missing page): a
       // probability of zero does not silence a NaN or an infinity, so those tokens' V elements are
@@ -372,8 +453,16 @@ __device__ __forceinline__ int attend_mfma_body(const AttnArgs& a, AttnSmem<Grou
       }
     }
     f32x4 s = f32x4{0.f, 0.f, 0.f, 0.f};
+    if constexpr (NATURAL) {
+      // (four partial sums: an fp32 rounding at the size of the whole sum three times fewer)
+      f32x4 part[4];
 #pragma unroll
-    for (int c = 0; c < 4; ++c) s = mfma_qk<BF16>(tl.k[c], LEAN ? sm.qf[c][lane] : qfrag[c], s);
+      for (int c = 0; c < 4; ++c) part[c] = mfma_qk<BF16>(tl.k[c], LEAN ? sm.qf[c][lane] : qfrag[c], s);
+      s = (part[0] + part[1]) + (part[2] + part[3]);
+    } else {
+#pragma unroll
+      for (int c = 0; c < 4; ++c) s = mfma_qk<BF16>(tl.k[c], LEAN ? sm.qf[c][lane] : qfrag[c], s);
+    }
     float x[4];
     float mx = -INFINITY;
 #pragma unroll
@@ -392,12 +481,48 @@ __device__ __forceinline__ int attend_mfma_body(const AttnArgs& a, AttnSmem<Grou
       m = m_new;
     }
     float p[4];
+    const float ms = NATURAL && m == -INFINITY ? 0.f : m;   // (logits of minus infinity so far: no weight, but no NaN either)
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      p[e] = exp2f(x[e] - m);
+      // (natural layout: without the rounding of x, which is larger than that of the difference)
+      p[e] = !NATURAL ? exp2f(x[e] - ms) : ((mine >> e) & 1u) ? exp2f(fmaf(s[e], a.scale_log2, -ms)) : 0.f;
       l += p[e];
     }
-    if (BF16) {
+    if constexpr (NATURAL) {
+      uint2 parts[BF16 ? 3 : 2];
+      typedef std::conditional_t<BF16, __bf16, _Float16> half_t;
+      typedef half_t half4 __attribute__((ext_vector_type(4)));
+#pragma unroll
+      for (int i = 0; i < (BF16 ? 3 : 2); ++i) {
+        if (i == 0) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) p[e] *= kPScale;
+        }
+        const half4 part = {(half_t)p[0], (half_t)p[1], (half_t)p[2], (half_t)p[3]};
+        parts[i] = __builtin_bit_cast(uint2, part);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) p[e] -= (float)part[e];
+      }
+      const u32* v0 = reinterpret_cast<const u32*>(&tl.v[0]);
+      const u32* v1 = reinterpret_cast<const u32*>(&tl.v[1]);
+      const u32* v2 = reinterpret_cast<const u32*>(&tl.v[2]);
+      const u32* v3 = reinterpret_cast<const u32*>(&tl.v[3]);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const u32 pick = (e & 1) ? 0x07060302u : 0x05040100u;   // the high or the low halves of two words
+        const uint2 v = make_uint2(__builtin_amdgcn_perm(v1[e >> 1], v0[e >> 1], pick), __builtin_amdgcn_perm(v3[e >> 1], v2[e >> 1], pick));
+        uint2 f = v;
+        if constexpr (decltype(careful)::value) {
+          constexpr u32 kOne = BF16 ? 0x00800080u : 0x04000400u;   // carries an exponent of all ones into the sign
+          auto finite = [&](u32 x) -> u32 { return x & ~((((x & 0x7fff7fffu) + kOne) >> 15 & 0x00010001u) * 0xffffu); };
+          f = make_uint2(finite(v.x), finite(v.y));
+        }
+        o[e] = mfma_pv2<BF16>(v, f, parts[0], parts[1], o[e]);
+        // (the third part through the same instruction: an accumulator that went from the 32-wide MFMA straight to the
+        // 16-wide one, without a wait between them, gave wrong sums)
+        if constexpr (BF16) o[e] = mfma_pv2<BF16>(f, f, parts[2], make_uint2(0u, 0u), o[e]);
+      }
+    } else if (BF16) {
       const bf16x4 hi = {(__bf16)p[0], (__bf16)p[1], (__bf16)p[2], (__bf16)p[3]};
       const bf16x4 lo = {(__bf16)(p[0] - (float)hi[0]), (__bf16)(p[1] - (float)hi[1]), (__bf16)(p[2] - (float)hi[2]),
                          (__bf16)(p[3] - (float)hi[3])};
@@ -421,26 +546,42 @@ __device__ __forceinline__ int attend_mfma_body(const AttnArgs& a, AttnSmem<Grou
       }
     }
   };
-  if (LEAN) {
-    Tile ta, tb2;
-    issue(ta, w);
-    for (int t = w; t < n_tiles; t += 2 * NW) {
-      issue(tb2, t + NW);
-      compute(ta);
-      issue(ta, t + 2 * NW);
-      compute(tb2);
+  auto run = [&](auto careful) {
+    if (LEAN) {
+      Tile ta, tb2;
+      issue(ta, w);
+      for (int t = w; t < n_tiles; t += 2 * NW) {
+        issue(tb2, t + NW);
+        compute(ta, careful);
+        issue(ta, t + 2 * NW);
+        compute(tb2, careful);
+      }
+    } else {
+      Tile ta, tb2, tc;
+      issue(ta, w);
+      issue(tb2, w + NW);
+      for (int t = w; t < n_tiles; t += 3 * NW) {
+        issue(tc, t + 2 * NW);
+        compute(ta, careful);
+        issue(ta, t + 3 * NW);
+        compute(tb2, careful);
+        issue(tb2, t + 4 * NW);
+        compute(tc, careful);
+      }
     }
-  } else {
-    Tile ta, tb2, tc;
-    issue(ta, w);
-    issue(tb2, w + NW);
-    for (int t = w; t < n_tiles; t += 3 * NW) {
-      issue(tc, t + 2 * NW);
-      compute(ta);
-      issue(ta, t + 3 * NW);
-      compute(tb2);
-      issue(tb2, t + 4 * NW);
-      compute(tc);
+  };
+  run(std::false_type());
+  if constexpr (NATURAL) {
+    // An infinity in V times a lower part of P, which may be zero or negative, is not the infinity that P times V
+    // is.  A sum that is not finite is therefore formed again with such elements meeting the first part only.
+    float sum = 0.f;
+#pragma unroll
+    for (int c = 0; c < 8; ++c) sum += (o[c][0] * 0.f + o[c][1] * 0.f) + (o[c][2] * 0.f + o[c][3] * 0.f);
+    if (__any(sum != 0.f)) {                             // (0 x infinity and 0 x NaN are NaN)
+#pragma unroll
+      for (int c = 0; c < 8; ++c) o[c] = f32x4{0.f, 0.f, 0.f, 0.f};
+      m = -INFINITY; l = 0.f;
+      run(std::true_type());
     }
   }
 
@@ -448,11 +589,11 @@ __device__ __forceinline__ int attend_mfma_body(const AttnArgs& a, AttnSmem<Grou
   l += __shfl_xor(l, 16, kWave);
   l += __shfl_xor(l, 32, kWave);
   if (j < G) {
-    // O^T C tiles: lane (j, g) register e of tile c holds dim 16c + 4g + e of head j
+    // O^T C tiles: lane (j, g) register e of tile c holds dim 16c + 4g + e of head j (natural layout: 8 (4g + e) + c)
 #pragma unroll
     for (int c = 0; c < 8; ++c)
 #pragma unroll
-      for (int e = 0; e < 4; ++e) sm.acc[w][j][16 * c + 4 * g + e] = o[c][e];
+      for (int e = 0; e < 4; ++e) sm.acc[w][j][NATURAL ? 8 * (4 * g + e) + c : 16 * c + 4 * g + e] = o[c][e] * (1.f / kPScale);
     if (g == 0) { sm.m[w][j] = m; sm.l[w][j] = l; }
   }
   return finish_split<GT, NT>(a, sm, u, split) ? 1 : 0;

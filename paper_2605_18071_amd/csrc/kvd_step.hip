@@ -227,7 +227,7 @@ __device__ __forceinline__ void step_attend_role(StepArgsPtr ap, int li, int u, 
   }
   if (ts) ts[4] = 2LL | ((long long)u << 8) | ((long long)split << 32);
   typename StepSmem<NT>::Attn& sm = *reinterpret_cast<typename StepSmem<NT>::Attn*>(smem_raw);
-  const int done = attend_mfma_body<BF16, 0, NT, true, LEAN, PACKED>(a.at, sm, u, split, ts ? ts + 1 : nullptr);
+  const int done = attend_mfma_body<BF16, 0, NT, true, LEAN, PACKED ? kLayoutPacked : kLayoutTiles>(a.at, sm, u, split, ts ? ts + 1 : nullptr);
   if (done < 0 && threadIdx.x == 0) __hip_atomic_store(a.at.error, 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   if (ts) ts[2] = ts[3] = wall_clock64();
 }
