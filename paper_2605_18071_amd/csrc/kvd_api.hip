@@ -258,14 +258,15 @@ int kvd_create(const kvd_config* cfg, kvd_ctx** out) {
   c->S = S;
   // The one-launch step runs one workgroup per CU: 512 threads with 256 registers per lane (three
   // tile buffers in the attention role), or, for units of more than 8192 pages, 1024 threads with
-  // 128.  Its attention splits: about one workgroup per CU in the first form (at least two tiles
-  // per wave), four tiles per wave in the second.
+  // 128.  Its attention splits: about one workgroup per CU in the first form (at least one tile per wave: with
+  // two, 8 units of 64 pages took 16.7 us instead of 15.9, of 32 pages 16.3 instead of 15.4), four tiles per
+  // wave in the second.
   c->S1 = S;
   c->step_threads = c->NP > 8192 ? 1024 : 512;
   if (cfg->attn_splits == 0) {
     const int tiles = sel_tiles;
     int S2 = c->step_threads == 1024 ? tiles / 64 : (c->n_cus + c->U / 2) / c->U;
-    const int cap = c->step_threads == 1024 ? KVD_MAX_SPLITS : tiles / 16;
+    const int cap = c->step_threads == 1024 ? KVD_MAX_SPLITS : tiles / 8;
     if (S2 > cap) S2 = cap;
     if (S2 > KVD_MAX_SPLITS) S2 = KVD_MAX_SPLITS;
     if (S2 < (c->k + 511) / 512) S2 = (c->k + 511) / 512;   // a split's entries are staged in LDS, 512 at most
@@ -992,12 +993,13 @@ int kvd_calibrate_step_shape(kvd_ctx* ctx, int32_t layer, int32_t n_layers, int3
   struct Timed { kvd_shape shape; double us; bool is_rule; };
   std::vector<Timed> shapes;
   const kvd_shape nothing = {0, 0, 0, 0};
-  const kvd_shape rule = kvd_step_shape(c, multi, &nothing);
+  const int per_launch = n_layers < c->n_sets ? n_layers : c->n_sets;
+  const kvd_shape rule = kvd_step_shape(c, multi, &nothing, per_launch);
   auto same = [](const kvd_shape& a, const kvd_shape& b) {
     return a.passes == b.passes && a.n_score == b.n_score && a.splits == b.splits && a.groups == b.groups;
   };
   auto add = [&](const kvd_shape& want) {
-    const kvd_shape e = kvd_step_shape(c, multi, &want);
+    const kvd_shape e = kvd_step_shape(c, multi, &want, per_launch);
     if (!kvd_step_shape_ok(c, e)) return;
     for (const Timed& x : shapes)
       if (same(x.shape, e)) return;

@@ -153,8 +153,9 @@ int kvd_attn_splits(int layout, int U, int k, int P, int cus);
 // The whole step as one launch (kvd_step.hip); usable when kvd_single_launch_ok.
 bool kvd_single_launch_ok(const kvd_ctx* c);
 // The shape a launch takes: `want` (default: what the context holds for that kind of launch) with
-// its zeros filled in by the rule and the scoring workgroups capped at the number of chunks.
-kvd_shape kvd_step_shape(const kvd_ctx* c, int multi_layer, const kvd_shape* want = nullptr);
+// its zeros filled in by the rule and the scoring workgroups capped at the number of chunks.  n_layers: layers of the
+// launch (0 = the most that one covers).
+kvd_shape kvd_step_shape(const kvd_ctx* c, int multi_layer, const kvd_shape* want = nullptr, int n_layers = 0);
 bool kvd_step_shape_ok(const kvd_ctx* c, const kvd_shape& effective);
 // Layers [layer, layer + n_layers) of one decode step in one launch, layer `layer + i` in scratch set i
 // (q / out / lse: the layers one after another); n_layers == 1: the context's current set.

@@ -300,10 +300,21 @@ static void launch_step(int threads, int ipt, const StepArgs& a, int n_blocks, h
 // such that the chunks of a group fill whole rounds of its scoring workgroups (time ~ rounds x
 // passes; at equal cost the coarser chunk wins while every scoring workgroup still gets one: fewer
 // reports and acknowledgement waits per byte); splits as kvd_create chose them.
-kvd_shape kvd_step_shape(const kvd_ctx* c, int multi_layer, const kvd_shape* want) {
+//
+// A launch of several layers does not need the splits to fill the chip, the other layers do that; what more splits
+// cost (start, polls, partials, merge) is then all that is left of them.  Measured over 2 to 128 units, 2 to 8 layers,
+// 512-thread form: the fewest splits with which the launch has 5/8 of a workgroup per CU attending, or, where the
+// launch is so small that all its workgroups are resident at once, as many as keep it so; and scoring chunks of
+// two passes as soon as they fill 3/4 of the CUs.  us per layer-step before and after: 64 units of 2048 pages,
+// 8 layers 22.5 -> 18.1, 4 layers 23.5 -> 19.8, 2 layers 25.9 -> 23.5; 128 units (6 layers) 41.6 -> 36.0; 8 units of
+// 512 pages, 8 layers 3.85 -> 2.85, of 4096 pages 8.6 -> 6.9; 32 units of 8192 pages, 4 layers 29.1 -> 26.5.
+kvd_shape kvd_step_shape(const kvd_ctx* c, int multi_layer, const kvd_shape* want, int n_layers) {
   kvd_shape w = want ? *want : c->shape[multi_layer ? 1 : 0];
+  if (!multi_layer) n_layers = 1;
+  else if (n_layers <= 0) n_layers = c->n_sets;         // (the most layers a launch of this context covers)
+  const bool wide = c->step_threads == kvd::kStepThreadsWide;
   const int score_np = c->Nc > 0 ? c->Nc : c->NP;
-  const int chunk_pages = c->step_threads == kvd::kStepThreadsWide ? kvd::kStepThreadsWide : kvd::kStepThreads;
+  const int chunk_pages = wide ? kvd::kStepThreadsWide : kvd::kStepThreads;
   const int slots = c->n_cus;
   kvd_shape e;
   e.groups = w.groups > 0 ? w.groups : 1;
@@ -326,12 +337,24 @@ kvd_shape kvd_step_shape(const kvd_ctx* c, int multi_layer, const kvd_shape* wan
       const long long cost = rounds * cand;
       if (best_cost < 0 || cost < best_cost || (cost == best_cost && chunks * Ug >= ns)) { best_cost = cost; ps = cand; }
     }
+    if (ps == 1 && n_layers > 1 && !wide && score_np >= 2 * chunk_pages &&
+        (long long)n_layers * c->U * ((score_np + chunk_pages - 1) / chunk_pages) >= 3LL * slots / 4)
+      ps = 2;
   }
   const int chunks = (score_np + chunk_pages * ps - 1) / (chunk_pages * ps);
   if (ns > Ug * chunks) ns = Ug * chunks;
   e.passes = ps;
   e.n_score = ns;
   e.splits = w.splits > 0 ? w.splits : c->S1;
+  if (w.splits <= 0 && n_layers > 1 && !wide && c->cfg.attn_splits == 0) {
+    const int units = n_layers * c->U;
+    int s = (slots * 5 / 8 + units - 1) / units;
+    const int resident = (slots / n_layers - e.groups * ns - c->U) / c->U;
+    if (s < resident) s = resident;
+    const int least = (c->k + kvd::kAttnIdxCap - 1) / kvd::kAttnIdxCap;
+    if (s < least) s = least;
+    if (s < e.splits) e.splits = s;
+  }
   return e;
 }
 
@@ -368,7 +391,7 @@ hipError_t kvd_launch_step(kvd_ctx* c, int layer, int n_layers, int step, const 
   a.at = kvd_attn_args(c, layer, q, c->d_sel_pages, c->d_sel_slots, out, lse, 0);
   a.at.fuse_merge = 1;
   a.at.sel_entry = c->d_sel_entry;
-  const kvd_shape shape = kvd_step_shape(c, n_layers > 1);
+  const kvd_shape shape = kvd_step_shape(c, n_layers > 1, nullptr, n_layers);
   a.at.S = shape.splits;
   a.at.per_split = (c->k + shape.splits - 1) / shape.splits;
   a.score_done = c->d_score_done;
