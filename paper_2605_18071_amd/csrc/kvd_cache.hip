@@ -355,40 +355,58 @@ __global__ __launch_bounds__(kSummaryThreads) void summaries_kernel(const uint16
 // store (written across the host link), in the slot of its page if that page is resident, and the
 // page's index entry is recomputed as the mean over its valid tokens including the new one (fp64,
 // token order, rounded once — the same definition as summaries_kernel).
+// A chain of latencies, the longest of which is the read of the page's earlier keys across the host
+// link: their first 16 rows are asked for at once, 16 bytes per thread, and the search for the slot and
+// the stores to host and slot go on while they travel.  (32 units, pages of 16: 5.1 us
+// with the search first and 2-byte reads of the keys after it, 4.5 us so; 2.0 instead of 3.4 us for a page that begins.)
+constexpr int kAppendThreads = 256, kAppendRows = 16;
 template <bool BF16, int TILED>
-__global__ __launch_bounds__(256) void append_kernel(uint16_t* __restrict__ store,          // [U][NP][2][P][D] of the layer
-                                                    uint16_t* __restrict__ summ,           // [U][NP][D]
-                                                    char* __restrict__ pool,               // [U][Cmax] slots
-                                                    const int32_t* __restrict__ slot_page, // [U][Cmax]
-                                                    const int32_t* __restrict__ capacity,  // [U]
-                                                    const uint16_t* __restrict__ k_new,    // [U][D]
-                                                    const uint16_t* __restrict__ v_new,    // [U][D]
-                                                    const int32_t* __restrict__ seq_len, int NP, int P, int Cmax,
-                                                    int Hkv, unsigned page_bytes) {
+__global__ __launch_bounds__(kAppendThreads) void append_kernel(uint16_t* __restrict__ store,          // [U][NP][2][P][D] of the layer
+                                                               uint16_t* __restrict__ summ,           // [U][NP][D]
+                                                               char* __restrict__ pool,               // [U][Cmax] slots
+                                                               const int32_t* __restrict__ slot_page, // [U][Cmax]
+                                                               const int32_t* __restrict__ capacity,  // [U]
+                                                               const uint16_t* __restrict__ k_new,    // [U][D]
+                                                               const uint16_t* __restrict__ v_new,    // [U][D]
+                                                               const int32_t* __restrict__ seq_len, int NP, int P, int Cmax,
+                                                               int Hkv, unsigned page_bytes) {
   __shared__ int found_slot;
+  __shared__ uint4 rows[kAppendRows][kHeadDim / 8];
   const int u = blockIdx.x, tid = threadIdx.x;
   const int b = u / Hkv;
   const int t = seq_len[b];
-  const int page = t / P, o = t % P;
-  if (page >= NP) return;                                // no room: the host checks this before launching
-  if (tid == 0) found_slot = -1;
-  __syncthreads();
-  uint16_t* kpage = store + ((size_t)u * NP + page) * (size_t)(2 * P * kHeadDim);
-  uint16_t* vpage = kpage + (size_t)P * kHeadDim;
+  const int C = capacity[u];
   const uint16_t* kn = k_new + (size_t)u * kHeadDim;
   const uint16_t* vn = v_new + (size_t)u * kHeadDim;
+  const uint4 fresh = tid < 32 ? *reinterpret_cast<const uint4*>((tid < 16 ? kn : vn) + (tid & 15) * 8) : make_uint4(0u, 0u, 0u, 0u);
+  const uint16_t k_d = kn[tid % kHeadDim], v_d = vn[tid % kHeadDim];
+  if (tid == 0) found_slot = -1;
+  __syncthreads();
+  const int page = t / P, o = t % P;
+  if (page >= NP) return;                                // no room: the host checks this before launching
+  uint16_t* kpage = store + ((size_t)u * NP + page) * (size_t)(2 * P * kHeadDim);
+  uint16_t* vpage = kpage + (size_t)P * kHeadDim;
+
+  // the first earlier keys set out
+  uint4 early = make_uint4(0u, 0u, 0u, 0u);
+  if (tid / 16 < o) early = reinterpret_cast<const uint4*>(kpage)[tid];
 
   // 1. the host store: 16 lanes x 16 bytes for K, 16 for V
-  if (tid < 32) {
-    const int ch = tid & 15;
-    const uint4 val = *reinterpret_cast<const uint4*>((tid < 16 ? kn : vn) + ch * 8);
-    *reinterpret_cast<uint4*>((tid < 16 ? kpage : vpage) + (size_t)o * kHeadDim + ch * 8) = val;
-  }
+  if (tid < 32) *reinterpret_cast<uint4*>((tid < 16 ? kpage : vpage) + (size_t)o * kHeadDim + (tid & 15) * 8) = fresh;
 
   // 2. is the page resident?
-  const int C = capacity[u];
-  for (int s = tid; s < C; s += 256)
-    if (slot_page[(size_t)u * Cmax + s] == page) found_slot = s;      // at most one slot holds the page
+  const int32_t* spage = slot_page + (size_t)u * Cmax;
+  for (int s0 = 0; s0 < C; s0 += 4 * kAppendThreads) {
+    int sp[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int s = s0 + i * kAppendThreads + tid;
+      sp[i] = s < C ? spage[s] : -1;
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      if (sp[i] == page) found_slot = s0 + i * kAppendThreads + tid;    // at most one slot holds the page
+  }
   __syncthreads();
   const int slot = found_slot;
   if (slot >= 0 && tid < kHeadDim) {
@@ -401,8 +419,8 @@ __global__ __launch_bounds__(256) void append_kernel(uint16_t* __restrict__ stor
       uint16_t* kdst = reinterpret_cast<uint16_t*>(sl + (size_t)((c * 4 + (r32 >> 3)) * P + o) * 16) + (d & 7);
       uint16_t* vdst = reinterpret_cast<uint16_t*>(sl + (size_t)P * kRowBytes + (size_t)((c * (P >> 2) + (o >> 2)) * 16 + (d & 15)) * 16) +
                        4 * (r32 >> 4) + (o & 3);
-      *kdst = kn[d];
-      *vdst = vn[d];
+      *kdst = k_d;
+      *vdst = v_d;
     } else if (TILED) {
       // tile layout (kvd_tile_layout.h): K element [row][d] sits in chunk d/32, lane row + 16 ((d%32)/8),
       // element d%8; V element [row][d] in chunk d/32, lane d%16 + 16 (row/4), element 4 ((d%32)/16) + row%4
@@ -412,33 +430,36 @@ __global__ __launch_bounds__(256) void append_kernel(uint16_t* __restrict__ stor
       uint16_t* kdst = reinterpret_cast<uint16_t*>(tile + (c * 64 + (r32 >> 3) * 16 + row) * 16) + (d & 7);
       uint16_t* vdst = reinterpret_cast<uint16_t*>(tile + kTilePartBytes + (c * 64 + (row >> 2) * 16 + (d & 15)) * 16) +
                        4 * (r32 >> 4) + (row & 3);
-      *kdst = kn[d];
-      *vdst = vn[d];
+      *kdst = k_d;
+      *vdst = v_d;
     } else {
       uint16_t* k16 = reinterpret_cast<uint16_t*>(sl);
-      k16[(size_t)o * kHeadDim + d] = kn[d];
-      k16[(size_t)(P + o) * kHeadDim + d] = vn[d];
+      k16[(size_t)o * kHeadDim + d] = k_d;
+      k16[(size_t)(P + o) * kHeadDim + d] = v_d;
     }
   }
 
   // 3. the index entry of the page: tokens 0..o-1 from the host store, then the new key
-  if (tid < kHeadDim) {
-    const int d = tid;
-    double acc = 0.0;
-    for (int t0 = 0; t0 < o; t0 += 16) {
-      uint16_t raw[16];
-#pragma unroll
-      for (int j = 0; j < 16; ++j) {
-        const int tt = (t0 + j) < o ? (t0 + j) : (o - 1);
-        raw[j] = kpage[(size_t)tt * kHeadDim + d];
-      }
-#pragma unroll
-      for (int j = 0; j < 16; ++j)
-        if (t0 + j < o) acc += (double)(BF16 ? as_f32((u32)raw[j] << 16) : (float)__builtin_bit_cast(_Float16, raw[j]));
+  double acc = 0.0;
+  for (int t0 = 0; t0 < o; t0 += kAppendRows) {
+    if (t0 > 0) {
+      __syncthreads();                                   // the rows before these have been added up
+      if (t0 + tid / 16 < o) early = reinterpret_cast<const uint4*>(kpage)[t0 * 16 + tid];
     }
-    const uint16_t kb = kn[d];
-    acc += (double)(BF16 ? as_f32((u32)kb << 16) : (float)__builtin_bit_cast(_Float16, kb));
-    summ[((size_t)u * NP + page) * kHeadDim + d] = f64_to_kv<BF16>(acc / (double)(o + 1));
+    rows[tid / 16][tid % 16] = early;
+    __syncthreads();
+    if (tid < kHeadDim) {
+      const uint16_t* col = reinterpret_cast<const uint16_t*>(&rows[0][0]) + tid;
+      const int n = o - t0 < kAppendRows ? o - t0 : kAppendRows;
+      for (int r = 0; r < n; ++r) {
+        const uint16_t e = col[r * kHeadDim];
+        acc += (double)(BF16 ? as_f32((u32)e << 16) : (float)__builtin_bit_cast(_Float16, e));
+      }
+    }
+  }
+  if (tid < kHeadDim) {
+    acc += (double)(BF16 ? as_f32((u32)k_d << 16) : (float)__builtin_bit_cast(_Float16, k_d));
+    summ[((size_t)u * NP + page) * kHeadDim + tid] = f64_to_kv<BF16>(acc / (double)(o + 1));
   }
 }
 
@@ -542,7 +563,7 @@ hipError_t kvd_launch_append(kvd_ctx* c, int layer, const void* k_new, const voi
   const int32_t* cap = c->d_capacity + lu;
   const uint16_t* kn = reinterpret_cast<const uint16_t*>(k_new);
   const uint16_t* vn = reinterpret_cast<const uint16_t*>(v_new);
-  dim3 grid(c->U), block(256);
+  dim3 grid(c->U), block(kvd::kAppendThreads);
 #define KVD_APPEND(BF, TL)                                                                                          \
   hipLaunchKernelGGL((append_kernel<BF, TL>), grid, block, 0, s, store, summ, pool, slot_page, cap, kn, vn, c->d_seq_len, \
                      c->NP, c->P, c->Cmax, c->Hkv, (unsigned)c->page_bytes)
