@@ -898,7 +898,7 @@ __device__ __forceinline__ bool select_resolve_body(const FastArgs& a, int u, Fa
       if (on && slot >= 0) tile_copy_phase_b<HANDOFF>(dst_tile, sm.a.vt[grp], gt);
       __syncthreads();
     }
-  } else {
+  } else if constexpr (!HANDOFF) {                      // (the one-launch step has no natural slots)
     const unsigned units = a.page_bytes / 16;
     auto ends = [&](int jm, const uint4*& src, uint4*& dst) -> bool {
       if (jm >= m || sm.assign[jm] == kAbsent) return false;
@@ -906,8 +906,8 @@ __device__ __forceinline__ bool select_resolve_body(const FastArgs& a, int u, Fa
       dst = reinterpret_cast<uint4*>(pool_u + (size_t)sm.assign[jm] * a.page_bytes);
       return true;
     };
-    // two pages of a group in flight where one does not give each of its threads a load
-    const int pages = units <= 256 ? 2 : 1;
+    // BIG: two pages of a group in flight where one does not give each of its threads a load
+    const int pages = BIG && units <= 256 ? 2 : 1;
     for (int jm = grp; jm < m; jm += pages * kCopyGroups) {
       const uint4 *s0 = nullptr, *s1 = nullptr;
       uint4 *d0 = nullptr, *d1 = nullptr;
