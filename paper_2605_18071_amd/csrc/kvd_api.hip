@@ -251,23 +251,18 @@ int kvd_create(const kvd_config* cfg, kvd_ctx** out) {
   c->scale = cfg->softmax_scale > 0.f ? cfg->softmax_scale : 1.0f / sqrtf((float)c->D);
   c->page_bytes = (size_t)2 * c->P * c->D * 2;
   int S = cfg->attn_splits;
-  // 16-token tiles of a unit's selection (only pages of a multiple of 16 tokens do not share tiles)
-  const int sel_tiles = (c->k * c->P + 15) / 16;
-  if (S == 0) S = kvd_attn_splits(c->tiled, c->U, c->k, c->P, c->n_cus);
+  if (S == 0) S = kvd_attn_splits(c->tiled == kvd::kLayoutNatural ? 4 : 16, c->U, c->k, c->P, c->n_cus);
   if (S > c->k) S = c->k;
   c->S = S;
   // The one-launch step runs one workgroup per CU: 512 threads with 256 registers per lane (three
   // tile buffers in the attention role), or, for units of more than 8192 pages, 1024 threads with
-  // 128.  Its attention splits: about one workgroup per CU in the first form (at least one tile per wave: with
-  // two, 8 units of 64 pages took 16.7 us instead of 15.9, of 32 pages 16.3 instead of 15.4), four tiles per
-  // wave in the second.
+  // 128.  Its attention splits: the rule of the stand-alone kernel in the first form, four tiles per wave in the
+  // second.
   c->S1 = S;
   c->step_threads = c->NP > 8192 ? 1024 : 512;
   if (cfg->attn_splits == 0) {
-    const int tiles = sel_tiles;
-    int S2 = c->step_threads == 1024 ? tiles / 64 : (c->n_cus + c->U / 2) / c->U;
-    const int cap = c->step_threads == 1024 ? KVD_MAX_SPLITS : tiles / 8;
-    if (S2 > cap) S2 = cap;
+    const int sel_tiles = (c->k * c->P + 15) / 16;      // 16-token tiles of a unit's selection
+    int S2 = c->step_threads == 1024 ? sel_tiles / 64 : kvd_attn_splits(c->P <= 16 && sel_tiles >= 32 ? 8 : 16, c->U, c->k, c->P, c->n_cus);
     if (S2 > KVD_MAX_SPLITS) S2 = KVD_MAX_SPLITS;
     if (S2 < (c->k + 511) / 512) S2 = (c->k + 511) / 512;   // a split's entries are staged in LDS, 512 at most
     if (S2 > c->k) S2 = c->k;

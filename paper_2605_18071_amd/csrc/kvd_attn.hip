@@ -73,15 +73,26 @@ static bool dispatch_group(int G, int layout, const AttnArgs& a, dim3 grid, hipS
 }  // namespace kvd
 
 // Split-K factor where the caller leaves it open: one 512-thread workgroup runs per CU, so about one workgroup per
-// CU in the grid.  Every wave keeps at least two tiles of 16 tokens; over natural slots, where a tile costs a
-// wave more, one (2 units of 40 pages of 12 tokens: 23.8 us a step with the first rule, 19.8 with the second).
-int kvd_attn_splits(int layout, int U, int k, int P, int cus) {
+// CU in the grid, but
+//  - a split keeps at least `least` tiles of 16 tokens for its eight waves: 16 in the stand-alone kernel over tiles (where
+//    fewer made no difference), 8 in the one-launch step with pages of up to 16 tokens and at least 32 tiles (8 units
+//    of 64 pages: 16.7 us with two tiles per wave, 15.9 with one; 2 splits instead of 1 gain nothing, and with larger
+//    pages a split's share comes in steps of several tiles: 20 units of 21 pages of 64 tokens 21.1 and 21.8), 4 over
+//    natural slots, where a tile costs a wave more (2 units of 40 pages of 12 tokens: 23.8 us with 16, 18.8 with 4);
+//  - beyond 16 splits a split keeps 32 tiles: the last split to arrive fetches the partials of all the others, and
+//    with few units that costs more than shorter splits save.  us per step with a split per CU and with this rule: 8
+//    units of 128 pages of 64 tokens 36.1 and 34.4, 2 units of 1024 pages of 16 31.1 and 29.1;
+//  - no split is left without pages.
+int kvd_attn_splits(int least, int U, int k, int P, int cus) {
   const int tiles = (k * P + 15) / 16;                 // of a unit's selection
   int S = (cus + U / 2) / U;
-  const int most = layout == kvd::kLayoutNatural ? tiles / 8 : tiles / 16;
-  if (S > most) S = most;
+  if (S > tiles / least) S = tiles / least;
+  if (S > 16 && S > tiles / 32) S = tiles / 32 > 16 ? tiles / 32 : 16;
   if (S > KVD_MAX_SPLITS) S = KVD_MAX_SPLITS;
-  return S < 1 ? 1 : S;
+  if (S > k) S = k;
+  if (S < 1) S = 1;
+  const int per_split = (k + S - 1) / S;
+  return (k + per_split - 1) / per_split;
 }
 
 kvd::AttnArgs kvd_attn_args(kvd_ctx* c, int layer, const void* q, const int32_t* sel_pages, const int32_t* sel_slots,
@@ -190,7 +201,7 @@ extern "C" int kvd_sparse_decode_attn_noalloc(const void* q, const void* slot_po
   }
   const int U = batch * n_kv_heads;
   const int layout = slot_layout_of(page_size);
-  int S = attn_splits == 0 ? kvd_attn_splits(layout, U, topk_pages, page_size, cus) : attn_splits;
+  int S = attn_splits == 0 ? kvd_attn_splits(layout == kLayoutNatural ? 4 : 16, U, topk_pages, page_size, cus) : attn_splits;
   if (S > topk_pages) S = topk_pages;
   // the scratch array, cut into tickets [U], (max, sum) [U][S][G][2] and accumulators [U][S][G][D]
   const size_t rows = (size_t)U * S * G;

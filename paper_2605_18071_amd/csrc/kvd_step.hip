@@ -301,13 +301,12 @@ static void launch_step(int threads, int ipt, const StepArgs& a, int n_blocks, h
 // passes; at equal cost the coarser chunk wins while every scoring workgroup still gets one: fewer
 // reports and acknowledgement waits per byte); splits as kvd_create chose them.
 //
-// A launch of several layers does not need the splits to fill the chip, the other layers do that; what more splits
-// cost (start, polls, partials, merge) is then all that is left of them.  Measured over 2 to 128 units, 2 to 8 layers,
-// 512-thread form: the fewest splits with which the launch has 5/8 of a workgroup per CU attending, or, where the
-// launch is so small that all its workgroups are resident at once, as many as keep it so; and scoring chunks of
-// two passes as soon as they fill 3/4 of the CUs.  us per layer-step before and after: 64 units of 2048 pages,
-// 8 layers 22.5 -> 18.1, 4 layers 23.5 -> 19.8, 2 layers 25.9 -> 23.5; 128 units (6 layers) 41.6 -> 36.0; 8 units of
-// 512 pages, 8 layers 3.85 -> 2.85, of 4096 pages 8.6 -> 6.9; 32 units of 8192 pages, 4 layers 29.1 -> 26.5.
+// Launches of several layers take scoring chunks of two passes as soon as those fill 3/4 of the CUs: the other layers
+// cover what a coarser chunk leaves idle (us per layer-step with one pass and with two: 64 units of 2048 pages, 8
+// layers 22.6 and 21.7, 8 units of 4096 pages 7.2 and 6.7, 128 units of 2048 pages 41.5 and 39.4; but 8 units of
+// 1024 pages, 4 layers 5.7 and 6.1).  Fewer splits would gain more there (64 units: 18.1 with one instead of four),
+// but the order of the fp32 sums would then differ from that of the layers stepped one by one: the calibration may
+// choose them, the rule does not.
 kvd_shape kvd_step_shape(const kvd_ctx* c, int multi_layer, const kvd_shape* want, int n_layers) {
   kvd_shape w = want ? *want : c->shape[multi_layer ? 1 : 0];
   if (!multi_layer) n_layers = 1;
@@ -346,15 +345,6 @@ kvd_shape kvd_step_shape(const kvd_ctx* c, int multi_layer, const kvd_shape* wan
   e.passes = ps;
   e.n_score = ns;
   e.splits = w.splits > 0 ? w.splits : c->S1;
-  if (w.splits <= 0 && n_layers > 1 && !wide && c->cfg.attn_splits == 0) {
-    const int units = n_layers * c->U;
-    int s = (slots * 5 / 8 + units - 1) / units;
-    const int resident = (slots / n_layers - e.groups * ns - c->U) / c->U;
-    if (s < resident) s = resident;
-    const int least = (c->k + kvd::kAttnIdxCap - 1) / kvd::kAttnIdxCap;
-    if (s < least) s = least;
-    if (s < e.splits) e.splits = s;
-  }
   return e;
 }
 
