@@ -268,8 +268,14 @@ int kvd_create(const kvd_config* cfg, kvd_ctx** out) {
     if (S2 > c->k) S2 = c->k;
     c->S1 = S2 < 1 ? 1 : S2;
   }
-  // (room in the partials for the splits a calibration of the launch shape may try: twice the rule's)
+  // room in the partials for the splits that kvd_set_step_shape takes and a calibration of the launch shape tries: twice
+  // the rule's, or twice an attention workgroup per CU with two tiles per wave where that is more
   c->S1_max = cfg->attn_splits == 0 ? 2 * c->S1 : c->S1;
+  if (cfg->attn_splits == 0 && c->step_threads == 512) {
+    const int tiles = (c->k * c->P + 15) / 16, full = (c->n_cus + c->U / 2) / c->U;
+    const int most = full < tiles / 16 ? full : tiles / 16;
+    if (c->S1_max < 2 * most) c->S1_max = 2 * most;
+  }
   if (c->S1_max > KVD_MAX_SPLITS) c->S1_max = KVD_MAX_SPLITS;
   if (c->S1_max > c->k) c->S1_max = c->k;
   if (c->S1_max < c->S1) c->S1_max = c->S1;

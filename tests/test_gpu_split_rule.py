@@ -1,0 +1,35 @@
+"""Where the split-K rule changes: a split keeps whole pages, none is empty, what kvd_set_step_shape took before it still
+takes, and the outputs do not depend on the split (against one split, up to the order of the fp32 sums)."""
+import pytest
+import torch
+
+from tests import helpers as H
+from tests.test_gpu_parity import small
+
+pytestmark = pytest.mark.gpu
+
+if torch.cuda.is_available():
+    from tests import gpu_rig as R
+
+
+@pytest.mark.parametrize("kw,rule,most", [
+    (dict(ctx=16 * 300, topk_pages=31, capacity=40), 1, 2),              # 31 tiles: too few for a tile per wave
+    (dict(ctx=16 * 300, topk_pages=32, capacity=40), 4, 8),              # 32
+    (dict(ctx=16 * 600, topk_pages=256, capacity=300), 16, 32),          # 256 tiles: the most splits before 32 tiles each
+    (dict(ctx=16 * 2000, topk_pages=1024, capacity=1100), 32, 64),       # 1024 tiles
+    (dict(ctx=64 * 100, page=64, topk_pages=21, capacity=30), 5, 10),    # 84 tiles in 21 pages
+])
+def test_rule_and_limits(kw, rule, most):
+    w = small("split-rule", **{**dict(batch=1, n_kv_heads=4, n_q_heads=8, heavy_count=3, steps=2), **kw})
+    rig, one = R.Rig(w, micro_batches=-1), R.Rig(w, micro_batches=-1, attn_splits=max(1, -(-w.topk_pages // 512)))
+    assert rig.kvd.step_shape()[2] == rule
+    rig.kvd.set_step_shape(attn_splits=most)                            # accepted
+    rig.kvd.set_step_shape()
+    for t, q in enumerate(R.W.query_stream(w, rig.q0, w.steps, R.DEV)):
+        rig.step(0, t, q[0])
+        one.step(0, t, q[0])
+        assert torch.equal(rig.sel_pages, one.sel_pages)
+        # (the probabilities that multiply V keep 16 bits, relative to each split's own maximum)
+        assert H.attn_rel_err(rig.n_out.reshape(-1, 128), one.n_out.reshape(-1, 128)) <= 2.0 ** -14
+    rig.close()
+    one.close()
