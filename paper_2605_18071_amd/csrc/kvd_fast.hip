@@ -15,17 +15,19 @@ __global__ __launch_bounds__(kFastThreads) void select_resolve_kernel(FastArgs a
   select_resolve_body<kFastThreads, IPT, DO_SELECT, DO_RESOLVE, false>(a, blockIdx.x + a.u0, sm);
 }
 
-template <bool DO_SELECT, bool DO_RESOLVE>
+template <bool DO_SELECT, bool DO_RESOLVE, bool HELD>
 __global__ __launch_bounds__(kFastThreads) void select_resolve_big_kernel(FastArgs a) {
   __shared__ FastSmem<kFastThreads, true> sm;
-  select_resolve_body<kFastThreads, 4, DO_SELECT, DO_RESOLVE, false, ScoresAlreadyThere, false, true>(a, blockIdx.x + a.u0, sm);
+  select_resolve_body<kFastThreads, 4, DO_SELECT, DO_RESOLVE, false, ScoresAlreadyThere, false, true, HELD>(a, blockIdx.x + a.u0, sm);
 }
 
 template <bool SEL, bool RES>
 static void launch_fast(bool big, int ipt, const FastArgs& a, int n_units, hipStream_t s) {
   dim3 grid(n_units), block(kFastThreads);
-  if (big)
-    hipLaunchKernelGGL((select_resolve_big_kernel<SEL, RES>), grid, block, 0, s, a);
+  if (big && SEL && ipt <= 32)
+    hipLaunchKernelGGL((select_resolve_big_kernel<SEL, RES, SEL>), grid, block, 0, s, a);
+  else if (big)
+    hipLaunchKernelGGL((select_resolve_big_kernel<SEL, RES, false>), grid, block, 0, s, a);
   else if (ipt <= 4)
     hipLaunchKernelGGL((select_resolve_kernel<4, SEL, RES>), grid, block, 0, s, a);
   else if (ipt <= 8)

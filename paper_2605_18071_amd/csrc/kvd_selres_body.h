@@ -232,7 +232,9 @@ __device__ __forceinline__ int victim_bucket(long long age, int page, int NP) {
 // by instruction issue.  32 units of 32768 pages and 8192 slots:
 // selection, directory update and fetch of an all-hit step 23 us, against 115 us as the size-agnostic kernels,
 // which refine their keys over global memory pass by pass (select 90, resolve 20, fetch 5).
-template <int NT>
+// HELD: at most 8 quads per lane (NP <= 32 NT), which the registers do hold: read once (the step of the shape above
+// 86.0 us with three reads, 84.6 with one).
+template <int NT, bool HELD>
 __device__ __forceinline__ void select_big(const FastArgs& a, int u, int seq, FastSmem<NT, true>& sm, int& flip) {
   constexpr int NW = NT / kWave;
   static_assert(KVD_BIG_MAX_PAGES <= NT * 64, "one mask bit per page of a lane");
@@ -261,8 +263,19 @@ __device__ __forceinline__ void select_big(const FastArgs& a, int u, int seq, Fa
     return (1u << (n < 0 ? 0 : (n > 4 ? 4 : n))) - 1u;
   };
   auto free_of = [&](int q) -> u32 { return upto(q, recent_from) & ~upto(q, a.sink); };
+  float held[HELD ? 8 : 1][4];
+  if constexpr (HELD) {
+#pragma unroll
+    for (int q = 0; q < 8; ++q) quad(q < nq ? q : 0, held[q]);
+  }
   // calls f(q, scores, free bits) for this lane's pages, four quads' loads in flight
   auto for_quads = [&](auto f) {
+    if constexpr (HELD) {
+#pragma unroll
+      for (int q = 0; q < 8; ++q)
+        if (q < nq) f(q, held[q], free_of(q));
+      return;
+    }
     for (int q0 = 0; q0 < nq; q0 += 4) {
       float s[4][4];
 #pragma unroll
@@ -383,7 +396,7 @@ __device__ __forceinline__ void select_big(const FastArgs& a, int u, int seq, Fa
 // without HANDOFF): the unit's scores are read once per pass over the pages instead.
 struct ScoresAlreadyThere { __device__ bool operator()() const { return true; } };
 template <int NT, int IPT, bool DO_SELECT, bool DO_RESOLVE, bool HANDOFF, class ScoresReady = ScoresAlreadyThere,
-          bool SEL_IN_LDS = false, bool BIG = false>
+          bool SEL_IN_LDS = false, bool BIG = false, bool HELD = false>
 __device__ __forceinline__ bool select_resolve_body(const FastArgs& a, int u, FastSmem<NT, BIG>& sm,
                                                     ScoresReady scores_ready = ScoresReady()) {
   static_assert(!(BIG && HANDOFF), "the big form is a kernel of its own");
@@ -494,7 +507,7 @@ __device__ __forceinline__ bool select_resolve_body(const FastArgs& a, int u, Fa
 
   // ---- selection
   if constexpr (DO_SELECT && BIG) {
-    select_big<NT>(a, u, seq, sm, flip);
+    select_big<NT, HELD>(a, u, seq, sm, flip);
     if (!DO_RESOLVE) return true;
     for (int i = tid; i < kRadixBins; i += NT) sm.a.sel.hist[i] = 0;
     if (tid == 0) sm.cand_n = 0;
