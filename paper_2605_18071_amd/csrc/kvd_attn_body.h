@@ -222,11 +222,11 @@ __device__ __forceinline__ f32x4 mfma_pv(const uint2& vfrag, const uint2& pfrag,
 // 4 (i % 4) + i / 4 of the tile, so that lane (j, g) of the C tile holds the logits of tokens g, 4 + g, 8 + g
 // and 12 + g; lane (i, g) fetches 16 bytes of the V rows of the same four tokens, eight dims of each, and the
 // halves of dim 8i + e, put together in pairs, are its V^T operand of the e-th MFMA (16 byte permutes a
-// tile, no LDS), whose C tile then holds dims 8 (4g + 0..3) + e.  P keeps as many bits as fp32 has, since this
-// layout used to be computed in fp32 throughout: three bf16 parts, or two fp16 parts of P scaled by 2^15, which
-// puts the fp16 subnormals out of the way.  (32 units x 85 pages of 24 tokens, G = 7: 35 us in fp32 VALU
-// arithmetic, 13.6 us so; 128 units x 100 pages of 20 tokens, G = 1 / 4 / 8: steps of 47 / 64 / 119 us became
-// 45 / 46 / 49.)
+// tile, no LDS), whose C tile then holds dims 8 (4g + 0..3) + e.  P keeps all its 24 bits: in three 16-bit parts where
+// these hold them (bf16 above 2^-100; fp16 parts of 2^15 P above 2^-15, so that the third ends at fp16's smallest
+// number), and in fp32 MFMAs (16x16x4, four times the cycles) for a tile that has a smaller one.  (us per step, three
+// parts and fp32 throughout: 32 units x 85 pages of 24 tokens, G = 7, fp16 31.2 and 32.1; 32 units x 102 pages of
+// 20 tokens, bf16 26.5 and 28.3.  With two fp16 parts the first was 30.6; in fp32 VALU arithmetic 50.6 and 36.5.)
 // Returns 1 in the workgroup that completed the unit's output, 0 in the others, -1 (from all
 // threads, no output) when a HANDOFF wait ran out.  inputs_ready_tick (one thread passes it)
 // receives the wall clock at which the split's entries were all there.
@@ -433,8 +433,8 @@ __device__ __forceinline__ int attend_mfma_body(const AttnArgs& a, AttnSmem<Grou
 #pragma unroll
     for (int c = 0; c < 4; ++c) tl.v[c] = load_stream16(tb + 256 + c * 64);
   };
-  // careful: see below
-  auto compute = [&](Tile& tl, auto careful) {
+  // exact: P.V in fp32 whatever the probabilities
+  auto compute = [&](Tile& tl, auto exact) {
     const u32 valid = tl.valid;
     if (valid == 0) return;
     const u32 mine = (valid >> (4 * g)) & 15u;          // this lane's four tokens 4g..4g+3
@@ -489,38 +489,48 @@ __device__ __forceinline__ int attend_mfma_body(const AttnArgs& a, AttnSmem<Grou
       l += p[e];
     }
     if constexpr (NATURAL) {
-      uint2 parts[BF16 ? 3 : 2];
-      typedef std::conditional_t<BF16, __bf16, _Float16> half_t;
-      typedef half_t half4 __attribute__((ext_vector_type(4)));
+      u32 least = 0xffffffffu;                           // bits of the smallest probability that is not zero, less one
 #pragma unroll
-      for (int i = 0; i < (BF16 ? 3 : 2); ++i) {
-        if (i == 0) {
-#pragma unroll
-          for (int e = 0; e < 4; ++e) p[e] *= kPScale;
-        }
-        const half4 part = {(half_t)p[0], (half_t)p[1], (half_t)p[2], (half_t)p[3]};
-        parts[i] = __builtin_bit_cast(uint2, part);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) p[e] -= (float)part[e];
+      for (int e = 0; e < 4; ++e) {
+        const u32 bits = __float_as_uint(p[e]) - 1u;
+        least = least < bits ? least : bits;
+        p[e] *= kPScale;
       }
       const u32* v0 = reinterpret_cast<const u32*>(&tl.v[0]);
       const u32* v1 = reinterpret_cast<const u32*>(&tl.v[1]);
       const u32* v2 = reinterpret_cast<const u32*>(&tl.v[2]);
       const u32* v3 = reinterpret_cast<const u32*>(&tl.v[3]);
+      if (decltype(exact)::value || __any(least < __float_as_uint(BF16 ? 0x1p-100f : 0x1p-15f) - 1u)) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          f32x4 sum = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const u32 word = (i == 0 ? v0 : i == 1 ? v1 : i == 2 ? v2 : v3)[e >> 1];
+            const uint16_t h = (uint16_t)((e & 1) ? word >> 16 : word);
+            const float ve = BF16 ? as_f32((u32)h << 16) : (float)__builtin_bit_cast(_Float16, h);
+            sum = __builtin_amdgcn_mfma_f32_16x16x4f32(ve, p[i], sum, 0, 0, 0);
+          }
+          o[e] += sum;
+        }
+        return;
+      }
+      uint2 parts[3];
+      typedef std::conditional_t<BF16, __bf16, _Float16> half_t;
+      typedef half_t half4 __attribute__((ext_vector_type(4)));
+#pragma unroll
+      for (int i = 0; i < 3; ++i) {
+        const half4 part = {(half_t)p[0], (half_t)p[1], (half_t)p[2], (half_t)p[3]};
+        parts[i] = __builtin_bit_cast(uint2, part);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) p[e] -= (float)part[e];
+      }
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
         const u32 pick = (e & 1) ? 0x07060302u : 0x05040100u;   // the high or the low halves of two words
         const uint2 v = make_uint2(__builtin_amdgcn_perm(v1[e >> 1], v0[e >> 1], pick), __builtin_amdgcn_perm(v3[e >> 1], v2[e >> 1], pick));
-        uint2 f = v;
-        if constexpr (decltype(careful)::value) {
-          constexpr u32 kOne = BF16 ? 0x00800080u : 0x04000400u;   // carries an exponent of all ones into the sign
-          auto finite = [&](u32 x) -> u32 { return x & ~((((x & 0x7fff7fffu) + kOne) >> 15 & 0x00010001u) * 0xffffu); };
-          f = make_uint2(finite(v.x), finite(v.y));
-        }
-        o[e] = mfma_pv2<BF16>(v, f, parts[0], parts[1], o[e]);
-        // (the third part through the same instruction: an accumulator that went from the 32-wide MFMA straight to the
-        // 16-wide one, without a wait between them, gave wrong sums)
-        if constexpr (BF16) o[e] = mfma_pv2<BF16>(f, f, parts[2], make_uint2(0u, 0u), o[e]);
+        o[e] = mfma_pv2<BF16>(v, v, parts[0], parts[1], o[e]);
+        o[e] = mfma_pv2<BF16>(v, v, parts[2], make_uint2(0u, 0u), o[e]);
       }
     } else if (BF16) {
       const bf16x4 hi = {(__bf16)p[0], (__bf16)p[1], (__bf16)p[2], (__bf16)p[3]};
@@ -546,15 +556,15 @@ __device__ __forceinline__ int attend_mfma_body(const AttnArgs& a, AttnSmem<Grou
       }
     }
   };
-  auto run = [&](auto careful) {
+  auto run = [&](auto exact) {
     if (LEAN) {
       Tile ta, tb2;
       issue(ta, w);
       for (int t = w; t < n_tiles; t += 2 * NW) {
         issue(tb2, t + NW);
-        compute(ta, careful);
+        compute(ta, exact);
         issue(ta, t + 2 * NW);
-        compute(tb2, careful);
+        compute(tb2, exact);
       }
     } else {
       Tile ta, tb2, tc;
@@ -562,18 +572,18 @@ __device__ __forceinline__ int attend_mfma_body(const AttnArgs& a, AttnSmem<Grou
       issue(tb2, w + NW);
       for (int t = w; t < n_tiles; t += 3 * NW) {
         issue(tc, t + 2 * NW);
-        compute(ta, careful);
+        compute(ta, exact);
         issue(ta, t + 3 * NW);
-        compute(tb2, careful);
+        compute(tb2, exact);
         issue(tb2, t + 4 * NW);
-        compute(tc, careful);
+        compute(tc, exact);
       }
     }
   };
   run(std::false_type());
   if constexpr (NATURAL) {
     // An infinity in V times a lower part of P, which may be zero or negative, is not the infinity that P times V
-    // is.  A sum that is not finite is therefore formed again with such elements meeting the first part only.
+    // is.  Sums that are not finite are therefore formed again in fp32.
     float sum = 0.f;
 #pragma unroll
     for (int c = 0; c < 8; ++c) sum += (o[c][0] * 0.f + o[c][1] * 0.f) + (o[c][2] * 0.f + o[c][3] * 0.f);
