@@ -472,16 +472,16 @@ __device__ __forceinline__ int attend_mfma_body(const AttnArgs& a, AttnSmem<Grou
     }
     mx = fmaxf(mx, __shfl_xor(mx, 16, kWave));
     mx = fmaxf(mx, __shfl_xor(mx, 32, kWave));
-    const float m_new = fmaxf(m, mx);                // finite: some token of the tile is valid
+    const float m_new = fmaxf(m, mx);
+    const float ms = m_new == -INFINITY ? 0.f : m_new;   // (a head with no logit above minus infinity yet: no weight, no NaN)
     if (__any(m_new > m)) {
-      const float alpha = exp2f(m - m_new);
+      const float alpha = exp2f(m - ms);
       l *= alpha;
 #pragma unroll
       for (int c = 0; c < 8; ++c) o[c] *= alpha;
       m = m_new;
     }
     float p[4];
-    const float ms = NATURAL && m == -INFINITY ? 0.f : m;   // (logits of minus infinity so far: no weight, but no NaN either)
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       // (natural layout: without the rounding of x, which is larger than that of the difference)

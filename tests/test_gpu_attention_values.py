@@ -1,5 +1,5 @@
-"""Attention over keys and values chosen for their arithmetic: probabilities far below one, against 64-bit sums of the
-same selection."""
+"""Attention over keys and values chosen for their arithmetic (probabilities far below one, logits of minus infinity),
+against 64-bit sums of the same selection."""
 import math
 
 import pytest
@@ -78,3 +78,27 @@ def test_logits_of_every_spread_over_natural_pages(page, splits, dtype, heads):
     # logits of up to 60 x log2(e), rounded once in q.k (a sum of 128 products) and once or twice in the exponent
     assert float(((out - want).norm(dim=1) / want.norm(dim=1)).max()) < 90 * 4 * 2 ** -24
     assert float((lse - want_lse).abs().max()) < 90 * 4 * 2 ** -24
+
+
+@pytest.mark.parametrize("page", [16, 8, 20, 64])
+@pytest.mark.parametrize("dtype,which", [("bf16", "one head"), ("bf16", "all heads"), ("f16", "all heads")])
+@pytest.mark.parametrize("splits", [1, 3])
+def test_logits_of_minus_infinity_have_no_weight(page, dtype, which, splits):
+    """The first 150 tokens, and with them the first tile of every wave of the first split, have a logit of minus infinity
+    in one head or in all of them: the output is that of the other tokens."""
+    gen = torch.Generator().manual_seed(13)
+
+    def fill(q, k, v):
+        for x in (q, k, v):
+            x[:] = torch.randn(x.shape, generator=gen, dtype=torch.float64)
+        q[:, 0], k[:, 0] = 0.0, 0.0
+        if which == "one head":
+            q[1, 0], k[:150, 0] = -3e38, 3e38           # finite factors, the product beyond fp32
+        else:
+            q[:, 0], k[:150, 0] = 1.0, -math.inf
+
+    (out, lse), (want, want_lse) = attend(page, dtype, 3, fill, splits)
+    assert torch.isfinite(want).all() and torch.isfinite(out).all() and torch.isfinite(lse).all()
+    # probabilities multiply V in 16 bits (two parts of them for bf16) over pages kept as tiles
+    assert float(((out - want).norm(dim=1) / want.norm(dim=1)).max()) < (2 ** -11 if dtype == "f16" else 2 ** -16)
+    assert float((lse - want_lse).abs().max()) < 1e-5
