@@ -467,7 +467,8 @@ __device__ __forceinline__ int attend_mfma_body(const AttnArgs& a, AttnSmem<Grou
     float mx = -INFINITY;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      x[e] = ((mine >> e) & 1u) ? s[e] * a.scale_log2 : -INFINITY;
+      if (NATURAL) s[e] = ((mine >> e) & 1u) ? s[e] : -INFINITY;
+      x[e] = NATURAL || ((mine >> e) & 1u) ? s[e] * a.scale_log2 : -INFINITY;
       mx = fmaxf(mx, x[e]);
     }
     mx = fmaxf(mx, __shfl_xor(mx, 16, kWave));
@@ -482,10 +483,12 @@ __device__ __forceinline__ int attend_mfma_body(const AttnArgs& a, AttnSmem<Grou
       m = m_new;
     }
     float p[4];
+    const bool coarse = fabsf(ms) > 4194304.f;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      // (natural layout: without the rounding of x, which is larger than that of the difference)
-      p[e] = !NATURAL ? exp2f(x[e] - ms) : ((mine >> e) & 1u) ? exp2f(fmaf(s[e], a.scale_log2, -ms)) : 0.f;
+      // (natural layout: without the rounding of x, which is larger than that of the difference; but not for logits
+      // beyond 2^22, where the rounding of their maximum would leave that token far from a probability of one)
+      p[e] = exp2f(!NATURAL || coarse ? x[e] - ms : fmaf(s[e], a.scale_log2, -ms));
       l += p[e];
     }
     if constexpr (NATURAL) {

@@ -102,3 +102,21 @@ def test_logits_of_minus_infinity_have_no_weight(page, dtype, which, splits):
     # probabilities multiply V in 16 bits (two parts of them for bf16) over pages kept as tiles
     assert float(((out - want).norm(dim=1) / want.norm(dim=1)).max()) < (2 ** -11 if dtype == "f16" else 2 ** -16)
     assert float((lse - want_lse).abs().max()) < 1e-5
+
+
+@pytest.mark.parametrize("page", [16, 20])
+@pytest.mark.parametrize("dtype,size", [("f16", 3e2), ("f16", 3e4), ("bf16", 1e6), ("bf16", 1e15)])
+def test_logits_beyond_the_integers_of_fp32(page, dtype, size):
+    """Logits of 1e6 to 1e31: the largest token takes all, whatever the rounding of its logit."""
+    gen = torch.Generator().manual_seed(17)
+
+    def fill(q, k, v):
+        for x in (q, k):
+            x[:] = size * torch.rand(x.shape, generator=gen, dtype=torch.float64)
+        v[:] = torch.randn(v.shape, generator=gen, dtype=torch.float64)
+        k[3::7] *= torch.linspace(0.5, 0.9, k[3::7].shape[0], dtype=torch.float64)[:, None]
+
+    (out, lse), (want, want_lse) = attend(page, dtype, 4, fill)
+    assert torch.isfinite(out).all() and torch.isfinite(lse).all()
+    assert float((lse / want_lse - 1).abs().max()) < 1e-6
+    assert float(((out - want).norm(dim=1) / want.norm(dim=1)).max()) < 2 ** -16
