@@ -490,7 +490,9 @@ int kvd_calibrate_step_form(kvd_ctx* ctx, int32_t layer, int32_t first_step, con
  * makes per chunk it takes (1..8); how many persistent scoring workgroups a group has (1..compute
  * units; the other compute units are left to the selection workgroups, and to attention workgroups
  * of units already selected, while scoring goes on); the attention splits per unit (at most twice
- * what kvd_create chose, at most 512 selected pages per split); and the number of groups (1..8) the
+ * what kvd_create chose, or, where that is more and a unit has at most 8192 pages, twice one
+ * workgroup per compute unit with 16 tiles of 16 tokens each; at most 64, and at most 512 selected
+ * pages per split); and the number of groups (1..8) the
  * units of a layer are cut into: the groups follow each other through the launch, group g+1 being
  * scored while group g is selected and its missed pages are fetched, group g attended while group g+1
  * is selected — the micro-batches of SFC Disaggregation, pipelined by the order of the launch's
@@ -498,7 +500,10 @@ int kvd_calibrate_step_form(kvd_ctx* ctx, int32_t layer, int32_t first_step, con
  * != 0 for launches of several layers (kvd_step_layers, where consecutive layers are pipelined the
  * same way).  0 leaves a number to the library's rule.  kvd_set_step_shape waits for the device;
  * KVD_ERR_SHAPE for a shape the context cannot run.  kvd_get_step_shape writes the four numbers a
- * launch would take now (host, 4 ints).  Results do not depend on the shape. */
+ * launch would take now (host, 4 ints); for launches of several layers, one of as many as the
+ * context's launches cover (its layers, at most 8).  The rule makes two passes there once the layers'
+ * chunks fill most of the compute units: a launch of fewer layers, whose chunks would not, makes
+ * one, and takes more scoring workgroups if there are chunks for them.  Results do not depend on the shape. */
 int kvd_set_step_shape(kvd_ctx* ctx, int32_t multi_layer, int32_t passes, int32_t scoring_workgroups, int32_t attn_splits,
                        int32_t groups);
 int kvd_get_step_shape(const kvd_ctx* ctx, int32_t multi_layer, int32_t* shape);

@@ -33,3 +33,25 @@ def test_rule_and_limits(kw, rule, most):
         assert H.attn_rel_err(rig.n_out.reshape(-1, 128), one.n_out.reshape(-1, 128)) <= 2.0 ** -14
     rig.close()
     one.close()
+
+
+def test_the_shape_reported_for_several_layers_is_that_of_the_longest_launch():
+    """16 units of 1024 pages: eight layers' chunks fill the compute units (two passes per chunk), two layers' do not."""
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    w, two = (small("shape-query", ctx=16 * 1024, topk_pages=16, capacity=20, batch=4, n_kv_heads=4, n_q_heads=4, n_layers=n,
+                    physical_layers=1, heavy_count=2) for n in (8, 2))
+    rig, one, short = R.Rig(w, micro_batches=-1), R.Rig(w, micro_batches=-1), R.Rig(two, micro_batches=-1)
+    chunks = lambda passes: -(-1024 // (512 * passes))                   # per unit
+    for r, passes in ((rig, 2), (short, 1)):
+        assert (r.w.n_layers * r.w.units * chunks(1) >= 0.75 * cus) == (passes == 2)
+        assert r.kvd.step_shape(multi_layer=True)[:2] == (passes, r.w.units * chunks(passes))
+        assert r.kvd.step_shape()[0] == 1
+    # a launch of two of the eight layers gives what the layers give one by one
+    for t, q in enumerate(R.W.query_stream(w, rig.q0, 2, R.DEV)):
+        out = torch.empty((2, w.batch, w.n_q_heads, w.head_dim), dtype=torch.float32, device=R.DEV)
+        rig.kvd.step_layers(0, 2, t, q[:2].contiguous(), out)
+        for l in range(2):
+            one.step(l, t, q[l])
+            assert torch.equal(out[l], one.out)
+    for r in (rig, one, short):
+        r.close()
