@@ -81,7 +81,7 @@ __global__ __launch_bounds__(kCentroidWaves* kWave) void kmeans_init_kernel(cons
 // Nearest centroid of every page, exactly as the definition has it: squared distance summed in
 // fp64 in dim order, ties to the lower centroid.  Computing all of them in fp64 is bound by the
 // fp64 rate (8 units of 8192 pages against 4096 centroids: 4.4 ms a round); so
-// the distances are first bounded on the matrix cores, where a round is 137 GFLOP of 16-bit MFMA:
+// the distances are first bounded on the matrix cores, where a round is 275 GFLOP of 16-bit MFMA (two sweeps of 137):
 //   v = x . (c_hi + c_lo) - |c|^2 / 2        (the larger, the nearer)
 // in fp32, each within E of its true value, E = 2^-14 (|x| C + C^2 / 2) + 2^-20 |x| with C the unit's
 // largest centroid norm.  That covers the part of c that two 16-bit parts leave out (2^-18 |x| |c| for
@@ -89,7 +89,9 @@ __global__ __launch_bounds__(kCentroidWaves* kWave) void kmeans_init_kernel(cons
 // larger than |x| |c| + |c|^2 / 2 (2^-16 of that).  The nearest centroid is among those whose v is
 // within 2 E of the largest: one of them, as a rule, and then it is the answer; several are compared
 // in fp64, in the definition's order of operations; more than kAssignCap (exact ties, or data whose
-// differences the screening cannot see) and the page is compared with every centroid in fp64.
+// differences the screening cannot see) and the page is compared with every centroid in fp64.  So it is
+// where E would not hold for the range of fp32: norms above 2^60 could carry v or E to infinity, and a
+// largest centroid norm below 2^-45 leaves v among the subnormals.
 //
 // Block (x, u): points 256x .. 256x+255 of unit u.  Wave w takes 64 of them (B operands kept in
 // registers) and one half of the centroid tiles, which the block stages through LDS, double
@@ -211,6 +213,7 @@ __global__ __launch_bounds__(kAssignThreads, 2) void kmeans_assign_kernel(const 
   // B operands: lane (j, g) of group q holds dims 32c + 8g .. +7 of point pw + 16 q + j
   uint4 x[4][4];
   float slack[4];                                           // 2 E of the point
+  bool in_range[4];                                         // E holds
   {
     float cmax2 = 0.f;                                      // largest squared norm of the unit's centroids
     for (int c = tid; c < Nc; c += kAssignThreads) cmax2 = fmaxf(cmax2, -2.f * neg_u[c]);
@@ -235,6 +238,7 @@ __global__ __launch_bounds__(kAssignThreads, 2) void kmeans_assign_kernel(const 
       n += __shfl_xor(n, 16, kWave);
       n += __shfl_xor(n, 32, kWave);
       // (2^-14 instead of the 2^-15.5 that the terms above add up to leaves room for the roundings of E itself)
+      in_range[q] = n <= 0x1p120f && cmax2 <= 0x1p120f && cmax2 >= 0x1p-90f;
       const float xn = sqrtf(n);
       slack[q] = 2.f * (6.103515625e-5f * (xn * sqrtf(cmax2) + 0.5f * cmax2) + 9.5367431640625e-7f * xn);
     }
@@ -296,7 +300,10 @@ __global__ __launch_bounds__(kAssignThreads, 2) void kmeans_assign_kernel(const 
   }
   __syncthreads();
 #pragma unroll
-  for (int q = 0; q < 4; ++q) top[q] = fmaxf(top[q], sm.best[half ^ 1][pw + 16 * q + j]) - slack[q];
+  for (int q = 0; q < 4; ++q) {
+    top[q] = fmaxf(top[q], sm.best[half ^ 1][pw + 16 * q + j]) - slack[q];
+    if (!in_range[q] && g == 0 && half == 0) sm.n_cand[pw + 16 * q + j] = kAssignCap + 1;
+  }
   sweep([&](int t, const f32x4_c (&v)[4]) {
 #pragma unroll
     for (int q = 0; q < 4; ++q) {

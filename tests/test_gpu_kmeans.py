@@ -25,6 +25,12 @@ def points(kind, units, pages, dtype, gen):
         x = torch.cumsum(0.1 * x, dim=1)
     elif kind == "same":                   # every page the same vector
         x = x[:, :1].expand(-1, pages, -1)
+    elif kind == "huge":                   # squared norms beyond fp32
+        x = 3e19 * x
+    elif kind == "few huge":               # ... of every 50th page only, so that some centroids stay in range
+        x[:, 3::50] *= 1e25
+    elif kind == "minute":                 # squared norms among the subnormals of fp32, or zero there
+        x = 2e-22 * (x[:, :1] + 0.02 * x)
     elif kind == "pairs":                  # every vector 40 times: more equal centroids than are compared one by one
         x = x[:, torch.arange(pages, device=R.DEV) % max(1, pages // 40)]
     return x.to(dtype)
@@ -42,6 +48,12 @@ def points(kind, units, pages, dtype, gen):
     (300, 64, "tiny", "bf16", None),
     (300, 50, "same", "bf16", None),                       # all distances tie
     (700, 100, "pairs", "f16", None),
+    (300, 5, "huge", "bf16", None),
+    (300, 150, "huge", "bf16", None),
+    (600, 9, "few huge", "bf16", None),
+    (600, 200, "few huge", "bf16", None),
+    (300, 5, "minute", "bf16", None),
+    (600, 64, "minute", "bf16", None),
 ])
 def test_build_matches_the_oracle_round_by_round(pages, nc, kind, dtype, seq):
     w = small("kmeans", ctx=16 * pages, topk_pages=min(24, pages), capacity=min(60, pages), heavy_count=0, dtype=dtype,
