@@ -35,6 +35,8 @@ struct ScreenArgs {
   uint16_t* frag;       // [U][tiles][kScreenTile]
   float* neg_half;      // [U][16 * tiles] minus half the squared norm; minus infinity beyond the last centroid
   int tiles;            // ceil(Nc / 16)
+  int32_t* hard;        // [U][NP] pages of the round that kmeans_exhaustive_kernel decides, in any order
+  int32_t* n_hard;      // [U] how many; zero before a round
 };
 
 // One wave, centroid c of unit u, lane l holding dims 2l and 2l + 1.
@@ -63,6 +65,7 @@ __global__ __launch_bounds__(kCentroidWaves* kWave) void kmeans_init_kernel(cons
                                                                            int P, int Hkv) {
   const int c = blockIdx.x * kCentroidWaves + threadIdx.x / kWave, u = blockIdx.y, lane = threadIdx.x & (kWave - 1);
   if (c >= sa.tiles * 16) return;
+  if (c == 0 && lane == 0) sa.n_hard[u] = 0;
   if (c >= Nc) {                                            // the last tile's empty places
     if (lane == 0) sa.neg_half[(size_t)u * sa.tiles * 16 + c] = -INFINITY;
     uint16_t* tile = sa.frag + ((size_t)u * sa.tiles + (c >> 4)) * kScreenTile;
@@ -101,7 +104,6 @@ __global__ __launch_bounds__(kCentroidWaves* kWave) void kmeans_init_kernel(cons
 constexpr int kAssignThreads = 512;
 constexpr int kAssignBlock = 256;     // points per block
 constexpr int kAssignCap = 8;         // candidates per point that are compared one by one
-constexpr int kAssignPoints = 16;     // points at a time that are compared with every centroid
 
 typedef float f32x4_c __attribute__((ext_vector_type(4)));
 template <bool BF16>
@@ -116,81 +118,12 @@ __device__ __forceinline__ f32x4_c mfma_16x16x32(const uint4& a, const uint4& b,
 }
 
 struct AssignSmem {
-  union {
-    uint4 tile[2][2][kScreenTile / 8];                      // [buffer][half of the centroids]
-    struct {
-      double pts[kAssignPoints][kHeadDim];
-      double best_d[kAssignPoints][kAssignThreads / kWave];
-      int best_c[kAssignPoints][kAssignThreads / kWave];
-    } all;
-  } a;
+  uint4 tile[2][2][kScreenTile / 8];                        // [buffer][half of the centroids]
   float best[2][kAssignBlock];                              // largest v of a point in each half
   float norm[kAssignThreads / kWave];
   int n_cand[kAssignBlock];
   uint16_t cand[kAssignBlock][kAssignCap];
-  int hard[kAssignBlock];                                   // points to compare with every centroid
-  int n_hard;
 };
-
-// Points sm.hard[first ..] (at most kAssignPoints of them) against all centroids in fp64.
-template <bool BF16>
-__device__ __forceinline__ void assign_exhaustive(AssignSmem& sm, int first, const uint16_t* __restrict__ summ_u,
-                                                  const double* __restrict__ cent_u, int32_t* __restrict__ assign_u, int p0, int Nc) {
-  const int tid = threadIdx.x, lane = tid & (kWave - 1), w = tid / kWave;
-  const int n = sm.n_hard - first < kAssignPoints ? sm.n_hard - first : kAssignPoints;
-  __syncthreads();                                          // (the staging area is free, the batch before this one is done)
-  for (int i = tid; i < kAssignPoints * kHeadDim; i += kAssignThreads) {
-    const int pi = i / kHeadDim, d = i % kHeadDim;
-    sm.a.all.pts[pi][d] = pi < n ? widen_kv<BF16>(summ_u[(size_t)(p0 + sm.hard[first + pi]) * kHeadDim + d]) : 0.0;
-  }
-  __syncthreads();
-  double bd[kAssignPoints];
-  int bc[kAssignPoints];
-#pragma unroll
-  for (int i = 0; i < kAssignPoints; ++i) { bd[i] = INFINITY; bc[i] = 0x7fffffff; }
-  for (int c = tid; c < Nc; c += kAssignThreads) {
-    const double* crow = cent_u + (size_t)c * kHeadDim;
-    double acc[kAssignPoints];
-#pragma unroll
-    for (int i = 0; i < kAssignPoints; ++i) acc[i] = 0.0;
-    for (int d = 0; d < kHeadDim; d += 2) {
-      const double2 cv = *reinterpret_cast<const double2*>(crow + d);
-#pragma unroll
-      for (int i = 0; i < kAssignPoints; ++i) {
-        const double e0 = sm.a.all.pts[i][d] - cv.x, e1 = sm.a.all.pts[i][d + 1] - cv.y;
-        acc[i] = fma(e0, e0, acc[i]);
-        acc[i] = fma(e1, e1, acc[i]);
-      }
-    }
-#pragma unroll
-    for (int i = 0; i < kAssignPoints; ++i)
-      if (acc[i] < bd[i]) { bd[i] = acc[i]; bc[i] = c; }    // centroids come in ascending order per thread
-  }
-  // smallest (distance, centroid) per point over the block
-#pragma unroll
-  for (int i = 0; i < kAssignPoints; ++i) {
-    double d = bd[i];
-    int c = bc[i];
-#pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) {
-      const double od = __shfl_xor(d, m, kWave);
-      const int oc = __shfl_xor(c, m, kWave);
-      if (od < d || (od == d && oc < c)) { d = od; c = oc; }
-    }
-    if (lane == 0) { sm.a.all.best_d[i][w] = d; sm.a.all.best_c[i][w] = c; }
-  }
-  __syncthreads();
-  if (tid < n) {
-    double d = sm.a.all.best_d[tid][0];
-    int c = sm.a.all.best_c[tid][0];
-    for (int j = 1; j < kAssignThreads / kWave; ++j) {
-      const double od = sm.a.all.best_d[tid][j];
-      const int oc = sm.a.all.best_c[tid][j];
-      if (od < d || (od == d && oc < c)) { d = od; c = oc; }
-    }
-    assign_u[p0 + sm.hard[first + tid]] = c < Nc ? c : 0;   // (no distance is a number: any cluster, within bounds)
-  }
-}
 
 template <bool BF16>
 __global__ __launch_bounds__(kAssignThreads, 2) void kmeans_assign_kernel(const uint16_t* __restrict__ summ,
@@ -244,7 +177,6 @@ __global__ __launch_bounds__(kAssignThreads, 2) void kmeans_assign_kernel(const 
     }
   }
   for (int i = tid; i < kAssignBlock; i += kAssignThreads) sm.n_cand[i] = 0;
-  if (tid == 0) sm.n_hard = 0;
 
   // iteration i stages tile i of the lower half and tile n_half + i of the upper half (the last tile
   // again where the halves are uneven: the waves of that half then skip it)
@@ -261,8 +193,8 @@ __global__ __launch_bounds__(kAssignThreads, 2) void kmeans_assign_kernel(const 
   auto sweep = [&](auto f) {
     fetch(0);
     for (int i = 0; i < n_half; ++i) {
-      sm.a.tile[i & 1][0][tid] = lower;
-      sm.a.tile[i & 1][1][tid] = upper;
+      sm.tile[i & 1][0][tid] = lower;
+      sm.tile[i & 1][1][tid] = upper;
       if (i + 1 < n_half) fetch(i + 1);
       __syncthreads();                                      // (buffer i & 1 is written again two iterations on, after the next barrier)
       const int t = half * n_half + i;
@@ -275,7 +207,7 @@ __global__ __launch_bounds__(kAssignThreads, 2) void kmeans_assign_kernel(const 
         for (int part = 0; part < 2; ++part)
 #pragma unroll
           for (int c = 0; c < 4; ++c) {
-            const uint4 a = sm.a.tile[i & 1][half][(part * 4 + c) * kWave + lane];
+            const uint4 a = sm.tile[i & 1][half][(part * 4 + c) * kWave + lane];
 #pragma unroll
             for (int q = 0; q < 4; ++q) v[q] = mfma_16x16x32<BF16>(a, x[q][c], v[q]);
           }
@@ -320,7 +252,7 @@ __global__ __launch_bounds__(kAssignThreads, 2) void kmeans_assign_kernel(const 
   if (tid < kAssignBlock && p0 + tid < n_valid) {
     const int n = sm.n_cand[tid];
     if (n < 1 || n > kAssignCap) {
-      sm.hard[atomicAdd(&sm.n_hard, 1)] = tid;
+      sa.hard[(size_t)u * NP + atomicAdd(&sa.n_hard[u], 1)] = p0 + tid;
     } else {
       int bc = sm.cand[tid][0];
       if (n > 1) {
@@ -344,9 +276,99 @@ __global__ __launch_bounds__(kAssignThreads, 2) void kmeans_assign_kernel(const 
       assign_u[p0 + tid] = bc < Nc ? bc : 0;
     }
   }
-  __syncthreads();
-  for (int first = 0; first < sm.n_hard; first += kAssignPoints)
-    assign_exhaustive<BF16>(sm, first, summ_u, cent_u, assign_u, p0, Nc);
+}
+
+// The pages that the screening leaves open against all centroids of their unit in fp64.  A launch of its own, so
+// that they spread over the chip however they lie among the blocks of the screening, 4 blocks per CU over all units.
+// A block takes 16 pages at a time, so that a centroid is read once for 16, or 4 where all of a unit's blocks have
+// no more than that to do: bound by the latency of one block's run through the centroids.  (ms of a build of
+// 4 rounds, 8192 pages against 4096 centroids, done by the block of the screening that met the page, and so: one unit,
+// nearly all pages open 24.8 and 5.2, every vector 40 times 16.4 and 4.2, few pages open 3.2 and 2.0; eight units 26.4
+// and 18.5, 18.4 and 13.6, 3.5 and 4.0.)
+constexpr int kExhaustiveThreads = 256, kExhaustivePages = 16, kExhaustiveFew = 4;
+struct ExhaustiveSmem {
+  static constexpr int NW = kExhaustiveThreads / kWave;
+  double pts[kExhaustivePages][kHeadDim];
+  double best_d[kExhaustivePages][NW];
+  int best_c[kExhaustivePages][NW];
+};
+
+template <bool BF16, int PAGES>
+__device__ __forceinline__ void assign_exhaustive(ExhaustiveSmem& sm, const uint16_t* __restrict__ summ_u, const double* __restrict__ cent_u,
+                                                  int32_t* __restrict__ assign_u, const int32_t* __restrict__ hard, int n_hard, int Nc) {
+  constexpr int NW = ExhaustiveSmem::NW;
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), w = tid / kWave;
+  for (int first = blockIdx.x * PAGES; first < n_hard; first += gridDim.x * PAGES) {
+    const int n = n_hard - first < PAGES ? n_hard - first : PAGES;
+    __syncthreads();                                        // (the pages before these are done)
+    for (int i = tid; i < PAGES * kHeadDim; i += kExhaustiveThreads) {
+      const int pi = i / kHeadDim, d = i % kHeadDim;
+      sm.pts[pi][d] = pi < n ? widen_kv<BF16>(summ_u[(size_t)hard[first + pi] * kHeadDim + d]) : 0.0;
+    }
+    __syncthreads();
+    double bd[PAGES];
+    int bc[PAGES];
+#pragma unroll
+    for (int i = 0; i < PAGES; ++i) { bd[i] = INFINITY; bc[i] = 0x7fffffff; }
+    for (int c = tid; c < Nc; c += kExhaustiveThreads) {
+      const double* crow = cent_u + (size_t)c * kHeadDim;
+      double acc[PAGES];
+#pragma unroll
+      for (int i = 0; i < PAGES; ++i) acc[i] = 0.0;
+      for (int d = 0; d < kHeadDim; d += 2) {
+        const double2 cv = *reinterpret_cast<const double2*>(crow + d);
+#pragma unroll
+        for (int i = 0; i < PAGES; ++i) {
+          const double e0 = sm.pts[i][d] - cv.x, e1 = sm.pts[i][d + 1] - cv.y;
+          acc[i] = fma(e0, e0, acc[i]);
+          acc[i] = fma(e1, e1, acc[i]);
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < PAGES; ++i)
+        if (acc[i] < bd[i]) { bd[i] = acc[i]; bc[i] = c; }  // centroids come in ascending order per thread
+    }
+    // smallest (distance, centroid) per page over the block
+#pragma unroll
+    for (int i = 0; i < PAGES; ++i) {
+      double d = bd[i];
+      int c = bc[i];
+#pragma unroll
+      for (int m = 32; m >= 1; m >>= 1) {
+        const double od = __shfl_xor(d, m, kWave);
+        const int oc = __shfl_xor(c, m, kWave);
+        if (od < d || (od == d && oc < c)) { d = od; c = oc; }
+      }
+      if (lane == 0) { sm.best_d[i][w] = d; sm.best_c[i][w] = c; }
+    }
+    __syncthreads();
+    if (tid < n) {
+      double d = sm.best_d[tid][0];
+      int c = sm.best_c[tid][0];
+      for (int j = 1; j < NW; ++j) {
+        const double od = sm.best_d[tid][j];
+        const int oc = sm.best_c[tid][j];
+        if (od < d || (od == d && oc < c)) { d = od; c = oc; }
+      }
+      assign_u[hard[first + tid]] = c < Nc ? c : 0;   // (no distance is a number: any cluster, within bounds)
+    }
+  }
+}
+
+template <bool BF16>
+__global__ __launch_bounds__(kExhaustiveThreads) void kmeans_exhaustive_kernel(const uint16_t* __restrict__ summ,
+                                                                             const double* __restrict__ cent64, ScreenArgs sa,
+                                                                             int32_t* __restrict__ assign, int NP, int Nc) {
+  __shared__ ExhaustiveSmem sm;
+  const int u = blockIdx.y, n_hard = sa.n_hard[u];
+  const uint16_t* summ_u = summ + (size_t)u * NP * kHeadDim;
+  const double* cent_u = cent64 + (size_t)u * Nc * kHeadDim;
+  int32_t* assign_u = assign + (size_t)u * NP;
+  const int32_t* hard = sa.hard + (size_t)u * NP;
+  if (n_hard <= kExhaustiveFew * (int)gridDim.x)
+    assign_exhaustive<BF16, kExhaustiveFew>(sm, summ_u, cent_u, assign_u, hard, n_hard, Nc);
+  else
+    assign_exhaustive<BF16, kExhaustivePages>(sm, summ_u, cent_u, assign_u, hard, n_hard, Nc);
 }
 
 constexpr int kCsrThreads = 1024;
@@ -433,6 +455,7 @@ __global__ __launch_bounds__(kCentroidWaves* kWave) void kmeans_update_kernel(co
                                                                              int Nc) {
   const int c = blockIdx.x * kCentroidWaves + threadIdx.x / kWave, u = blockIdx.y, lane = threadIdx.x & (kWave - 1);
   if (c >= Nc) return;
+  if (c == 0 && lane == 0) sa.n_hard[u] = 0;                // for the next round
   const int b = cluster_start[(size_t)u * (Nc + 1) + c], e = cluster_start[(size_t)u * (Nc + 1) + c + 1];
   double2* cent = reinterpret_cast<double2*>(cent64 + ((size_t)u * Nc + c) * kHeadDim) + lane;
   double2 x;
@@ -537,12 +560,13 @@ hipError_t kvd_run_build_centroids(kvd_ctx* c, int layer, int iterations, int32_
   int32_t* cpages = c->cluster_pages + lu * c->NP;
   ScreenArgs sa;
   sa.tiles = (c->Nc + 15) / 16;
-  // one temporary block: fp64 centroids, screening tiles, half norms, assignment
+  // one temporary block: fp64 centroids, screening tiles, half norms, assignment, pages left open by the screening
   const size_t n_cent = (size_t)c->U * c->Nc, n_tiles = (size_t)c->U * sa.tiles, n_points = (size_t)c->U * c->NP;
   size_t at = 0;
   auto place = [&](size_t bytes) { const size_t o = at; at += (bytes + 255) & ~(size_t)255; return o; };
   const size_t o_cent = place(n_cent * kHeadDim * sizeof(double)), o_frag = place(n_tiles * kScreenTile * 2),
-               o_neg = place(n_tiles * 16 * sizeof(float)), o_assign = place(n_points * sizeof(int32_t));
+               o_neg = place(n_tiles * 16 * sizeof(float)), o_assign = place(n_points * sizeof(int32_t)),
+               o_hard = place(n_points * sizeof(int32_t)), o_n_hard = place((size_t)c->U * sizeof(int32_t));
   char* temp = nullptr;
   hipError_t e = hipMalloc(reinterpret_cast<void**>(&temp), at);
   if (e == hipSuccess) {
@@ -550,6 +574,10 @@ hipError_t kvd_run_build_centroids(kvd_ctx* c, int layer, int iterations, int32_
     int32_t* assign = reinterpret_cast<int32_t*>(temp + o_assign);
     sa.frag = reinterpret_cast<uint16_t*>(temp + o_frag);
     sa.neg_half = reinterpret_cast<float*>(temp + o_neg);
+    sa.hard = reinterpret_cast<int32_t*>(temp + o_hard);
+    sa.n_hard = reinterpret_cast<int32_t*>(temp + o_n_hard);
+    int open_blocks = (4 * c->n_cus + c->U - 1) / c->U;
+    if (open_blocks > (c->NP + kExhaustiveFew - 1) / kExhaustiveFew) open_blocks = (c->NP + kExhaustiveFew - 1) / kExhaustiveFew;
     const dim3 per_centroid(c->Nc, c->U), per_tile_row((sa.tiles * 16 + kCentroidWaves - 1) / kCentroidWaves, c->U);
     const dim3 per_points((c->NP + kAssignBlock - 1) / kAssignBlock, c->U), centroid_block(kCentroidWaves * kWave);
 #define KVD_DT(KERNEL, ...)                                                    \
@@ -561,6 +589,7 @@ hipError_t kvd_run_build_centroids(kvd_ctx* c, int layer, int iterations, int32_
     for (int it = 0; it < iterations && e == hipSuccess; ++it) {
       KVD_DT(kmeans_assign_kernel, per_points, dim3(kAssignThreads), 0, s, summ, cent64, sa, assign, c->d_seq_len, c->NP, c->Nc,
              c->P, c->Hkv);
+      KVD_DT(kmeans_exhaustive_kernel, dim3(open_blocks, c->U), dim3(kExhaustiveThreads), 0, s, summ, cent64, sa, assign, c->NP, c->Nc);
       if (assign_trace != nullptr)
         e = hipMemcpyAsync(assign_trace + (size_t)it * c->U * c->NP, assign, (size_t)c->U * c->NP * sizeof(int32_t),
                            hipMemcpyDeviceToDevice, s);

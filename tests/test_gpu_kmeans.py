@@ -48,6 +48,7 @@ def points(kind, units, pages, dtype, gen):
     (300, 64, "tiny", "bf16", None),
     (300, 50, "same", "bf16", None),                       # all distances tie
     (700, 100, "pairs", "f16", None),
+    (1100, 20, "same", "bf16", (1100 * 16, 1030 * 16)),    # more open pages than blocks of four
     (300, 5, "huge", "bf16", None),
     (300, 150, "huge", "bf16", None),
     (600, 9, "few huge", "bf16", None),
