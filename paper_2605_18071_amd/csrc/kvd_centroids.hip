@@ -29,11 +29,13 @@ __device__ __forceinline__ double widen_kv(uint16_t raw) {
 
 // What the assignment screens with, per 16 centroids: [2 parts][4 chunks of 32 dims][64 lanes][8 elements], lane i + 16 g of
 // chunk c holding dims 32c + 8g .. +7 of centroid i, which is the A operand of a 16x16x32 MFMA as a wave loads it (1 KiB
-// contiguous per chunk).  Part 0 is the centroid rounded to the KV dtype, part 1 the rest rounded once more.
+// contiguous per chunk).  Part 0 is the centroid, less the unit's shift, rounded to the KV dtype, part 1 the rest
+// rounded once more.
 constexpr int kScreenTile = 2 * 4 * kWave * 8;            // elements
 struct ScreenArgs {
   uint16_t* frag;       // [U][tiles][kScreenTile]
-  float* neg_half;      // [U][16 * tiles] minus half the squared norm; minus infinity beyond the last centroid
+  float* neg_half;      // [U][16 * tiles] minus half the squared norm (of the same); minus infinity beyond the last centroid
+  uint16_t* shift;      // [U][D] see kmeans_shift_kernel
   int tiles;            // ceil(Nc / 16)
   int32_t* hard;        // [U][NP] pages of the round that kmeans_exhaustive_kernel decides, in any order
   int32_t* n_hard;      // [U] how many; zero before a round
@@ -43,6 +45,9 @@ struct ScreenArgs {
 template <bool BF16>
 __device__ __forceinline__ void store_screen(const ScreenArgs& sa, int u, int c, double x0, double x1) {
   const int lane = threadIdx.x & (kWave - 1);
+  const u32 shift = *reinterpret_cast<const u32*>(sa.shift + (size_t)u * kHeadDim + 2 * lane);
+  x0 -= widen_kv<BF16>((uint16_t)shift);
+  x1 -= widen_kv<BF16>((uint16_t)(shift >> 16));
   const u32 h0 = f64_to_kv<BF16>(x0), h1 = f64_to_kv<BF16>(x1);
   const u32 l0 = f64_to_kv<BF16>(x0 - widen_kv<BF16>((uint16_t)h0)), l1 = f64_to_kv<BF16>(x1 - widen_kv<BF16>((uint16_t)h1));
   const int d = 2 * lane, at = ((d >> 5) * kWave + ((d & 31) >> 3) * 16 + (c & 15)) * 8 + (d & 7);
@@ -53,6 +58,50 @@ __device__ __forceinline__ void store_screen(const ScreenArgs& sa, int u, int c,
 #pragma unroll
   for (int m = 32; m >= 1; m >>= 1) n += __shfl_xor(n, m, kWave);
   if (lane == 0) sa.neg_half[(size_t)u * sa.tiles * 16 + c] = (float)(-0.5 * n);
+}
+
+// The shift that the screening takes off all points and centroids of a unit: its bound grows with their norms, and
+// keys often have a large component in common, which makes no difference to a distance.  A dim whose values all lie
+// between some a > 0 and 3a (or between -3a and -a) is shifted by the middle of the extremes rounded to the KV
+// dtype, which every value is within a factor of two of, and every mean of them, so that all differences are exact; other
+// dims by zero.  Values below 2^-12 (fp16) and 2^-40 are left alone, so that halves of them are still normal numbers.
+// Block (x, u): dims 8x .. 8x+7 of unit u.  (ms of a build of 4 rounds, 8192 pages against 4096 centroids, a common
+// component 200 times the spread, without and with the shift: one unit 5.2 and 1.3, eight units 18.5 and 1.6; 20 us of it are
+// this kernel's.)
+constexpr int kShiftThreads = 256;
+template <bool BF16>
+__global__ __launch_bounds__(kShiftThreads) void kmeans_shift_kernel(const uint16_t* __restrict__ summ, ScreenArgs sa,
+                                                                   const int32_t* __restrict__ seq_len, int NP, int P, int Hkv) {
+  constexpr int NW = kShiftThreads / kWave;
+  __shared__ float least[NW][8], most[NW][8];
+  const int u = blockIdx.y, tid = threadIdx.x, lane = tid & (kWave - 1), w = tid / kWave;
+  int n_valid = (seq_len[u / Hkv] + P - 1) / P;
+  n_valid = n_valid < NP ? n_valid : NP;
+  const uint16_t* col = summ + (size_t)u * NP * kHeadDim + 8 * blockIdx.x;
+  float lo[8], hi[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) { lo[e] = INFINITY; hi[e] = -INFINITY; }
+  for (int p = tid; p < n_valid; p += kShiftThreads) {
+    float f[8];
+    cvt8<BF16>(*reinterpret_cast<const uint4*>(col + (size_t)p * kHeadDim), f);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) { lo[e] = fminf(lo[e], f[e]); hi[e] = fmaxf(hi[e], f[e]); }
+  }
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    lo[e] = wave_allreduce_min(lo[e]);
+    hi[e] = wave_allreduce_max(hi[e]);
+    if (lane == 0) { least[w][e] = lo[e]; most[w][e] = hi[e]; }
+  }
+  __syncthreads();
+  if (tid < 8) {
+    float a = least[0][tid], b = most[0][tid];
+#pragma unroll
+    for (int i = 1; i < NW; ++i) { a = fminf(a, least[i][tid]); b = fmaxf(b, most[i][tid]); }
+    const float small = BF16 ? 0x1p-40f : 0x1p-12f;
+    const bool alike = (a >= small && b <= 3.f * a && b < INFINITY) || (b <= -small && a >= 3.f * b && a > -INFINITY);
+    sa.shift[(size_t)u * kHeadDim + 8 * blockIdx.x + tid] = alike ? f64_to_kv<BF16>(0.5 * ((double)a + (double)b)) : (uint16_t)0;
+  }
 }
 
 constexpr int kCentroidWaves = 4;     // centroids per block of the kernels that write them
@@ -85,7 +134,7 @@ __global__ __launch_bounds__(kCentroidWaves* kWave) void kmeans_init_kernel(cons
 // fp64 in dim order, ties to the lower centroid.  Computing all of them in fp64 is bound by the
 // fp64 rate (8 units of 8192 pages against 4096 centroids: 4.4 ms a round); so
 // the distances are first bounded on the matrix cores, where a round is 275 GFLOP of 16-bit MFMA (two sweeps of 137):
-//   v = x . (c_hi + c_lo) - |c|^2 / 2        (the larger, the nearer)
+//   v = x . (c_hi + c_lo) - |c|^2 / 2        (the larger, the nearer; x and c less the unit's shift)
 // in fp32, each within E of its true value, E = 2^-14 (|x| C + C^2 / 2) + 2^-20 |x| with C the unit's
 // largest centroid norm.  That covers the part of c that two 16-bit parts leave out (2^-18 |x| |c| for
 // bf16; for fp16 2^-24, or 2^-25 per dim among its subnormals), and 256 fp32 roundings of sums no
@@ -117,6 +166,12 @@ __device__ __forceinline__ f32x4_c mfma_16x16x32(const uint4& a, const uint4& b,
   }
 }
 
+// a number that the KV dtype holds exactly, as its bits
+template <bool BF16>
+__device__ __forceinline__ u32 narrow_exact(float f) {
+  return BF16 ? __float_as_uint(f) >> 16 : (u32)__builtin_bit_cast(uint16_t, (_Float16)f);
+}
+
 struct AssignSmem {
   uint4 tile[2][2][kScreenTile / 8];                        // [buffer][half of the centroids]
   float best[2][kAssignBlock];                              // largest v of a point in each half
@@ -143,6 +198,8 @@ __global__ __launch_bounds__(kAssignThreads, 2) void kmeans_assign_kernel(const 
   const float* neg_u = sa.neg_half + (size_t)u * sa.tiles * 16;
   const int half = w >> 2, pw = (w & 3) * 64, j = lane & 15, g = lane >> 4;
 
+  const uint16_t* shift_u = sa.shift + (size_t)u * kHeadDim + 8 * g;
+
   // B operands: lane (j, g) of group q holds dims 32c + 8g .. +7 of point pw + 16 q + j
   uint4 x[4][4];
   float slack[4];                                           // 2 E of the point
@@ -162,11 +219,18 @@ __global__ __launch_bounds__(kAssignThreads, 2) void kmeans_assign_kernel(const 
       float n = 0.f;
 #pragma unroll
       for (int c = 0; c < 4; ++c) {
-        x[q][c] = *reinterpret_cast<const uint4*>(row + 32 * c);
-        float f[8];
-        cvt8<BF16>(x[q][c], f);
+        const uint4 raw = *reinterpret_cast<const uint4*>(row + 32 * c), shift = *reinterpret_cast<const uint4*>(shift_u + 32 * c);
+        float f[8], sh[8];
+        cvt8<BF16>(raw, f);
+        cvt8<BF16>(shift, sh);
+        u32* packed = reinterpret_cast<u32*>(&x[q][c]);
 #pragma unroll
-        for (int e = 0; e < 8; ++e) n = fmaf(f[e], f[e], n);
+        for (int e = 0; e < 8; e += 2) {
+          const float f0 = f[e] - sh[e], f1 = f[e + 1] - sh[e + 1];
+          n = fmaf(f0, f0, n);
+          n = fmaf(f1, f1, n);
+          packed[e / 2] = narrow_exact<BF16>(f0) | (narrow_exact<BF16>(f1) << 16);
+        }
       }
       n += __shfl_xor(n, 16, kWave);
       n += __shfl_xor(n, 32, kWave);
@@ -560,13 +624,13 @@ hipError_t kvd_run_build_centroids(kvd_ctx* c, int layer, int iterations, int32_
   int32_t* cpages = c->cluster_pages + lu * c->NP;
   ScreenArgs sa;
   sa.tiles = (c->Nc + 15) / 16;
-  // one temporary block: fp64 centroids, screening tiles, half norms, assignment, pages left open by the screening
+  // one temporary block: fp64 centroids, screening tiles, half norms, assignment, shifts, pages left open by the screening
   const size_t n_cent = (size_t)c->U * c->Nc, n_tiles = (size_t)c->U * sa.tiles, n_points = (size_t)c->U * c->NP;
   size_t at = 0;
   auto place = [&](size_t bytes) { const size_t o = at; at += (bytes + 255) & ~(size_t)255; return o; };
   const size_t o_cent = place(n_cent * kHeadDim * sizeof(double)), o_frag = place(n_tiles * kScreenTile * 2),
                o_neg = place(n_tiles * 16 * sizeof(float)), o_assign = place(n_points * sizeof(int32_t)),
-               o_hard = place(n_points * sizeof(int32_t)), o_n_hard = place((size_t)c->U * sizeof(int32_t));
+               o_shift = place((size_t)c->U * kHeadDim * 2), o_hard = place(n_points * sizeof(int32_t)), o_n_hard = place((size_t)c->U * sizeof(int32_t));
   char* temp = nullptr;
   hipError_t e = hipMalloc(reinterpret_cast<void**>(&temp), at);
   if (e == hipSuccess) {
@@ -574,6 +638,7 @@ hipError_t kvd_run_build_centroids(kvd_ctx* c, int layer, int iterations, int32_
     int32_t* assign = reinterpret_cast<int32_t*>(temp + o_assign);
     sa.frag = reinterpret_cast<uint16_t*>(temp + o_frag);
     sa.neg_half = reinterpret_cast<float*>(temp + o_neg);
+    sa.shift = reinterpret_cast<uint16_t*>(temp + o_shift);
     sa.hard = reinterpret_cast<int32_t*>(temp + o_hard);
     sa.n_hard = reinterpret_cast<int32_t*>(temp + o_n_hard);
     int open_blocks = (4 * c->n_cus + c->U - 1) / c->U;
@@ -585,6 +650,7 @@ hipError_t kvd_run_build_centroids(kvd_ctx* c, int layer, int iterations, int32_
     if (c->bf16) hipLaunchKernelGGL((KERNEL<true>), __VA_ARGS__);              \
     else hipLaunchKernelGGL((KERNEL<false>), __VA_ARGS__);                     \
   } while (0)
+    KVD_DT(kmeans_shift_kernel, dim3(kHeadDim / 8, c->U), dim3(kShiftThreads), 0, s, summ, sa, c->d_seq_len, c->NP, c->P, c->Hkv);
     KVD_DT(kmeans_init_kernel, per_tile_row, centroid_block, 0, s, summ, cent64, sa, c->d_seq_len, c->NP, c->Nc, c->P, c->Hkv);
     for (int it = 0; it < iterations && e == hipSuccess; ++it) {
       KVD_DT(kmeans_assign_kernel, per_points, dim3(kAssignThreads), 0, s, summ, cent64, sa, assign, c->d_seq_len, c->NP, c->Nc,

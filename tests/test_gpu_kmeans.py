@@ -19,6 +19,12 @@ def points(kind, units, pages, dtype, gen):
     x = torch.randn(units, pages, 128, device=R.DEV, generator=gen)
     if kind == "offset":                   # a common mean 200 times the spread
         x = 0.05 * x + 10.0 * torch.randn(units, 1, 128, device=R.DEV, generator=gen).sign()
+    elif kind == "components":             # dims at and beyond the span that is shifted, of either sign, among ordinary ones
+        lo, hi = 1.0, torch.tensor([1.0, 1.5, 3.0, 3.03125, 8.0], device=R.DEV)[torch.arange(128, device=R.DEV) % 5]
+        z = lo + (hi - lo) * torch.rand(x.shape, device=R.DEV, generator=gen)
+        z[:, 0], z[:, 1] = lo, hi
+        size = torch.tensor([100.0, 2.0 ** -12, 2.0 ** -13, 8e3, -30.0, -2.0 ** -12, -1.0], device=R.DEV)[torch.arange(128, device=R.DEV) % 7]
+        x = torch.where(torch.arange(128, device=R.DEV) % 3 == 0, x, z * size)
     elif kind == "tiny":                   # fp16: mostly subnormals
         x = 2e-5 * x
     elif kind == "drift":                  # neighbouring pages alike, so that distances fall slowly along the pages
@@ -44,6 +50,8 @@ def points(kind, units, pages, dtype, gen):
     (300, 300, "normal", "bf16", None),                    # a centroid per page
     (520, 200, "offset", "bf16", None),
     (520, 200, "offset", "f16", None),
+    (520, 200, "components", "bf16", (520 * 16, 300 * 16 + 7)),
+    (520, 200, "components", "f16", (520 * 16, 300 * 16 + 7)),
     (300, 64, "tiny", "f16", None),
     (300, 64, "tiny", "bf16", None),
     (300, 50, "same", "bf16", None),                       # all distances tie
