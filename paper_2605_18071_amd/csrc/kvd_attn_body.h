@@ -226,7 +226,8 @@ __device__ __forceinline__ f32x4 mfma_pv(const uint2& vfrag, const uint2& pfrag,
 // these hold them (bf16 above 2^-100; fp16 parts of 2^15 P above 2^-15, so that the third ends at fp16's smallest
 // number), and in fp32 MFMAs (16x16x4, four times the cycles) for a tile that has a smaller one.  (us per step, three
 // parts and fp32 throughout: 32 units x 85 pages of 24 tokens, G = 7, fp16 31.2 and 32.1; 32 units x 102 pages of
-// 20 tokens, bf16 26.5 and 28.3.  With two fp16 parts the first was 30.6; in fp32 VALU arithmetic 50.6 and 36.5.)
+// 20 tokens, bf16 26.5 and 28.3.  With two fp16 parts the first was 30.6; in fp32 VALU arithmetic 50.6 and 36.5.
+// Of the shapes measured that was faster in one only: 4 units of 14 pages of 40 tokens with one query head, 17.4 and 18.1.)
 // Returns 1 in the workgroup that completed the unit's output, 0 in the others, -1 (from all
 // threads, no output) when a HANDOFF wait ran out.  inputs_ready_tick (one thread passes it)
 // receives the wall clock at which the split's entries were all there.

@@ -919,8 +919,11 @@ __device__ __forceinline__ bool select_resolve_body(const FastArgs& a, int u, Fa
       dst = reinterpret_cast<uint4*>(pool_u + (size_t)sm.assign[jm] * a.page_bytes);
       return true;
     };
-    // BIG: two pages of a group in flight where one does not give each of its threads a load
-    const int pages = BIG && units <= 256 ? 2 : 1;
+    // two pages of a group in flight where one does not give each of its threads a load, that is up to 7 tokens (us per
+    // step with one and two: 8 units of 8000 pages of 1, 2 and 3 tokens 74.3, 77.8, 76.8 and 58.2, 62.1, 64.5, of 6 and
+    // 7 tokens 70.0, 56.7 and 67.7, 55.2; units of 20000 pages and more, 6, 3 and 1 tokens 83.8, 91.8, 123.2 and 73.0,
+    // 77.3, 95.2; but with pages of 20 tokens 221.7 and 225.7)
+    const int pages = units <= 256 ? 2 : 1;
     for (int jm = grp; jm < m; jm += pages * kCopyGroups) {
       const uint4 *s0 = nullptr, *s1 = nullptr;
       uint4 *d0 = nullptr, *d1 = nullptr;
