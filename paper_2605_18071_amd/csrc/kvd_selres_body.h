@@ -224,16 +224,15 @@ __device__ __forceinline__ int victim_bucket(long long age, int page, int NP) {
   return (int)(2048 - 32 * age) + (int)(((long long)page * 32) / NP);
 }
 
-// Top-K selection of a unit whose scores do not fit the workgroup's registers (see
-// select_resolve_body for the rules).  The scores are read three times, 16 bytes per lane: for the
-// extremes, for the histogram, and for which pages lie before the decisive bucket and which in it; the
-// later passes find them in the L2.  A wave owns 256 * nq consecutive pages, of which a lane holds
+// Top-K selection of a unit of more pages than the ordinary form holds (see select_resolve_body for
+// the rules).  Three passes over the scores: for the extremes, for the histogram, and for which pages
+// lie before the decisive bucket and which in it.  HELD: at most 8 quads per lane (NP <= 32 NT), read once, 16
+// bytes per lane, and kept in registers; with more pages every pass reads them, the later ones from the L2 (32 units
+// of 32768 pages: 86.0 us a step with three reads, 84.6 with one).  A wave owns 256 * nq consecutive pages, of which a lane holds
 // two 64-bit masks.  One workgroup per unit, so the passes are bound by what one CU reads from its L2 and
 // by instruction issue.  32 units of 32768 pages and 8192 slots:
 // selection, directory update and fetch of an all-hit step 23 us, against 115 us as the size-agnostic kernels,
 // which refine their keys over global memory pass by pass (select 90, resolve 20, fetch 5).
-// HELD: at most 8 quads per lane (NP <= 32 NT), which the registers do hold: read once (the step of the shape above
-// 86.0 us with three reads, 84.6 with one).
 template <int NT, bool HELD>
 __device__ __forceinline__ void select_big(const FastArgs& a, int u, int seq, FastSmem<NT, true>& sm, int& flip) {
   constexpr int NW = NT / kWave;

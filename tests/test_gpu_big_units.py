@@ -69,3 +69,37 @@ def test_stages_one_by_one():
         assert torch.equal(rig.out, whole.out) and torch.equal(rig.lse, whole.lse)
     rig.close()
     whole.close()
+
+
+@pytest.mark.parametrize("mb,pool", [(1, 0), (2, 0), (1, 700)])
+def test_hierarchical_index_with_more_slots_than_the_registers_hold(mb, pool):
+    """Selection through the centroids, victims by the score of their cluster among 4300 slots, all taken."""
+    w = small("big-hier", ctx=4 * 6000, page=4, topk_pages=500, capacity=4300, batch=2, n_kv_heads=1, n_q_heads=4,
+              heavy_count=32, steps=4, policy="lookahead", lookahead_pool=pool, index_centroids=1200, index_iterations=2)
+    rig = R.Rig(w, seq_lens=[w.ctx - 1, w.ctx - 4 * 900], micro_batches=mb)
+    assert rig.kvd.step_form() == mb
+    warm = list(range(700, 5000))
+    rig.kvd.cache_warm(0, warm * w.units, [len(warm)] * w.units)
+    units = [R.OracleUnit(rig, 0, b, 0) for b in range(w.batch)]
+    for ou in units:
+        ou.window.warm(warm, stamp=-1)
+    rep = R.run_steps(rig, units, w.steps, check_dir_every=2, progress=f"big-hier-{mb}-{pool}")
+    assert rep.unit_steps == w.steps * w.units and rig.kvd.stats().evictions > w.units
+    assert rep.tie_divergences <= 2 and rep.victim_tie_divergences <= 4
+    rig.close()
+
+
+def test_every_way_through_a_step_gives_the_same(tmp_path):
+    """Two groups on streams, the tier behind the window and the profiled step against the plain chain of kernels."""
+    w = small("big-ways", ctx=4 * 17000, page=4, topk_pages=200, capacity=500, batch=2, n_kv_heads=1, n_q_heads=4, steps=4)
+    plain, groups, tiered, profiled = (R.Rig(w, seq_lens=[w.ctx - 2, w.ctx // 2], micro_batches=mb) for mb in (1, 2, 1, 1))
+    tiered.attach_tier(str(tmp_path / "kv.bin"), extent_pages=8, pool_extents=600, max_run_extents=8)
+    profiled.kvd.set_profiling(1)
+    for t, q in enumerate(R.W.query_stream(w, plain.q0, w.steps, R.DEV)):
+        for rig in (plain, groups, tiered, profiled):
+            rig.step(0, t, q[0])
+        for rig in (groups, tiered, profiled):
+            for name in ("sel_pages", "sel_slots", "hit_mask", "counts", "out", "lse"):
+                assert torch.equal(getattr(rig, name), getattr(plain, name)), name
+    for rig in (plain, groups, tiered, profiled):
+        rig.close()

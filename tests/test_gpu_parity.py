@@ -468,8 +468,8 @@ def test_step_parity_at_the_largest_sizes_of_the_fused_kernels(mb, policy):
 
 
 def test_step_parity_beyond_the_fused_kernels_sizes():
-    """More pages (16400) and more slots (4100) than the register-resident kernels take: the
-    size-agnostic select / resolve / fetch kernels run without being asked for."""
+    """More pages (16400) and more slots (4100) than the register-resident kernels hold: the form of
+    the fused kernel that reads slots and, beyond 32768 pages, scores again from memory runs without being asked for."""
     w = small("beyond", ctx=16 * 16400, topk_pages=300, capacity=4100, batch=1, n_kv_heads=2, n_q_heads=4,
               heavy_count=32, steps=3, seed=31338)
     rig = R.Rig(w, seq_lens=[w.ctx - 21])
@@ -1590,8 +1590,8 @@ def test_hierarchical_index_argument_errors():
 
 @pytest.mark.parametrize("cfg", [2, 5])
 def test_size_agnostic_select_resolve_kernels(cfg, monkeypatch):
-    """The register-resident fused kernel covers up to 16384 pages and 4096 slots per unit; larger
-    units take separate select / resolve / fetch kernels.  Force that path on a small workload."""
+    """The fused kernel covers up to 65536 pages and 16384 slots per unit (in registers up to 16384 and
+    4096); larger units take separate select / resolve / fetch kernels.  Force that path on a small workload."""
     monkeypatch.setenv("KVD_GENERIC_SELECT", "1")
     w = SCALED[cfg]
     rig = R.Rig(w)

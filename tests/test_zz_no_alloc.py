@@ -1,7 +1,7 @@
 """kvd_sparse_decode_attn_noalloc (the attention stage for callers that cannot allocate) against
 kvd_sparse_decode_attn on the same pool, selection and slots, through the C ABI: two calls in a
-row on the library's one scratch array, the second with a smaller input; page sizes of both
-attention kernels; the refusal of sizes beyond the array."""
+row on the library's one scratch array, the second with a smaller input; page sizes of all three
+slot layouts; the refusal of sizes beyond the array."""
 import ctypes as C
 
 import numpy as np
@@ -32,7 +32,7 @@ def _filled_context(page, dtype, batch, seq_lens):
     return w, rig, qs[-1]
 
 
-@pytest.mark.parametrize("page,dtype", [(16, "bf16"), (32, "f16"), (8, "bf16")])
+@pytest.mark.parametrize("page,dtype", [(16, "bf16"), (32, "f16"), (8, "bf16"), (12, "bf16"), (24, "f16"), (1, "f16")])
 def test_noalloc_attention_matches_the_context_entry_point_twice_in_a_row(page, dtype):
     B = 5
     seq_lens = [page * 200, page * 200 - 3, page * 150 + 1, page * 200, page * 97]
