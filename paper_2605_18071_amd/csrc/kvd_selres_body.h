@@ -392,7 +392,7 @@ __device__ __forceinline__ void select_big(const FastArgs& a, int u, int seq, Fa
 // the hierarchical index's cluster selection, by the same workgroup — and leaves it in sm.sel
 // (16-bit pages, kAbsent = padding) and in a.sel_pages; nothing is read back from global memory.
 // BIG: more pages than the registers hold (NP <= KVD_BIG_MAX_PAGES whatever IPT, Cmax <= KVD_BIG_MAX_CAPACITY;
-// without HANDOFF): the unit's scores are read once per pass over the pages instead.
+// without HANDOFF): select_big takes the pages, slots are read again where they are needed.
 struct ScoresAlreadyThere { __device__ bool operator()() const { return true; } };
 template <int NT, int IPT, bool DO_SELECT, bool DO_RESOLVE, bool HANDOFF, class ScoresReady = ScoresAlreadyThere,
           bool SEL_IN_LDS = false, bool BIG = false, bool HELD = false>
