@@ -251,7 +251,7 @@ int kvd_create(const kvd_config* cfg, kvd_ctx** out) {
   c->scale = cfg->softmax_scale > 0.f ? cfg->softmax_scale : 1.0f / sqrtf((float)c->D);
   c->page_bytes = (size_t)2 * c->P * c->D * 2;
   int S = cfg->attn_splits;
-  if (S == 0) S = kvd_attn_splits(c->tiled == kvd::kLayoutNatural ? 4 : 16, c->U, c->k, c->P, c->n_cus);
+  if (S == 0) S = kvd_attn_splits(c->tiled == kvd::kLayoutNatural ? kNaturalLeast : 16, c->U, c->k, c->P, c->n_cus);
   if (S > c->k) S = c->k;
   c->S = S;
   // The one-launch step runs one workgroup per CU: 512 threads with 256 registers per lane (three

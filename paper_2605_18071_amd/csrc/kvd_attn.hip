@@ -83,9 +83,12 @@ static bool dispatch_group(int G, int layout, const AttnArgs& a, dim3 grid, hipS
 //    with few units that costs more than shorter splits save.  us per step with a split per CU and with this rule: 8
 //    units of 128 pages of 64 tokens 36.1 and 34.4, 2 units of 1024 pages of 16 31.1 and 29.1;
 //  - no split is left without pages.
+//  - over natural slots there are never more workgroups than CUs: the few of a second round take as long again (24
+//    units x 53 pages of 24 tokens 25.5 us a step with 11 splits, 23.6 with 10; 96 units x 102 pages of 20 tokens 49.4
+//    with 3, 41.0 with 2).
 int kvd_attn_splits(int least, int U, int k, int P, int cus) {
   const int tiles = (k * P + 15) / 16;                 // of a unit's selection
-  int S = (cus + U / 2) / U;
+  int S = least == kNaturalLeast ? cus / U : (cus + U / 2) / U;
   if (S > tiles / least) S = tiles / least;
   if (S > 16 && S > tiles / 32) S = tiles / 32 > 16 ? tiles / 32 : 16;
   if (S > KVD_MAX_SPLITS) S = KVD_MAX_SPLITS;
@@ -201,7 +204,7 @@ extern "C" int kvd_sparse_decode_attn_noalloc(const void* q, const void* slot_po
   }
   const int U = batch * n_kv_heads;
   const int layout = slot_layout_of(page_size);
-  int S = attn_splits == 0 ? kvd_attn_splits(layout == kLayoutNatural ? 4 : 16, U, topk_pages, page_size, cus) : attn_splits;
+  int S = attn_splits == 0 ? kvd_attn_splits(layout == kLayoutNatural ? kNaturalLeast : 16, U, topk_pages, page_size, cus) : attn_splits;
   if (S > topk_pages) S = topk_pages;
   // the scratch array, cut into tickets [U], (max, sum) [U][S][G][2] and accumulators [U][S][G][D]
   const size_t rows = (size_t)U * S * G;

@@ -149,6 +149,7 @@ void* kvd_tier_pool_of(const kvd_tier* t);
 hipError_t kvd_launch_attend(kvd_ctx* c, int layer, const void* q, const int32_t* sel_pages,
                              const int32_t* sel_slots, float* out, float* lse, int u0, int u1, hipStream_t s,
                              hipEvent_t between = nullptr);   // `between`: recorded after the attention kernel, before the merge
+constexpr int kNaturalLeast = 4;            // `least` of kvd_attn_splits over natural slots
 int kvd_attn_splits(int least, int U, int k, int P, int cus);
 // The whole step as one launch (kvd_step.hip); usable when kvd_single_launch_ok.
 bool kvd_single_launch_ok(const kvd_ctx* c);
