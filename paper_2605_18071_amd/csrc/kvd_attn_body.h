@@ -227,7 +227,9 @@ __device__ __forceinline__ f32x4 mfma_pv(const uint2& vfrag, const uint2& pfrag,
 // number), and in fp32 MFMAs (16x16x4, four times the cycles) for a tile that has a smaller one.  (us per step, three
 // parts and fp32 throughout: 32 units x 85 pages of 24 tokens, G = 7, fp16 31.2 and 32.1; 32 units x 102 pages of
 // 20 tokens, bf16 26.5 and 28.3.  With two fp16 parts the first was 30.6; in fp32 VALU arithmetic 50.6 and 36.5.
-// Of the shapes measured that was faster in one only: 4 units of 14 pages of 40 tokens with one query head, 17.4 and 18.1.)
+// Of the shapes measured that was faster only with one query head to a KV head, for small ones above all: 4 units x 14
+// pages of 40 tokens 17.5 and 18.4, 16 x 26 of 20 19.4 and 20.3, 8 x 170 of 12 22.2 and 22.7, 64 x 102 of 20 30.7 and 31.4,
+// but 256 x 51 of 20 44.9 and 41.0.)
 // Returns 1 in the workgroup that completed the unit's output, 0 in the others, -1 (from all
 // threads, no output) when a HANDOFF wait ran out.  inputs_ready_tick (one thread passes it)
 // receives the wall clock at which the split's entries were all there.
@@ -357,7 +359,11 @@ __device__ __forceinline__ int attend_mfma_body(const AttnArgs& a, AttnSmem<Grou
       return;
     }
     if (NATURAL) {
-      // token d of the tile: row (16 t + d) % P of entry (16 t + d) / P
+      // token d of the tile: row (16 t + d) % P of entry (16 t + d) / P.  Each lane looks up the token of its K row, and
+      // learns where its V rows are from the lanes 4g .. 4g+3, which have looked up their tokens.  (us per step with five
+      // lookups per lane and so: 160 units x 85 pages of 12 tokens, G = 2 and 7, 49.7, 52.0 and 37.5, 40.0; 40 x 300
+      // pages of 6 34.8 and 31.4; 96 x 102 pages of 20 41.0 and 40.4; 16 x 26 pages of 20 20.0 and 20.3.  Ways of their own
+      // for pages of more and of up to 16 tokens: the last gained nothing, large ones lost 10 % to the longer code.)
       const int t_u = __builtin_amdgcn_readfirstlane(t);
       const int e0 = (int)((u32)(((u64)(16 * t_u) * recip) >> 32)) + (a.P == 1 ? 16 * t_u : 0), row0 = 16 * t_u - e0 * a.P;
       auto entry = [&](int e, int& page, int& slot) {
@@ -368,48 +374,42 @@ __device__ __forceinline__ int attend_mfma_body(const AttnArgs& a, AttnSmem<Grou
         }
         if (slot >= a.Cmax) slot = -1;
       };
-      int page0 = -1, slot0 = -1, page1 = -1, slot1 = -1;   // P > 16: the tile lies in entries e0 and e0 + 1
-      if (a.P > 16) {
-        entry(e0, page0, slot0);
+      int page, slot, row = row0 + 4 * (j & 3) + (j >> 2);
+      if (a.P > 16) {                                    // the tile lies in entries e0 and e0 + 1
+        int page1, slot1;
+        entry(e0, page, slot);
         entry(e0 + 1, page1, slot1);
-        page0 = __builtin_amdgcn_readfirstlane(page0); slot0 = __builtin_amdgcn_readfirstlane(slot0);
+        page = __builtin_amdgcn_readfirstlane(page); slot = __builtin_amdgcn_readfirstlane(slot);
         page1 = __builtin_amdgcn_readfirstlane(page1); slot1 = __builtin_amdgcn_readfirstlane(slot1);
+        const bool next = row >= a.P;
+        row -= next ? a.P : 0;
+        page = next ? page1 : page;
+        slot = next ? slot1 : slot;
+      } else {
+        const int de = a.P == 1 ? row : (int)__umulhi((u32)row, recip);
+        row -= de * a.P;
+        entry(e0 + de, page, slot);
       }
-      auto place = [&](int d, int& page, int& slot, int& row) {
-        row = row0 + d;
-        if (a.P > 16) {
-          const bool next = row >= a.P;
-          row -= next ? a.P : 0;
-          page = next ? page1 : page0;
-          slot = next ? slot1 : slot0;
-        } else {
-          const int de = a.P == 1 ? row : (int)__umulhi((u32)row, recip);
-          row -= de * a.P;
-          entry(e0 + de, page, slot);
-        }
-      };
-      int page, slot, row;
-      place(4 * (j & 3) + (j >> 2), page, slot, row);
       const bool kok = page >= 0 && slot >= 0 && page * a.P + row < seq;
       const u32 valid = (u32)(__ballot(kok) & 0xffffull);   // bit i: the token of row i takes part
       tl.valid = valid;
       if (valid == 0) return;
+      const int krow = slot * 2 * a.P + row;             // of the unit's slots, in rows of 256 bytes (below 2^25)
+      int vrow[4];
+#pragma unroll
+      for (int m = 0; m < 4; ++m) vrow[m] = __shfl(krow, 4 * g + m, kWave) + a.P;
 #pragma unroll
       for (int c = 0; c < 4; ++c) { tl.k[c] = make_uint4(0u, 0u, 0u, 0u); tl.v[c] = make_uint4(0u, 0u, 0u, 0u); }
       if (kok) {
         // (each 128-byte line is the business of two of these loads: no streaming hint)
-        const char* kb = pool_u + (size_t)slot * a.page_bytes + (u32)(row * kRowBytes + g * 16);
+        const char* kb = pool_u + (size_t)krow * kRowBytes + g * 16;
 #pragma unroll
         for (int c = 0; c < 4; ++c) tl.k[c] = *reinterpret_cast<const uint4*>(kb + c * 64);
       }
       const u32 mine = (valid >> (4 * g)) & 15u;
 #pragma unroll
-      for (int m = 0; m < 4; ++m) {
-        if ((mine >> m) & 1u) {                        // (a token that takes no part may hold anything: its V stays zero)
-          place(4 * m + g, page, slot, row);
-          tl.v[m] = load_stream16(pool_u + (size_t)slot * a.page_bytes + (u32)((a.P + row) * kRowBytes + j * 16));
-        }
-      }
+      for (int m = 0; m < 4; ++m)                        // (a token that takes no part may hold anything: its V stays zero)
+        if ((mine >> m) & 1u) tl.v[m] = load_stream16(pool_u + (size_t)vrow[m] * kRowBytes + j * 16);
       return;
     }
     const int e = t / tiles_per_page, tile = t % tiles_per_page;
