@@ -4,6 +4,7 @@
 // single-launch layer-step kernel.
 #pragma once
 #include "kvd_device.h"
+#include "kvd_internal.h"
 
 namespace kvd {
 
@@ -11,8 +12,11 @@ namespace kvd {
 // load covers 4 summary rows (4 x 256 B): lane (r, c) = (lane / 16, lane % 16) holds dims
 // 8c..8c+7 of row r.  The 16 partial dot products of a row are summed with DPP row rotations;
 // after 16 loads lane (r, c) keeps the score of page base + 4c + r and the wave stores 64
-// consecutive scores.  The first summary loads are issued before the query is fetched, so the
-// wave does not sit idle for a round trip before it starts streaming.
+// consecutive scores.  The query's rows and the first summaries are on their way together: with a load and a wait per row
+// the summaries were waited for with the first row and each further row took a trip to the L2, with nothing streaming
+// (us per step so and with all loads ahead: 128 units x 2048 pages, G = 7, 46.6 and 43.9; 32 units x 2084 pages, G = 7, as a
+// chain 30.9 and 29.2; 4 layers of 32 x 1001 pages, G = 4, 114.1 and 111.6; 128 x 8192 pages 96.3 and 94.7).  16 loads
+// ahead of the first pass instead of 8 gained nothing (43.8 to 44.2, 29.4, 111.3, 95.5).
 //   summ_u   [NP][D]  summaries of the unit
 //   q_group  [G][D]   the unit's G query heads
 //   scores_u [NP]
@@ -27,6 +31,14 @@ __device__ __forceinline__ void score_wave(const uint16_t* __restrict__ summ_u, 
   if (wave_base >= NP) return;
   const uint16_t* srow = summ_u + c * 8;
 
+  // All of the query's rows are asked for at once and before the first summaries: loads return in order, so the wait for
+  // the rows leaves the summaries in flight.  Rows beyond the group are out of the buffer's bounds and read as zero,
+  // which the sums do not notice.
+  const __amdgpu_buffer_rsrc_t q_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(q_group), 0, G * kRowBytes, 0x00020000);
+  u32x4_t qraw[KVD_MAX_GROUP];
+#pragma unroll
+  for (int g = 0; g < KVD_MAX_GROUP; ++g) qraw[g] = __builtin_amdgcn_raw_buffer_load_b128(q_rsrc, c * 16 + g * kRowBytes, 0, 0);
+
   uint4 raw[8];
   auto issue = [&](int base, int half) {
 #pragma unroll
@@ -37,15 +49,15 @@ __device__ __forceinline__ void score_wave(const uint16_t* __restrict__ summ_u, 
     }
   };
   issue(wave_base, 0);
+  __builtin_amdgcn_sched_barrier(0);                   // (the conversions of the query stay behind the loads)
 
   float qbar[8];
 #pragma unroll
   for (int e = 0; e < 8; ++e) qbar[e] = 0.f;
-  const uint16_t* qrow = q_group + c * 8;
-  for (int g = 0; g < G; ++g) {
-    const uint4 qraw = *reinterpret_cast<const uint4*>(qrow + (size_t)g * kHeadDim);
+#pragma unroll
+  for (int g = 0; g < KVD_MAX_GROUP; ++g) {
     float f[8];
-    cvt8<BF16>(qraw, f);
+    cvt8<BF16>(make_uint4(qraw[g].x, qraw[g].y, qraw[g].z, qraw[g].w), f);
 #pragma unroll
     for (int e = 0; e < 8; ++e) qbar[e] += f[e];
   }
