@@ -294,7 +294,7 @@ __device__ __forceinline__ int attend_mfma_body(const AttnArgs& a, AttnSmem<Grou
       u64 v = load_agent(ent + i);
       while (!(v >> 63)) {
         if (t0 == 0) t0 = wall_clock64();
-        __builtin_amdgcn_s_sleep(8);
+        __builtin_amdgcn_s_sleep(2);
         v = load_agent(ent + i);
         if (!(v >> 63) && wall_clock64() - t0 > a.wait_limit) { failed = 1; break; }
       }

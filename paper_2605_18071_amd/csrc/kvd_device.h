@@ -71,6 +71,17 @@ __device__ __forceinline__ bool block_wait_equal(const int32_t* flag, int32_t wa
   return *lds_ok != 0;
 }
 
+// The same by one wave for itself, without a barrier: every lane of the wave gets the verdict.
+__device__ __forceinline__ bool wave_wait_equal(const int32_t* flag, int32_t want, long long limit) {
+  if (__builtin_amdgcn_readfirstlane(load_agent(flag)) == want) return true;
+  const long long t0 = wall_clock64();
+  for (;;) {
+    __builtin_amdgcn_s_sleep(1);
+    if (__builtin_amdgcn_readfirstlane(load_agent(flag)) == want) return true;
+    if (wall_clock64() - t0 > limit) return false;
+  }
+}
+
 // ---- 16-bit -> fp32, eight elements of one 16-byte load -------------------------------------
 template <bool BF16>
 __device__ __forceinline__ void cvt8(const uint4& raw, float (&f)[8]) {
@@ -141,23 +152,28 @@ __device__ __forceinline__ int block_exclusive_scan(int v, int* smem, int& total
   return base + inc - v;
 }
 
-// min / max / sum over the 64 lanes with DPP rotations inside the rows of 16 and two cross-row
-// exchanges; every lane gets the result
+// min / max over the 64 lanes with DPP moves only (the cross-row steps of wave_inclusive_scan); every lane gets lane 63's result
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ float dpp_keep(float v) {   // lanes of rows outside ROW_MASK keep v
+  return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(v), __float_as_int(v), CTRL, ROW_MASK, 0xf, false));
+}
 __device__ __forceinline__ float wave_allreduce_min(float v) {
   v = fminf(v, dpp_mov<0x128>(v));
   v = fminf(v, dpp_mov<0x124>(v));
   v = fminf(v, dpp_mov<0x122>(v));
   v = fminf(v, dpp_mov<0x121>(v));
-  v = fminf(v, __shfl_xor(v, 16, kWave));
-  return fminf(v, __shfl_xor(v, 32, kWave));
+  v = fminf(v, dpp_keep<0x142, 0xa>(v));
+  v = fminf(v, dpp_keep<0x143, 0xc>(v));
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), kWave - 1));
 }
 __device__ __forceinline__ float wave_allreduce_max(float v) {
   v = fmaxf(v, dpp_mov<0x128>(v));
   v = fmaxf(v, dpp_mov<0x124>(v));
   v = fmaxf(v, dpp_mov<0x122>(v));
   v = fmaxf(v, dpp_mov<0x121>(v));
-  v = fmaxf(v, __shfl_xor(v, 16, kWave));
-  return fmaxf(v, __shfl_xor(v, 32, kWave));
+  v = fmaxf(v, dpp_keep<0x142, 0xa>(v));
+  v = fmaxf(v, dpp_keep<0x143, 0xc>(v));
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), kWave - 1));
 }
 
 __device__ __forceinline__ u64 shfl_xor_u64(u64 v, int m) {

@@ -5,11 +5,18 @@
 // move — Roofline section).  Shared by the stand-alone kernel and the single-launch layer-step
 // kernel.
 //
-// Selection and victim choice are both "the n smallest of distinct 64-bit keys" problems and share
-// one two-level routine: an LDS histogram over a monotone bucket function narrows the answer to
+// Selection and victim choice are both "the n smallest of distinct 64-bit keys" problems: an LDS
+// histogram over a monotone bucket function narrows the answer to
 // one bucket, whose few members are ranked exactly.  The items stay in registers; only a bucket
 // with more than 1024 members (degenerate inputs, e.g. all scores equal) falls back to radix
-// refinement.  The page -> slot map of the unit is rebuilt in LDS from the slot array at every
+// refinement.  What bounds it is the chain of instructions and barriers that one workgroup goes through (cycles until the
+// entries are out, 512 threads and up to 2048 pages: 11600 with block scans, a threshold handed around through LDS and
+// one store at a time from the lanes that own the pages, 7400 to 9300 so), hence: each wave reads the whole histogram and
+// finds the bucket for itself; a list is ranked only when the decisive bucket does not go in whole; what is selected goes to
+// LDS at its place and out from there, by full waves.  (us per step before and after: 8 units x 256 pages 14.7 and 13.5, 4
+// layers of 32 x 1001 pages 111.6 and 108.5, 20 x 335 pages 30.1 and 28.8.  The wait between scoring and selection is no
+// matter of cold code: a rehearsal of the selection on the scores of the step before, while those of this step come in,
+// made it no faster.)  The page -> slot map of the unit is rebuilt in LDS from the slot array at every
 // launch, so a lookup never waits on a dependent global load; every global load the block needs
 // is issued in its first instructions.
 #pragma once
@@ -89,14 +96,18 @@ struct FastSmem {
     uint16_t vt[kCopyGroups][kTileTokens * kHeadDim];    // V tiles in flight during the fetch
   } a;
   uint16_t p2s[kMaxPages];                               // page -> slot of this unit, kAbsent = not resident
-  page_t sel[KVD_MAX_TOPK];                              // selected pages (kNoPage = padding)
+  union {
+    page_t sel[KVD_MAX_TOPK + (BIG ? 0 : kWave)];        // selected pages (kNoPage = padding)
+    u32 miss[KVD_MAX_TOPK];                              // then: page (low half) and entry of the selection of the i-th miss
+    static_assert(BIG || sizeof(page_t) * (KVD_MAX_TOPK + kWave) <= sizeof(u32) * KVD_MAX_TOPK, "room behind sel for what is not selected");
+  };
   uint16_t assign[KVD_MAX_TOPK];                         // slot handed to the i-th miss
   u32 hit_bitmap[kMaxCapacity / 32];
   int scan[2][NW];
-  float red_min[NW], red_max[NW];
+  float2 red[NW];                                        // extremes over the waves
   int red_cnt[NW];
   u64 thr;
-  int cand_n, bin, below, n_ev;
+  int cand_n, bin, below, n_ev, late;
   SelectSmem generic;
 };
 
@@ -159,6 +170,69 @@ __device__ __forceinline__ void find_bucket(int need, FastSmem<NT, BIG>& sm, int
   __syncthreads();
 }
 
+// A histogram of 128 * W buckets, two 16-bit counts to a word (a unit of the ordinary form has at most 16384 items): lane l
+// of a wave reads the 2 W buckets from 2 W l on with W / 4 16-byte loads without bank conflicts.
+template <int W>
+__device__ __forceinline__ int packed_bin_word(int bucket) {
+  const int l = bucket / (2 * W), word = (bucket >> 1) & (W - 1);
+  return (((word >> 2) * kWave + l) << 2) | (word & 3);
+}
+template <int W>
+__device__ __forceinline__ void packed_bin_add(u32* hist, int bucket) {
+  atomicAdd(&hist[packed_bin_word<W>(bucket)], 1u << (16 * (bucket & 1)));
+}
+// The bucket that holds the need-th smallest item, the items before it and those in it, the same in every lane.  Each
+// wave finds out for itself: no barrier and nothing handed around.  The histogram is complete (a barrier before).
+template <int W>
+__device__ __forceinline__ void packed_bin_find(const u32* hist, int need, int& bin, int& below, int& count) {
+  const int lane = threadIdx.x & (kWave - 1);
+  u32 sum = 0;
+#pragma unroll
+  for (int i = 0; i < W / 4; ++i) {
+    const uint4 v = reinterpret_cast<const uint4*>(hist)[i * kWave + lane];
+    sum += (v.x + v.y) + (v.z + v.w);                   // (both halves at once: no half of the total reaches 2^16)
+  }
+  const int local = (int)((sum & 0xffffu) + (sum >> 16));
+  const int inc = wave_inclusive_scan(local);
+  const u64 reached = __ballot(inc >= need);
+  const int l = reached ? __ffsll((unsigned long long)reached) - 1 : kWave - 1;
+  const int before = __builtin_amdgcn_readlane(inc - local, l);
+  // lane j < 2 W: the j-th bucket of lane l
+  const int b = 2 * W * l + (lane & (2 * W - 1));
+  const u32 word = hist[packed_bin_word<W>(b)];
+  const int c = lane < 2 * W ? (int)((lane & 1) ? word >> 16 : word & 0xffffu) : 0;
+  const int cum = before + wave_inclusive_scan(c);
+  const u64 at = __ballot(cum >= need);
+  const int j = at ? __ffsll((unsigned long long)at) - 1 : 0;
+  bin = 2 * W * l + j;
+  count = __builtin_amdgcn_readlane(c, j);
+  below = __builtin_amdgcn_readlane(cum, j) - count;
+}
+
+// The r-th smallest of the m keys in the list, which is complete; each wave finds it for itself.
+__device__ __forceinline__ u64 kth_of_list(const u64* list, int m, int r) {
+  const int lane = threadIdx.x & (kWave - 1);
+  for (int c0 = 0; c0 < m; c0 += kWave) {
+    const u64 mine = c0 + lane < m ? list[c0 + lane] : ~0ull;
+    int rank = 0;
+    if (m <= kWave) {
+      // all keys are in the wave's lanes
+      for (int x = 0; x < m; ++x) {
+        const u64 other = ((u64)(u32)__builtin_amdgcn_readlane((int)(mine >> 32), x) << 32) | (u32)__builtin_amdgcn_readlane((int)(u32)mine, x);
+        rank += other < mine ? 1 : 0;
+      }
+    } else {
+      for (int x = 0; x < m; ++x) rank += list[x] < mine ? 1 : 0;
+    }
+    const u64 at = __ballot(c0 + lane < m && rank == r - 1);
+    if (at) {
+      const int l = __ffsll((unsigned long long)at) - 1;
+      return ((u64)(u32)__builtin_amdgcn_readlane((int)(mine >> 32), l) << 32) | (u32)__builtin_amdgcn_readlane((int)(u32)mine, l);
+    }
+  }
+  return ~0ull;                                          // (not reached: 1 <= r <= m)
+}
+
 // The r-th smallest of the m candidates in the list (no barrier since they were put there).
 template <int NT, bool BIG>
 __device__ __forceinline__ u64 rank_candidates(int m, int r, FastSmem<NT, BIG>& sm) {
@@ -186,12 +260,19 @@ __device__ __forceinline__ u64 two_level_select(KeyOf key, BktOf bkt, int need, 
 #pragma unroll UNROLL
   for (int j = 0; j < IPT; ++j) {
     const int bj = bkt(j);
-    if (bj >= 0) atomicAdd(&sm.a.sel.hist[bj], 1u);
+    if (bj < 0) continue;
+    if (BIG) atomicAdd(&sm.a.sel.hist[bj], 1u);
+    else packed_bin_add<16>(sm.a.sel.hist, bj);
   }
-  find_bucket<NT>(need, sm, flip);
-  const int bin = sm.bin;
-  const int r = need - sm.below;
-  const int m = (int)sm.a.sel.hist[bin];
+  int bin, below, m;
+  if (BIG) {
+    find_bucket<NT>(need, sm, flip);
+    bin = sm.bin; below = sm.below; m = (int)sm.a.sel.hist[bin];
+  } else {
+    __syncthreads();
+    packed_bin_find<16>(sm.a.sel.hist, need, bin, below, m);
+  }
+  const int r = need - below;
   if (m > kListCap) return refine(bin, r);
 #pragma unroll UNROLL
   for (int j = 0; j < IPT; ++j)
@@ -300,13 +381,13 @@ __device__ __forceinline__ void select_big(const FastArgs& a, int u, int seq, Fa
   fmin = wave_allreduce_min(fmin);
   fmax = wave_allreduce_max(fmax);
   n_forced = wave_inclusive_scan(n_forced);
-  if (lane == kWave - 1) { sm.red_min[w] = fmin; sm.red_max[w] = fmax; sm.red_cnt[w] = n_forced; }
+  if (lane == kWave - 1) { sm.red[w] = make_float2(fmin, fmax); sm.red_cnt[w] = n_forced; }
   __syncthreads();
   n_forced = 0;
 #pragma unroll
   for (int i = 0; i < NW; ++i) {
-    fmin = fminf(fmin, sm.red_min[i]);
-    fmax = fmaxf(fmax, sm.red_max[i]);
+    fmin = fminf(fmin, sm.red[i].x);
+    fmax = fmaxf(fmax, sm.red[i].y);
     n_forced += sm.red_cnt[i];
   }
   const int k_free = k_eff - n_forced;
@@ -387,17 +468,20 @@ __device__ __forceinline__ void select_big(const FastArgs& a, int u, int seq, Fa
 // is published at once, an entry that missed when the fetched pages have been written through.
 // Needs NP <= NT * IPT, Cmax <= KVD_FAST_MAX_CAPACITY, k <= KVD_MAX_TOPK.
 // scores_ready() (HANDOFF only) is called by all threads once everything that does not depend on
-// the scores has been done; it waits for them and returns false to give up.  Returns false then.
+// the scores has been done; it waits for them and returns false to give up: with DO_SELECT wave by wave, without a barrier
+// inside (a wave loads its scores as soon as it has seen them complete), else as a workgroup.  Returns false then.
+// scores_taken(): every wave has seen them complete (called by all threads).
 // SEL_IN_LDS (with HANDOFF and without DO_SELECT): scores_ready() itself produces the selection —
 // the hierarchical index's cluster selection, by the same workgroup — and leaves it in sm.sel
 // (16-bit pages, kAbsent = padding) and in a.sel_pages; nothing is read back from global memory.
 // BIG: more pages than the registers hold (NP <= KVD_BIG_MAX_PAGES whatever IPT, Cmax <= KVD_BIG_MAX_CAPACITY;
 // without HANDOFF): select_big takes the pages, slots are read again where they are needed.
 struct ScoresAlreadyThere { __device__ bool operator()() const { return true; } };
+struct NothingToDo { __device__ void operator()() const {} };
 template <int NT, int IPT, bool DO_SELECT, bool DO_RESOLVE, bool HANDOFF, class ScoresReady = ScoresAlreadyThere,
-          bool SEL_IN_LDS = false, bool BIG = false, bool HELD = false>
+          bool SEL_IN_LDS = false, bool BIG = false, bool HELD = false, class ScoresTaken = NothingToDo>
 __device__ __forceinline__ bool select_resolve_body(const FastArgs& a, int u, FastSmem<NT, BIG>& sm,
-                                                    ScoresReady scores_ready = ScoresReady()) {
+                                                    ScoresReady scores_ready = ScoresReady(), ScoresTaken scores_taken = ScoresTaken()) {
   static_assert(!(BIG && HANDOFF), "the big form is a kernel of its own");
   typedef typename FastSmem<NT, BIG>::page_t page_t;
   constexpr page_t kNoPage = FastSmem<NT, BIG>::kNoPage;
@@ -468,14 +552,15 @@ __device__ __forceinline__ bool select_resolve_body(const FastArgs& a, int u, Fa
   }
 
   // ---- LDS set-up while the loads are in flight
-  for (int i = tid; i < kRadixBins; i += NT) sm.a.sel.hist[i] = 0;
+  constexpr int kHistWords = BIG ? kRadixBins : kRadixBins / 2;   // (the ordinary form packs two buckets to a word)
+  for (int i = tid; i < kHistWords; i += NT) sm.a.sel.hist[i] = 0;
   if (DO_RESOLVE) {
     u32* p2s32 = reinterpret_cast<u32*>(sm.p2s);
     for (int i = tid; i < (a.NP + 1) / 2; i += NT) p2s32[i] = 0xffffffffu;
     for (int i = tid; i < FastSmem<NT, BIG>::kMaxCapacity / 32; i += NT) sm.hit_bitmap[i] = 0;
     for (int i = tid; i < k; i += NT) sm.assign[i] = kAbsent;
   }
-  if (tid == 0) { sm.cand_n = 0; sm.n_ev = 0; }
+  if (tid == 0) { sm.cand_n = 0; sm.n_ev = 0; sm.late = 0; }
   __syncthreads();
   float vs[BIG ? 1 : CPT];                             // lookahead eviction: this step's score of the page in each slot
   if constexpr (DO_RESOLVE && BIG) {
@@ -491,10 +576,19 @@ __device__ __forceinline__ bool select_resolve_body(const FastArgs& a, int u, Fa
       if (sp[j] >= 0) sm.p2s[sp[j]] = (uint16_t)sl;
     }
   }
+  int32_t* sslots = a.sel_slots + (size_t)u * k;
+  int32_t* hmask = a.hit_mask + (size_t)u * k;
+  int32_t* evout = a.evicted + (size_t)u * k;
+  u64* entry = HANDOFF ? a.sel_entry + (size_t)u * k : nullptr;
   if (HANDOFF) {
     // everything that does not need the scores is done: now wait for them
-    if (!scores_ready()) return false;
-    if (DO_SELECT) load_scores();
+    const bool there = scores_ready();
+    if (DO_SELECT) {
+      if (!there) sm.late = 1;                           // (the verdict is shared at the next barrier)
+      load_scores();
+    } else if (!there) {
+      return false;
+    }
   }
   if constexpr (DO_RESOLVE && !BIG) {
 #pragma unroll
@@ -508,9 +602,9 @@ __device__ __forceinline__ bool select_resolve_body(const FastArgs& a, int u, Fa
   if constexpr (DO_SELECT && BIG) {
     select_big<NT, HELD>(a, u, seq, sm, flip);
     if (!DO_RESOLVE) return true;
-    for (int i = tid; i < kRadixBins; i += NT) sm.a.sel.hist[i] = 0;
-    if (tid == 0) sm.cand_n = 0;
-  } else if (DO_SELECT) {
+  } else if constexpr (DO_SELECT) {
+    constexpr int kBinWords = IPT == 4 ? 8 : 16;       // 1024 or 2048 buckets
+    constexpr float kBins = 128.0f * kBinWords;
     int n_valid = (seq + a.P - 1) / a.P;
     n_valid = n_valid < a.NP ? n_valid : a.NP;
     const int k_eff = k < n_valid ? k : n_valid;
@@ -536,142 +630,156 @@ __device__ __forceinline__ bool select_resolve_body(const FastArgs& a, int u, Fa
       fmin = fminf(fmin, fr ? s[j] : INFINITY);
       fmax = fmaxf(fmax, fr ? s[j] : -INFINITY);
     }
-    int n_forced = __popc(forced_mask);
     fmin = wave_allreduce_min(fmin);
     fmax = wave_allreduce_max(fmax);
-    n_forced = wave_inclusive_scan(n_forced);          // lane 63 holds the wave's count
-    n_forced = __builtin_amdgcn_readlane(n_forced, 63);
-    if (lane == 0) { sm.red_min[w] = fmin; sm.red_max[w] = fmax; sm.red_cnt[w] = n_forced; }
+    if (lane == 0) sm.red[w] = make_float2(fmin, fmax);
     __syncthreads();
-    fmin = sm.red_min[0]; fmax = sm.red_max[0]; n_forced = sm.red_cnt[0];
+    if (HANDOFF && sm.late) return false;
+    scores_taken();
 #pragma unroll
-    for (int i = 1; i < NW; ++i) {
-      fmin = fminf(fmin, sm.red_min[i]);
-      fmax = fmaxf(fmax, sm.red_max[i]);
-      n_forced += sm.red_cnt[i];
+    for (int i = 0; i < NW; ++i) {
+      fmin = fminf(fmin, sm.red[i].x);
+      fmax = fmaxf(fmax, sm.red[i].y);
     }
-    const int k_free = k_eff - n_forced;
+    const int n_free = recent_from > a.sink ? recent_from - a.sink : 0;
+    const int k_free = k_eff - (n_valid - n_free);
     const float range = fmax - fmin;
-    const float inv = range > 0.f ? 2047.0f / range : 0.f;
-    auto bucket_of = [&](float v) -> int { return (int)fminf(fmaxf((fmax - v) * inv, 0.f), 2047.f); };
-    // every free page's bucket, computed once and kept (two per register); 0xffff = not free
-    u32 bk2[IPT / 2];
+    const float inv = range > 0.f ? (kBins - 1.0f) / range : 0.f;
+    auto bucket_of = [&](float v) -> int { return (int)fminf(fmaxf((fmax - v) * inv, 0.f), kBins - 1.0f); };
+    // every free page's bucket, computed once and kept, with many pages per lane two to a register; kNoBucket = not free
+    constexpr int kNoBucket = 0x7fff;
+    constexpr bool kPairs = IPT > 8;
+    u32 bk[kPairs ? IPT / 2 : IPT];
 #pragma unroll
-    for (int j = 0; j < IPT; j += 2) {
-      const u32 b0 = ((free_mask >> j) & 1u) ? (u32)bucket_of(s[j]) : 0xffffu;
-      const u32 b1 = ((free_mask >> (j + 1)) & 1u) ? (u32)bucket_of(s[j + 1]) : 0xffffu;
-      bk2[j / 2] = b0 | (b1 << 16);
+    for (int j = 0; j < IPT; ++j) {
+      const u32 bj = ((free_mask >> j) & 1u) ? (u32)bucket_of(s[j]) : (u32)kNoBucket;
+      if (!kPairs) bk[j] = bj;
+      else if (j & 1) bk[j >> 1] |= bj << 16;
+      else bk[j >> 1] = bj;
     }
-    auto bucket_at = [&](int j) -> int { return (int)((bk2[j >> 1] >> (16 * (j & 1))) & 0xffffu); };
-    auto key_of = [&](int j) -> u64 { return ((u64)fast_descending_key(s[j]) << 32) | (u32)page_of(j); };
-    auto bkt_of = [&](int j) -> int { const int bb = bucket_at(j); return bb == 0xffff ? -1 : bb; };
-    u64 thr = 0;
+    auto bucket_at = [&](int j) -> int { return kPairs ? (int)((bk[j >> 1] >> (16 * (j & 1))) & 0xffffu) : (int)bk[j]; };
+    u32 take = forced_mask;                            // bit j: page_of(j) is selected
     if (k_free > 0) {
-      const float* sc = a.scores + (size_t)u * a.NP;
-      auto refine = [&](int bin, int r) -> u64 {
+#pragma unroll
+      for (int j = 0; j < IPT; ++j)
+        if ((free_mask >> j) & 1u) packed_bin_add<kBinWords>(sm.a.sel.hist, bucket_at(j));
+      __syncthreads();
+      int bin, below, m;
+      packed_bin_find<kBinWords>(sm.a.sel.hist, k_free, bin, below, m);
+      const int r = k_free - below;                    // of the m pages of the decisive bucket r are in
+      // a page in a bucket before the decisive one is in, one in a later bucket is out
+      u32 tied = 0;
+#pragma unroll
+      for (int j = 0; j < IPT; ++j) {
+        const int bb = bucket_at(j);
+        take |= bb < bin ? (1u << j) : 0u;
+        tied |= bb == bin ? (1u << j) : 0u;
+      }
+      if (r == m) {
+        take |= tied;
+      } else if (m <= kListCap) {
+        // their keys go into one list, a wave's with one add to its length
+        if (__any(tied != 0)) {
+          const int mine = __popc(tied), inc = wave_inclusive_scan(mine);
+          int at = 0;
+          if (lane == kWave - 1) at = atomicAdd(&sm.cand_n, inc);
+          at = __builtin_amdgcn_readlane(at, kWave - 1) + inc - mine;
+#pragma unroll
+          for (int j = 0; j < IPT; ++j)
+            if ((tied >> j) & 1u) sm.a.sel.cand[at++] = selection_order_key(s[j], page_of(j));
+        }
+        __syncthreads();
+        const u64 thr = kth_of_list(sm.a.sel.cand, m, r);
+#pragma unroll
+        for (int j = 0; j < IPT; ++j)
+          if (((tied >> j) & 1u) && selection_order_key(s[j], page_of(j)) <= thr) take |= 1u << j;
+      } else {
+        const float* sc = a.scores + (size_t)u * a.NP;
         auto fn = [&](int i, u64& kk) -> bool {
           if (i < a.sink || i >= recent_from) return false;
           const float v = HANDOFF ? load_agent(sc + i) : sc[i];
           if (bucket_of(v) != bin) return false;
-          kk = ((u64)fast_descending_key(v) << 32) | (u32)i;
+          kk = selection_order_key(v, i);
           return true;
         };
-        return block_kth_smallest<NT>(fn, n_valid, r, sm.generic, sm.a.sel.hist);
-      };
-      thr = two_level_select<NT, IPT>(key_of, bkt_of, k_free, sm, flip, refine);
-    }
-    // a page in a bucket before the decisive one is in, one in a later bucket is out; only the
-    // members of the decisive bucket are compared with the threshold key
-    const int bin = k_free > 0 ? sm.bin : -1;
-    u32 take = forced_mask;                            // bit j: page_of(j) is selected
+        const u64 thr = block_kth_smallest<NT>(fn, n_valid, r, sm.generic, sm.a.sel.hist);
 #pragma unroll
-    for (int j = 0; j < IPT; ++j) {
-      const int bb = bucket_at(j);
-      bool t = bb < bin;
-      if (bb == bin) t = key_of(j) <= thr;
-      take |= t ? (1u << j) : 0u;
+        for (int j = 0; j < IPT; ++j)
+          if (((tied >> j) & 1u) && selection_order_key(s[j], page_of(j)) <= thr) take |= 1u << j;
+      }
     }
-    int cnt4[IPT / 4];
-    int cnt = __popc(take);
-#pragma unroll
-    for (int q4 = 0; q4 < IPT / 4; ++q4) cnt4[q4] = __popc((take >> (4 * q4)) & 15u);
+    int32_t* out = a.sel_pages + (size_t)u * k;
     // output in ascending page order = (wave, load, lane, element): one block scan over the
     // lanes' totals gives the wave's first position, wave scans per load give the rest
     int total;
-    const int lane_pos = fast_scan<NT>(cnt, sm, flip, total);
-    int pos_q = __builtin_amdgcn_readfirstlane(lane_pos);   // lane 0: what the waves before this one selected
-    int32_t* out = a.sel_pages + (size_t)u * k;
+    const int lane_pos = fast_scan<NT>(__popc(take), sm, flip, total);
+    if (IPT == 4) {
+      // (a lane's pages follow each other; a page that is not selected goes to a place of the lane's own behind the others)
+      int pos = lane_pos;
 #pragma unroll
-    for (int q4 = 0; q4 < IPT / 4; ++q4) {
-      const int inc = wave_inclusive_scan(cnt4[q4]);
-      int pos = pos_q + inc - cnt4[q4];
-      pos_q += __builtin_amdgcn_readlane(inc, kWave - 1);
+      for (int j = 0; j < IPT; ++j) {
+        const bool in = (take >> j) & 1u;
+        sm.sel[in ? pos : KVD_MAX_TOPK + lane] = (page_t)page_of(j);
+        pos += in ? 1 : 0;
+      }
+    } else {
+      int pos_q = __builtin_amdgcn_readfirstlane(lane_pos);   // lane 0: what the waves before this one selected
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int j = 4 * q4 + e;
-        if ((take >> j) & 1u) {
-          if (pos < k) {
-            const int p = page_of(j);
-            sm.sel[pos] = (page_t)p;
-            out[pos] = p;
-          }
-          ++pos;
-        }
+      for (int q4 = 0; q4 < IPT / 4; ++q4) {
+        const u32 bits = (take >> (4 * q4)) & 15u;
+        const int cnt = __popc(bits), inc = wave_inclusive_scan(cnt);
+        int pos = pos_q + inc - cnt;
+        pos_q += __builtin_amdgcn_readlane(inc, kWave - 1);
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if ((bits >> e) & 1u) sm.sel[pos++] = (page_t)page_of(4 * q4 + e);
       }
     }
-    for (int i = k_eff + tid; i < k; i += NT) {
-      sm.sel[i] = kNoPage;
-      out[i] = -1;
+    for (int i = k_eff + tid; i < k; i += NT) sm.sel[i] = kNoPage;
+    if (!DO_RESOLVE) {
+      __syncthreads();
+      for (int i = tid; i < k; i += NT) out[i] = i < k_eff ? (int)sm.sel[i] : -1;
+      return true;
     }
-    if (!DO_RESOLVE) return true;
-    // the histogram and the candidate counter serve the victim choice next
-    for (int i = tid; i < kRadixBins; i += NT) sm.a.sel.hist[i] = 0;
-    if (tid == 0) sm.cand_n = 0;
   }
-  __syncthreads();
 
   // ---- resolve: lookup in the LDS map
-  int32_t* sslots = a.sel_slots + (size_t)u * k;
-  int32_t* hmask = a.hit_mask + (size_t)u * k;
-  int32_t* evout = a.evicted + (size_t)u * k;
-  u64* entry = HANDOFF ? a.sel_entry + (size_t)u * k : nullptr;
-  const int per = (k + NT - 1) / NT;                  // consecutive selected entries per thread
+  __syncthreads();                                     // the selection is in LDS
+  const int per = (k + NT - 1) / NT;                   // consecutive selected entries per thread
   const int i0 = tid * per;
-  int my_page[KPT], my_slot[KPT];                     // this thread's misses and the slots they get
+  int my_page[KPT];                                    // this thread's misses
   int my_misses = 0, my_hits = 0;
 #pragma unroll
   for (int j = 0; j < KPT; ++j) {
     my_page[j] = -2;
-    my_slot[j] = -1;
     const int i = i0 + j;
     if (j < per && i < k) {
       const page_t entry_page = sm.sel[i];
-      const int p = (int)entry_page;
-      if (entry_page == kNoPage) {                    // padding (or a page the caller made up)
-        sslots[i] = -1;
-        if (HANDOFF) store_agent(entry + i, pack_sel_entry(-1, -1));
-        hmask[i] = 0;
-      } else {
-        const int sl = sm.p2s[p];
-        if (sl != kAbsent) {
-          sstamp[sl] = a.step;
-          atomicOr(&sm.hit_bitmap[sl >> 5], 1u << (sl & 31));
-          sslots[i] = sl;
-          if (HANDOFF) store_agent(entry + i, pack_sel_entry(p, sl));
-          hmask[i] = 1;
-          ++my_hits;
-        } else {
-          my_page[j] = p;
-          ++my_misses;
-        }
+      const bool none = entry_page == kNoPage;         // padding (or a page the caller made up)
+      const int p = none ? -1 : (int)entry_page;
+      const int sl = none ? -1 : (int)sm.p2s[p];
+      const bool hit = !none && sl != kAbsent, miss = !none && sl == kAbsent;
+      if (HANDOFF && !miss) store_agent(entry + i, pack_sel_entry(p, sl));
+      if (hit) {
+        sstamp[sl] = a.step;
+        atomicOr(&sm.hit_bitmap[sl >> 5], 1u << (sl & 31));
       }
+      if (!miss) sslots[i] = sl;
+      hmask[i] = hit ? 1 : 0;
+      if (DO_SELECT && !BIG) a.sel_pages[(size_t)u * k + i] = p;
+      my_hits += hit ? 1 : 0;
+      my_misses += miss ? 1 : 0;
+      if (miss) my_page[j] = p;
     }
   }
   // one scan counts both: misses in the low half, hits in the high half (k <= 2048 each)
   int mh;
-  const int packed_rank = fast_scan<NT>(my_misses | (my_hits << 16), sm, flip, mh);   // barrier inside: the hit bitmap is complete
+  const int ranks = fast_scan<NT>(my_misses | (my_hits << 16), sm, flip, mh);   // barrier inside: everyone is done with sm.sel
+  int miss_rank = ranks & 0xffff;
   const int m = mh & 0xffff, n_hits = mh >> 16;
-  int miss_rank = packed_rank & 0xffff;
+#pragma unroll
+  for (int j = 0; j < KPT; ++j)
+    if (my_page[j] >= 0) sm.miss[miss_rank++] = (u32)my_page[j] | ((u32)(i0 + j) << 16);
   const int e = (R + m - C) > 0 ? (R + m - C) : 0;
   if (m == 0) {
     // every selected page is resident: no slot to find, nothing leaves, nothing to fetch
@@ -685,6 +793,13 @@ __device__ __forceinline__ bool select_resolve_body(const FastArgs& a, int u, Fa
     }
     return true;
   }
+  // the histogram and the candidate counter serve the victim choice next
+  if (DO_SELECT) {
+    __syncthreads();                                   // (the candidates of the selection have been read)
+    for (int i = tid; i < kHistWords; i += NT) sm.a.sel.hist[i] = 0;
+    if (tid == 0) sm.cand_n = 0;
+  }
+  __syncthreads();                                     // ... and the hit bitmap and the misses are complete
 
   // ---- victims: the e smallest (stamp, page) among resident slots that were not hit
   // what this thread's j-th slot holds (the directory is written only after the slots have been handed out)
@@ -722,13 +837,12 @@ __device__ __forceinline__ bool select_resolve_body(const FastArgs& a, int u, Fa
     }
     lo = wave_allreduce_min(lo);
     hi = wave_allreduce_max(hi);
-    if (lane == 0) { sm.red_min[w] = lo; sm.red_max[w] = hi; }
+    if (lane == 0) sm.red[w] = make_float2(lo, hi);
     __syncthreads();
-    lo = sm.red_min[0]; hi = sm.red_max[0];
 #pragma unroll
-    for (int i = 1; i < NW; ++i) {
-      lo = fminf(lo, sm.red_min[i]);
-      hi = fmaxf(hi, sm.red_max[i]);
+    for (int i = 0; i < NW; ++i) {
+      lo = fminf(lo, sm.red[i].x);
+      hi = fmaxf(hi, sm.red[i].y);
     }
     vmin = lo;
     vinv = hi > lo ? 2047.0f / (hi - lo) : 0.f;
@@ -750,7 +864,7 @@ __device__ __forceinline__ bool select_resolve_body(const FastArgs& a, int u, Fa
       pool_thr = block_kth_smallest<NT>(fn, n_valid, a.la_pool, sm.generic, sm.a.sel.hist);
       // (the histogram serves the victim choice next: it must start from zero again)
       __syncthreads();
-      for (int i = tid; i < kRadixBins; i += NT) sm.a.sel.hist[i] = 0;
+      for (int i = tid; i < kHistWords; i += NT) sm.a.sel.hist[i] = 0;
       __syncthreads();
     }
   }
@@ -822,24 +936,17 @@ __device__ __forceinline__ bool select_resolve_body(const FastArgs& a, int u, Fa
     }
   }
   __syncthreads();
-#pragma unroll
-  for (int j = 0; j < KPT; ++j) {
-    const int p = my_page[j];
-    if (p >= 0) {
-      const int i = i0 + j;
-      const int sl = sm.assign[miss_rank];
-      const int slot = sl == kAbsent ? -1 : sl;       // always a slot while the directory is consistent
-      sslots[i] = slot;
-      my_slot[j] = slot;
-      hmask[i] = 0;
-      if (slot >= 0) {
-        spage[slot] = p;
-        sstamp[slot] = a.step;
-      }
-      a.miss_list[((size_t)u * k + miss_rank) * 2] = p;
-      a.miss_list[((size_t)u * k + miss_rank) * 2 + 1] = slot;
-      ++miss_rank;
+  for (int i = tid; i < m; i += NT) {
+    const int p = (int)(sm.miss[i] & 0xffffu), pos = (int)(sm.miss[i] >> 16);
+    const int sl = sm.assign[i];
+    const int slot = sl == kAbsent ? -1 : sl;         // always a slot while the directory is consistent
+    sslots[pos] = slot;
+    if (slot >= 0) {
+      spage[slot] = p;
+      sstamp[slot] = a.step;
     }
+    a.miss_list[((size_t)u * k + i) * 2] = p;
+    a.miss_list[((size_t)u * k + i) * 2 + 1] = slot;
   }
   for (int j = e + tid; j < k; j += NT) evout[j] = -1;
   if (tid == 0) {
@@ -857,9 +964,8 @@ __device__ __forceinline__ bool select_resolve_body(const FastArgs& a, int u, Fa
     if (!HANDOFF) return;
     wave_drain_memory();
     __syncthreads();
-#pragma unroll
-    for (int j = 0; j < KPT; ++j)
-      if (my_page[j] >= 0) store_agent(entry + i0 + j, pack_sel_entry(my_page[j], my_slot[j]));
+    for (int i = tid; i < m; i += NT)
+      store_agent(entry + (sm.miss[i] >> 16), pack_sel_entry((int)(sm.miss[i] & 0xffffu), sm.assign[i] == kAbsent ? -1 : (int)sm.assign[i]));
   };
   if (!a.do_gather) {
     publish_misses();
@@ -867,16 +973,8 @@ __device__ __forceinline__ bool select_resolve_body(const FastArgs& a, int u, Fa
   }
 
   // ---- fetch the unit's missed pages: groups of 256 threads, one 16-token tile (or one or two pages
-  // in the natural layout) each per round; packed pages by waves.  Miss j is (page, sm.assign[j]); the pages are staged in
-  // sm.sel[j], each thread writing the misses it found at their ranks.
-  __syncthreads();                                     // everyone is done with sm.sel / sm.a.sel
-#pragma unroll
-  for (int j = 0; j < KPT; ++j) {
-    // my misses keep their rank: miss_rank was advanced once per miss above
-    const int p = my_page[KPT - 1 - j];
-    if (p >= 0) sm.sel[--miss_rank] = (page_t)p;
-  }
-  __syncthreads();
+  // in the natural layout) each per round; packed pages by waves.  Miss j is page sm.miss[j], slot sm.assign[j].
+  __syncthreads();                                     // everyone is done with sm.a.sel
   const int grp = tid >> 8, gt = tid & 255;
   const char* store_u = a.store + (size_t)u * a.NP * a.page_bytes;
   char* pool_u = a.pool + (size_t)u * a.Cmax * a.page_bytes;
@@ -886,7 +984,7 @@ __device__ __forceinline__ bool select_resolve_body(const FastArgs& a, int u, Fa
     uint16_t* vt = &sm.a.vt[0][0] + w * (4 * kHeadDim);
     for (int it = w; it < n_items; it += NW) {
       const int jm = it / groups, tg = it % groups;
-      const int page = (int)sm.sel[jm];
+      const int page = (int)(sm.miss[jm] & 0xffffu);
       const int slot = sm.assign[jm] == kAbsent ? -1 : sm.assign[jm];
       if (slot >= 0)
         packed_copy_group<HANDOFF>(store_u + (size_t)page * a.page_bytes, a.P, tg, pool_u + (size_t)slot * a.page_bytes, vt);
@@ -901,7 +999,7 @@ __device__ __forceinline__ bool select_resolve_body(const FastArgs& a, int u, Fa
       if (on) {
         const int jm = it / tiles;
         tile = it % tiles;
-        page = (int)sm.sel[jm];
+        page = (int)(sm.miss[jm] & 0xffffu);
         slot = sm.assign[jm] == kAbsent ? -1 : sm.assign[jm];
       }
       char* dst_tile = pool_u + (size_t)(slot < 0 ? 0 : slot) * a.page_bytes + (size_t)tile * kTileBytes;
@@ -914,7 +1012,7 @@ __device__ __forceinline__ bool select_resolve_body(const FastArgs& a, int u, Fa
     const unsigned units = a.page_bytes / 16;
     auto ends = [&](int jm, const uint4*& src, uint4*& dst) -> bool {
       if (jm >= m || sm.assign[jm] == kAbsent) return false;
-      src = reinterpret_cast<const uint4*>(store_u + (size_t)sm.sel[jm] * a.page_bytes);
+      src = reinterpret_cast<const uint4*>(store_u + (size_t)(sm.miss[jm] & 0xffffu) * a.page_bytes);
       dst = reinterpret_cast<uint4*>(pool_u + (size_t)sm.assign[jm] * a.page_bytes);
       return true;
     };

@@ -177,11 +177,10 @@ __device__ __forceinline__ void step_select_role(StepArgsPtr ap, int li, int u, 
   __builtin_amdgcn_s_setprio(3);
   typename StepSmem<NT>::Fast& sm = *reinterpret_cast<typename StepSmem<NT>::Fast*>(smem_raw);
   // the directory is loaded and the LDS tables are set up while the unit's scores are still coming in
-  auto scores_ready = [&]() -> bool {
-    const bool ok = block_wait_equal(&a.score_done[u * kFlagStride], a.chunks * (NT / kWave), a.wait_limit, wait_ok);
+  const int arrivals = a.chunks * (NT / kWave);
+  auto scores_taken = [&]() {
     if (ts) ts[1] = wall_clock64();
-    if (ok && tid == 0) store_agent(&a.score_done[u * kFlagStride], 0);   // every arrival has been seen: ready for the next launch
-    return ok;
+    if (tid == 0) store_agent(&a.score_done[u * kFlagStride], 0);   // every arrival has been seen: ready for the next launch
   };
   bool done;
   if (ap->Nc > 0) {
@@ -196,14 +195,17 @@ __device__ __forceinline__ void step_select_role(StepArgsPtr ap, int li, int u, 
     auto select_clusters = [&]() -> bool {
       ClusterPrep<NT> prep;
       cluster_prepare<NT>(cstart, cpages, a.fa.seq_len, a.fa.NP, Nc, a.fa.P, a.fa.k, a.fa.sink, a.fa.recent, a.fa.Hkv, u, prep);
-      if (!scores_ready()) return false;
+      if (!block_wait_equal(&a.score_done[u * kFlagStride], arrivals, a.wait_limit, wait_ok)) return false;
+      scores_taken();
       cluster_finish<NT, true>(a.fa.scores, cpages, a.fa.sel_pages, sm.sel, a.fa.NP, Nc, a.fa.k, u, prep, cs);
       __syncthreads();                                 // the selection is complete
       return true;
     };
     done = select_resolve_body<NT, 4, false, true, true, decltype(select_clusters), true>(a.fa, u, sm, select_clusters);
   } else {
-    done = select_resolve_body<NT, IPT, true, true, true>(a.fa, u, sm, scores_ready);
+    auto scores_ready = [&]() -> bool { return wave_wait_equal(&a.score_done[u * kFlagStride], arrivals, a.wait_limit); };
+    done = select_resolve_body<NT, IPT, true, true, true, decltype(scores_ready), false, false, false, decltype(scores_taken)>(
+        a.fa, u, sm, scores_ready, scores_taken);
   }
   if (!done) {
     if (tid == 0) __hip_atomic_store(a.error, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
