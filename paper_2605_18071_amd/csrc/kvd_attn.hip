@@ -118,6 +118,7 @@ kvd::AttnArgs kvd_attn_args(kvd_ctx* c, int layer, const void* q, const int32_t*
   a.lse = lse;
   a.k = c->k; a.P = c->P; a.Cmax = c->Cmax; a.Hq = c->Hq; a.Hkv = c->Hkv; a.G = c->G; a.S = c->S;
   a.per_split = (c->k + c->S - 1) / c->S;
+  a.take = 1;
   a.fuse_merge = c->fuse_merge;
   a.page_bytes = (unsigned)c->page_bytes;
   a.scale_log2 = c->scale * kLog2e;
@@ -236,6 +237,7 @@ extern "C" int kvd_sparse_decode_attn_noalloc(const void* q, const void* slot_po
   a.lse = lse;
   a.k = topk_pages; a.P = page_size; a.Cmax = capacity_max; a.Hq = n_q_heads; a.Hkv = n_kv_heads; a.G = G; a.S = S;
   a.per_split = (topk_pages + S - 1) / S;
+  a.take = 1;
   a.fuse_merge = 1;
   a.page_bytes = (unsigned)((size_t)2 * page_size * kHeadDim * 2);
   a.scale_log2 = (softmax_scale > 0.f ? softmax_scale : 1.0f / sqrtf((float)kHeadDim)) * kLog2e;

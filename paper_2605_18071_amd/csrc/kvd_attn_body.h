@@ -32,19 +32,22 @@ struct AttnArgs {
   float* out;                // [B][Hq][D]
   float* lse;                // [B][Hq] or null
   int k, P, Cmax, Hq, Hkv, G, S, per_split, fuse_merge, u0;
+  int take;                  // consecutive splits that a workgroup takes (other than 1 only in launches of several layers)
   unsigned page_bytes;
   float scale_log2;          // softmax scale * log2(e)
 };
 
-// GMAX query heads per KV head at most, NW waves per workgroup
+// GMAX query heads per KV head at most, NW waves per workgroup.  What a wave leaves of a split is G rows of kPartStride
+// floats: the accumulators, then maximum and sum.  `part` holds one split of the waves; a caller with more LDS behind it may
+// have a workgroup take several splits (part_of).
+constexpr int kPartStride = kHeadDim + 4;   // (a multiple of 16 bytes)
 template <int GMAX, int NW>
 struct AttnSmem {
-  float acc[NW][GMAX][kHeadDim];
-  float m[NW][GMAX];
-  float l[NW][GMAX];
   int32_t page[kAttnIdxCap], slot[kAttnIdxCap];
   uint4 qf[4][kWave];                      // Q^T operand fragments, when they are not kept in registers
   int is_last;
+  __align__(16) float part[NW * GMAX * kPartStride];
+  __device__ __forceinline__ float* part_of(int v, int w, int g, int G) { return part + ((v * NW + w) * G + g) * kPartStride; }
 };
 
 // GT > 0: the group size is the compile-time GT; GT == 0: it is a.G (at most KVD_MAX_GROUP).
@@ -52,6 +55,16 @@ template <int GT>
 __device__ __forceinline__ int group_size(const AttnArgs& a) { return GT > 0 ? GT : a.G; }
 template <int GT>
 struct GroupMax { static constexpr int value = GT > 0 ? GT : KVD_MAX_GROUP; };
+
+// One split's (max, sum, acc) into the running (M, L, A).
+__device__ __forceinline__ void merge_one(float& M, float& L, float& A, float m, float l, float acc) {
+  const float Mn = fmaxf(M, m);
+  const float Ms = Mn == -INFINITY ? 0.f : Mn;
+  const float so = exp2f(M - Ms), sn = exp2f(m - Ms);
+  L = L * so + l * sn;
+  A = A * so + acc * sn;
+  M = Mn;
+}
 
 // Log-sum-exp merge of the S split partials of unit u into out / lse, by one workgroup of NT
 // threads.  The partials are fetched in batches of 8 splits whose loads are all issued before any
@@ -83,14 +96,7 @@ __device__ __forceinline__ void merge_splits(const AttnArgs& a, int u) {
       }
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
-        if (s0 + i < a.S) {
-          const float Mn = fmaxf(M, mv[i]);
-          const float Ms = Mn == -INFINITY ? 0.f : Mn;
-          const float so = exp2f(M - Ms), sn = exp2f(mv[i] - Ms);
-          L = L * so + lv[i] * sn;
-          A = A * so + av[i] * sn;
-          M = Mn;
-        }
+        if (s0 + i < a.S) merge_one(M, L, A, mv[i], lv[i], av[i]);
       }
     }
     const size_t row = (size_t)b * a.Hq + (size_t)h * G + g;
@@ -99,14 +105,18 @@ __device__ __forceinline__ void merge_splits(const AttnArgs& a, int u) {
   }
 }
 
-// Workgroup epilogue.  The waves have left their (max, sum, acc) in `sm`; merge them and write
-// this split's partial.  With fuse_merge the partials travel with device-scope stores and the
-// last split of the unit to arrive (a ticket counter) merges all S of them.
+// Workgroup epilogue.  The waves have left what they have of splits [split, split + n) in `sm`; merge them and write
+// the splits' partials.  With fuse_merge the partials travel with device-scope stores and the
+// last workgroup of the unit to arrive (a ticket counter) merges all S of them; a workgroup that has taken all S
+// merges them itself, in the same order and with the same operations, so that the output does not depend on how many splits
+// a workgroup takes.
 // Returns true in the workgroup that completed the unit's output (with a separate merge kernel:
 // never).
-template <int GT, int NT>
-__device__ __forceinline__ bool finish_split(const AttnArgs& a, AttnSmem<GroupMax<GT>::value, NT / kWave>& sm, int u,
-                                             int split) {
+// SEVERAL: a workgroup may have taken more than one split.
+template <int GT, int NT, bool SEVERAL>
+__device__ __forceinline__ bool finish_splits(const AttnArgs& a, AttnSmem<GroupMax<GT>::value, NT / kWave>& sm, int u,
+                                              int split, int n_taken) {
+  const int n = SEVERAL ? n_taken : 1;
   constexpr int NW = NT / kWave;
   const int G = group_size<GT>(a);
   const int tid = threadIdx.x;
@@ -115,39 +125,51 @@ __device__ __forceinline__ bool finish_split(const AttnArgs& a, AttnSmem<GroupMa
   __syncthreads();
   for (int idx = tid; idx < G * kHeadDim; idx += NT) {
     const int g = idx / kHeadDim, d = idx % kHeadDim;
-    float M = sm.m[0][g];
+    float MM = -INFINITY, LL = 0.f, AA = 0.f;            // over the splits, when they are all here
+    for (int v = 0; v < n; ++v) {
+      float m[NW];
 #pragma unroll
-    for (int w = 1; w < NW; ++w) M = fmaxf(M, sm.m[w][g]);
-    const float Ms = M == -INFINITY ? 0.f : M;
-    float L = 0.f, A = 0.f;
+      for (int w = 0; w < NW; ++w) m[w] = sm.part_of(v, w, g, G)[kHeadDim];
+      float M = m[0];
 #pragma unroll
-    for (int w = 0; w < NW; ++w) {
-      const float sc = exp2f(sm.m[w][g] - Ms);
-      L += sm.l[w][g] * sc;
-      A += sm.acc[w][g][d] * sc;
-    }
-    if (a.S == 1) {
-      const size_t row = (size_t)b * a.Hq + (size_t)h * G + g;
-      a.out[row * kHeadDim + d] = A / L;
-      if (a.lse != nullptr && d == 0) a.lse[row] = (M + log2f(L)) * kLn2;
-    } else {
-      const size_t base = ((size_t)u * a.S + split) * G + g;
-      if (fused) {
-        store_agent(&a.part_acc[base * kHeadDim + d], A);
-        if (d == 0) {
-          store_agent(&a.part_ml[base * 2], M);
-          store_agent(&a.part_ml[base * 2 + 1], L);
-        }
+      for (int w = 1; w < NW; ++w) M = fmaxf(M, m[w]);
+      const float Ms = M == -INFINITY ? 0.f : M;
+      float L = 0.f, A = 0.f;
+#pragma unroll
+      for (int w = 0; w < NW; ++w) {
+        const float* p = sm.part_of(v, w, g, G);
+        const float sc = exp2f(m[w] - Ms);
+        L += p[kHeadDim + 1] * sc;
+        A += p[d] * sc;
+      }
+      if (a.S == 1) {
+        MM = M; LL = L; AA = A;
+      } else if (n == a.S) {                             // (as merge_splits has it)
+        merge_one(MM, LL, AA, M, L, A);
       } else {
-        a.part_acc[base * kHeadDim + d] = A;
-        if (d == 0) {
-          a.part_ml[base * 2] = M;
-          a.part_ml[base * 2 + 1] = L;
+        const size_t base = ((size_t)u * a.S + split + v) * G + g;
+        if (fused) {
+          store_agent(&a.part_acc[base * kHeadDim + d], A);
+          if (d == 0) {
+            store_agent(&a.part_ml[base * 2], M);
+            store_agent(&a.part_ml[base * 2 + 1], L);
+          }
+        } else {
+          a.part_acc[base * kHeadDim + d] = A;
+          if (d == 0) {
+            a.part_ml[base * 2] = M;
+            a.part_ml[base * 2 + 1] = L;
+          }
         }
       }
     }
+    if (n == a.S) {
+      const size_t row = (size_t)b * a.Hq + (size_t)h * G + g;
+      a.out[row * kHeadDim + d] = AA / LL;
+      if (a.lse != nullptr && d == 0) a.lse[row] = (MM + log2f(LL)) * kLn2;
+    }
   }
-  if (a.S == 1) {
+  if (n == a.S) {
     // (a HANDOFF caller's entries were read into LDS before the first barrier: blank them for the next launch)
     if (a.sel_entry != nullptr)
       for (int i = tid; i < a.k; i += NT) store_agent(&a.sel_entry[(size_t)u * a.k + i], 0ull);
@@ -157,9 +179,10 @@ __device__ __forceinline__ bool finish_split(const AttnArgs& a, AttnSmem<GroupMa
   wave_drain_memory();                               // this wave's partials have been acknowledged
   __syncthreads();
   if (tid == 0) {
+    const int arrivals = SEVERAL ? (a.S + a.take - 1) / a.take : a.S;
     const int t = __hip_atomic_fetch_add(&a.ticket[u], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    sm.is_last = (t == a.S - 1) ? 1 : 0;
-    if (t == a.S - 1) store_agent(&a.ticket[u], 0);  // ready for the next launch
+    sm.is_last = (t == arrivals - 1) ? 1 : 0;
+    if (t == arrivals - 1) store_agent(&a.ticket[u], 0);  // ready for the next launch
   }
   __syncthreads();
   if (!sm.is_last) return false;
@@ -202,8 +225,8 @@ __device__ __forceinline__ f32x4 mfma_pv(const uint2& vfrag, const uint2& pfrag,
     return __builtin_amdgcn_mfma_f32_16x16x16f16(__builtin_bit_cast(f16x4, vfrag), __builtin_bit_cast(f16x4, pfrag), c, 0, 0, 0);
 }
 
-// Workgroup (split, u) of NT threads: wave w takes 16-token tiles first + w, first + w + NW, ... of
-// the split's pages.  Per tile: 4 loads give the K operand (lane (i, g) = token i, dims
+// Workgroup (split, u) of NT threads takes split `split`, or (SEVERAL) a.take splits from there on, one after the other: wave w takes 16-token tiles w, w +
+// NW, ... of each one's pages, without a pause between two splits, and leaves a partial of its own for each.  Per tile: 4 loads give the K operand (lane (i, g) = token i, dims
 // 32c+8g..+7), 4 loads the V^T operands; S^T[token][head] = sum_c mfma(K_c, Q^T_c); the C tile of
 // lane (j, g) holds head j, tokens 4g..4g+3, which is exactly the B operand of
 // O^T[dim][head] += V^T[dim][token] P^T[token][head].  Heads sit in the 16 MFMA columns; columns
@@ -233,7 +256,7 @@ __device__ __forceinline__ f32x4 mfma_pv(const uint2& vfrag, const uint2& pfrag,
 // Returns 1 in the workgroup that completed the unit's output, 0 in the others, -1 (from all
 // threads, no output) when a HANDOFF wait ran out.  inputs_ready_tick (one thread passes it)
 // receives the wall clock at which the split's entries were all there.
-template <bool BF16, int GT, int NT, bool HANDOFF, bool LEAN = false, int LAYOUT = kLayoutTiles>
+template <bool BF16, int GT, int NT, bool HANDOFF, bool LEAN = false, int LAYOUT = kLayoutTiles, bool SEVERAL = false>
 __device__ __forceinline__ int attend_mfma_body(const AttnArgs& a, AttnSmem<GroupMax<GT>::value, NT / kWave>& sm, int u,
                                                 int split, long long* inputs_ready_tick = nullptr) {
   constexpr int NW = NT / kWave;
@@ -268,10 +291,14 @@ __device__ __forceinline__ int attend_mfma_body(const AttnArgs& a, AttnSmem<Grou
   const int seq = a.seq_len[b];
   const int tiles_per_page = a.P >> 4;                  // (PACKED: 0; pages_per_tile counts instead)
   const int pages_per_tile = PACKED ? 16 / a.P : 1;
+  // splits [split, split + n_splits), whose entries are [first, last)
+  const int n_splits = !SEVERAL ? 1 : split + a.take < a.S ? a.take : a.S - split;
   const int first = split * a.per_split;
-  const int last = (first + a.per_split) < a.k ? (first + a.per_split) : a.k;
-  const int n_tiles = PACKED ? (last - first + pages_per_tile - 1) / pages_per_tile
-                      : NATURAL ? ((last - first) * a.P + 15) >> 4 : (last - first) * tiles_per_page;
+  const int last = (split + n_splits) * a.per_split < a.k ? (split + n_splits) * a.per_split : a.k;
+  auto tiles_of = [&](int v) -> int {                  // of the v-th of them
+    const int n = last - first - v * a.per_split < a.per_split ? last - first - v * a.per_split : a.per_split;
+    return PACKED ? (n + pages_per_tile - 1) / pages_per_tile : NATURAL ? (n * a.P + 15) >> 4 : n * tiles_per_page;
+  };
   // T / P for a token of the split (below 2^20): the product with the reciprocal rounded up, off by less than T P / 2^32
   const u32 recip = NATURAL ? 0xffffffffu / (u32)a.P + 1u : 0u;   // (P = 1: 2^32 wraps to 0, handled below)
   const int32_t* sel = a.sel_pages + (size_t)u * a.k;
@@ -318,26 +345,29 @@ __device__ __forceinline__ int attend_mfma_body(const AttnArgs& a, AttnSmem<Grou
 
   // software pipeline: three tile buffers rotate, so the operands of the next two tiles of this
   // wave (16 KiB) are in flight while one tile is computed
-  struct Tile { uint4 k[4], v[4]; u32 valid; };        // valid: bit i = token i of the tile takes part
-  auto issue = [&](Tile& tl, int t) {
+  struct Tile { uint4 k[4], v[4]; u32 valid; int split; };   // valid: bit i = token i of the tile takes part
+  auto issue_tile = [&](Tile& tl, int split_v, int t) {
+    // the split's entries in LDS, and behind `first`
+    const int e_base = SEVERAL ? split_v * a.per_split : 0;
+    const int e_end = SEVERAL && e_base + a.per_split < n_entries ? e_base + a.per_split : n_entries;
     tl.valid = 0;
-    if (t >= n_tiles) return;
     if (PACKED) {
       // lane (i, g): K units of token i of the tile = token i % P of entry i / P; V units of tokens
       // 4g..4g+3 = token group (4g % P) / 4 of entry 4g / P
       auto entry = [&](int e, int& page, int& slot) {
         page = -1; slot = -1;
-        if (e < n_entries) {
+        if (e < e_end) {
           if (idx_in_lds) { page = sm.page[e]; slot = sm.slot[e]; }
           else { page = sel[first + e]; slot = slots[first + e]; }
         }
         if (slot >= a.Cmax) slot = -1;
       };
-      const int e0 = t * pages_per_tile;
+      const int shift = a.P == 8 ? 3 : 2;               // (P is 4 or 8; a unit's slots span less than 4 GB)
+      const int e0 = e_base + t * pages_per_tile;
       int kp, ks, vp, vs;
-      entry(e0 + j / a.P, kp, ks);
-      entry(e0 + (4 * g) / a.P, vp, vs);
-      const int ktok = j % a.P;
+      entry(e0 + (j >> shift), kp, ks);
+      entry(e0 + ((4 * g) >> shift), vp, vs);
+      const int ktok = j & (a.P - 1);
       const bool kok = kp >= 0 && ks >= 0 && kp * a.P + ktok < seq;
       // the tile's valid tokens: lanes 0..15 (g = 0) speak for tokens 0..15
       const u32 valid = (u32)(__ballot(kok) & 0xffffull);
@@ -346,15 +376,15 @@ __device__ __forceinline__ int attend_mfma_body(const AttnArgs& a, AttnSmem<Grou
 #pragma unroll
       for (int c = 0; c < 4; ++c) { tl.k[c] = make_uint4(0u, 0u, 0u, 0u); tl.v[c] = make_uint4(0u, 0u, 0u, 0u); }
       if (kok) {
-        const char* kb = pool_u + (size_t)ks * a.page_bytes + (size_t)(g * a.P + ktok) * 16;
+        const u32 kb = (u32)ks * a.page_bytes + (u32)(g * a.P + ktok) * 16u;
 #pragma unroll
-        for (int c = 0; c < 4; ++c) tl.k[c] = load_stream16(kb + (size_t)c * 4 * a.P * 16);
+        for (int c = 0; c < 4; ++c) tl.k[c] = load_stream16(pool_u + (kb + (u32)(c * 64 * a.P)));
       }
       if (vp >= 0 && vs >= 0 && ((valid >> (4 * g)) & 15u)) {
-        const int groups = a.P >> 2, tg = ((4 * g) % a.P) >> 2;
-        const char* vb = pool_u + (size_t)vs * a.page_bytes + (size_t)a.P * kRowBytes + (size_t)(tg * 16 + j) * 16;
+        const u32 tg = (u32)((4 * g) & (a.P - 1)) >> 2;
+        const u32 vb = (u32)vs * a.page_bytes + (u32)a.P * kRowBytes + (tg * 16u + (u32)j) * 16u;
 #pragma unroll
-        for (int c = 0; c < 4; ++c) tl.v[c] = load_stream16(vb + (size_t)c * groups * 256);
+        for (int c = 0; c < 4; ++c) tl.v[c] = load_stream16(pool_u + (vb + (u32)(c * 64 * a.P)));
       }
       return;
     }
@@ -365,10 +395,11 @@ __device__ __forceinline__ int attend_mfma_body(const AttnArgs& a, AttnSmem<Grou
       // pages of 6 34.8 and 31.4; 96 x 102 pages of 20 41.0 and 40.4; 16 x 26 pages of 20 20.0 and 20.3.  Ways of their own
       // for pages of more and of up to 16 tokens: the last gained nothing, large ones lost 10 % to the longer code.)
       const int t_u = __builtin_amdgcn_readfirstlane(t);
-      const int e0 = (int)((u32)(((u64)(16 * t_u) * recip) >> 32)) + (a.P == 1 ? 16 * t_u : 0), row0 = 16 * t_u - e0 * a.P;
+      const int e0_v = (int)((u32)(((u64)(16 * t_u) * recip) >> 32)) + (a.P == 1 ? 16 * t_u : 0), row0 = 16 * t_u - e0_v * a.P;
+      const int e0 = e_base + e0_v;
       auto entry = [&](int e, int& page, int& slot) {
         page = -1; slot = -1;
-        if (e < n_entries) {
+        if (e < e_end) {
           if (idx_in_lds) { page = sm.page[e]; slot = sm.slot[e]; }
           else { page = sel[first + e]; slot = slots[first + e]; }
         }
@@ -412,7 +443,7 @@ __device__ __forceinline__ int attend_mfma_body(const AttnArgs& a, AttnSmem<Grou
         if ((mine >> m) & 1u) tl.v[m] = load_stream16(pool_u + (size_t)vrow[m] * kRowBytes + j * 16);
       return;
     }
-    const int e = t / tiles_per_page, tile = t % tiles_per_page;
+    const int e = e_base + t / tiles_per_page, tile = t % tiles_per_page;
     int page, slot;
     if (idx_in_lds) {
       page = sm.page[e];
@@ -560,57 +591,105 @@ __device__ __forceinline__ int attend_mfma_body(const AttnArgs& a, AttnSmem<Grou
       }
     }
   };
+  // what this wave has of the split is left for the epilogue
+  auto leave = [&](int v) {
+    // per-lane sums cover tokens 4g..4g+3 of every tile: add the four lane groups of a head
+    l += __shfl_xor(l, 16, kWave);
+    l += __shfl_xor(l, 32, kWave);
+    if (j < G) {
+      // O^T C tiles: lane (j, g) register e of tile c holds dim 16c + 4g + e of head j (natural layout: 8 (4g + e) + c)
+      float* p = sm.part_of(v, w, j, G);
+#pragma unroll
+      for (int c = 0; c < 8; ++c)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) p[NATURAL ? 8 * (4 * g + e) + c : 16 * c + 4 * g + e] = o[c][e] * (1.f / kPScale);
+      if (g == 0) { p[kHeadDim] = m; p[kHeadDim + 1] = l; }
+    }
+  };
+  auto start_over = [&]() {
+#pragma unroll
+    for (int c = 0; c < 8; ++c) o[c] = f32x4{0.f, 0.f, 0.f, 0.f};
+    m = -INFINITY; l = 0.f;
+  };
+  // the wave's tiles in order, split by split; ends with the accumulators of the last split
   auto run = [&](auto exact) {
-    if (LEAN) {
-      Tile ta, tb2;
-      issue(ta, w);
-      for (int t = w; t < n_tiles; t += 2 * NW) {
-        issue(tb2, t + NW);
-        compute(ta, exact);
-        issue(ta, t + 2 * NW);
-        compute(tb2, exact);
+    if constexpr (SEVERAL) {
+      int iv = 0, it = w, n_it = tiles_of(0), cv = 0;    // the next tile to ask for; the split that the accumulators are of
+      auto issue = [&](Tile& tl) {
+        while (it >= n_it && iv < n_splits) {
+          ++iv;
+          it = w;
+          n_it = iv < n_splits ? tiles_of(iv) : 0;
+        }
+        tl.split = iv;
+        if (iv == n_splits) return;
+        issue_tile(tl, iv, it);
+        it += NW;
+      };
+      auto next = [&](Tile& tl) -> bool {                // false: there is no tile left
+        while (cv < tl.split && cv < n_splits - 1) {
+          leave(cv++);
+          start_over();
+        }
+        if (tl.split == n_splits) return false;
+        compute(tl, exact);
+        return true;
+      };
+      Tile ta, tb2, tc;
+      issue(ta);
+      issue(tb2);
+      for (;;) {
+        issue(tc);
+        if (!next(ta)) break;
+        issue(ta);
+        if (!next(tb2)) break;
+        issue(tb2);
+        if (!next(tc)) break;
       }
     } else {
-      Tile ta, tb2, tc;
-      issue(ta, w);
-      issue(tb2, w + NW);
-      for (int t = w; t < n_tiles; t += 3 * NW) {
-        issue(tc, t + 2 * NW);
-        compute(ta, exact);
-        issue(ta, t + 3 * NW);
-        compute(tb2, exact);
-        issue(tb2, t + 4 * NW);
-        compute(tc, exact);
+      const int n_tiles = tiles_of(0);
+      auto issue = [&](Tile& tl, int t) {
+        tl.valid = 0;
+        if (t < n_tiles) issue_tile(tl, 0, t);
+      };
+      if (LEAN) {
+        Tile ta, tb2;
+        issue(ta, w);
+        for (int t = w; t < n_tiles; t += 2 * NW) {
+          issue(tb2, t + NW);
+          compute(ta, exact);
+          issue(ta, t + 2 * NW);
+          compute(tb2, exact);
+        }
+      } else {
+        Tile ta, tb2, tc;
+        issue(ta, w);
+        issue(tb2, w + NW);
+        for (int t = w; t < n_tiles; t += 3 * NW) {
+          issue(tc, t + 2 * NW);
+          compute(ta, exact);
+          issue(ta, t + 3 * NW);
+          compute(tb2, exact);
+          issue(tb2, t + 4 * NW);
+          compute(tc, exact);
+        }
       }
     }
   };
   run(std::false_type());
   if constexpr (NATURAL) {
-    // An infinity in V times a lower part of P, which may be zero or negative, is not the infinity that P times V
+    // (here a workgroup takes one split.)  An infinity in V times a lower part of P, which may be zero or negative, is not the infinity that P times V
     // is.  Sums that are not finite are therefore formed again in fp32.
     float sum = 0.f;
 #pragma unroll
     for (int c = 0; c < 8; ++c) sum += (o[c][0] * 0.f + o[c][1] * 0.f) + (o[c][2] * 0.f + o[c][3] * 0.f);
     if (__any(sum != 0.f)) {                             // (0 x infinity and 0 x NaN are NaN)
-#pragma unroll
-      for (int c = 0; c < 8; ++c) o[c] = f32x4{0.f, 0.f, 0.f, 0.f};
-      m = -INFINITY; l = 0.f;
+      start_over();
       run(std::true_type());
     }
   }
-
-  // per-lane sums cover tokens 4g..4g+3 of every tile: add the four lane groups of a head
-  l += __shfl_xor(l, 16, kWave);
-  l += __shfl_xor(l, 32, kWave);
-  if (j < G) {
-    // O^T C tiles: lane (j, g) register e of tile c holds dim 16c + 4g + e of head j (natural layout: 8 (4g + e) + c)
-#pragma unroll
-    for (int c = 0; c < 8; ++c)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) sm.acc[w][j][NATURAL ? 8 * (4 * g + e) + c : 16 * c + 4 * g + e] = o[c][e] * (1.f / kPScale);
-    if (g == 0) { sm.m[w][j] = m; sm.l[w][j] = l; }
-  }
-  return finish_split<GT, NT>(a, sm, u, split) ? 1 : 0;
+  leave(n_splits - 1);
+  return finish_splits<GT, NT, SEVERAL>(a, sm, u, split, n_splits) ? 1 : 0;
 }
 
 }  // namespace kvd

@@ -8,12 +8,11 @@
 // passes; at equal cost the coarser chunk wins while every scoring workgroup still gets one: fewer
 // reports and acknowledgement waits per byte); splits as kvd_create chose them.
 //
-// Launches of several layers take scoring chunks of two passes as soon as those fill 3/4 of the CUs: the other layers
-// cover what a coarser chunk leaves idle (us per layer-step with one pass and with two: 64 units of 2048 pages, 8
-// layers 22.6 and 21.7, 8 units of 4096 pages 7.2 and 6.7, 128 units of 2048 pages 41.5 and 39.4; but 8 units of
-// 1024 pages, 4 layers 5.7 and 6.1).  Fewer splits would gain more there (64 units: 18.1 with one instead of four),
-// but the order of the fp32 sums would then differ from that of the layers stepped one by one: the calibration may
-// choose them, the rule does not.
+// Launches of several layers take scoring chunks of two passes as soon as those of one fill 3/4 of the CUs, over all layers,
+// or, where the second chunk of a unit would be cut short, in one layer: the other layers cover what a coarser chunk leaves
+// idle (us per layer-step with one pass and with two: 64 units of 2048 pages, 8 layers 19.1 and 18.8, 4 layers 21.2 and
+// 20.8, 128 units of 538 pages 17.9 and 16.6, 128 of 2048 35.9 and 35.5; the fewer units lose a little: 8 of 4096 pages 6.4
+// and 6.5, 16 of 1024 7.4 and 7.6, 32 of 2048, 3 layers 13.9 and 14.5).
 kvd_shape kvd_step_shape(const kvd_ctx* c, int multi_layer, const kvd_shape* want, int n_layers) {
   kvd_shape w = want ? *want : c->shape[multi_layer ? 1 : 0];
   if (!multi_layer) n_layers = 1;
@@ -43,8 +42,8 @@ kvd_shape kvd_step_shape(const kvd_ctx* c, int multi_layer, const kvd_shape* wan
       const long long cost = rounds * cand;
       if (best_cost < 0 || cost < best_cost || (cost == best_cost && chunks * Ug >= ns)) { best_cost = cost; ps = cand; }
     }
-    if (ps == 1 && n_layers > 1 && !wide && score_np >= 2 * chunk_pages &&
-        (long long)n_layers * c->U * ((score_np + chunk_pages - 1) / chunk_pages) >= 3LL * slots / 4)
+    const long long layer_chunks = (long long)c->U * ((score_np + chunk_pages - 1) / chunk_pages);
+    if (ps == 1 && n_layers > 1 && !wide && (score_np >= 2 * chunk_pages ? n_layers * layer_chunks : score_np > chunk_pages ? layer_chunks : 0) >= 3LL * slots / 4)
       ps = 2;
   }
   const int chunks = (score_np + chunk_pages * ps - 1) / (chunk_pages * ps);
@@ -71,6 +70,25 @@ bool kvd_single_launch_ok(const kvd_ctx* c) {
          (c->k + c->S1 - 1) / c->S1 <= kvd::kAttnIdxCap;   // a split's entries are staged in LDS
 }
 
+// How many of a unit's splits an attention workgroup of a launch of several layers takes.  The layers fill each other's gaps
+// there, so fewer and longer workgroups are better as long as there is one for every CU over all layers; the workgroups of a
+// unit are to be about equally long, and what their waves leave of each split has to fit their LDS.  The splits themselves
+// stay those of a single layer, and with them the order of the sums.  (us per layer-step with one and with this many: 8
+// layers of 64 units x 4 splits 21.9 and 18.8, of 32 x 8 14.6 and 11.9, of 16 x 16 10.6 and 7.4, of 128 x 2 37.7 and
+// 35.5; 3 layers of 32 x 8 16.8 and 13.9, but 14.7 with 4 instead of 2; 2 of 64 x 4 25.4 and 23.4, 26.1 with 4; 4 of 8 x 8
+// 4.7 with one or two, 5.9 with 4.)
+static int kvd_step_take(const kvd_ctx* c, int splits, int n_layers) {
+  if (c->step_threads == kvd::kStepThreadsWide) return 1;   // (128 registers per lane: no room for it)
+  const int per_split = (c->k + splits - 1) / splits, held = kvd::StepSmem<kvd::kStepThreads>::splits_held(c->G);
+  const int room = held < kvd::kAttnIdxCap / per_split ? held : kvd::kAttnIdxCap / per_split;
+  int wgs = (c->n_cus + n_layers * c->U - 1) / (n_layers * c->U);
+  for (; wgs < splits; ++wgs) {
+    const int take = (splits + wgs - 1) / wgs;
+    if (take <= room && 8 * (take * wgs - splits) < splits) return take;
+  }
+  return 1;
+}
+
 hipError_t kvd_launch_step(kvd_ctx* c, int layer, int n_layers, int step, const void* q, float* out, float* lse, hipStream_t s) {
   using namespace kvd;
   if (n_layers < 1 || n_layers > kStepMaxLayers || n_layers > c->n_sets || layer + n_layers > c->L) return hipErrorInvalidValue;
@@ -91,6 +109,7 @@ hipError_t kvd_launch_step(kvd_ctx* c, int layer, int n_layers, int step, const 
   const kvd_shape shape = kvd_step_shape(c, n_layers > 1, nullptr, n_layers);
   a.at.S = shape.splits;
   a.at.per_split = (c->k + shape.splits - 1) / shape.splits;
+  a.at.take = n_layers > 1 && c->shape[1].splits == 0 ? kvd_step_take(c, shape.splits, n_layers) : 1;   // (splits that the caller has set stay as they are)
   a.score_done = c->d_score_done;
   a.error = c->error_dev;
   a.timeline = nullptr;
@@ -138,12 +157,19 @@ hipError_t kvd_launch_step(kvd_ctx* c, int layer, int n_layers, int step, const 
   a.groups = shape.groups;
   a.group_units = (c->U + shape.groups - 1) / shape.groups;
   a.chunks = (score_np + chunk_pages * a.passes - 1) / (chunk_pages * a.passes);
-  const int n_blocks = n_layers * a.groups * (a.n_score + a.group_units + a.group_units * shape.splits);
+  const int attn_wgs = (shape.splits + a.at.take - 1) / a.at.take;
+  const int n_blocks = n_layers * a.groups * (a.n_score + a.group_units + a.group_units * attn_wgs);
   c->tl_workgroups = n_blocks;
   if (c->profiling == 2 && n_blocks <= KVD_TIMELINE_MAX) a.timeline = c->d_timeline;
   const int ipt = (c->NP + chunk_pages - 1) / chunk_pages;
   const bool packed = c->tiled == kLayoutPacked;
-  if (c->bf16) { if (packed) launch_step<true, true>(threads, ipt, a, n_blocks, s); else launch_step<true, false>(threads, ipt, a, n_blocks, s); }
-  else { if (packed) launch_step<false, true>(threads, ipt, a, n_blocks, s); else launch_step<false, false>(threads, ipt, a, n_blocks, s); }
+  auto launch = [&](auto bf16, auto pk) {
+    if (n_layers > 1) launch_step<decltype(bf16)::value, decltype(pk)::value, true>(threads, ipt, a, n_blocks, s);
+    else launch_step<decltype(bf16)::value, decltype(pk)::value, false>(threads, ipt, a, n_blocks, s);
+  };
+  const std::true_type yes;
+  const std::false_type no;
+  if (c->bf16) { if (packed) launch(yes, yes); else launch(yes, no); }
+  else { if (packed) launch(no, yes); else launch(no, no); }
   return hipGetLastError();
 }

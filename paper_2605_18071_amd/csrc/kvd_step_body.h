@@ -39,6 +39,8 @@
 // ordinary loads: no workgroup of the launch touches a slot before the page's entry has been
 // published, so no cache can hold an older copy.
 #pragma once
+#include <stddef.h>
+
 #include "kvd_attn_body.h"
 #include "kvd_cluster_body.h"
 #include "kvd_device.h"
@@ -100,6 +102,8 @@ struct StepSmem {
   static constexpr size_t cluster_at = (sizeof(Fast) + 15) & ~(size_t)15;
   static constexpr size_t bytes_fc = cluster_at + sizeof(Cluster);
   static constexpr size_t bytes = sizeof(Attn) > bytes_fc ? sizeof(Attn) : bytes_fc;
+  // splits of G query heads that an attention workgroup has room for
+  static constexpr int splits_held(int G) { return (int)((bytes - offsetof(Attn, part)) / (NT / kWave * G * kPartStride * sizeof(float))); }
 };
 
 // The three roles read the launch arguments from the kernel-argument segment (constant address
@@ -214,8 +218,8 @@ __device__ __forceinline__ void step_select_role(StepArgsPtr ap, int li, int u, 
   if (ts) ts[2] = ts[3] = wall_clock64();              // (the entries have been published inside)
 }
 
-// Attention workgroup (u, split).
-template <bool BF16, int NT, bool LEAN, bool PACKED>
+// Attention workgroup (u, split): a.at.take splits from `split` on.
+template <bool BF16, int NT, bool LEAN, bool PACKED, bool SEVERAL>
 __device__ __forceinline__ void step_attend_role(StepArgsPtr ap, int li, int u, int split, unsigned char* smem_raw, long long* ts) {
   struct { AttnArgs at; } a;
   __builtin_memcpy(&a.at, &ap->at, sizeof(AttnArgs));
@@ -230,19 +234,20 @@ __device__ __forceinline__ void step_attend_role(StepArgsPtr ap, int li, int u, 
   }
   if (ts) ts[4] = 2LL | ((long long)u << 8) | ((long long)split << 32);
   typename StepSmem<NT>::Attn& sm = *reinterpret_cast<typename StepSmem<NT>::Attn*>(smem_raw);
-  const int done = attend_mfma_body<BF16, 0, NT, true, LEAN, PACKED ? kLayoutPacked : kLayoutTiles>(a.at, sm, u, split, ts ? ts + 1 : nullptr);
+  const int done = attend_mfma_body<BF16, 0, NT, true, LEAN, PACKED ? kLayoutPacked : kLayoutTiles, SEVERAL>(a.at, sm, u, split, ts ? ts + 1 : nullptr);
   if (done < 0 && threadIdx.x == 0) __hip_atomic_store(a.at.error, 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   if (ts) ts[2] = ts[3] = wall_clock64();
 }
 
-template <bool BF16, int NT, int IPT, bool LEAN, bool PACKED>
+template <bool BF16, int NT, int IPT, bool LEAN, bool PACKED, bool MANY>
 __device__ __forceinline__ void step_body(StepArgsPtr ap, unsigned char* smem_raw, int& wait_ok) {
+  constexpr bool SEVERAL = MANY && !LEAN;
   const int bid = blockIdx.x;
   long long* timeline = ap->timeline;
   long long* ts = timeline != nullptr && threadIdx.x == 0 ? timeline + (size_t)bid * 5 : nullptr;
   if (ts) { ts[0] = ts[1] = ts[2] = ts[3] = wall_clock64(); ts[4] = 3LL; }   // (role 3: a workgroup beyond its group's units, which leaves at once)
-  const int n_score = ap->n_score, S = ap->at.S, groups = ap->groups, Ug = ap->group_units;
-  const int n_stages = ap->n_layers * groups;          // (layer, group) pairs, in order
+  const int n_score = ap->n_score, take = SEVERAL ? ap->at.take : 1, S = (ap->at.S + take - 1) / take, groups = ap->groups, Ug = ap->group_units;
+  const int n_stages = (MANY ? ap->n_layers : 1) * groups;          // (layer, group) pairs, in order
   const int front = n_score + Ug, back = Ug * S;
   // block order: front(0) | front(1) back(0) | front(2) back(1) | ... | back(n-1), where front(i) =
   // the scoring and selection workgroups of stage i and back(i) its attention workgroups
@@ -258,11 +263,11 @@ __device__ __forceinline__ void step_body(StepArgsPtr ap, unsigned char* smem_ra
       st = n_stages - 1; is_back = true;
     }
   }
-  const int li = st / groups, u0 = ap->u0 + (st % groups) * Ug;
-  int n_units = ap->n_units - (st % groups) * Ug;       // units of this group
+  const int li = MANY ? st / groups : 0, gi = MANY ? st % groups : st, u0 = ap->u0 + gi * Ug;
+  int n_units = ap->n_units - gi * Ug;                  // units of this group
   n_units = n_units < Ug ? n_units : Ug;
   if (is_back) {
-    if (o / S < n_units) step_attend_role<BF16, NT, LEAN, PACKED>(ap, li, o / S + u0, o % S, smem_raw, ts);
+    if (o / S < n_units) step_attend_role<BF16, NT, LEAN, PACKED, SEVERAL>(ap, li, o / S + u0, (o % S) * take, smem_raw, ts);
   } else if (o < n_score) {
     step_score_role<BF16, NT>(ap, li, u0, n_units, o, smem_raw, ts);
   } else {
@@ -270,17 +275,19 @@ __device__ __forceinline__ void step_body(StepArgsPtr ap, unsigned char* smem_ra
   }
 }
 
-// LEAN: 128 registers per lane (the 1024-thread form); otherwise 256.  PACKED: pages of 4 or 8 tokens.
-template <bool BF16, int NT, int IPT, bool PACKED, bool LEAN = (NT > kStepThreads)>
+// LEAN: 128 registers per lane (the 1024-thread form); otherwise 256.  PACKED: pages of 4 or 8 tokens.  MANY: a launch of
+// several layers; a kernel of its own, since what only such a launch needs (a layer's strides, attention workgroups that take
+// several splits) costs a launch of one layer 0.6 to 1 us (8 units of 256 pages 13.6 and 14.2, 128 of 2048 43.5 and 44.5).
+template <bool BF16, int NT, int IPT, bool PACKED, bool MANY, bool LEAN = (NT > kStepThreads)>
 __global__ __launch_bounds__(NT, LEAN ? 4 : 2) void step_kernel(StepArgs a) {
   __shared__ __align__(16) unsigned char smem_raw[StepSmem<NT>::bytes];
   __shared__ int wait_ok;
   // the launch arguments are the first thing in the kernel-argument segment
-  step_body<BF16, NT, IPT, LEAN, PACKED>((StepArgsPtr)__builtin_amdgcn_kernarg_segment_ptr(), smem_raw, wait_ok);
+  step_body<BF16, NT, IPT, LEAN, PACKED, MANY>((StepArgsPtr)__builtin_amdgcn_kernarg_segment_ptr(), smem_raw, wait_ok);
 }
 
-// Defined in one source file per dtype and layout (kvd_step_*.hip), since each takes the compiler most of a minute.
-template <bool BF16, bool PACKED>
+// Defined in a source file each (kvd_step_*.hip), since each takes the compiler half a minute.
+template <bool BF16, bool PACKED, bool MANY>
 void launch_step(int threads, int ipt, const StepArgs& a, int n_blocks, hipStream_t s);
 
 }  // namespace kvd

@@ -1,20 +1,20 @@
-// The kernels of the one-launch step, instantiated by the source files of one dtype and layout each.
+// The kernels of the one-launch step, instantiated by source files of one dtype, layout and kind of launch each.
 #pragma once
 #include "kvd_step_body.h"
 
 namespace kvd {
 
-template <bool BF16, bool PACKED>
+template <bool BF16, bool PACKED, bool MANY>
 void launch_step(int threads, int ipt, const StepArgs& a, int n_blocks, hipStream_t s) {
   dim3 grid(n_blocks), block(threads);
   if (threads == kStepThreadsWide) {
-    hipLaunchKernelGGL((step_kernel<BF16, kStepThreadsWide, 16, PACKED>), grid, block, 0, s, a);   // (more than 8192 pages)
+    hipLaunchKernelGGL((step_kernel<BF16, kStepThreadsWide, 16, PACKED, MANY>), grid, block, 0, s, a);   // (more than 8192 pages)
   } else if (ipt <= 4) {
-    hipLaunchKernelGGL((step_kernel<BF16, kStepThreads, 4, PACKED>), grid, block, 0, s, a);
+    hipLaunchKernelGGL((step_kernel<BF16, kStepThreads, 4, PACKED, MANY>), grid, block, 0, s, a);
   } else if (ipt <= 8) {
-    hipLaunchKernelGGL((step_kernel<BF16, kStepThreads, 8, PACKED>), grid, block, 0, s, a);
+    hipLaunchKernelGGL((step_kernel<BF16, kStepThreads, 8, PACKED, MANY>), grid, block, 0, s, a);
   } else {
-    hipLaunchKernelGGL((step_kernel<BF16, kStepThreads, 16, PACKED>), grid, block, 0, s, a);
+    hipLaunchKernelGGL((step_kernel<BF16, kStepThreads, 16, PACKED, MANY>), grid, block, 0, s, a);
   }
 }
 
