@@ -95,8 +95,8 @@ typedef struct {
                                    inside each launch).  The programming model does not promise that order,
                                    so every wait is bounded (kvd_set_wait_limit_us); should one run out, the
                                    library recovers by itself as described there;
-                              0  = chosen by the library: the one launch where it can run (with units of
-                                   more than 8192 pages only from 24 units on), else as for 1;
+                              0  = chosen by the library: the one launch where it can run (for one layer with units
+                                   of more than 8192 pages only from 8 units on), else as for 1;
                               1  = one chain of kernels on the caller's stream, no overlap;
                               n >= 2 = the B sequences are split into n groups, each running
                                    select -> fetch -> attend as its own chain on one of the library's

@@ -7,6 +7,7 @@
 #include <algorithm>
 #include <vector>
 
+#include "kvd_attn_body.h"
 #include "kvd_internal.h"
 #include "kvd_tile_layout.h"
 
@@ -22,14 +23,20 @@
   } while (0)
 
 // micro_batches -1 asks for the one-launch step wherever it can run; 0 leaves the choice to the
-// library, which takes it where it has measured faster than the chain of kernels: everywhere in
-// the 512-thread form (4 to 128 units measured, 2-6 us per step), and from 24 units on in the
-// 1024-thread form (units of more than 8192 pages: 3-5 % slower than the chain with 8 and 16
-// units, 18 % faster with 24).
+// library, which takes it where it has measured faster than the chain of kernels: units of up to 8192 pages everywhere (4
+// to 128 units measured, 2-6 us per step), larger ones from 8 units on (us per step, chain and one launch: 8 units of 10109
+// pages 28.7 and 27.6, 16 33.5 and 32.3, 16 of 16384 38.3 and 35.4, but 2 of 12500 23.5 and 24.7).
 static bool kvd_wants_single_launch(const kvd_ctx* c) {
   if (!kvd_single_launch_ok(c)) return false;
   if (c->cfg.micro_batches == -1) return true;
-  return c->cfg.micro_batches == 0 && (c->step_threads != 1024 || c->U >= 24);
+  return c->cfg.micro_batches == 0 && (c->NP <= 8192 || c->U >= 8);
+}
+
+// Several layers share a launch wherever one can run, unless the caller has asked for another form (us per layer-step of
+// the few units above, two chains of kernels in flight and one launch: 7 layers of 8 units of 10109 pages 19.3 and 11.2, 4
+// layers of 4 units of 12500 20.0 and 9.3).
+static bool kvd_layers_share_launch(const kvd_ctx* c) {
+  return c->single_launch || (c->cfg.micro_batches == 0 && kvd_single_launch_ok(c) && (c->k + c->S - 1) / c->S <= kvd::kAttnIdxCap);
 }
 
 static bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
@@ -254,15 +261,12 @@ int kvd_create(const kvd_config* cfg, kvd_ctx** out) {
   if (S == 0) S = kvd_attn_splits(c->tiled == kvd::kLayoutNatural ? kNaturalLeast : 16, c->U, c->k, c->P, c->n_cus);
   if (S > c->k) S = c->k;
   c->S = S;
-  // The one-launch step runs one workgroup per CU: 512 threads with 256 registers per lane (three
-  // tile buffers in the attention role), or, for units of more than 8192 pages, 1024 threads with
-  // 128.  Its attention splits: the rule of the stand-alone kernel in the first form, four tiles per wave in the
-  // second.
+  // The one-launch step runs one workgroup of 512 threads per CU, with 256 registers per lane (three
+  // tile buffers in the attention role); its attention splits follow the rule of the stand-alone kernel.
   c->S1 = S;
-  c->step_threads = c->NP > 8192 ? 1024 : 512;
   if (cfg->attn_splits == 0) {
     const int sel_tiles = (c->k * c->P + 15) / 16;      // 16-token tiles of a unit's selection
-    int S2 = c->step_threads == 1024 ? sel_tiles / 64 : kvd_attn_splits(c->P <= 16 && sel_tiles >= 32 ? 8 : 16, c->U, c->k, c->P, c->n_cus);
+    int S2 = kvd_attn_splits(c->P <= 16 && sel_tiles >= 32 ? 8 : 16, c->U, c->k, c->P, c->n_cus);
     if (S2 > KVD_MAX_SPLITS) S2 = KVD_MAX_SPLITS;
     if (S2 < (c->k + 511) / 512) S2 = (c->k + 511) / 512;   // a split's entries are staged in LDS, 512 at most
     if (S2 > c->k) S2 = c->k;
@@ -271,7 +275,7 @@ int kvd_create(const kvd_config* cfg, kvd_ctx** out) {
   // room in the partials for the splits that kvd_set_step_shape takes and a calibration of the launch shape tries: twice
   // the rule's, or twice an attention workgroup per CU with two tiles per wave where that is more
   c->S1_max = cfg->attn_splits == 0 ? 2 * c->S1 : c->S1;
-  if (cfg->attn_splits == 0 && c->step_threads == 512) {
+  if (cfg->attn_splits == 0) {
     const int tiles = (c->k * c->P + 15) / 16, full = (c->n_cus + c->U / 2) / c->U;
     const int most = full < tiles / 16 ? full : tiles / 16;
     if (c->S1_max < 2 * most) c->S1_max = 2 * most;
@@ -762,7 +766,7 @@ int kvd_step_layers(kvd_ctx* ctx, int32_t layer0, int32_t n_layers, int32_t step
   auto q_of = [&](int i) { return static_cast<const void*>(q + (size_t)i * rows * c->D * 2); };
   auto out_of = [&](int i) { return out_layers + (size_t)i * rows * c->D; };
   auto lse_of = [&](int i) { return lse_layers ? lse_layers + (size_t)i * rows : nullptr; };
-  if (c->single_launch && c->profiling == 0 && c->n_sets >= 2 && n_layers >= 2) {
+  if (kvd_layers_share_launch(c) && c->profiling == 0 && c->n_sets >= 2 && n_layers >= 2) {
     // one launch for up to n_sets layers at a time, the layers pipelined through the compute units by
     // the launch's block order; everything on the caller's stream
     int done = 0;
@@ -771,7 +775,13 @@ int kvd_step_layers(kvd_ctx* ctx, int32_t layer0, int32_t n_layers, int32_t step
       c->n_steps += (uint64_t)n;
       c->last_scores = nullptr;
       if (n == 1) use_scratch_set(c, 0);
-      HIP_TRY(c, kvd_launch_step(c, layer0 + done, n, step, q_of(done), out_of(done), lse_of(done), s));
+      if (n == 1 && !c->single_launch) {                // (a layer left over goes as single layers do)
+        --c->n_steps;
+        const int r = enqueue_step(c, layer0 + done, step, q_of(done), out_of(done), lse_of(done), s, false);
+        if (r != KVD_OK) return r;
+      } else {
+        HIP_TRY(c, kvd_launch_step(c, layer0 + done, n, step, q_of(done), out_of(done), lse_of(done), s));
+      }
       use_scratch_set(c, n - 1);                       // kvd_step_trace reports the last layer
       c->last_scores = c->d_scores;
       done += n;

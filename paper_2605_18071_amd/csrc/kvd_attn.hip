@@ -39,7 +39,7 @@ constexpr int kAttnMfmaThreads = 512;
 template <bool BF16, int G, int LAYOUT>
 __global__ __launch_bounds__(kAttnMfmaThreads, 2) void attend_mfma_kernel(AttnArgs a) {
   __shared__ AttnSmem<G, kAttnMfmaThreads / kWave> sm;
-  attend_mfma_body<BF16, G, kAttnMfmaThreads, false, false, LAYOUT>(a, sm, blockIdx.y + a.u0, blockIdx.x);
+  attend_mfma_body<BF16, G, kAttnMfmaThreads, false, LAYOUT>(a, sm, blockIdx.y + a.u0, blockIdx.x);
 }
 
 template <bool BF16, int G>

@@ -44,7 +44,6 @@ constexpr int kPartStride = kHeadDim + 4;   // (a multiple of 16 bytes)
 template <int GMAX, int NW>
 struct AttnSmem {
   int32_t page[kAttnIdxCap], slot[kAttnIdxCap];
-  uint4 qf[4][kWave];                      // Q^T operand fragments, when they are not kept in registers
   int is_last;
   __align__(16) float part[NW * GMAX * kPartStride];
   __device__ __forceinline__ float* part_of(int v, int w, int g, int G) { return part + ((v * NW + w) * G + g) * kPartStride; }
@@ -233,8 +232,6 @@ __device__ __forceinline__ f32x4 mfma_pv(const uint2& vfrag, const uint2& pfrag,
 // >= G carry zeros and are never read.  For bf16 the probabilities are split into a high and a
 // low bf16 part (two MFMAs) so that P keeps 16 bits of mantissa; fp16 P has 11 bits and needs one.
 // HANDOFF: the selection was written by another workgroup of the same launch.
-// LEAN: for 128 registers per lane (two workgroups of 8 waves per CU): two tile buffers instead of
-// three and the Q^T fragments re-read from LDS for every tile.
 // LAYOUT kLayoutPacked: pages of 4 or 8 tokens in the packed slot layout: a tile is made of 16 / P consecutive
 // entries of the split, every lane fetching its 16-byte units from the slot of its own page, and
 // every token of the tile is valid or not on its own (a page beyond the selection's end, a made-up
@@ -256,7 +253,7 @@ __device__ __forceinline__ f32x4 mfma_pv(const uint2& vfrag, const uint2& pfrag,
 // Returns 1 in the workgroup that completed the unit's output, 0 in the others, -1 (from all
 // threads, no output) when a HANDOFF wait ran out.  inputs_ready_tick (one thread passes it)
 // receives the wall clock at which the split's entries were all there.
-template <bool BF16, int GT, int NT, bool HANDOFF, bool LEAN = false, int LAYOUT = kLayoutTiles, bool SEVERAL = false>
+template <bool BF16, int GT, int NT, bool HANDOFF, int LAYOUT = kLayoutTiles, bool SEVERAL = false>
 __device__ __forceinline__ int attend_mfma_body(const AttnArgs& a, AttnSmem<GroupMax<GT>::value, NT / kWave>& sm, int u,
                                                 int split, long long* inputs_ready_tick = nullptr) {
   constexpr int NW = NT / kWave;
@@ -271,16 +268,10 @@ __device__ __forceinline__ int attend_mfma_body(const AttnArgs& a, AttnSmem<Grou
   uint4 qfrag[4];
 #pragma unroll
   for (int c = 0; c < 4; ++c) qfrag[c] = make_uint4(0u, 0u, 0u, 0u);
-  if (!LEAN || w == 0) {
-    if (j < G) {
-      const uint16_t* qrow = a.q + ((size_t)b * a.Hq + (size_t)h * G + j) * kHeadDim + 8 * g;
+  if (j < G) {
+    const uint16_t* qrow = a.q + ((size_t)b * a.Hq + (size_t)h * G + j) * kHeadDim + 8 * g;
 #pragma unroll
-      for (int c = 0; c < 4; ++c) qfrag[c] = *reinterpret_cast<const uint4*>(qrow + 32 * c);
-    }
-    if (LEAN) {
-#pragma unroll
-      for (int c = 0; c < 4; ++c) sm.qf[c][lane] = qfrag[c];
-    }
+    for (int c = 0; c < 4; ++c) qfrag[c] = *reinterpret_cast<const uint4*>(qrow + 32 * c);
   }
 
   f32x4 o[8];
@@ -489,11 +480,11 @@ __device__ __forceinline__ int attend_mfma_body(const AttnArgs& a, AttnSmem<Grou
       // (four partial sums: an fp32 rounding at the size of the whole sum three times fewer)
       f32x4 part[4];
 #pragma unroll
-      for (int c = 0; c < 4; ++c) part[c] = mfma_qk<BF16>(tl.k[c], LEAN ? sm.qf[c][lane] : qfrag[c], s);
+      for (int c = 0; c < 4; ++c) part[c] = mfma_qk<BF16>(tl.k[c], qfrag[c], s);
       s = (part[0] + part[1]) + (part[2] + part[3]);
     } else {
 #pragma unroll
-      for (int c = 0; c < 4; ++c) s = mfma_qk<BF16>(tl.k[c], LEAN ? sm.qf[c][lane] : qfrag[c], s);
+      for (int c = 0; c < 4; ++c) s = mfma_qk<BF16>(tl.k[c], qfrag[c], s);
     }
     float x[4];
     float mx = -INFINITY;
@@ -652,27 +643,16 @@ __device__ __forceinline__ int attend_mfma_body(const AttnArgs& a, AttnSmem<Grou
         tl.valid = 0;
         if (t < n_tiles) issue_tile(tl, 0, t);
       };
-      if (LEAN) {
-        Tile ta, tb2;
-        issue(ta, w);
-        for (int t = w; t < n_tiles; t += 2 * NW) {
-          issue(tb2, t + NW);
-          compute(ta, exact);
-          issue(ta, t + 2 * NW);
-          compute(tb2, exact);
-        }
-      } else {
-        Tile ta, tb2, tc;
-        issue(ta, w);
-        issue(tb2, w + NW);
-        for (int t = w; t < n_tiles; t += 3 * NW) {
-          issue(tc, t + 2 * NW);
-          compute(ta, exact);
-          issue(ta, t + 3 * NW);
-          compute(tb2, exact);
-          issue(tb2, t + 4 * NW);
-          compute(tc, exact);
-        }
+      Tile ta, tb2, tc;
+      issue(ta, w);
+      issue(tb2, w + NW);
+      for (int t = w; t < n_tiles; t += 3 * NW) {
+        issue(tc, t + 2 * NW);
+        compute(ta, exact);
+        issue(ta, t + 3 * NW);
+        compute(tb2, exact);
+        issue(tb2, t + 4 * NW);
+        compute(tc, exact);
       }
     }
   };

@@ -8,8 +8,8 @@
 constexpr int KVD_MAX_GROUP = 8;        // G = Hq / Hkv
 constexpr int KVD_MAX_TOPK = 2048;      // k
 constexpr int KVD_MAX_CAPACITY = 65536; // Cmax
-constexpr int KVD_FAST_MAX_PAGES = 16384;    // register-resident selection: 1024 threads x 16 pages
-constexpr int KVD_FAST_MAX_CAPACITY = 4096; // register-resident directory scan: 1024 threads x 4 slots
+constexpr int KVD_FAST_MAX_PAGES = 16384;    // register-resident selection: 1024 threads x 16 pages, or 512 x 32
+constexpr int KVD_FAST_MAX_CAPACITY = 4096; // register-resident directory scan: 1024 threads x 4 slots, or 512 x 8
 constexpr int KVD_BIG_MAX_PAGES = 65536;     // the same kernel reading the scores once per pass: 64 pages of a thread as mask bits
 constexpr int KVD_BIG_MAX_CAPACITY = 16384;  // 16 slots per thread
 constexpr int KVD_MAX_PAGE = 256;       // P
@@ -47,7 +47,6 @@ struct kvd_ctx {
   int S1_max;              // the largest split factor the partials were allocated for
   kvd_shape shape[2];      // launch shape of the one-launch step as set or calibrated, 0 = left to the rule:
                            // [0] launches of one layer (kvd_step), [1] launches of several layers (kvd_step_layers)
-  int step_threads;        // workgroup size of the one-launch step: one per CU; 512 (256 registers per lane) or 1024 (128 registers)
   int Nc;                  // centroids per unit of the hierarchical index, 0 = flat page index
   int bf16;
   int score_blocks;        // target number of blocks of a scoring launch

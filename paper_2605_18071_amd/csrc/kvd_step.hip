@@ -8,6 +8,10 @@
 // passes; at equal cost the coarser chunk wins while every scoring workgroup still gets one: fewer
 // reports and acknowledgement waits per byte); splits as kvd_create chose them.
 //
+// Units of more than 8192 pages make at most two passes: with more, few large chunks complete all units at once, and nothing
+// overlaps their selection (us per step with the passes that the above would take and with this: 32 units of 16384 pages 5: 50.9
+// and 49.2, 32 of 12500 4: 45.2 and 43.3, 64 of 9375 3: 61.1 and 59.8).
+//
 // Launches of several layers take scoring chunks of two passes as soon as those of one fill 3/4 of the CUs, over all layers,
 // or, where the second chunk of a unit would be cut short, in one layer: the other layers cover what a coarser chunk leaves
 // idle (us per layer-step with one pass and with two: 64 units of 2048 pages, 8 layers 19.1 and 18.8, 4 layers 21.2 and
@@ -17,9 +21,8 @@ kvd_shape kvd_step_shape(const kvd_ctx* c, int multi_layer, const kvd_shape* wan
   kvd_shape w = want ? *want : c->shape[multi_layer ? 1 : 0];
   if (!multi_layer) n_layers = 1;
   else if (n_layers <= 0) n_layers = c->n_sets;         // (the most layers a launch of this context covers)
-  const bool wide = c->step_threads == kvd::kStepThreadsWide;
   const int score_np = c->Nc > 0 ? c->Nc : c->NP;
-  const int chunk_pages = wide ? kvd::kStepThreadsWide : kvd::kStepThreads;
+  const int chunk_pages = kvd::kStepThreads;
   const int slots = c->n_cus;
   kvd_shape e;
   e.groups = w.groups > 0 ? w.groups : 1;
@@ -35,22 +38,24 @@ kvd_shape kvd_step_shape(const kvd_ctx* c, int multi_layer, const kvd_shape* wan
   if (ns < 1) ns = 1;
   int ps = w.passes;
   if (ps <= 0) {
+    const int most = c->NP > 8192 ? 2 : 8;
     long long best_cost = -1;
-    for (int cand = 1; cand <= 8; ++cand) {
+    for (int cand = 1; cand <= most; ++cand) {
       const long long chunks = (score_np + (long long)chunk_pages * cand - 1) / ((long long)chunk_pages * cand);
       const long long rounds = (chunks * Ug + ns - 1) / ns;
       const long long cost = rounds * cand;
       if (best_cost < 0 || cost < best_cost || (cost == best_cost && chunks * Ug >= ns)) { best_cost = cost; ps = cand; }
     }
     const long long layer_chunks = (long long)c->U * ((score_np + chunk_pages - 1) / chunk_pages);
-    if (ps == 1 && n_layers > 1 && !wide && (score_np >= 2 * chunk_pages ? n_layers * layer_chunks : score_np > chunk_pages ? layer_chunks : 0) >= 3LL * slots / 4)
+    if (ps == 1 && n_layers > 1 && (score_np >= 2 * chunk_pages ? n_layers * layer_chunks : score_np > chunk_pages ? layer_chunks : 0) >= 3LL * slots / 4)
       ps = 2;
   }
   const int chunks = (score_np + chunk_pages * ps - 1) / (chunk_pages * ps);
   if (ns > Ug * chunks) ns = Ug * chunks;
   e.passes = ps;
   e.n_score = ns;
-  e.splits = w.splits > 0 ? w.splits : c->S1;
+  // (where the library takes one layer as a chain of kernels, several have that chain's splits, for the same order of the sums)
+  e.splits = w.splits > 0 ? w.splits : multi_layer && !c->single_launch ? c->S : c->S1;
   return e;
 }
 
@@ -59,7 +64,7 @@ kvd_shape kvd_step_shape(const kvd_ctx* c, int multi_layer, const kvd_shape* wan
 // area; 1..8 groups.
 bool kvd_step_shape_ok(const kvd_ctx* c, const kvd_shape& e) {
   if (e.passes < 1 || e.passes > 8 || e.n_score < 1 || e.n_score > c->n_cus) return false;
-  if (e.splits < 1 || e.splits > c->S1_max || e.splits > c->k) return false;
+  if (e.splits < 1 || e.splits > (c->S > c->S1_max ? c->S : c->S1_max) || e.splits > c->k) return false;
   if ((c->k + e.splits - 1) / e.splits > kvd::kAttnIdxCap) return false;
   if (e.groups < 1 || e.groups > 8) return false;
   return true;
@@ -78,7 +83,6 @@ bool kvd_single_launch_ok(const kvd_ctx* c) {
 // 35.5; 3 layers of 32 x 8 16.8 and 13.9, but 14.7 with 4 instead of 2; 2 of 64 x 4 25.4 and 23.4, 26.1 with 4; 4 of 8 x 8
 // 4.7 with one or two, 5.9 with 4.)
 static int kvd_step_take(const kvd_ctx* c, int splits, int n_layers) {
-  if (c->step_threads == kvd::kStepThreadsWide) return 1;   // (128 registers per lane: no room for it)
   const int per_split = (c->k + splits - 1) / splits, held = kvd::StepSmem<kvd::kStepThreads>::splits_held(c->G);
   const int room = held < kvd::kAttnIdxCap / per_split ? held : kvd::kAttnIdxCap / per_split;
   int wgs = (c->n_cus + n_layers * c->U - 1) / (n_layers * c->U);
@@ -148,10 +152,7 @@ hipError_t kvd_launch_step(kvd_ctx* c, int layer, int n_layers, int step, const 
     d.part_acc = c->d_part_acc; d.part_ml = c->d_part_ml; d.attn_ticket = c->d_attn_ticket; d.score_done = c->d_score_done;
     d.sel_entry = c->d_sel_entry;
   }
-  // Units of more than 8192 pages take the 1024-thread form, whose selection role keeps at most
-  // 16 pages per thread in registers like the 512-thread form does for the others.
-  const int threads = c->step_threads == kStepThreadsWide ? kStepThreadsWide : kStepThreads;
-  const int chunk_pages = threads;                    // a scoring chunk: every wave 64 pages x passes
+  const int chunk_pages = kStepThreads;                // a scoring chunk: every wave 64 pages x passes
   a.passes = shape.passes;
   a.n_score = shape.n_score;
   a.groups = shape.groups;
@@ -164,8 +165,8 @@ hipError_t kvd_launch_step(kvd_ctx* c, int layer, int n_layers, int step, const 
   const int ipt = (c->NP + chunk_pages - 1) / chunk_pages;
   const bool packed = c->tiled == kLayoutPacked;
   auto launch = [&](auto bf16, auto pk) {
-    if (n_layers > 1) launch_step<decltype(bf16)::value, decltype(pk)::value, true>(threads, ipt, a, n_blocks, s);
-    else launch_step<decltype(bf16)::value, decltype(pk)::value, false>(threads, ipt, a, n_blocks, s);
+    if (n_layers > 1) launch_step<decltype(bf16)::value, decltype(pk)::value, true>(ipt, a, n_blocks, s);
+    else launch_step<decltype(bf16)::value, decltype(pk)::value, false>(ipt, a, n_blocks, s);
   };
   const std::true_type yes;
   const std::false_type no;

@@ -50,9 +50,12 @@
 
 namespace kvd {
 
-// One workgroup per CU in both forms:
-constexpr int kStepThreads = 512;            // 256 registers per lane: three tile buffers in the attention role
-constexpr int kStepThreadsWide = 1024;       // 128 registers per lane: units of more pages than 512 threads keep in registers
+// One workgroup per CU, 256 registers per lane: three tile buffers in the attention role, up to 32 pages per thread in the
+// selection role.  (A form of 1024 threads with 128 registers served units of more than 8192 pages; its two tile buffers and its
+// coarser scoring chunks cost more than the selection gained, us per step so and with 512 threads: 32 units of 16384 pages 55.4
+// and 48.8, with pages of 8 tokens 64.6 and 49.7, 24 of 12500 43.0 and 35.6, 48 of 16384 65.5 and 59.4, 96 of
+// 8438 85.5 and 80.9.)
+constexpr int kStepThreads = 512;
 
 constexpr int kStepMaxLayers = KVD_MAX_SETS;   // layers one launch can cover: each needs a set of per-step scratch
 
@@ -219,7 +222,7 @@ __device__ __forceinline__ void step_select_role(StepArgsPtr ap, int li, int u, 
 }
 
 // Attention workgroup (u, split): a.at.take splits from `split` on.
-template <bool BF16, int NT, bool LEAN, bool PACKED, bool SEVERAL>
+template <bool BF16, int NT, bool PACKED, bool SEVERAL>
 __device__ __forceinline__ void step_attend_role(StepArgsPtr ap, int li, int u, int split, unsigned char* smem_raw, long long* ts) {
   struct { AttnArgs at; } a;
   __builtin_memcpy(&a.at, &ap->at, sizeof(AttnArgs));
@@ -234,19 +237,18 @@ __device__ __forceinline__ void step_attend_role(StepArgsPtr ap, int li, int u, 
   }
   if (ts) ts[4] = 2LL | ((long long)u << 8) | ((long long)split << 32);
   typename StepSmem<NT>::Attn& sm = *reinterpret_cast<typename StepSmem<NT>::Attn*>(smem_raw);
-  const int done = attend_mfma_body<BF16, 0, NT, true, LEAN, PACKED ? kLayoutPacked : kLayoutTiles, SEVERAL>(a.at, sm, u, split, ts ? ts + 1 : nullptr);
+  const int done = attend_mfma_body<BF16, 0, NT, true, PACKED ? kLayoutPacked : kLayoutTiles, SEVERAL>(a.at, sm, u, split, ts ? ts + 1 : nullptr);
   if (done < 0 && threadIdx.x == 0) __hip_atomic_store(a.at.error, 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   if (ts) ts[2] = ts[3] = wall_clock64();
 }
 
-template <bool BF16, int NT, int IPT, bool LEAN, bool PACKED, bool MANY>
+template <bool BF16, int NT, int IPT, bool PACKED, bool MANY>
 __device__ __forceinline__ void step_body(StepArgsPtr ap, unsigned char* smem_raw, int& wait_ok) {
-  constexpr bool SEVERAL = MANY && !LEAN;
   const int bid = blockIdx.x;
   long long* timeline = ap->timeline;
   long long* ts = timeline != nullptr && threadIdx.x == 0 ? timeline + (size_t)bid * 5 : nullptr;
   if (ts) { ts[0] = ts[1] = ts[2] = ts[3] = wall_clock64(); ts[4] = 3LL; }   // (role 3: a workgroup beyond its group's units, which leaves at once)
-  const int n_score = ap->n_score, take = SEVERAL ? ap->at.take : 1, S = (ap->at.S + take - 1) / take, groups = ap->groups, Ug = ap->group_units;
+  const int n_score = ap->n_score, take = MANY ? ap->at.take : 1, S = (ap->at.S + take - 1) / take, groups = ap->groups, Ug = ap->group_units;
   const int n_stages = (MANY ? ap->n_layers : 1) * groups;          // (layer, group) pairs, in order
   const int front = n_score + Ug, back = Ug * S;
   // block order: front(0) | front(1) back(0) | front(2) back(1) | ... | back(n-1), where front(i) =
@@ -267,7 +269,7 @@ __device__ __forceinline__ void step_body(StepArgsPtr ap, unsigned char* smem_ra
   int n_units = ap->n_units - gi * Ug;                  // units of this group
   n_units = n_units < Ug ? n_units : Ug;
   if (is_back) {
-    if (o / S < n_units) step_attend_role<BF16, NT, LEAN, PACKED, SEVERAL>(ap, li, o / S + u0, (o % S) * take, smem_raw, ts);
+    if (o / S < n_units) step_attend_role<BF16, NT, PACKED, MANY>(ap, li, o / S + u0, (o % S) * take, smem_raw, ts);
   } else if (o < n_score) {
     step_score_role<BF16, NT>(ap, li, u0, n_units, o, smem_raw, ts);
   } else {
@@ -275,19 +277,19 @@ __device__ __forceinline__ void step_body(StepArgsPtr ap, unsigned char* smem_ra
   }
 }
 
-// LEAN: 128 registers per lane (the 1024-thread form); otherwise 256.  PACKED: pages of 4 or 8 tokens.  MANY: a launch of
+// PACKED: pages of 4 or 8 tokens.  MANY: a launch of
 // several layers; a kernel of its own, since what only such a launch needs (a layer's strides, attention workgroups that take
 // several splits) costs a launch of one layer 0.6 to 1 us (8 units of 256 pages 13.6 and 14.2, 128 of 2048 43.5 and 44.5).
-template <bool BF16, int NT, int IPT, bool PACKED, bool MANY, bool LEAN = (NT > kStepThreads)>
-__global__ __launch_bounds__(NT, LEAN ? 4 : 2) void step_kernel(StepArgs a) {
+template <bool BF16, int NT, int IPT, bool PACKED, bool MANY>
+__global__ __launch_bounds__(NT, 2) void step_kernel(StepArgs a) {
   __shared__ __align__(16) unsigned char smem_raw[StepSmem<NT>::bytes];
   __shared__ int wait_ok;
   // the launch arguments are the first thing in the kernel-argument segment
-  step_body<BF16, NT, IPT, LEAN, PACKED, MANY>((StepArgsPtr)__builtin_amdgcn_kernarg_segment_ptr(), smem_raw, wait_ok);
+  step_body<BF16, NT, IPT, PACKED, MANY>((StepArgsPtr)__builtin_amdgcn_kernarg_segment_ptr(), smem_raw, wait_ok);
 }
 
 // Defined in a source file each (kvd_step_*.hip), since each takes the compiler half a minute.
 template <bool BF16, bool PACKED, bool MANY>
-void launch_step(int threads, int ipt, const StepArgs& a, int n_blocks, hipStream_t s);
+void launch_step(int ipt, const StepArgs& a, int n_blocks, hipStream_t s);
 
 }  // namespace kvd

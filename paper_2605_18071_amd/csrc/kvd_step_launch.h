@@ -5,17 +5,12 @@
 namespace kvd {
 
 template <bool BF16, bool PACKED, bool MANY>
-void launch_step(int threads, int ipt, const StepArgs& a, int n_blocks, hipStream_t s) {
-  dim3 grid(n_blocks), block(threads);
-  if (threads == kStepThreadsWide) {
-    hipLaunchKernelGGL((step_kernel<BF16, kStepThreadsWide, 16, PACKED, MANY>), grid, block, 0, s, a);   // (more than 8192 pages)
-  } else if (ipt <= 4) {
-    hipLaunchKernelGGL((step_kernel<BF16, kStepThreads, 4, PACKED, MANY>), grid, block, 0, s, a);
-  } else if (ipt <= 8) {
-    hipLaunchKernelGGL((step_kernel<BF16, kStepThreads, 8, PACKED, MANY>), grid, block, 0, s, a);
-  } else {
-    hipLaunchKernelGGL((step_kernel<BF16, kStepThreads, 16, PACKED, MANY>), grid, block, 0, s, a);
-  }
+void launch_step(int ipt, const StepArgs& a, int n_blocks, hipStream_t s) {
+  dim3 grid(n_blocks), block(kStepThreads);
+  if (ipt <= 4) hipLaunchKernelGGL((step_kernel<BF16, kStepThreads, 4, PACKED, MANY>), grid, block, 0, s, a);
+  else if (ipt <= 8) hipLaunchKernelGGL((step_kernel<BF16, kStepThreads, 8, PACKED, MANY>), grid, block, 0, s, a);
+  else if (ipt <= 16) hipLaunchKernelGGL((step_kernel<BF16, kStepThreads, 16, PACKED, MANY>), grid, block, 0, s, a);
+  else hipLaunchKernelGGL((step_kernel<BF16, kStepThreads, 32, PACKED, MANY>), grid, block, 0, s, a);
 }
 
 }  // namespace kvd
