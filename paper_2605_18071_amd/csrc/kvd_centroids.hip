@@ -41,6 +41,12 @@ struct ScreenArgs {
   int32_t* n_hard;      // [U] how many; zero before a round
 };
 
+template <bool BF16>
+__device__ __forceinline__ u32 narrow_screen(double x) {
+  const float f = (float)x;
+  return BF16 ? (u32)__builtin_bit_cast(uint16_t, (__bf16)f) : (u32)__builtin_bit_cast(uint16_t, (_Float16)f);
+}
+
 // One wave, centroid c of unit u, lane l holding dims 2l and 2l + 1.
 template <bool BF16>
 __device__ __forceinline__ void store_screen(const ScreenArgs& sa, int u, int c, double x0, double x1) {
@@ -48,8 +54,10 @@ __device__ __forceinline__ void store_screen(const ScreenArgs& sa, int u, int c,
   const u32 shift = *reinterpret_cast<const u32*>(sa.shift + (size_t)u * kHeadDim + 2 * lane);
   x0 -= widen_kv<BF16>((uint16_t)shift);
   x1 -= widen_kv<BF16>((uint16_t)(shift >> 16));
-  const u32 h0 = f64_to_kv<BF16>(x0), h1 = f64_to_kv<BF16>(x1);
-  const u32 l0 = f64_to_kv<BF16>(x0 - widen_kv<BF16>((uint16_t)h0)), l1 = f64_to_kv<BF16>(x1 - widen_kv<BF16>((uint16_t)h1));
+  // (by way of fp32: a second rounding of 2^-24 does not matter to the screening's bound, and four conversions of 64-bit
+  // integer arithmetic were half of what kmeans_update_kernel did)
+  const u32 h0 = narrow_screen<BF16>(x0), h1 = narrow_screen<BF16>(x1);
+  const u32 l0 = narrow_screen<BF16>(x0 - widen_kv<BF16>((uint16_t)h0)), l1 = narrow_screen<BF16>(x1 - widen_kv<BF16>((uint16_t)h1));
   const int d = 2 * lane, at = ((d >> 5) * kWave + ((d & 31) >> 3) * 16 + (c & 15)) * 8 + (d & 7);
   uint16_t* tile = sa.frag + ((size_t)u * sa.tiles + (c >> 4)) * kScreenTile;
   *reinterpret_cast<u32*>(tile + at) = h0 | (h1 << 16);
@@ -146,10 +154,13 @@ __global__ __launch_bounds__(kCentroidWaves* kWave) void kmeans_init_kernel(cons
 // largest centroid norm below 2^-45 leaves v among the subnormals.
 //
 // Block (x, u): points 256x .. 256x+255 of unit u.  Wave w takes 64 of them (B operands kept in
-// registers) and one half of the centroid tiles, which the block stages through LDS, double
-// buffered: each tile is read once per 256 points and feeds 32 MFMAs per wave.  The tiles are gone
-// through twice, for the largest v of every point and then for the candidates: recomputing v is
-// cheaper than keeping sorted lists, whose length depends on the order of the centroids.
+// registers) and one half of the centroid tiles, which the block stages through LDS, two of each half at a time and double
+// buffered: each tile is read once per 256 points and feeds 32 MFMAs per wave.  The first round goes through the tiles
+// twice, for the largest v of every point and then for the candidates.  Later rounds start from v of the centroid that the
+// point had before, which the largest v is not below, and go through the tiles once: what is within the slack of the
+// largest v so far is listed, and the list is filtered when the largest of all is known (a list that is too short sends its
+// block through the tiles again).  (us a round of 8 x 8192 pages against 4096 centroids: two sweeps with one tile of a
+// half at a time and its norms read when they are needed 295, two as they are now 256, one 159.)
 constexpr int kAssignThreads = 512;
 constexpr int kAssignBlock = 256;     // points per block
 constexpr int kAssignCap = 8;         // candidates per point that are compared one by one
@@ -172,12 +183,17 @@ __device__ __forceinline__ u32 narrow_exact(float f) {
   return BF16 ? __float_as_uint(f) >> 16 : (u32)__builtin_bit_cast(uint16_t, (_Float16)f);
 }
 
+constexpr int kAssignList = 24;       // candidates per point that a single sweep may collect before the largest v is known
+constexpr int kAssignTiles = 2;       // tiles of each half staged at a time
+
 struct AssignSmem {
-  uint4 tile[2][2][kScreenTile / 8];                        // [buffer][half of the centroids]
+  uint4 tile[2][2][kAssignTiles][kScreenTile / 8];          // [buffer][half of the centroids]
   float best[2][kAssignBlock];                              // largest v of a point in each half
   float norm[kAssignThreads / kWave];
   int n_cand[kAssignBlock];
-  uint16_t cand[kAssignBlock][kAssignCap];
+  int again;                                                // some point's list is too short
+  uint16_t cand[kAssignBlock][kAssignList];
+  float cand_v[kAssignBlock][kAssignList];
 };
 
 template <bool BF16>
@@ -185,7 +201,7 @@ __global__ __launch_bounds__(kAssignThreads, 2) void kmeans_assign_kernel(const 
                                                                          const double* __restrict__ cent64, ScreenArgs sa,
                                                                          int32_t* __restrict__ assign,   // [U][NP]
                                                                          const int32_t* __restrict__ seq_len, int NP, int Nc,
-                                                                         int P, int Hkv) {
+                                                                         int P, int Hkv, int first_round) {
   __shared__ AssignSmem sm;
   const int u = blockIdx.y, tid = threadIdx.x, lane = tid & (kWave - 1), w = tid / kWave;
   int n_valid = (seq_len[u / Hkv] + P - 1) / P;
@@ -196,6 +212,7 @@ __global__ __launch_bounds__(kAssignThreads, 2) void kmeans_assign_kernel(const 
   const double* cent_u = cent64 + (size_t)u * Nc * kHeadDim;
   int32_t* assign_u = assign + (size_t)u * NP;
   const float* neg_u = sa.neg_half + (size_t)u * sa.tiles * 16;
+  const uint4* frag_u = reinterpret_cast<const uint4*>(sa.frag) + (size_t)u * sa.tiles * (kScreenTile / 8);
   const int half = w >> 2, pw = (w & 3) * 64, j = lane & 15, g = lane >> 4;
 
   const uint16_t* shift_u = sa.shift + (size_t)u * kHeadDim + 8 * g;
@@ -203,12 +220,14 @@ __global__ __launch_bounds__(kAssignThreads, 2) void kmeans_assign_kernel(const 
   // B operands: lane (j, g) of group q holds dims 32c + 8g .. +7 of point pw + 16 q + j
   uint4 x[4][4];
   float slack[4];                                           // 2 E of the point
+  float floor_v[4];                                         // what the point's largest v is not below, less the slack
   bool in_range[4];                                         // E holds
   {
     float cmax2 = 0.f;                                      // largest squared norm of the unit's centroids
     for (int c = tid; c < Nc; c += kAssignThreads) cmax2 = fmaxf(cmax2, -2.f * neg_u[c]);
     cmax2 = wave_allreduce_max(cmax2);
     if (lane == 0) sm.norm[w] = cmax2;
+    if (tid == 0) sm.again = 0;
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < kAssignThreads / kWave; ++i) cmax2 = fmaxf(cmax2, sm.norm[i]);
@@ -238,84 +257,163 @@ __global__ __launch_bounds__(kAssignThreads, 2) void kmeans_assign_kernel(const 
       in_range[q] = n <= 0x1p120f && cmax2 <= 0x1p120f && cmax2 >= 0x1p-90f;
       const float xn = sqrtf(n);
       slack[q] = 2.f * (6.103515625e-5f * (xn * sqrtf(cmax2) + 0.5f * cmax2) + 9.5367431640625e-7f * xn);
+      floor_v[q] = -INFINITY;
     }
-  }
-  for (int i = tid; i < kAssignBlock; i += kAssignThreads) sm.n_cand[i] = 0;
-
-  // iteration i stages tile i of the lower half and tile n_half + i of the upper half (the last tile
-  // again where the halves are uneven: the waves of that half then skip it)
-  const int n_half = (sa.tiles + 1) / 2;
-  const uint4* frag_u = reinterpret_cast<const uint4*>(sa.frag) + (size_t)u * sa.tiles * (kScreenTile / 8);
-  uint4 lower, upper;
-  auto fetch = [&](int i) {
-    const int t = n_half + i < sa.tiles ? n_half + i : sa.tiles - 1;
-    lower = frag_u[(size_t)i * (kScreenTile / 8) + tid];
-    upper = frag_u[(size_t)t * (kScreenTile / 8) + tid];
-  };
-  static_assert(kScreenTile / 8 == kAssignThreads, "one 16-byte unit of a tile per thread");
-  // f(t, v): v[q] = the values of rows 4g .. 4g+3 of tile t for this lane's point of group q
-  auto sweep = [&](auto f) {
-    fetch(0);
-    for (int i = 0; i < n_half; ++i) {
-      sm.tile[i & 1][0][tid] = lower;
-      sm.tile[i & 1][1][tid] = upper;
-      if (i + 1 < n_half) fetch(i + 1);
-      __syncthreads();                                      // (buffer i & 1 is written again two iterations on, after the next barrier)
-      const int t = half * n_half + i;
-      if (t < sa.tiles) {
-        const float4 nh = *reinterpret_cast<const float4*>(neg_u + t * 16 + 4 * g);
-        f32x4_c v[4];
+    if (!first_round) {
+      // v of the centroid that the point had before, summed in another order: within 2 E of what the sweep will find for it
 #pragma unroll
-        for (int q = 0; q < 4; ++q) v[q] = f32x4_c{nh.x, nh.y, nh.z, nh.w};
+      for (int q = 0; q < 4; ++q) {
+        const int p = p0 + pw + 16 * q + j;
+        int c0 = assign_u[p < n_valid ? p : n_valid - 1];
+        c0 = c0 < 0 ? 0 : (c0 < Nc ? c0 : Nc - 1);
+        const uint4* row = frag_u + (size_t)(c0 >> 4) * (kScreenTile / 8) + (c0 & 15) + 16 * g;
+        float dot = 0.f;
 #pragma unroll
         for (int part = 0; part < 2; ++part)
 #pragma unroll
           for (int c = 0; c < 4; ++c) {
-            const uint4 a = sm.tile[i & 1][half][(part * 4 + c) * kWave + lane];
+            float f[8], e[8];
+            cvt8<BF16>(x[q][c], f);
+            cvt8<BF16>(row[(part * 4 + c) * kWave], e);
 #pragma unroll
-            for (int q = 0; q < 4; ++q) v[q] = mfma_16x16x32<BF16>(a, x[q][c], v[q]);
+            for (int k = 0; k < 8; ++k) dot = fmaf(f[k], e[k], dot);
           }
-        f(t, v);
+        dot += __shfl_xor(dot, 16, kWave);
+        dot += __shfl_xor(dot, 32, kWave);
+        floor_v[q] = (dot + neg_u[c0]) - 2.f * slack[q];
       }
+    }
+  }
+  for (int i = tid; i < kAssignBlock; i += kAssignThreads) sm.n_cand[i] = 0;
+
+  // iteration i stages tiles 2i, 2i + 1 of the lower half and the same of the upper half, which begins with tile n_half
+  // (the last tile again where there are fewer: the waves of that half then skip it)
+  const int n_half = (sa.tiles + 1) / 2, n_iter = (n_half + kAssignTiles - 1) / kAssignTiles;
+  static_assert(kAssignTiles == 2, "what is on its way is held in variables of their own, not in an array");
+  uint4 lower0, lower1, upper0, upper1;
+  float4 nh0, nh1;                                          // the norms of this wave's next tiles
+  auto tile_at = [&](int h, int i, int k) -> int {
+    const int t = h * n_half + i * kAssignTiles + k;
+    return t < sa.tiles ? t : sa.tiles - 1;
+  };
+  auto fetch = [&](int i) {
+    lower0 = frag_u[(size_t)tile_at(0, i, 0) * (kScreenTile / 8) + tid];
+    lower1 = frag_u[(size_t)tile_at(0, i, 1) * (kScreenTile / 8) + tid];
+    upper0 = frag_u[(size_t)tile_at(1, i, 0) * (kScreenTile / 8) + tid];
+    upper1 = frag_u[(size_t)tile_at(1, i, 1) * (kScreenTile / 8) + tid];
+    nh0 = *reinterpret_cast<const float4*>(neg_u + tile_at(half, i, 0) * 16 + 4 * g);
+    nh1 = *reinterpret_cast<const float4*>(neg_u + tile_at(half, i, 1) * 16 + 4 * g);
+  };
+  static_assert(kScreenTile / 8 == kAssignThreads, "one 16-byte unit of a tile per thread");
+  // f(t, v): v[q] = the values of rows 4g .. 4g+3 of tile t for this lane's point of group q
+  auto sweep = [&](auto f) {
+    auto product = [&](int i, int k, const float4& nh) {
+      const int in_half = i * kAssignTiles + k, t = half * n_half + in_half;
+      if (in_half >= n_half || t >= sa.tiles) return;
+      const f32x4_c start = f32x4_c{nh.x, nh.y, nh.z, nh.w};
+      f32x4_c v[4] = {start, start, start, start};
+#pragma unroll
+      for (int part = 0; part < 2; ++part)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          const uint4 a = sm.tile[i & 1][half][k][(part * 4 + c) * kWave + lane];
+#pragma unroll
+          for (int q = 0; q < 4; ++q) v[q] = mfma_16x16x32<BF16>(a, x[q][c], v[q]);
+        }
+      f(t, v);
+    };
+    fetch(0);
+    for (int i = 0; i < n_iter; ++i) {
+      sm.tile[i & 1][0][0][tid] = lower0;
+      sm.tile[i & 1][0][1][tid] = lower1;
+      sm.tile[i & 1][1][0][tid] = upper0;
+      sm.tile[i & 1][1][1][tid] = upper1;
+      const float4 n0 = nh0, n1 = nh1;
+      if (i + 1 < n_iter) fetch(i + 1);
+      __syncthreads();                                      // (buffer i & 1 is written again two iterations on, after the next barrier)
+      product(i, 0, n0);
+      product(i, 1, n1);
     }
     __syncthreads();
   };
-
-  float top[4];
-#pragma unroll
-  for (int q = 0; q < 4; ++q) top[q] = -INFINITY;
-  sweep([&](int, const f32x4_c (&v)[4]) {
-#pragma unroll
-    for (int q = 0; q < 4; ++q) top[q] = fmaxf(fmaxf(top[q], fmaxf(v[q][0], v[q][1])), fmaxf(v[q][2], v[q][3]));
-  });
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    top[q] = fmaxf(top[q], __shfl_xor(top[q], 16, kWave));
-    top[q] = fmaxf(top[q], __shfl_xor(top[q], 32, kWave));
-    if (g == 0) sm.best[half][pw + 16 * q + j] = top[q];
-  }
-  __syncthreads();
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    top[q] = fmaxf(top[q], sm.best[half ^ 1][pw + 16 * q + j]) - slack[q];
-    if (!in_range[q] && g == 0 && half == 0) sm.n_cand[pw + 16 * q + j] = kAssignCap + 1;
-  }
-  sweep([&](int t, const f32x4_c (&v)[4]) {
+  auto largest = [](const f32x4_c& v) -> float { return fmaxf(fmaxf(v[0], v[1]), fmaxf(v[2], v[3])); };
+  auto collect = [&](int t, const f32x4_c (&v)[4], const float (&least)[4]) {
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      if (!(fmaxf(fmaxf(v[q][0], v[q][1]), fmaxf(v[q][2], v[q][3])) >= top[q])) continue;
+      if (!(largest(v[q]) >= least[q])) continue;
 #pragma unroll
       for (int e = 0; e < 4; ++e)
-        if (v[q][e] >= top[q] && t * 16 + 4 * g + e < Nc) {
+        if (v[q][e] >= least[q] && t * 16 + 4 * g + e < Nc) {
           const int at = atomicAdd(&sm.n_cand[pw + 16 * q + j], 1);
-          if (at < kAssignCap) sm.cand[pw + 16 * q + j][at] = (uint16_t)(t * 16 + 4 * g + e);
+          if (at < kAssignList) {
+            sm.cand[pw + 16 * q + j][at] = (uint16_t)(t * 16 + 4 * g + e);
+            sm.cand_v[pw + 16 * q + j][at] = v[q][e];
+          }
         }
     }
-  });
+  };
+
+  bool two_sweeps = first_round != 0;
+  float top[4];
+  if (!two_sweeps) {
+    // one sweep: whatever is within the slack of the largest v so far, or of the floor; the largest v of all is in the list
+#pragma unroll
+    for (int q = 0; q < 4; ++q) top[q] = floor_v[q];
+    sweep([&](int t, const f32x4_c (&v)[4]) {
+      collect(t, v, top);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) top[q] = fmaxf(top[q], largest(v[q]) - slack[q]);
+    });
+    for (int i = tid; i < kAssignBlock; i += kAssignThreads)
+      if (sm.n_cand[i] > kAssignList) sm.again = 1;
+    __syncthreads();
+    if (sm.again) {
+      // a list did not hold them all (every wave sees it): as in the first round, with what this sweep has found
+      two_sweeps = true;
+      __syncthreads();
+      for (int i = tid; i < kAssignBlock; i += kAssignThreads) sm.n_cand[i] = 0;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) top[q] += slack[q];
+    }
+  } else {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) top[q] = -INFINITY;
+    sweep([&](int, const f32x4_c (&v)[4]) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) top[q] = fmaxf(top[q], largest(v[q]));
+    });
+  }
+  if (two_sweeps) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      top[q] = fmaxf(top[q], __shfl_xor(top[q], 16, kWave));
+      top[q] = fmaxf(top[q], __shfl_xor(top[q], 32, kWave));
+      if (g == 0) sm.best[half][pw + 16 * q + j] = top[q];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 4; ++q) top[q] = fmaxf(top[q], sm.best[half ^ 1][pw + 16 * q + j]) - slack[q];
+    sweep([&](int t, const f32x4_c (&v)[4]) { collect(t, v, top); });
+  }
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+    if (g == 0 && half == 0) sm.best[0][pw + 16 * q + j] = in_range[q] ? slack[q] : -1.f;   // (for the point's thread)
+  __syncthreads();
 
   if (tid < kAssignBlock && p0 + tid < n_valid) {
-    const int n = sm.n_cand[tid];
-    if (n < 1 || n > kAssignCap) {
+    int n = sm.n_cand[tid];
+    const float within = sm.best[0][tid];
+    int kept = 0;
+    bool open = n < 1 || n > kAssignList || !(within >= 0.f);
+    if (!open) {
+      float most = sm.cand_v[tid][0];
+      for (int k = 1; k < n; ++k) most = fmaxf(most, sm.cand_v[tid][k]);
+      for (int k = 0; k < n; ++k)
+        if (sm.cand_v[tid][k] >= most - within) sm.cand[tid][kept++] = sm.cand[tid][k];
+      open = kept > kAssignCap;
+      n = kept;
+    }
+    if (open) {
       sa.hard[(size_t)u * NP + atomicAdd(&sa.n_hard[u], 1)] = p0 + tid;
     } else {
       int bc = sm.cand[tid][0];
@@ -528,10 +626,24 @@ __global__ __launch_bounds__(kCentroidWaves* kWave) void kmeans_update_kernel(co
   } else {
     const int32_t* pages = cluster_pages + (size_t)u * NP;
     double a0 = 0.0, a1 = 0.0;
-    for (int i = b; i < e; ++i) {
-      const u32 raw = *reinterpret_cast<const u32*>(summ + ((size_t)u * NP + pages[i]) * kHeadDim + 2 * lane);
-      a0 += widen_kv<BF16>((uint16_t)raw);
-      a1 += widen_kv<BF16>((uint16_t)(raw >> 16));
+    for (int i0 = b; i0 < e; i0 += kWave) {
+      // a wave's worth of members at a time, the rows of four on their way together
+      const int n = e - i0 < kWave ? e - i0 : kWave;
+      const int mine = pages[i0 + (lane < n ? lane : n - 1)];
+      for (int i = 0; i < n; i += 4) {
+        u32 raw[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          const int page = __builtin_amdgcn_readlane(mine, i + k < n ? i + k : n - 1);
+          raw[k] = *reinterpret_cast<const u32*>(summ + ((size_t)u * NP + page) * kHeadDim + 2 * lane);
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+          if (i + k < n) {
+            a0 += widen_kv<BF16>((uint16_t)raw[k]);
+            a1 += widen_kv<BF16>((uint16_t)(raw[k] >> 16));
+          }
+      }
     }
     x = make_double2(a0 / (double)(e - b), a1 / (double)(e - b));
     *cent = x;
@@ -654,7 +766,7 @@ hipError_t kvd_run_build_centroids(kvd_ctx* c, int layer, int iterations, int32_
     KVD_DT(kmeans_init_kernel, per_tile_row, centroid_block, 0, s, summ, cent64, sa, c->d_seq_len, c->NP, c->Nc, c->P, c->Hkv);
     for (int it = 0; it < iterations && e == hipSuccess; ++it) {
       KVD_DT(kmeans_assign_kernel, per_points, dim3(kAssignThreads), 0, s, summ, cent64, sa, assign, c->d_seq_len, c->NP, c->Nc,
-             c->P, c->Hkv);
+             c->P, c->Hkv, it == 0 ? 1 : 0);
       KVD_DT(kmeans_exhaustive_kernel, dim3(open_blocks, c->U), dim3(kExhaustiveThreads), 0, s, summ, cent64, sa, assign, c->NP, c->Nc);
       if (assign_trace != nullptr)
         e = hipMemcpyAsync(assign_trace + (size_t)it * c->U * c->NP, assign, (size_t)c->U * c->NP * sizeof(int32_t),
