@@ -30,7 +30,8 @@ constexpr int kMergeThreads = 256;
 
 template <int G>
 __global__ __launch_bounds__(kMergeThreads) void combine_kernel(AttnArgs a) {
-  merge_splits<G, kMergeThreads, false>(a, blockIdx.x + a.u0);
+  __shared__ float lds[kMergeFloats];
+  merge_splits<G, kMergeThreads, false>(a, blockIdx.x + a.u0, lds);
 }
 
 // 512 threads and up to 256 registers per lane: one workgroup per CU, three tile buffers (24 KiB)
@@ -79,9 +80,10 @@ static bool dispatch_group(int G, int layout, const AttnArgs& a, dim3 grid, hipS
 //    of 64 pages: 16.7 us with two tiles per wave, 15.9 with one; 2 splits instead of 1 gain nothing, and with larger
 //    pages a split's share comes in steps of several tiles: 20 units of 21 pages of 64 tokens 21.1 and 21.8), 4 over
 //    natural slots, where a tile costs a wave more (2 units of 40 pages of 12 tokens: 23.8 us with 16, 18.8 with 4);
-//  - beyond 16 splits a split keeps 32 tiles: the last split to arrive fetches the partials of all the others, and
-//    with few units that costs more than shorter splits save.  us per step with a split per CU and with this rule: 8
-//    units of 128 pages of 64 tokens 36.1 and 34.4, 2 units of 1024 pages of 16 31.1 and 29.1;
+//  - beyond 16 splits a split keeps 18 tiles, beyond 32 splits 32: the last split to arrive fetches the partials of all the
+//    others, and with few units that costs more than shorter splits save.  us per step with 16, this and 32 or twice as many: 8
+//    units of 128 pages of 64 tokens 24.3, 23.0 (28 splits) and 23.6, 8 of 512 pages of 16 23.6, 23.2 and 23.7, 2 units of 1024
+//    pages of 16 27.5, 24.1 (32) and 24.5; 8 of 256 pages of 16 20.2 and 21.5;
 //  - no split is left without pages.
 //  - over natural slots there are never more workgroups than CUs: the few of a second round take as long again (24
 //    units x 53 pages of 24 tokens 25.5 us a step with 11 splits, 23.6 with 10; 96 units x 102 pages of 20 tokens 49.4
@@ -90,7 +92,8 @@ int kvd_attn_splits(int least, int U, int k, int P, int cus) {
   const int tiles = (k * P + 15) / 16;                 // of a unit's selection
   int S = least == kNaturalLeast ? cus / U : (cus + U / 2) / U;
   if (S > tiles / least) S = tiles / least;
-  if (S > 16 && S > tiles / 32) S = tiles / 32 > 16 ? tiles / 32 : 16;
+  const int longest = tiles / 18 < 32 ? tiles / 18 : tiles / 32 > 32 ? tiles / 32 : 32;
+  if (S > 16 && S > longest) S = longest > 16 ? longest : 16;
   if (S > KVD_MAX_SPLITS) S = KVD_MAX_SPLITS;
   if (S > k) S = k;
   if (S < 1) S = 1;

@@ -55,34 +55,28 @@ __device__ __forceinline__ int group_size(const AttnArgs& a) { return GT > 0 ? G
 template <int GT>
 struct GroupMax { static constexpr int value = GT > 0 ? GT : KVD_MAX_GROUP; };
 
-// One split's (max, sum, acc) into the running (M, L, A).
-__device__ __forceinline__ void merge_one(float& M, float& L, float& A, float m, float l, float acc) {
-  const float Mn = fmaxf(M, m);
-  const float Ms = Mn == -INFINITY ? 0.f : Mn;
-  const float so = exp2f(M - Ms), sn = exp2f(m - Ms);
-  L = L * so + l * sn;
-  A = A * so + acc * sn;
-  M = Mn;
-}
-
-// Log-sum-exp merge of the S split partials of unit u into out / lse, by one workgroup of NT
-// threads.  The partials are fetched in batches of 8 splits whose loads are all issued before any
-// is used.  HANDOFF: the partials were written by other workgroups of the same launch.
+// Log-sum-exp merge of the S split partials of unit u into out / lse, by one workgroup of NT threads: the largest of the
+// maxima, then the sums in the order of the splits, each times 2^(its maximum - the largest).  Bound by the trips to memory.
+// Up to 8 splits every thread fetches all it needs at once and works the weights out for itself.  With more, the maxima and
+// sums go through LDS (`lds`, kMergeFloats), where a weight is computed once per split and head, while the accumulators are on
+// their way, up to 32 at a time.  (us per step with batches of 8 for any number and so: 2 units with 15 splits, G = 7, 17.1
+// and 15.8; 8 with 16 splits of 32 tiles 31.9 and 31.4; but through LDS 8 units with 8 splits 13.4 and 13.7.)  HANDOFF: the
+// partials were written by other workgroups of the same launch.
+constexpr int kMergeFloats = (3 * KVD_MAX_SPLITS + 1) * KVD_MAX_GROUP;
 template <int GT, int NT, bool HANDOFF>
-__device__ __forceinline__ void merge_splits(const AttnArgs& a, int u) {
-  const int G = group_size<GT>(a);
+__device__ __forceinline__ void merge_splits(const AttnArgs& a, int u, float* lds) {
+  const int G = group_size<GT>(a), S = a.S;
   const int tid = threadIdx.x;
   const int b = u / a.Hkv, h = u % a.Hkv;
-  for (int idx = tid; idx < G * kHeadDim; idx += NT) {
-    const int g = idx / kHeadDim, d = idx % kHeadDim;
-    const float* ml = a.part_ml + ((size_t)u * a.S * G + g) * 2;
-    const float* pa = a.part_acc + ((size_t)u * a.S * G + g) * kHeadDim + d;
-    float M = -INFINITY, L = 0.f, A = 0.f;
-    for (int s0 = 0; s0 < a.S; s0 += 8) {
+  if (S <= 8) {
+    for (int idx = tid; idx < G * kHeadDim; idx += NT) {
+      const int g = idx / kHeadDim, d = idx % kHeadDim;
+      const float* ml = a.part_ml + ((size_t)u * S * G + g) * 2;
+      const float* pa = a.part_acc + ((size_t)u * S * G + g) * kHeadDim + d;
       float mv[8], lv[8], av[8];
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
-        const int s = (s0 + i) < a.S ? (s0 + i) : (a.S - 1);
+        const int s = i < S ? i : S - 1;
         if (HANDOFF) {
           mv[i] = load_agent(ml + (size_t)s * G * 2);
           lv[i] = load_agent(ml + (size_t)s * G * 2 + 1);
@@ -93,15 +87,77 @@ __device__ __forceinline__ void merge_splits(const AttnArgs& a, int u) {
           av[i] = pa[(size_t)s * G * kHeadDim];
         }
       }
+      float M = -INFINITY, L = 0.f, A = 0.f;
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        if (s0 + i < a.S) merge_one(M, L, A, mv[i], lv[i], av[i]);
-      }
+      for (int i = 0; i < 8; ++i) M = fmaxf(M, mv[i]);
+      const float Ms = M == -INFINITY ? 0.f : M;
+#pragma unroll
+      for (int i = 0; i < 8; ++i)
+        if (i < S) {
+          const float sc = exp2f(mv[i] - Ms);
+          L += lv[i] * sc;
+          A += av[i] * sc;
+        }
+      const size_t row = (size_t)b * a.Hq + (size_t)h * G + g;
+      a.out[row * kHeadDim + d] = A / L;
+      if (a.lse != nullptr && d == 0) a.lse[row] = (M + log2f(L)) * kLn2;
     }
-    const size_t row = (size_t)b * a.Hq + (size_t)h * G + g;
-    a.out[row * kHeadDim + d] = A / L;
-    if (a.lse != nullptr && d == 0) a.lse[row] = (M + log2f(L)) * kLn2;
+    return;
   }
+  auto merge = [&](auto batch) {
+    constexpr int N = decltype(batch)::value;            // splits whose accumulators are fetched at a time; those beyond S read as zero
+    const int SP = (S + N - 1) / N * N;
+    float* mx = lds;                                     // [G][SP] maxima
+    float* weight = lds + SP * G;                        // [G][SP]
+    float* sum = lds + 2 * SP * G;                       // [G][SP]
+    float* top = lds + 3 * SP * G;                       // [G]
+    const u64* ml = reinterpret_cast<const u64*>(a.part_ml) + (size_t)u * S * G;
+    for (int i = tid; i < SP * G; i += NT) {
+      const int s = i / G, at = (i % G) * SP + s;
+      u64 v = ((u64)0 << 32) | as_u32(-INFINITY);
+      if (s < S) v = HANDOFF ? load_agent(ml + i) : ml[i];
+      mx[at] = as_f32((u32)v);
+      sum[at] = as_f32((u32)(v >> 32));
+    }
+    const __amdgpu_buffer_rsrc_t acc = __builtin_amdgcn_make_buffer_rsrc(a.part_acc + (size_t)u * S * G * kHeadDim, 0, S * G * kHeadDim * 4, 0x00020000);
+    for (int idx0 = 0; idx0 < G * kHeadDim; idx0 += NT) {
+      const int idx = idx0 + tid, g = idx / kHeadDim, d = idx % kHeadDim;
+      float av[N];
+      auto fetch = [&](int s0) {
+#pragma unroll
+        for (int i = 0; i < N; ++i)
+          av[i] = as_f32(__builtin_amdgcn_raw_buffer_load_b32(acc, idx * 4, (s0 + i) * G * kHeadDim * 4, HANDOFF ? 16 : 0));
+      };
+      fetch(0);
+      if (idx0 == 0) {
+        __syncthreads();
+        for (int i = tid; i < SP * G; i += NT) {
+          const int gi = i / SP;
+          float m = -INFINITY;
+          for (int s = 0; s < S; ++s) m = fmaxf(m, mx[gi * SP + s]);
+          weight[i] = exp2f(mx[i] - (m == -INFINITY ? 0.f : m));
+          if (i == gi * SP) top[gi] = m;
+        }
+        __syncthreads();
+      }
+      if (idx >= G * kHeadDim) continue;
+      float L = 0.f, A = 0.f;
+      for (int s0 = 0; s0 < SP; s0 += N) {
+        if (s0 > 0) fetch(s0);
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+          const float sc = weight[g * SP + s0 + i];
+          L += sum[g * SP + s0 + i] * sc;
+          A += av[i] * sc;
+        }
+      }
+      const size_t row = (size_t)b * a.Hq + (size_t)h * G + g;
+      a.out[row * kHeadDim + d] = A / L;
+      if (a.lse != nullptr && d == 0) a.lse[row] = (top[g] + log2f(L)) * kLn2;
+    }
+  };
+  if (S <= 16) merge(std::integral_constant<int, 16>());
+  else merge(std::integral_constant<int, 32>());
 }
 
 // Workgroup epilogue.  The waves have left what they have of splits [split, split + n) in `sm`; merge them and write
@@ -124,7 +180,11 @@ __device__ __forceinline__ bool finish_splits(const AttnArgs& a, AttnSmem<GroupM
   __syncthreads();
   for (int idx = tid; idx < G * kHeadDim; idx += NT) {
     const int g = idx / kHeadDim, d = idx % kHeadDim;
-    float MM = -INFINITY, LL = 0.f, AA = 0.f;            // over the splits, when they are all here
+    float MM = -INFINITY, LL = 0.f, AA = 0.f;            // over the splits, when they are all here (as merge_splits has it)
+    if (SEVERAL && n == a.S)
+      for (int v = 0; v < n; ++v)
+#pragma unroll
+        for (int w = 0; w < NW; ++w) MM = fmaxf(MM, sm.part_of(v, w, g, G)[kHeadDim]);
     for (int v = 0; v < n; ++v) {
       float m[NW];
 #pragma unroll
@@ -143,8 +203,10 @@ __device__ __forceinline__ bool finish_splits(const AttnArgs& a, AttnSmem<GroupM
       }
       if (a.S == 1) {
         MM = M; LL = L; AA = A;
-      } else if (n == a.S) {                             // (as merge_splits has it)
-        merge_one(MM, LL, AA, M, L, A);
+      } else if (SEVERAL && n == a.S) {
+        const float sc = exp2f(M - (MM == -INFINITY ? 0.f : MM));
+        LL += L * sc;
+        AA += A * sc;
       } else {
         const size_t base = ((size_t)u * a.S + split + v) * G + g;
         if (fused) {
@@ -185,7 +247,7 @@ __device__ __forceinline__ bool finish_splits(const AttnArgs& a, AttnSmem<GroupM
   }
   __syncthreads();
   if (!sm.is_last) return false;
-  merge_splits<GT, NT, true>(a, u);
+  merge_splits<GT, NT, true>(a, u, sm.part);
   // every split of the unit has read its entries: blank them for the next launch
   if (a.sel_entry != nullptr)
     for (int i = tid; i < a.k; i += NT) store_agent(&a.sel_entry[(size_t)u * a.k + i], 0ull);
