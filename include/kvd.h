@@ -269,7 +269,7 @@ int kvd_bind_centroids(kvd_ctx* ctx, void* dev_centroids, int32_t* dev_cluster_s
  * ascending page order, an empty cluster keeps its centroid}; the stored centroid is rounded once to
  * kv_dtype; the cluster lists are those of the last round.  Covers the pages valid at the time of the
  * call.  dev_assign_trace: device [iterations][B][Hkv][NP] int32 receiving every round's assignment,
- * or NULL.  Allocates temporary device memory and waits for `stream`. */
+ * or NULL.  Uses temporary device memory (up to 64 MB of it stay with the context) and waits for `stream`. */
 int kvd_build_centroids(kvd_ctx* ctx, int32_t layer, int32_t iterations, int32_t* dev_assign_trace, void* stream);
 /* After the caller has written a layer's cluster lists itself (instead of kvd_build_centroids):
  * recomputes the library's page -> cluster table from them, which lookahead eviction reads.  Enqueued

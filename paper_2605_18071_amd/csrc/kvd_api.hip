@@ -105,6 +105,7 @@ static void free_ctx(kvd_ctx* c) {
   if (c->h_miss_count) (void)hipHostFree(c->h_miss_count);
   if (c->h_src_offset) (void)hipHostFree(c->h_src_offset);
   if (c->d_src_offset) (void)hipFree(c->d_src_offset);
+  if (c->build_temp) (void)hipFree(c->build_temp);
   free(c->h_capacity);
   free(c->h_seq_len);
   free(c);
