@@ -267,18 +267,22 @@ int kvd_create(const kvd_config* cfg, kvd_ctx** out) {
   c->S1 = S;
   if (cfg->attn_splits == 0) {
     const int sel_tiles = (c->k * c->P + 15) / 16;      // 16-token tiles of a unit's selection
-    int S2 = kvd_attn_splits(c->P <= 16 && sel_tiles >= 32 ? 8 : 16, c->U, c->k, c->P, c->n_cus);
+    const int least = c->P <= 16 && sel_tiles >= 32 ? 8 : 16;
+    int S2 = kvd_attn_splits(least, c->U, c->k, c->P, c->n_cus, true);
     if (S2 > KVD_MAX_SPLITS) S2 = KVD_MAX_SPLITS;
     if (S2 < (c->k + 511) / 512) S2 = (c->k + 511) / 512;   // a split's entries are staged in LDS, 512 at most
     if (S2 > c->k) S2 = c->k;
     c->S1 = S2 < 1 ? 1 : S2;
   }
   // room in the partials for the splits that kvd_set_step_shape takes and a calibration of the launch shape tries: twice
-  // the rule's, or twice an attention workgroup per CU with two tiles per wave where that is more
+  // the rule's with its workgroups rounded up to one per CU, or twice an attention workgroup per CU with two tiles per wave
+  // where that is more
   c->S1_max = cfg->attn_splits == 0 ? 2 * c->S1 : c->S1;
   if (cfg->attn_splits == 0) {
     const int tiles = (c->k * c->P + 15) / 16, full = (c->n_cus + c->U / 2) / c->U;
+    const int rounded = kvd_attn_splits(c->P <= 16 && tiles >= 32 ? 8 : 16, c->U, c->k, c->P, full * c->U);
     const int most = full < tiles / 16 ? full : tiles / 16;
+    if (c->S1_max < 2 * rounded) c->S1_max = 2 * rounded;
     if (c->S1_max < 2 * most) c->S1_max = 2 * most;
   }
   if (c->S1_max > KVD_MAX_SPLITS) c->S1_max = KVD_MAX_SPLITS;
@@ -1030,7 +1034,11 @@ int kvd_calibrate_step_shape(kvd_ctx* ctx, int32_t layer, int32_t n_layers, int3
         for (int p = 1; p <= 4; ++p)
           if (sp >= 1) add({p, c->n_cus * eighths / 8, sp, g});
   }
-  auto apply = [&](const kvd_shape& x) { c->shape[multi] = x; };
+  // (the rule's splits are left to the rule, which in launches of several layers also says how many a workgroup takes)
+  auto apply = [&](kvd_shape x) {
+    if (multi && x.splits == rule.splits) x.splits = 0;
+    c->shape[multi] = x;
+  };
   const kvd_shape before = c->shape[multi];
   for (Timed& x : shapes) {
     apply(x.shape);

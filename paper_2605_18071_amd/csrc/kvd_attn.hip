@@ -73,8 +73,15 @@ static bool dispatch_group(int G, int layout, const AttnArgs& a, dim3 grid, hipS
 
 }  // namespace kvd
 
-// Split-K factor where the caller leaves it open: one 512-thread workgroup runs per CU, so about one workgroup per
-// CU in the grid, but
+// Split-K factor where the caller leaves it open: one 512-thread workgroup runs per CU, so at most one workgroup per
+// CU in the grid; the few of a second round take as long again.  In the one-launch step (beside_selection) the units' selection
+// workgroups hold CUs of their own until their entries are out: these are left to them where that costs an attention
+// workgroup no more than a quarter of its length, unless the splits are 8 or 16, which launches of several layers deal out
+// evenly.  us per step with the nearest number to a workgroup per CU, with at most one, and without the selections' CUs: one
+// launch, 24 units of 2048 pages S = 11, 10 and 9 23.3, 20.2 and 19.7, 40 of 363 6, 6 and 5 18.3, 18.3 and 17.2, 56 of 2969
+// 5, 4 and 3 39.1, 33.5 and 34.8, 96 of 1250 3, 2 and 1 38.5, 33.1 and 38.2; 32 of 1001 8, 8 and 7 20.2, 20.2 and 19.8, but per layer
+// of 8 layers x 16 units of 1024 pages 7.6 with 16 and 8.5 with 15, of 3 x 32 of 2048 14.6 with 8 and 16.0 with 7; over natural slots 24 units x
+// 53 pages of 24 tokens 25.5 with 11 and 23.6 with 10, 96 x 102 pages of 20 49.4 with 3 and 41.0 with 2.  But
 //  - a split keeps at least `least` tiles of 16 tokens for its eight waves: 16 in the stand-alone kernel over tiles (where
 //    fewer made no difference), 8 in the one-launch step with pages of up to 16 tokens and at least 32 tiles (8 units
 //    of 64 pages: 16.7 us with two tiles per wave, 15.9 with one; 2 splits instead of 1 gain nothing, and with larger
@@ -85,12 +92,10 @@ static bool dispatch_group(int G, int layout, const AttnArgs& a, dim3 grid, hipS
 //    units of 128 pages of 64 tokens 24.3, 23.0 (28 splits) and 23.6, 8 of 512 pages of 16 23.6, 23.2 and 23.7, 2 units of 1024
 //    pages of 16 27.5, 24.1 (32) and 24.5; 8 of 256 pages of 16 20.2 and 21.5;
 //  - no split is left without pages.
-//  - over natural slots there are never more workgroups than CUs: the few of a second round take as long again (24
-//    units x 53 pages of 24 tokens 25.5 us a step with 11 splits, 23.6 with 10; 96 units x 102 pages of 20 tokens 49.4
-//    with 3, 41.0 with 2).
-int kvd_attn_splits(int least, int U, int k, int P, int cus) {
+int kvd_attn_splits(int least, int U, int k, int P, int cus, bool beside_selection) {
   const int tiles = (k * P + 15) / 16;                 // of a unit's selection
-  int S = least == kNaturalLeast ? cus / U : (cus + U / 2) / U;
+  int S = cus / U;
+  if (beside_selection && S >= 5 && S % 8 != 0) S = (cus - U) / U;
   if (S > tiles / least) S = tiles / least;
   const int longest = tiles / 18 < 32 ? tiles / 18 : tiles / 32 > 32 ? tiles / 32 : 32;
   if (S > 16 && S > longest) S = longest > 16 ? longest : 16;

@@ -151,7 +151,7 @@ hipError_t kvd_launch_attend(kvd_ctx* c, int layer, const void* q, const int32_t
                              const int32_t* sel_slots, float* out, float* lse, int u0, int u1, hipStream_t s,
                              hipEvent_t between = nullptr);   // `between`: recorded after the attention kernel, before the merge
 constexpr int kNaturalLeast = 4;            // `least` of kvd_attn_splits over natural slots
-int kvd_attn_splits(int least, int U, int k, int P, int cus);
+int kvd_attn_splits(int least, int U, int k, int P, int cus, bool beside_selection = false);
 // The whole step as one launch (kvd_step.hip); usable when kvd_single_launch_ok.
 bool kvd_single_launch_ok(const kvd_ctx* c);
 // The shape a launch takes: `want` (default: what the context holds for that kind of launch) with

@@ -76,16 +76,16 @@ bool kvd_single_launch_ok(const kvd_ctx* c) {
 }
 
 // How many of a unit's splits an attention workgroup of a launch of several layers takes.  The layers fill each other's gaps
-// there, so fewer and longer workgroups are better as long as there is one for every CU over all layers; the workgroups of a
-// unit are to be about equally long, and what their waves leave of each split has to fit their LDS.  The splits themselves
+// there, so fewer and longer workgroups are better as long as there is one for seven of eight CUs over all layers; the
+// workgroups of a unit are to be about equally long, and what their waves leave of each split has to fit their LDS.  The splits themselves
 // stay those of a single layer, and with them the order of the sums.  (us per layer-step with one and with this many: 8
 // layers of 64 units x 4 splits 21.9 and 18.8, of 32 x 8 14.6 and 11.9, of 16 x 16 10.6 and 7.4, of 128 x 2 37.7 and
 // 35.5; 3 layers of 32 x 8 16.8 and 13.9, but 14.7 with 4 instead of 2; 2 of 64 x 4 25.4 and 23.4, 26.1 with 4; 4 of 8 x 8
-// 4.7 with one or two, 5.9 with 4.)
+// 4.7 with one or two, 5.9 with 4; 6 of 40 x 5 and 4 of 56 x 4, with a workgroup for every CU and for seven of eight, 14.6 and 12.3, 17.1 and 16.5.)
 static int kvd_step_take(const kvd_ctx* c, int splits, int n_layers) {
   const int per_split = (c->k + splits - 1) / splits, held = kvd::StepSmem<kvd::kStepThreads>::splits_held(c->G);
   const int room = held < kvd::kAttnIdxCap / per_split ? held : kvd::kAttnIdxCap / per_split;
-  int wgs = (c->n_cus + n_layers * c->U - 1) / (n_layers * c->U);
+  int wgs = (c->n_cus * 7 / 8 + n_layers * c->U - 1) / (n_layers * c->U);
   for (; wgs < splits; ++wgs) {
     const int take = (splits + wgs - 1) / wgs;
     if (take <= room && 8 * (take * wgs - splits) < splits) return take;
