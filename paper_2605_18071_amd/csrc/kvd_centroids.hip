@@ -743,23 +743,13 @@ hipError_t kvd_run_build_centroids(kvd_ctx* c, int layer, int iterations, int32_
   const size_t o_cent = place(n_cent * kHeadDim * sizeof(double)), o_frag = place(n_tiles * kScreenTile * 2),
                o_neg = place(n_tiles * 16 * sizeof(float)), o_assign = place(n_points * sizeof(int32_t)),
                o_shift = place((size_t)c->U * kHeadDim * 2), o_hard = place(n_points * sizeof(int32_t)), o_n_hard = place((size_t)c->U * sizeof(int32_t));
-  // Kept with the context up to 64 MB: allocating and freeing it took 90 us of a call (a build of 4 units x 152 pages and 76
-  // centroids, 5 rounds, with its summaries 306 us with and 286 without); a larger one is as long-lived as the call.
+  // Kept with the context up to 64 MB (its size is the same in every call): allocating and freeing it took 20 to 100 us of one
+  // (4 units x 152 pages and 76 centroids, 5 rounds, with its summaries 306 us with and 286 without).  Two calls at once, from two
+  // threads, have one each: the kept one is taken out of the context meanwhile.
   constexpr size_t kKept = (size_t)64 << 20;
   hipError_t e = hipSuccess;
-  char* temp = at <= kKept && at <= c->build_temp_bytes ? c->build_temp : nullptr;
-  if (temp == nullptr) {
-    if (at <= kKept && c->build_temp != nullptr) {
-      (void)hipFree(c->build_temp);
-      c->build_temp = nullptr;
-      c->build_temp_bytes = 0;
-    }
-    e = hipMalloc(reinterpret_cast<void**>(&temp), at);
-    if (e == hipSuccess && at <= kKept) {
-      c->build_temp = temp;
-      c->build_temp_bytes = at;
-    }
-  }
+  char* temp = __atomic_exchange_n(&c->build_temp, static_cast<char*>(nullptr), __ATOMIC_ACQ_REL);
+  if (temp == nullptr) e = hipMalloc(reinterpret_cast<void**>(&temp), at);
   if (e == hipSuccess) {
     double* cent64 = reinterpret_cast<double*>(temp + o_cent);
     int32_t* assign = reinterpret_cast<int32_t*>(temp + o_assign);
@@ -796,6 +786,7 @@ hipError_t kvd_run_build_centroids(kvd_ctx* c, int layer, int iterations, int32_
     const hipError_t e2 = hipStreamSynchronize(s);
     if (e == hipSuccess) e = e2;
   }
-  if (temp != nullptr && temp != c->build_temp) (void)hipFree(temp);
+  if (e == hipSuccess && at <= kKept) temp = __atomic_exchange_n(&c->build_temp, temp, __ATOMIC_ACQ_REL);
+  if (temp != nullptr) (void)hipFree(temp);
   return e;
 }

@@ -109,8 +109,7 @@ struct kvd_ctx {
   int n_cus;                // compute units of the device
   long long* d_timeline;    // [KVD_TIMELINE_MAX][5] per-workgroup record of the last single-launch step
   int tl_workgroups;        // workgroups of that launch
-  char* build_temp;         // working memory of the index build, kept between its calls when it is small
-  size_t build_temp_bytes;
+  char* build_temp;         // working memory of the index build, kept between its calls when it is small; null while one uses it
   // third tier (borrowed) and what kvd_step_tiered hands across the host boundary
   kvd_tier* tier;
   const char* tier_pool_dev;  // the tier's pool as the GPU addresses it
