@@ -1,0 +1,108 @@
+"""The step's launch forms at the edges of what they hold: selections around the sizes of a wave's registers and with ties that
+end in each of the three ways in which the decisive bucket is resolved, several splits per attention workgroup in launches of
+several layers, and the merge on both sides of the splits that it fetches at once."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2605_18071_amd import workloads as W
+from tests import helpers as H
+from tests.test_gpu_parity import small
+
+pytestmark = pytest.mark.gpu
+
+if torch.cuda.is_available():
+    from tests import gpu_rig as R
+
+
+@pytest.mark.parametrize("pages,same,k,kw", [
+    (2048, 40, 100, dict()),                              # every 2048 / 40 th page has the same score: a short list in the decisive bucket
+    (2049, 300, 100, dict(sink_pages=3, recent_pages=5)),
+    (2050, 1, 1, dict()),                                 # no ties, one page
+    (4096, 1500, 333, dict(sink_pages=1)),                # more candidates than the list holds
+    (4097, 65, 64, dict(dtype="f16")),
+    (8192, 64, 256, dict(recent_pages=2)),
+    (8193, 2000, 700, dict()),
+    (12001, 1024, 512, dict(sink_pages=7, recent_pages=9, dtype="f16")),
+    (16383, 1025, 90, dict()),
+    (16384, 300, 2048, dict()),
+])
+def test_selection_equals_the_size_agnostic_kernels(pages, same, k, kw, monkeypatch):
+    w = small("selection-edges", **{**dict(ctx=4 * pages, page=4, topk_pages=k, capacity=min(k + 40, pages), batch=2, n_kv_heads=1,
+                                           n_q_heads=4, heavy_count=0, steps=3), **kw})
+    seq = [w.ctx, w.ctx - w.ctx // 5 - 3]
+    one = R.Rig(w, seq_lens=seq, micro_batches=-1, build_index=False)
+    monkeypatch.setenv("KVD_GENERIC_SELECT", "1")
+    plain = R.Rig(w, seq_lens=seq, micro_batches=1, build_index=False)
+    gen = torch.Generator(device=R.DEV)
+    gen.manual_seed(90_000 + pages)
+    rows = max(1, pages // same)
+    base = torch.randn(w.units, rows, 128, device=R.DEV, generator=gen)
+    summ = base[:, torch.randperm(pages, device=R.DEV, generator=gen) % rows].to(w.torch_dtype)
+    for r in (one, plain):
+        r.summaries.copy_(summ.view(r.summaries.shape))
+    assert one.kvd.step_form() == -1
+    for t, q in enumerate(W.query_stream(w, one.q0, w.steps, R.DEV)):
+        one.step(0, t, q[0])
+        plain.step(0, t, q[0])
+        for what in ("n_scores", "n_sel_pages", "n_hit_mask", "n_sel_slots", "n_counts"):
+            assert np.array_equal(getattr(one, what), getattr(plain, what)), (what, t)
+    one.close()
+    plain.close()
+
+
+@pytest.mark.parametrize("layers,kw", [
+    (8, dict(batch=8, n_kv_heads=4, n_q_heads=32, topk_pages=128)),                       # 8 splits of 16 pages, eight heads
+    (6, dict(batch=10, n_kv_heads=4, n_q_heads=4, topk_pages=101)),                       # 5 splits, the last one shorter
+    (4, dict(batch=7, n_kv_heads=8, n_q_heads=32, topk_pages=127, dtype="f16")),
+    (5, dict(batch=6, n_kv_heads=4, n_q_heads=20, topk_pages=333, page=8, ctx=8 * 500)),  # packed pages, uneven shares of the splits
+    (3, dict(batch=3, n_kv_heads=2, n_q_heads=14, topk_pages=43, page=64, ctx=64 * 60)),
+    (9, dict(batch=2, n_kv_heads=2, n_q_heads=4, topk_pages=64, page=4, ctx=4 * 8197)),   # 8 layers share a launch, one is left
+])
+def test_splits_shared_by_the_workgroups_of_several_layers(layers, kw):
+    """Outputs bit for bit those of the layers one by one: the splits and the order of their sums are the same."""
+    w = small("several-splits", **{**dict(ctx=16 * 200, heavy_count=3, steps=3, n_layers=layers, physical_layers=1,
+                                          capacity=kw["topk_pages"] + 10), **kw})
+    seq = [w.ctx - 37 * b for b in range(w.batch)]
+    one, together = R.Rig(w, seq_lens=seq, micro_batches=-1), R.Rig(w, seq_lens=seq, micro_batches=-1)
+    shape = (layers, w.batch, w.n_q_heads, w.head_dim)
+    a, b = (torch.empty(shape, dtype=torch.float32, device=R.DEV) for _ in range(2))
+    for t, q in enumerate(W.query_stream(w, one.q0, w.steps, R.DEV)):
+        b.fill_(float("nan"))
+        for l in range(layers):
+            one.kvd.step(l, t, q[l], a[l])
+        together.kvd.step_layers(0, layers, t, q.contiguous(), b)
+        torch.cuda.synchronize()
+        assert torch.equal(a, b), t
+    for l in range(layers):
+        for x, y in zip(one.kvd.cache_export(l), together.kvd.cache_export(l)):
+            assert torch.equal(x, y), l
+    one.close()
+    together.close()
+
+
+@pytest.mark.parametrize("mb", [-1, 1], ids=["single-launch", "kernel-chain"])
+@pytest.mark.parametrize("splits,kw", [
+    (8, dict()),
+    (9, dict()),                                          # more than eight: the partials go through LDS
+    (16, dict(n_q_heads=2)),
+    (17, dict(n_q_heads=16)),
+    (31, dict(dtype="f16")),
+    (32, dict(page=4, ctx=4 * 600)),
+    (33, dict()),
+    (64, dict(n_q_heads=14)),
+])
+def test_merge_of_many_splits_equals_one_split(splits, kw, mb):
+    w = small("merge-edges", **{**dict(ctx=16 * 600, topk_pages=257, capacity=300, heavy_count=3, steps=2), **kw})
+    many, one = R.Rig(w, micro_batches=mb, attn_splits=splits), R.Rig(w, micro_batches=mb, attn_splits=1)
+    assert many.kvd.step_form() == mb
+    for t, q in enumerate(W.query_stream(w, many.q0, w.steps, R.DEV)):
+        many.step(0, t, q[0])
+        one.step(0, t, q[0])
+        assert np.array_equal(many.n_sel_pages, one.n_sel_pages), t
+        # (the probabilities that multiply V keep 16 bits in bf16 and 11 in fp16, relative to each split's own maximum)
+        err = H.attn_rel_err(many.n_out.reshape(-1, 128), one.n_out.reshape(-1, 128))
+        assert err <= (2.0 ** -14 if w.dtype == "bf16" else 2.0 ** -11), (t, err)
+        assert np.abs(many.n_lse - one.n_lse).max() <= 1e-4, t
+    many.close()
+    one.close()
