@@ -263,7 +263,8 @@ int kvd_create(const kvd_config* cfg, kvd_ctx** out) {
   if (S > c->k) S = c->k;
   c->S = S;
   // The one-launch step runs one workgroup of 512 threads per CU, with 256 registers per lane (three
-  // tile buffers in the attention role); its attention splits follow the rule of the stand-alone kernel.
+  // tile buffers in the attention role); its attention splits follow the rule of the stand-alone kernel, with the units'
+  // selection workgroups beside them.
   c->S1 = S;
   if (cfg->attn_splits == 0) {
     const int sel_tiles = (c->k * c->P + 15) / 16;      // 16-token tiles of a unit's selection

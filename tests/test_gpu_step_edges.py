@@ -20,6 +20,8 @@ if torch.cuda.is_available():
     (2049, 300, 100, dict(sink_pages=3, recent_pages=5)),
     (2050, 1, 1, dict()),                                 # no ties, one page
     (4096, 1500, 333, dict(sink_pages=1)),                # more candidates than the list holds
+    (3001, 32, 20, dict()),                               # lists that a wave ranks by itself and that the threads share
+    (3300, 33, 20, dict()),
     (4097, 65, 64, dict(dtype="f16")),
     (8192, 64, 256, dict(recent_pages=2)),
     (8193, 2000, 700, dict()),
