@@ -310,7 +310,8 @@ int kvd_step(kvd_ctx* ctx, int32_t layer, int32_t step, const void* q, float* ou
  * layer's attention output are stepped one by one with kvd_step).  Every layer has its own cache
  * directory and slots, so the results are those of the layers stepped one after another; what
  * changes is that the layers overlap (SFC Disaggregation applied across layers):
- *   - where the step runs as one launch, up to 8 layers share a launch whose workgroups are ordered
+ *   - where the step runs as one launch, or could with the choice left to the library (micro_batches 0),
+ *     up to 8 layers share a launch whose workgroups are ordered
  *     so that layer l+1 is scored while layer l is being selected and its missed pages are fetched,
  *     and layer l is attended while layer l+1 is selected; everything stays on `stream`;
  *   - where it runs as a chain of kernels, two layers are kept in flight: layers alternate between
