@@ -105,7 +105,7 @@ __device__ __forceinline__ void merge_splits(const AttnArgs& a, int u, float* ld
     return;
   }
   auto merge = [&](auto batch) {
-    constexpr int N = decltype(batch)::value;            // splits whose accumulators are fetched at a time; those beyond S read as zero
+    constexpr int N = decltype(batch)::value;            // splits whose accumulators are fetched at a time
     const int SP = (S + N - 1) / N * N;
     float* mx = lds;                                     // [G][SP] maxima
     float* weight = lds + SP * G;                        // [G][SP]
@@ -123,10 +123,12 @@ __device__ __forceinline__ void merge_splits(const AttnArgs& a, int u, float* ld
     for (int idx0 = 0; idx0 < G * kHeadDim; idx0 += NT) {
       const int idx = idx0 + tid, g = idx / kHeadDim, d = idx % kHeadDim;
       float av[N];
+      // (splits beyond S read as zero: the whole offset is in the operand that the buffer's bounds are checked against, which
+      // the scalar offset is not)
       auto fetch = [&](int s0) {
 #pragma unroll
         for (int i = 0; i < N; ++i)
-          av[i] = as_f32(__builtin_amdgcn_raw_buffer_load_b32(acc, idx * 4, (s0 + i) * G * kHeadDim * 4, HANDOFF ? 16 : 0));
+          av[i] = as_f32(__builtin_amdgcn_raw_buffer_load_b32(acc, (idx + (s0 + i) * G * kHeadDim) * 4, 0, HANDOFF ? 16 : 0));
       };
       fetch(0);
       if (idx0 == 0) {

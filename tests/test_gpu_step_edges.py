@@ -5,6 +5,7 @@ import numpy as np
 import pytest
 import torch
 
+from paper_2605_18071_amd import kvd as K
 from paper_2605_18071_amd import workloads as W
 from tests import helpers as H
 from tests.test_gpu_parity import small
@@ -108,3 +109,51 @@ def test_merge_of_many_splits_equals_one_split(splits, kw, mb):
         assert np.abs(many.n_lse - one.n_lse).max() <= 1e-4, t
     many.close()
     one.close()
+
+
+@pytest.mark.parametrize("mb", [-1, 1], ids=["single-launch", "kernel-chain"])
+@pytest.mark.parametrize("splits,kw", [
+    (9, dict()),
+    (9, dict(n_q_heads=2)),                                # a head has fewer dims than the workgroup threads
+    (17, dict(n_q_heads=16)),
+    (33, dict(dtype="f16")),
+])
+def test_merge_of_many_splits_reads_no_other_units_partials(splits, kw, mb):
+    """The merge fetches partials 16 or 32 at a time, more than there are; what lies behind a unit's partials is the next
+    unit's, and here that holds infinities and NaN in every other unit."""
+    w = small("merge-bounds", **{**dict(ctx=16 * 600, topk_pages=257, capacity=300, heavy_count=3, steps=3, batch=4), **kw})
+    many, one = R.Rig(w, micro_batches=mb, attn_splits=splits), R.Rig(w, micro_batches=mb, attn_splits=1)
+    for r in (many, one):
+        r.store[:, 1::2, :, :, 1] = float("inf")           # V of every second sequence, whatever its pages
+        r.store[:, 1::2, :, :, 1, :, ::2] = float("nan")
+    for t, q in enumerate(W.query_stream(w, many.q0, w.steps, R.DEV)):
+        many.step(0, t, q[0])
+        one.step(0, t, q[0])
+        assert not np.isfinite(many.n_out[1::2]).any()
+        got, want = many.n_out[::2].reshape(-1, 128), one.n_out[::2].reshape(-1, 128)
+        assert np.isfinite(got).all() and np.isfinite(many.n_lse).all(), t
+        # (as in the test above)
+        assert H.attn_rel_err(got, want) <= (2.0 ** -14 if w.dtype == "bf16" else 2.0 ** -11), t
+    many.close()
+    one.close()
+
+
+@pytest.mark.parametrize("splits", [9, 17, 33])
+def test_merge_of_many_splits_in_used_scratch(splits):
+    """The call without a context works in one array of the library: first 64 splits of values that are no numbers, then
+    fewer splits of ordinary ones, whose last unit's partials have the old ones right behind them."""
+    w = small("merge-scratch", ctx=16 * 300, topk_pages=129, capacity=140, heavy_count=3, steps=1, batch=2)
+    rig = R.Rig(w, micro_batches=1, attn_splits=1)
+    q = next(W.query_stream(w, rig.q0, 1, R.DEV))[0].contiguous()
+    rig.step(0, 0, q)
+    seq = torch.tensor(rig.seq_lens, dtype=torch.int32, device=R.DEV)
+    shape = dict(batch=w.batch, n_q_heads=w.n_q_heads, n_kv_heads=w.n_kv_heads, page_size=w.page, topk_pages=w.topk_pages,
+                 capacity_max=w.capacity, kv_dtype=w.torch_dtype)
+    bad, got = torch.full_like(rig.pool[0], float("nan")), torch.empty_like(rig.out)
+    K.sparse_decode_attn_noalloc(q, bad, rig.sel_pages, rig.sel_slots, seq, got, None, attn_splits=64, **shape)
+    K.sparse_decode_attn_noalloc(q, rig.pool[0], rig.sel_pages, rig.sel_slots, seq, got, None, attn_splits=splits, **shape)
+    torch.cuda.synchronize()
+    got = got.cpu().numpy().reshape(-1, 128)
+    assert np.isfinite(got).all()
+    assert H.attn_rel_err(got, rig.n_out.reshape(-1, 128)) <= 2.0 ** -14
+    rig.close()
