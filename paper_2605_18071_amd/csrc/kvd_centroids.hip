@@ -280,7 +280,9 @@ __global__ __launch_bounds__(kAssignThreads, 2) void kmeans_assign_kernel(const 
           }
         dot += __shfl_xor(dot, 16, kWave);
         dot += __shfl_xor(dot, 32, kWave);
-        floor_v[q] = (dot + neg_u[c0]) - 2.f * slack[q];
+        const float at_least = (dot + neg_u[c0]) - 2.f * slack[q];
+        // (a cluster with a page that is no number has no v: no floor then; no v compares with a NaN)
+        floor_v[q] = at_least == at_least ? at_least : -INFINITY;
       }
     }
   }
