@@ -490,10 +490,11 @@ int kvd_calibrate_step_form(kvd_ctx* ctx, int32_t layer, int32_t first_step, con
 /* Launch shape of the one-launch step.  Four numbers: how many passes of 64 pages a scoring wave
  * makes per chunk it takes (1..8); how many persistent scoring workgroups a group has (1..compute
  * units; the other compute units are left to the selection workgroups, and to attention workgroups
- * of units already selected, while scoring goes on); the attention splits per unit (at most twice
- * what kvd_create chose, or, where that is more and a unit has at most 8192 pages, twice one
- * workgroup per compute unit with 16 tiles of 16 tokens each; at most 64, and at most 512 selected
- * pages per split); and the number of groups (1..8) the
+ * of units already selected, while scoring goes on); the attention splits per unit (at most the
+ * largest of: twice what kvd_create chose, also with its workgroups rounded to the nearest number per
+ * compute unit instead of down; twice one workgroup per compute unit, rounded likewise, with 16 tiles
+ * of 16 tokens each; and, for units of more than 8192 pages, twice one split per 64 tiles; at most 64,
+ * and at most 512 selected pages per split); and the number of groups (1..8) the
  * units of a layer are cut into: the groups follow each other through the launch, group g+1 being
  * scored while group g is selected and its missed pages are fetched, group g attended while group g+1
  * is selected — the micro-batches of SFC Disaggregation, pipelined by the order of the launch's

@@ -276,8 +276,9 @@ int kvd_create(const kvd_config* cfg, kvd_ctx** out) {
     c->S1 = S2 < 1 ? 1 : S2;
   }
   // room in the partials for the splits that kvd_set_step_shape takes and a calibration of the launch shape tries: twice
-  // the rule's with its workgroups rounded up to one per CU, or twice an attention workgroup per CU with two tiles per wave
-  // where that is more
+  // the rule's, with its workgroups rounded to the nearest number per CU, or twice an attention workgroup per CU with two
+  // tiles per wave, or, for units of more than 8192 pages, twice a split per 64 tiles (whatever the number of units: calls
+  // may hold such a shape from when that was their rule), whichever is most
   c->S1_max = cfg->attn_splits == 0 ? 2 * c->S1 : c->S1;
   if (cfg->attn_splits == 0) {
     const int tiles = (c->k * c->P + 15) / 16, full = (c->n_cus + c->U / 2) / c->U;
@@ -285,6 +286,7 @@ int kvd_create(const kvd_config* cfg, kvd_ctx** out) {
     const int most = full < tiles / 16 ? full : tiles / 16;
     if (c->S1_max < 2 * rounded) c->S1_max = 2 * rounded;
     if (c->S1_max < 2 * most) c->S1_max = 2 * most;
+    if (c->NP > 8192 && c->S1_max < 2 * (tiles / 64)) c->S1_max = 2 * (tiles / 64);
   }
   if (c->S1_max > KVD_MAX_SPLITS) c->S1_max = KVD_MAX_SPLITS;
   if (c->S1_max > c->k) c->S1_max = c->k;

@@ -3,6 +3,7 @@ takes, and the outputs do not depend on the split (against one split, up to the 
 import pytest
 import torch
 
+from paper_2605_18071_amd import kvd as K
 from tests import helpers as H
 from tests.test_gpu_parity import small
 
@@ -55,3 +56,19 @@ def test_the_shape_reported_for_several_layers_is_that_of_the_longest_launch():
             assert torch.equal(out[l], one.out)
     for r in (rig, one, short):
         r.close()
+
+
+@pytest.mark.parametrize("units,k,page,most", [
+    (128, 512, 16, 16),         # 512 tiles: two splits of 64 tiles each, whatever the number of units
+    (140, 289, 256, 64),        # 4624 tiles: as many as there are at most
+    (30, 56, 256, 28),
+])
+def test_units_of_many_pages_take_twice_a_split_per_64_tiles(units, k, page, most):
+    ctx = K.Kvd(n_layers=1, batch=units, n_q_heads=4, n_kv_heads=1, page_size=page, max_pages=8200, topk_pages=k,
+                capacity_max=k + 8, kv_dtype=torch.bfloat16, micro_batches=-1)
+    assert ctx.step_form() == -1
+    ctx.set_step_shape(attn_splits=most)
+    assert ctx.step_shape()[2] == most
+    with pytest.raises(K.KvdError):
+        ctx.set_step_shape(attn_splits=most + 1)
+    ctx.close()
