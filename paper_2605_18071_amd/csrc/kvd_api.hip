@@ -7,7 +7,6 @@
 #include <algorithm>
 #include <vector>
 
-#include "kvd_attn_body.h"
 #include "kvd_internal.h"
 #include "kvd_tile_layout.h"
 
@@ -30,13 +29,6 @@ static bool kvd_wants_single_launch(const kvd_ctx* c) {
   if (!kvd_single_launch_ok(c)) return false;
   if (c->cfg.micro_batches == -1) return true;
   return c->cfg.micro_batches == 0 && (c->NP <= 8192 || c->U >= 8);
-}
-
-// Several layers share a launch wherever one can run, unless the caller has asked for another form (us per layer-step of
-// the few units above, two chains of kernels in flight and one launch: 7 layers of 8 units of 10109 pages 19.3 and 11.2, 4
-// layers of 4 units of 12500 20.0 and 9.3).
-static bool kvd_layers_share_launch(const kvd_ctx* c) {
-  return c->single_launch || (c->cfg.micro_batches == 0 && kvd_single_launch_ok(c) && (c->k + c->S - 1) / c->S <= kvd::kAttnIdxCap);
 }
 
 static bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }

@@ -153,6 +153,7 @@ constexpr int kNaturalLeast = 4;            // `least` of kvd_attn_splits over n
 int kvd_attn_splits(int least, int U, int k, int P, int cus, bool beside_selection = false);
 // The whole step as one launch (kvd_step.hip); usable when kvd_single_launch_ok.
 bool kvd_single_launch_ok(const kvd_ctx* c);
+bool kvd_layers_share_launch(const kvd_ctx* c);
 // The shape a launch takes: `want` (default: what the context holds for that kind of launch) with
 // its zeros filled in by the rule and the scoring workgroups capped at the number of chunks.  n_layers: layers of the
 // launch (0 = the most that one covers).

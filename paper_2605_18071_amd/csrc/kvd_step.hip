@@ -54,8 +54,9 @@ kvd_shape kvd_step_shape(const kvd_ctx* c, int multi_layer, const kvd_shape* wan
   if (ns > Ug * chunks) ns = Ug * chunks;
   e.passes = ps;
   e.n_score = ns;
-  // (where the library takes one layer as a chain of kernels, several have that chain's splits, for the same order of the sums)
-  e.splits = w.splits > 0 ? w.splits : multi_layer && !c->single_launch ? c->S : c->S1;
+  // (where the library takes one layer as a chain of kernels and several in a launch, these have that chain's splits, for the
+  // same order of the sums)
+  e.splits = w.splits > 0 ? w.splits : multi_layer && !c->single_launch && kvd_layers_share_launch(c) ? c->S : c->S1;
   return e;
 }
 
@@ -73,6 +74,13 @@ bool kvd_step_shape_ok(const kvd_ctx* c, const kvd_shape& e) {
 bool kvd_single_launch_ok(const kvd_ctx* c) {
   return kvd_fast_path_ok(c) && !kvd_fast_path_big(c) && c->tiled &&
          (c->k + c->S1 - 1) / c->S1 <= kvd::kAttnIdxCap;   // a split's entries are staged in LDS
+}
+
+// Several layers share a launch wherever one can run, unless the caller has asked for another form (us per layer-step of
+// the few units above, two chains of kernels in flight and one launch: 7 layers of 8 units of 10109 pages 19.3 and 11.2, 4
+// layers of 4 units of 12500 20.0 and 9.3).
+bool kvd_layers_share_launch(const kvd_ctx* c) {
+  return c->single_launch || (c->cfg.micro_batches == 0 && kvd_single_launch_ok(c) && (c->k + c->S - 1) / c->S <= kvd::kAttnIdxCap);
 }
 
 // How many of a unit's splits an attention workgroup of a launch of several layers takes.  The layers fill each other's gaps

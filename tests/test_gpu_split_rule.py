@@ -72,3 +72,19 @@ def test_units_of_many_pages_take_twice_a_split_per_64_tiles(units, k, page, mos
     with pytest.raises(K.KvdError):
         ctx.set_step_shape(attn_splits=most + 1)
     ctx.close()
+
+
+def test_shapes_of_several_layers_are_taken_whatever_the_form():
+    """251 units: the stand-alone attention kernel has one split of 691 pages, more than a workgroup of the one-launch step
+    stages; what is set for launches of several layers has that step's two splits in every form of the context."""
+    ctx = K.Kvd(n_layers=2, batch=251, n_q_heads=2, n_kv_heads=1, page_size=16, max_pages=800, topk_pages=691, capacity_max=700,
+                kv_dtype=torch.bfloat16)
+    assert ctx.step_form() == -1
+    for form in (0, -1, 1, 2):
+        ctx.set_step_form(form)
+        for multi in (False, True):
+            ctx.set_step_shape(multi_layer=multi)
+            assert ctx.step_shape(multi_layer=multi)[2] == 2
+            ctx.set_step_shape(passes=2, multi_layer=multi)
+            assert ctx.step_shape(multi_layer=multi)[0] == 2
+    ctx.close()
