@@ -505,7 +505,9 @@ int kvd_calibrate_step_form(kvd_ctx* ctx, int32_t layer, int32_t first_step, con
  * launch would take now (host, 4 ints); for launches of several layers, one of as many as the
  * context's launches cover (its layers, at most 8).  The rule makes two passes there once the layers'
  * chunks fill most of the compute units: a launch of fewer layers, whose chunks would not, makes
- * one, and takes more scoring workgroups if there are chunks for them.  Results do not depend on the shape. */
+ * one, and takes more scoring workgroups if there are chunks for them.  With the rule's number of splits,
+ * left to it or set, an attention workgroup of a launch of several layers may take several of a unit's
+ * splits; splits of any other number have a workgroup each.  Results do not depend on the shape. */
 int kvd_set_step_shape(kvd_ctx* ctx, int32_t multi_layer, int32_t passes, int32_t scoring_workgroups, int32_t attn_splits,
                        int32_t groups);
 int kvd_get_step_shape(const kvd_ctx* ctx, int32_t multi_layer, int32_t* shape);

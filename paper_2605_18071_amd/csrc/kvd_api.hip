@@ -1029,11 +1029,7 @@ int kvd_calibrate_step_shape(kvd_ctx* ctx, int32_t layer, int32_t n_layers, int3
         for (int p = 1; p <= 4; ++p)
           if (sp >= 1) add({p, c->n_cus * eighths / 8, sp, g});
   }
-  // (the rule's splits are left to the rule, which in launches of several layers also says how many a workgroup takes)
-  auto apply = [&](kvd_shape x) {
-    if (multi && x.splits == rule.splits) x.splits = 0;
-    c->shape[multi] = x;
-  };
+  auto apply = [&](const kvd_shape& x) { c->shape[multi] = x; };
   const kvd_shape before = c->shape[multi];
   for (Timed& x : shapes) {
     apply(x.shape);

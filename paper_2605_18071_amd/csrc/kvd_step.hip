@@ -1,6 +1,12 @@
 // Host side of the one-launch step: its launch shape, where it can run, and the launch (the kernel: kvd_step_body.h).
 #include "kvd_step_body.h"
 
+// The splits that the rule leaves a launch with.  Where the library takes one layer as a chain of kernels and several in a launch, these have that chain's splits, for the
+// same order of the sums.
+static int rule_splits(const kvd_ctx* c, int multi_layer) {
+  return multi_layer && !c->single_launch && kvd_layers_share_launch(c) ? c->S : c->S1;
+}
+
 // The launch shape of the one-launch step.  What kvd_set_step_shape / kvd_calibrate_step_shape fixed
 // is taken; the rest follows the rule: one group; scoring workgroups = one round of resident
 // workgroups (one per CU) minus 1/8 left to the selection workgroups that run beside them; passes
@@ -54,9 +60,7 @@ kvd_shape kvd_step_shape(const kvd_ctx* c, int multi_layer, const kvd_shape* wan
   if (ns > Ug * chunks) ns = Ug * chunks;
   e.passes = ps;
   e.n_score = ns;
-  // (where the library takes one layer as a chain of kernels and several in a launch, these have that chain's splits, for the
-  // same order of the sums)
-  e.splits = w.splits > 0 ? w.splits : multi_layer && !c->single_launch && kvd_layers_share_launch(c) ? c->S : c->S1;
+  e.splits = w.splits > 0 ? w.splits : rule_splits(c, multi_layer);
   return e;
 }
 
@@ -121,7 +125,9 @@ hipError_t kvd_launch_step(kvd_ctx* c, int layer, int n_layers, int step, const 
   const kvd_shape shape = kvd_step_shape(c, n_layers > 1, nullptr, n_layers);
   a.at.S = shape.splits;
   a.at.per_split = (c->k + shape.splits - 1) / shape.splits;
-  a.at.take = n_layers > 1 && c->shape[1].splits == 0 ? kvd_step_take(c, shape.splits, n_layers) : 1;   // (splits that the caller has set stay as they are)
+  // (the rule's number of splits, whether it was left to the rule or set: a shape that a context reports gives the same launch
+  // when it is set; any other number that the caller has set stays as it is)
+  a.at.take = n_layers > 1 && shape.splits == rule_splits(c, 1) ? kvd_step_take(c, shape.splits, n_layers) : 1;
   a.score_done = c->d_score_done;
   a.error = c->error_dev;
   a.timeline = nullptr;

@@ -88,3 +88,40 @@ def test_shapes_of_several_layers_are_taken_whatever_the_form():
             ctx.set_step_shape(passes=2, multi_layer=multi)
             assert ctx.step_shape(multi_layer=multi)[0] == 2
     ctx.close()
+
+
+def test_a_reported_shape_of_several_layers_gives_the_same_launch_when_it_is_set():
+    """8 layers of 16 units with 16 splits, of which a workgroup takes several (9.3 us a layer, 12.3 with a workgroup each)."""
+    w = small("shape-again", ctx=16 * 1024, topk_pages=256, capacity=280, batch=4, n_kv_heads=4, n_q_heads=8, n_layers=8,
+              physical_layers=1, heavy_count=3)
+    rig = R.Rig(w, micro_batches=-1)
+    q = next(R.W.query_stream(w, rig.q0, 1, R.DEV)).contiguous()
+    outs = [torch.empty((8, w.batch, w.n_q_heads, w.head_dim), dtype=torch.float32, device=R.DEV) for _ in range(3)]
+    rig.kvd.step_layers(0, 8, 0, q, outs[0])
+
+    def us(out):                                                        # the least of several, each of 30 launches
+        ev = [torch.cuda.Event(enable_timing=True) for _ in range(9)]
+        for e in ev:
+            e.record()
+            for _ in range(30):
+                rig.kvd.step_layers(0, 8, 0, q, out)
+        torch.cuda.synchronize()
+        return min(a.elapsed_time(b) for a, b in zip(ev[1:], ev[2:])) / 30 * 1e3 / 8
+
+    rule = us(outs[1])
+    shape = rig.kvd.step_shape(multi_layer=True)
+    assert shape[2] == 16
+    rig.kvd.set_step_shape(*shape, multi_layer=True)
+    again = us(outs[2])
+    print(f"rule {rule:.2f} us a layer, set {again:.2f}")
+    assert again < 1.2 * rule
+    chosen, us_chosen, us_rule = rig.kvd.calibrate_step_shape(0, 0, q, outs[2], launches_per_shape=4, n_layers=8)
+    kept = us(outs[2])
+    rig.kvd.set_step_shape(*chosen, multi_layer=True)
+    assert rig.kvd.step_shape(multi_layer=True) == chosen
+    assert us(outs[2]) < 1.2 * kept
+    rig.kvd.set_step_shape(multi_layer=True)
+    rig.kvd.step_layers(0, 8, 0, q, outs[2])
+    torch.cuda.synchronize()
+    assert torch.equal(outs[1], outs[0]) and torch.equal(outs[2], outs[0])
+    rig.close()
