@@ -71,15 +71,20 @@ __device__ __forceinline__ bool block_wait_equal(const int32_t* flag, int32_t wa
   return *lds_ok != 0;
 }
 
-// The same by one wave for itself, without a barrier: every lane of the wave gets the verdict.
+// The same by one wave for itself, without a barrier: every lane of the wave gets the verdict.  What the flag announces is
+// read after the flag: the hardware issues a wave's loads in order and this one has been waited for, and the fence (no
+// instruction of its own) keeps the compiler from moving the loads that follow, which need not be atomic, ahead of it.
 __device__ __forceinline__ bool wave_wait_equal(const int32_t* flag, int32_t want, long long limit) {
-  if (__builtin_amdgcn_readfirstlane(load_agent(flag)) == want) return true;
-  const long long t0 = wall_clock64();
-  for (;;) {
-    __builtin_amdgcn_s_sleep(1);
-    if (__builtin_amdgcn_readfirstlane(load_agent(flag)) == want) return true;
-    if (wall_clock64() - t0 > limit) return false;
+  bool there = __builtin_amdgcn_readfirstlane(load_agent(flag)) == want;
+  if (!there) {
+    const long long t0 = wall_clock64();
+    do {
+      __builtin_amdgcn_s_sleep(1);
+      there = __builtin_amdgcn_readfirstlane(load_agent(flag)) == want;
+    } while (!there && wall_clock64() - t0 <= limit);
   }
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  return there;
 }
 
 // ---- 16-bit -> fp32, eight elements of one 16-byte load -------------------------------------

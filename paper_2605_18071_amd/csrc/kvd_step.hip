@@ -1,8 +1,8 @@
 // Host side of the one-launch step: its launch shape, where it can run, and the launch (the kernel: kvd_step_body.h).
 #include "kvd_step_body.h"
 
-// The splits that the rule leaves a launch with.  Where the library takes one layer as a chain of kernels and several in a launch, these have that chain's splits, for the
-// same order of the sums.
+// The splits that the rule leaves a launch with.  Where the library takes one layer as a chain of kernels and several in a
+// launch, these have that chain's splits, for the same order of the sums.
 static int rule_splits(const kvd_ctx* c, int multi_layer) {
   return multi_layer && !c->single_launch && kvd_layers_share_launch(c) ? c->S : c->S1;
 }
