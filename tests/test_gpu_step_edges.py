@@ -157,3 +157,77 @@ def test_merge_of_many_splits_in_used_scratch(splits):
     assert np.isfinite(got).all()
     assert H.attn_rel_err(got, rig.n_out.reshape(-1, 128)) <= 2.0 ** -14
     rig.close()
+
+
+def few_large_units(**kw):
+    """4 units of more than 8192 pages: with the form left to the library a layer steps as a chain of kernels, and several
+    share a launch."""
+    return small("few-large", **{**dict(ctx=16 * 8200, topk_pages=100, capacity=150, batch=2, n_kv_heads=2, n_q_heads=8, n_layers=9,
+                                        physical_layers=1, heavy_count=5, steps=4, rho=0.3), **kw})
+
+
+@pytest.mark.parametrize("kw", [dict(), dict(policy="lookahead", dtype="f16", n_q_heads=14), dict(page=8, ctx=8 * 8301, n_layers=3),
+                                dict(index_centroids=300, index_iterations=2, n_layers=2)],
+                         ids=["lru", "lookahead-f16", "packed", "clusters"])
+def test_layers_that_share_a_launch_only_together(kw):
+    """Outputs, directory, trace and counters are those of the layers one by one: the launch has the chain's splits.  Of nine
+    layers eight share a launch and the last one goes as a single layer, in the first one's scratch."""
+    w = few_large_units(**kw)
+    L = w.n_layers
+    one, together = R.Rig(w, seq_lens=[w.ctx - 5, w.ctx - 700]), R.Rig(w, seq_lens=[w.ctx - 5, w.ctx - 700])
+    assert one.kvd.step_form() == together.kvd.step_form() == 1
+    shape = (L, w.batch, w.n_q_heads, w.head_dim)
+    a, b = (torch.empty(shape, dtype=torch.float32, device=R.DEV) for _ in range(2))
+    la, lb = (torch.empty(shape[:-1], dtype=torch.float32, device=R.DEV) for _ in range(2))
+    for t, q in enumerate(W.query_stream(w, one.q0, w.steps, R.DEV)):
+        b.fill_(float("nan"))
+        for l in range(L):
+            one.kvd.step(l, t, q[l], a[l], la[l])
+        n = L if t % 2 == 0 else L - 1                       # with and without the one that is left over
+        together.kvd.step_layers(0, n, t, q[:n].contiguous(), b, lb)
+        if n < L:
+            together.kvd.step(n, t, q[n], b[n], lb[n])
+        traces = []
+        for r in (one, together):
+            r.kvd.step_trace(r.sel_pages, r.sel_slots, r.hit_mask, r.evicted, r.counts, r.scores)
+            torch.cuda.synchronize()
+            scores = r.scores.flatten()[:w.units * (w.index_centroids or w.n_pages)]
+            traces.append([x.clone() for x in (r.sel_pages, r.sel_slots, r.hit_mask, r.evicted.sort().values, r.counts, scores)])
+        assert torch.equal(a, b) and torch.equal(la, lb), t
+        for i, (x, y) in enumerate(zip(*traces)):
+            assert torch.equal(x, y), (t, i)
+    for l in range(L):
+        for x, y in zip(one.kvd.cache_export(l), together.kvd.cache_export(l)):
+            assert torch.equal(x, y), l
+    s1, s2 = one.kvd.stats(), together.kvd.stats()
+    assert (s1.steps, s1.hits, s1.misses, s1.evictions) == (s2.steps, s2.hits, s2.misses, s2.evictions) and s1.evictions > 0
+    one.close()
+    together.close()
+
+
+def test_layers_that_share_a_launch_only_together_recover_from_a_wait():
+    w = few_large_units(n_layers=3)
+    rig, cold = R.Rig(w), R.Rig(w)
+    out, want = (torch.empty((3, w.batch, w.n_q_heads, w.head_dim), dtype=torch.float32, device=R.DEV) for _ in range(2))
+    qs = [q.contiguous() for q in W.query_stream(w, rig.q0, w.steps, R.DEV)]
+    rig.kvd.step_layers(0, 3, 0, qs[0], out)
+    rig.kvd.set_wait_limit_us(0)
+    rig.kvd.step_layers(0, 3, 1, qs[1], out)                 # workgroups that have to wait give up
+    torch.cuda.synchronize()
+    for call in (rig.kvd.stats, lambda: rig.kvd.step_layers(0, 3, 2, qs[2], out)):
+        with pytest.raises(K.KvdError) as e:
+            call()
+        assert e.value.status == K.ERR_STATE
+    # told once; the layers go on from empty windows, each as a chain (the limit is still 0: nothing waits any more)
+    for t in (2, 3):
+        rig.kvd.step_layers(0, 3, t, qs[t], out)
+        for l in range(3):
+            cold.kvd.step(l, t, qs[t][l], want[l])
+        torch.cuda.synchronize()
+        rig.kvd.stats()
+        assert rig.kvd.step_form() == 1 and torch.equal(out, want), t
+        for l in range(3):
+            for x, y in zip(rig.kvd.cache_export(l), cold.kvd.cache_export(l)):
+                assert torch.equal(x, y), (t, l)
+    rig.close()
+    cold.close()
