@@ -528,11 +528,12 @@ int kvd_get_step_shape(const kvd_ctx* ctx, int32_t multi_layer, int32_t* shape);
 int kvd_calibrate_step_shape(kvd_ctx* ctx, int32_t layer, int32_t n_layers, int32_t step, const void* q_layers,
                              float* out_layers, void* stream, int32_t launches_per_shape, int32_t* chosen_shape,
                              float* us_chosen, float* us_rule);
-/* Bound of every wait inside the one-launch kvd_step (micro_batches = -1), where workgroups wait on
+/* Bound of every wait inside the one-launch kvd_step and the launches of kvd_step_layers, where workgroups wait on
  * counters and published words in device memory that the workgroups before them write.  Default 2 s.
  * A wait that runs out makes its workgroup leave without output and raises an error word in host
  * memory.  While the word is set kvd_get_stats and kvd_step_trace return KVD_ERR_STATE (the step that
- * failed has no valid output or trace).  The next kvd_step / kvd_step_layers call finds the word,
+ * failed has no valid output or trace).  The next kvd_step, kvd_step_layers, kvd_step_tiered,
+ * kvd_cache_resolve or kvd_sparse_decode_attn call finds the word,
  * waits for the device, empties the window of every layer (the failed step may have left a
  * directory half updated), clears the word, switches the context to the chain of kernels
  * (kvd_step_form() == 1 from then on, until kvd_set_step_form says otherwise) and returns

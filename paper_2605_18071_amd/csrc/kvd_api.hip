@@ -610,6 +610,7 @@ int kvd_cache_resolve(kvd_ctx* ctx, int32_t layer, int32_t step, const int32_t* 
   if (!ctx || !sel_pages || !sel_slots || layer < 0 || layer >= ctx->L) return KVD_ERR_ARG;
   if (do_gather && (!ctx->pool || !ctx->store_dev)) return KVD_ERR_STATE;
   if (ctx->cfg.policy == KVD_EVICT_LOOKAHEAD && ctx->last_scores == nullptr) return KVD_ERR_STATE;
+  if (*ctx->error_host != 0) return recover_from_wait_timeout(ctx);   // (the directory may be half updated)
   hipStream_t s = static_cast<hipStream_t>(stream);
   int32_t* hm = hit_mask ? hit_mask : ctx->d_hit_mask;
   int32_t* ev = evicted ? evicted : ctx->d_evicted;
@@ -630,6 +631,7 @@ int kvd_sparse_decode_attn(kvd_ctx* ctx, int32_t layer, const void* q, const int
   if (!ctx || !q || !sel_pages || !sel_slots || !out || layer < 0 || layer >= ctx->L || !aligned16(q))
     return KVD_ERR_ARG;
   if (!ctx->pool) return KVD_ERR_STATE;
+  if (*ctx->error_host != 0) return recover_from_wait_timeout(ctx);   // (the tickets of the splits may not be at zero)
   HIP_TRY(ctx, kvd_launch_attend(ctx, layer, q, sel_pages, sel_slots, out, lse, 0, ctx->U, static_cast<hipStream_t>(stream)));
   return KVD_OK;
 }
@@ -825,6 +827,7 @@ int kvd_step_tiered(kvd_ctx* ctx, int32_t layer, int32_t step, const void* q, fl
   if (!ctx->summaries || !ctx->pool || !ctx->tier || (ctx->Nc > 0 && !ctx->centroids)) return KVD_ERR_STATE;
   kvd_ctx* c = ctx;
   hipStream_t s = static_cast<hipStream_t>(stream);
+  if (*c->error_host != 0) return recover_from_wait_timeout(c);
   ++c->n_steps;
   c->last_scores = c->d_scores;
   // (1) select, and the directory update, on the GPU; nothing is fetched yet

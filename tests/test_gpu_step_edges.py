@@ -231,3 +231,33 @@ def test_layers_that_share_a_launch_only_together_recover_from_a_wait():
                 assert torch.equal(x, y), (t, l)
     rig.close()
     cold.close()
+
+
+@pytest.mark.parametrize("call", ["resolve", "attention", "tiered"])
+def test_calls_after_a_wait_that_ran_out_report_it(call, tmp_path):
+    """What the failed launch left (directories half updated, tickets not at zero) is not worked on by the stage calls and
+    the tiered step either: they report the failure once, and the next call starts from empty windows."""
+    w = few_large_units(n_layers=2, ctx=16 * 8193)
+    rig = R.Rig(w)
+    if call == "tiered":
+        rig.attach_tier(str(tmp_path / "pages"), extent_pages=8, pool_extents=4000)
+        rig.kvd.bind_host_store(rig.store)
+    out = torch.empty((2, w.batch, w.n_q_heads, w.head_dim), dtype=torch.float32, device=R.DEV)
+    qs = [q.contiguous() for q in W.query_stream(w, rig.q0, w.steps, R.DEV)]
+    rig.kvd.score_select(0, qs[1][0], rig.sel_pages)
+    rig.kvd.step_layers(0, 2, 0, qs[0], out)
+    rig.kvd.set_wait_limit_us(0)
+    rig.kvd.step_layers(0, 2, 1, qs[1], out)
+    torch.cuda.synchronize()
+    run = {"resolve": lambda: rig.kvd.cache_resolve(0, 2, rig.sel_pages, rig.sel_slots),
+           "attention": lambda: rig.kvd.sparse_decode_attn(0, qs[1][0], rig.sel_pages, rig.sel_slots, rig.out),
+           "tiered": lambda: rig.kvd.step_tiered(0, 2, qs[1][0], rig.out)}[call]
+    rig.sel_slots.fill_(-1)
+    with pytest.raises(K.KvdError) as e:
+        run()
+    assert e.value.status == K.ERR_STATE
+    assert rig.kvd.step_form() == 1 and all((rig.kvd.cache_export(l)[0] == -1).all() for l in range(2))
+    run()
+    torch.cuda.synchronize()
+    rig.kvd.stats()
+    rig.close()
