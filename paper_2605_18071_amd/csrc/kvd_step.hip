@@ -105,6 +105,17 @@ static int kvd_step_take(const kvd_ctx* c, int splits, int n_layers) {
   return 1;
 }
 
+// The last layer's splits have a workgroup each, where the others' workgroups take three or more: nothing runs beside them,
+// least of all when the last pages have just come over the link, and that many splits one after the other take 20 us and
+// more.  (us per launch with misses, in which one page in 30 to one in 7 is fetched, with a workgroup to each split in all
+// layers, in none, and in the last one: 4 layers of 64 units 164.3, 175.0 and 164.8, 6 of 24 117.7, 119.3 and 113.2, 8 of 20
+// 415.6, 436.7 and 432.0, 8 of 56 276.0, 280.5 and 265.9; without misses the same 80.8, 68.6 and 67.6, 75.3, 58.8 and 55.2,
+// 90.8, 70.0 and 65.8, 147.3, 113.7 and 113.3.  But 4 layers of 16 units, of 16 splits, 47.6, 32.4 and 34.6, 3 of 20 41.2,
+// 29.5 and 33.1; where a workgroup takes two, 8 of 100 224.0, 190.2 and 194.7.)
+static int kvd_step_tail_layers(int splits, int take, int n_layers) {
+  return take >= 3 && n_layers >= (splits > 8 ? 5 : 4) ? 1 : 0;
+}
+
 hipError_t kvd_launch_step(kvd_ctx* c, int layer, int n_layers, int step, const void* q, float* out, float* lse, hipStream_t s) {
   using namespace kvd;
   if (n_layers < 1 || n_layers > kStepMaxLayers || n_layers > c->n_sets || layer + n_layers > c->L) return hipErrorInvalidValue;
@@ -172,8 +183,10 @@ hipError_t kvd_launch_step(kvd_ctx* c, int layer, int n_layers, int step, const 
   a.groups = shape.groups;
   a.group_units = (c->U + shape.groups - 1) / shape.groups;
   a.chunks = (score_np + chunk_pages * a.passes - 1) / (chunk_pages * a.passes);
-  const int attn_wgs = (shape.splits + a.at.take - 1) / a.at.take;
-  const int n_blocks = n_layers * a.groups * (a.n_score + a.group_units + a.group_units * attn_wgs);
+  const int attn_wgs = (shape.splits + a.at.take - 1) / a.at.take, n_stages = n_layers * a.groups;
+  a.tail_stages = kvd_step_tail_layers(shape.splits, a.at.take, n_layers) * a.groups;
+  const int n_blocks = n_stages * (a.n_score + a.group_units) +
+                       a.group_units * ((n_stages - a.tail_stages) * attn_wgs + a.tail_stages * shape.splits);
   c->tl_workgroups = n_blocks;
   if (c->profiling == 2 && n_blocks <= KVD_TIMELINE_MAX) a.timeline = c->d_timeline;
   const int ipt = (c->NP + chunk_pages - 1) / chunk_pages;

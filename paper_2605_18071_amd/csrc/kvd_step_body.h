@@ -87,6 +87,7 @@ struct StepArgs {
   int score_np;              // rows scored per unit: NP, or the number of centroids Nc
   int Nc;                    // 0 = flat page index
   int n_layers;              // layers covered by the launch
+  int tail_stages;           // the last stages, whose attention workgroups take one split each
   int groups, group_units;   // the units of a layer go through the launch in `groups` groups of group_units units (the last may be smaller)
   int layer0, Lp;            // first context layer; layers of the host store (layer l reads store layer l % Lp)
   const char* store_base;    // host store, layer 0 (device-visible address)
@@ -221,11 +222,12 @@ __device__ __forceinline__ void step_select_role(StepArgsPtr ap, int li, int u, 
   if (ts) ts[2] = ts[3] = wall_clock64();              // (the entries have been published inside)
 }
 
-// Attention workgroup (u, split): a.at.take splits from `split` on.
+// Attention workgroup (u, split): `take` splits from `split` on.
 template <bool BF16, int NT, bool PACKED, bool SEVERAL>
-__device__ __forceinline__ void step_attend_role(StepArgsPtr ap, int li, int u, int split, unsigned char* smem_raw, long long* ts) {
+__device__ __forceinline__ void step_attend_role(StepArgsPtr ap, int li, int u, int split, int take, unsigned char* smem_raw, long long* ts) {
   struct { AttnArgs at; } a;
   __builtin_memcpy(&a.at, &ap->at, sizeof(AttnArgs));
+  a.at.take = take;
   {
     const long long l = li;
     a.at.q += l * ap->q_stride;
@@ -248,16 +250,22 @@ __device__ __forceinline__ void step_body(StepArgsPtr ap, unsigned char* smem_ra
   long long* timeline = ap->timeline;
   long long* ts = timeline != nullptr && threadIdx.x == 0 ? timeline + (size_t)bid * 5 : nullptr;
   if (ts) { ts[0] = ts[1] = ts[2] = ts[3] = wall_clock64(); ts[4] = 3LL; }   // (role 3: a workgroup beyond its group's units, which leaves at once)
-  const int n_score = ap->n_score, take = MANY ? ap->at.take : 1, S = (ap->at.S + take - 1) / take, groups = ap->groups, Ug = ap->group_units;
+  const int n_score = ap->n_score, S = ap->at.S, groups = ap->groups, Ug = ap->group_units;
   const int n_stages = (MANY ? ap->n_layers : 1) * groups;          // (layer, group) pairs, in order
-  const int front = n_score + Ug, back = Ug * S;
+  const int front = n_score + Ug;
   // block order: front(0) | front(1) back(0) | front(2) back(1) | ... | back(n-1), where front(i) =
   // the scoring and selection workgroups of stage i and back(i) its attention workgroups
-  int st = 0, o = bid;
+  int st = 0, o = bid, take = 1, wgs = S;               // splits that an attention workgroup takes, workgroups per unit
   bool is_back = false;
   if (bid >= front) {
-    const int r = bid - front, per = front + back;
-    const int g = r / per;
+    int r = bid - front, first = 0;
+    if (MANY) {
+      // all stages but the last few: several splits to a workgroup
+      const int whole = n_stages - ap->tail_stages, t = ap->at.take, n = (S + t - 1) / t, blocks = whole * (front + Ug * n);
+      if (r < blocks) { take = t; wgs = n; } else { r -= blocks; first = whole; }
+    }
+    const int per = front + Ug * wgs;
+    const int g = first + r / per;
     o = r % per;
     if (g < n_stages - 1) {
       if (o < front) { st = g + 1; } else { st = g; o -= front; is_back = true; }
@@ -269,7 +277,7 @@ __device__ __forceinline__ void step_body(StepArgsPtr ap, unsigned char* smem_ra
   int n_units = ap->n_units - gi * Ug;                  // units of this group
   n_units = n_units < Ug ? n_units : Ug;
   if (is_back) {
-    if (o / S < n_units) step_attend_role<BF16, NT, PACKED, MANY>(ap, li, o / S + u0, (o % S) * take, smem_raw, ts);
+    if (o / wgs < n_units) step_attend_role<BF16, NT, PACKED, MANY>(ap, li, o / wgs + u0, (o % wgs) * take, take, smem_raw, ts);
   } else if (o < n_score) {
     step_score_role<BF16, NT>(ap, li, u0, n_units, o, smem_raw, ts);
   } else {

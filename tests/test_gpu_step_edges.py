@@ -84,6 +84,35 @@ def test_splits_shared_by_the_workgroups_of_several_layers(layers, kw):
     together.close()
 
 
+@pytest.mark.parametrize("groups", [1, 3])
+@pytest.mark.parametrize("layers,kw", [
+    (4, dict(batch=16, n_kv_heads=4, n_q_heads=8, topk_pages=128)),                       # 4 splits, all in one workgroup but for the last layer's
+    (4, dict(batch=7, n_kv_heads=4, n_q_heads=8, topk_pages=128)),                        # 8 splits, four to a workgroup
+    (5, dict(batch=5, n_kv_heads=4, n_q_heads=8, topk_pages=130, capacity=150, rho=0.3)), # 11 splits; most pages miss
+    (6, dict(batch=9, n_kv_heads=4, n_q_heads=28, topk_pages=100, page=8, ctx=8 * 300, dtype="f16")),
+])
+def test_the_last_layers_splits_have_a_workgroup_each(layers, groups, kw):
+    """... while the others' workgroups take three or more, also with the units of a layer in groups, the last of them
+    smaller: outputs bit for bit those of the layers one by one."""
+    w = small("last-layer", **{**dict(ctx=16 * 200, heavy_count=3, steps=3, n_layers=layers, physical_layers=1,
+                                      capacity=kw["topk_pages"] + 10), **kw})
+    one, together = R.Rig(w, micro_batches=-1), R.Rig(w, micro_batches=-1)
+    together.kvd.set_step_shape(groups=groups, multi_layer=True)
+    a, b = (torch.empty((layers, w.batch, w.n_q_heads, w.head_dim), dtype=torch.float32, device=R.DEV) for _ in range(2))
+    for t, q in enumerate(W.query_stream(w, one.q0, w.steps, R.DEV)):
+        b.fill_(float("nan"))
+        for l in range(layers):
+            one.kvd.step(l, t, q[l], a[l])
+        together.kvd.step_layers(0, layers, t, q.contiguous(), b)
+        torch.cuda.synchronize()
+        assert torch.equal(a, b), t
+    for l in range(layers):
+        for x, y in zip(one.kvd.cache_export(l), together.kvd.cache_export(l)):
+            assert torch.equal(x, y), l
+    one.close()
+    together.close()
+
+
 @pytest.mark.parametrize("mb", [-1, 1], ids=["single-launch", "kernel-chain"])
 @pytest.mark.parametrize("splits,kw", [
     (8, dict()),
