@@ -203,18 +203,30 @@ struct SelectSmem {
 // at most the number of valid items.  Returns the need-th smallest key.  All threads of the block
 // must call it with the same arguments.  Radix refinement: at most ceil(64/11) counting passes,
 // each narrowing the inclusive key range [lo, hi] to one of 2048 equal sub-ranges.
-template <int NT, class KeyFn>
+// AHEAD items of a thread are looked at together, which lets their loads be on their way together where keyfn does not branch.
+template <int NT, int AHEAD = 1, class KeyFn>
 __device__ u64 block_kth_smallest(KeyFn keyfn, int n, int need, SelectSmem& sm, u32* hist) {
   constexpr int NW = NT / kWave;
   const int tid = threadIdx.x, lane = tid & (kWave - 1), w = tid / kWave;
-  u64 mn = ~0ull, mx = 0ull;
-  for (int i = tid; i < n; i += NT) {
-    u64 key;
-    if (keyfn(i, key)) {
-      mn = key < mn ? key : mn;
-      mx = key > mx ? key : mx;
+  auto for_items = [&](auto f) {                       // f(key) for this thread's valid items
+    for (int i0 = tid; i0 < n; i0 += AHEAD * NT) {
+      u64 key[AHEAD];
+      bool ok[AHEAD];
+#pragma unroll
+      for (int x = 0; x < AHEAD; ++x) {
+        const int i = i0 + x * NT;
+        ok[x] = keyfn(AHEAD == 1 || i < n ? i : n - 1, key[x]) && (AHEAD == 1 || i < n);
+      }
+#pragma unroll
+      for (int x = 0; x < AHEAD; ++x)
+        if (ok[x]) f(key[x]);
     }
-  }
+  };
+  u64 mn = ~0ull, mx = 0ull;
+  for_items([&](u64 key) {
+    mn = key < mn ? key : mn;
+    mx = key > mx ? key : mx;
+  });
 #pragma unroll
   for (int m = 32; m >= 1; m >>= 1) {
     const u64 a = shfl_xor_u64(mn, m), b = shfl_xor_u64(mx, m);
@@ -242,10 +254,9 @@ __device__ u64 block_kth_smallest(KeyFn keyfn, int n, int need, SelectSmem& sm, 
     const int shift = bits > kRadixBits ? bits - kRadixBits : 0;
     for (int i = tid; i < kRadixBins; i += NT) hist[i] = 0;
     __syncthreads();
-    for (int i = tid; i < n; i += NT) {
-      u64 key;
-      if (keyfn(i, key) && key >= lo && key <= hi) atomicAdd(&hist[(u32)((key - lo) >> shift)], 1u);
-    }
+    for_items([&](u64 key) {
+      if (key >= lo && key <= hi) atomicAdd(&hist[(u32)((key - lo) >> shift)], 1u);
+    });
     __syncthreads();
     constexpr int BPT = kRadixBins / NT;           // consecutive bins per thread
     int local = 0;

@@ -854,11 +854,27 @@ __device__ __forceinline__ bool select_resolve_body(const FastArgs& a, int u, Fa
     n_valid = n_valid < a.NP ? n_valid : a.NP;
     if (a.la_pool < n_valid) {
       pooled = true;
-      auto fn = [&](int p, u64& kk) -> bool {
-        kk = selection_order_key(victim_score<HANDOFF>(a, u, p), p);
+      // Bound by the latency of the loads, of which a thread makes up to seven rounds.  (us per step with misses, a load at
+      // a time with 1024 threads, with 512, and four at a time with 512: 8 units of 9000 pages 142, 149 and 133, 24 of 16384
+      // 313, 338 and 302, 64 of 9000 583, 587 and 576, with clusters 16 of 9000 168, 186 and 171; eight at a time gain no
+      // more, and 176 there.  Scores fetched once and kept in registers cost every step 20 % through the code they add.)
+      // Without branches: a page of no cluster reads some score and has minus infinity.
+      const float* sc = a.scores + (size_t)u * a.score_stride;
+      const int32_t* cl = a.page_cluster != nullptr ? a.page_cluster + (size_t)u * a.NP : nullptr;
+      auto score_of = [&](int at) -> float { return HANDOFF ? load_agent(sc + at) : sc[at]; };
+      auto of_page = [&](int p, u64& kk) -> bool {
+        kk = selection_order_key(score_of(p), p);
         return true;
       };
-      pool_thr = block_kth_smallest<NT>(fn, n_valid, a.la_pool, sm.generic, sm.a.sel.hist);
+      auto of_cluster = [&](int p, u64& kk) -> bool {
+        const int c = cl[p];
+        const float v = score_of(c < 0 ? 0 : c);
+        kk = selection_order_key(c < 0 ? -INFINITY : v, p);
+        return true;
+      };
+      constexpr int kAhead = 4;
+      pool_thr = cl == nullptr ? block_kth_smallest<NT, kAhead>(of_page, n_valid, a.la_pool, sm.generic, sm.a.sel.hist)
+                               : block_kth_smallest<NT, kAhead>(of_cluster, n_valid, a.la_pool, sm.generic, sm.a.sel.hist);
       // (the histogram serves the victim choice next: it must start from zero again)
       __syncthreads();
       for (int i = tid; i < kHistWords; i += NT) sm.a.sel.hist[i] = 0;

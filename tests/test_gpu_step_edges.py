@@ -54,6 +54,50 @@ def test_selection_equals_the_size_agnostic_kernels(pages, same, k, kw, monkeypa
     plain.close()
 
 
+@pytest.mark.parametrize("mb", [-1, 1], ids=["single-launch", "kernel-chain"])
+@pytest.mark.parametrize("pages,pool,same,kw", [
+    (300, 30, 1, dict()),
+    (512, 511, 1, dict()),                                # all pages but one: the key of the last but one
+    (2049, 60, 40, dict(dtype="f16")),                    # ties at the pool's edge
+    (4097, 1500, 300, dict(sink_pages=2)),
+    (8193, 100, 1, dict()),
+    (8200, 3000, 8200, dict()),                           # one score for all: more than the list holds
+    (16384, 16383, 2000, dict()),
+    (9001, 64, 1, dict(values=True)),                     # scores of both infinities and none
+])
+def test_pool_of_the_best_pages_equals_the_size_agnostic_kernels(pages, pool, same, kw, mb, monkeypatch):
+    kw, values = dict(kw), kw.get("values")
+    kw.pop("values", None)
+    w = small("pool-edges", **{**dict(ctx=4 * pages, page=4, topk_pages=24, capacity=40, batch=2, n_kv_heads=2, n_q_heads=4,
+                                      heavy_count=0, steps=6, policy="lookahead", lookahead_pool=pool, rho=0.2), **kw})
+    seq = [w.ctx, w.ctx - 7]
+    fused = R.Rig(w, seq_lens=seq, micro_batches=mb, build_index=False)
+    monkeypatch.setenv("KVD_GENERIC_SELECT", "1")
+    plain = R.Rig(w, seq_lens=seq, micro_batches=1, build_index=False)
+    gen = torch.Generator(device=R.DEV)
+    gen.manual_seed(91_000 + pages)
+    rows = max(1, pages // same)
+    base = torch.randn(w.units, rows, 128, device=R.DEV, generator=gen)
+    summ = base[:, torch.randperm(pages, device=R.DEV, generator=gen) % rows].to(w.torch_dtype)
+    if values:
+        summ[:, 5::700, 0] = float("inf")
+        summ[:, 7::3000, 1] = float("nan")
+    for r in (fused, plain):
+        r.summaries.copy_(summ.view(r.summaries.shape))
+    evicted = 0
+    for t, q in enumerate(W.query_stream(w, fused.q0, w.steps, R.DEV)):
+        fused.step(0, t, q[0])
+        plain.step(0, t, q[0])
+        evicted += fused.n_counts[:, 2]
+        assert np.array_equal(fused.n_scores, plain.n_scores, equal_nan=True), t
+        for what in ("n_sel_pages", "n_hit_mask", "n_sel_slots", "n_counts"):
+            assert np.array_equal(getattr(fused, what), getattr(plain, what)), (what, t)
+        assert np.array_equal(np.sort(fused.n_evicted), np.sort(plain.n_evicted)), t
+    assert (evicted > 0).all() or same == pages
+    fused.close()
+    plain.close()
+
+
 @pytest.mark.parametrize("layers,kw", [
     (8, dict(batch=8, n_kv_heads=4, n_q_heads=32, topk_pages=128)),                       # 8 splits of 16 pages, eight heads
     (6, dict(batch=10, n_kv_heads=4, n_q_heads=4, topk_pages=101)),                       # 5 splits, the last one shorter
