@@ -80,24 +80,29 @@ static bool dispatch_group(int G, int layout, const AttnArgs& a, dim3 grid, hipS
 // evenly.  us per step with the nearest number to a workgroup per CU, with at most one, and without the selections' CUs: one
 // launch, 24 units of 2048 pages S = 11, 10 and 9 23.3, 20.2 and 19.7, 40 of 363 6, 6 and 5 18.3, 18.3 and 17.2, 56 of 2969
 // 5, 4 and 3 39.1, 33.5 and 34.8, 96 of 1250 3, 2 and 1 38.5, 33.1 and 38.2; 32 of 1001 8, 8 and 7 20.2, 20.2 and 19.8, but per layer
-// of 8 layers x 16 units of 1024 pages 7.6 with 16 and 8.5 with 15, of 3 x 32 of 2048 14.6 with 8 and 16.0 with 7; over natural slots 24 units x
-// 53 pages of 24 tokens 25.5 with 11 and 23.6 with 10, 96 x 102 pages of 20 49.4 with 3 and 41.0 with 2.  But
+// of 8 layers x 16 units of 1024 pages 7.6 with 16 and 8.5 with 15, of 3 x 32 of 2048 14.6 with 8 and 16.0 with 7 (contexts of
+// one layer keep 8 and 16 too, and lose 2 % by it); over natural slots 24 units x 53 pages of 24 tokens 25.5 with 11 and 23.6
+// with 10, 96 x 102 pages of 20 49.4 with 3 and 41.0 with 2.  But
 //  - a split keeps at least `least` tiles of 16 tokens for its eight waves: 16 in the stand-alone kernel over tiles (where
 //    fewer made no difference), 8 in the one-launch step with pages of up to 16 tokens and at least 32 tiles (8 units
 //    of 64 pages: 16.7 us with two tiles per wave, 15.9 with one; 2 splits instead of 1 gain nothing, and with larger
 //    pages a split's share comes in steps of several tiles: 20 units of 21 pages of 64 tokens 21.1 and 21.8), 4 over
 //    natural slots, where a tile costs a wave more (2 units of 40 pages of 12 tokens: 23.8 us with 16, 18.8 with 4);
-//  - beyond 16 splits a split keeps 18 tiles, beyond 32 splits 32: the last split to arrive fetches the partials of all the
-//    others, and with few units that costs more than shorter splits save.  us per step with 16, this and 32 or twice as many: 8
-//    units of 128 pages of 64 tokens 24.3, 23.0 (28 splits) and 23.6, 8 of 512 pages of 16 23.6, 23.2 and 23.7, 2 units of 1024
-//    pages of 16 27.5, 24.1 (32) and 24.5; 8 of 256 pages of 16 20.2 and 21.5;
+//  - beyond 16 splits a split keeps 32 tiles: the last split to arrive fetches the partials of all the others, and that costs
+//    more than shorter splits save.  With room for 32 splits per unit, that is up to 8 units, up to 32 splits keep 18 tiles
+//    each.  us per step of one launch, pages of 16 tokens, with 16 splits, this and 32: 4 units of 320 pages 18.5, 18.3 and
+//    18.5, of 448 20.2, 19.2 and 19.6, of 576 22.3, 20.5 and 20.5; 8 units of 320 19.6, 19.9 and 20.8, of 448 21.1, 21.2 and
+//    21.8, of 512 22.0, 21.7 and 22.1, of 640 23.7, 23.6 and 23.5; as a chain, 2 units of 1024 27.5, 24.1 and 24.5.  With 16
+//    splits and with 18 tiles each where there is less room: 9 units of 320 19.8 and 20.2, of 512 22.3 and 22.1, 10 of 512 22.9
+//    and 23.2, 12 of 448 22.6 and 23.3, 14 of 576 25.7 and 26.5;
 //  - no split is left without pages.
 int kvd_attn_splits(int least, int U, int k, int P, int cus, bool beside_selection) {
   const int tiles = (k * P + 15) / 16;                 // of a unit's selection
   int S = cus / U;
   if (beside_selection && S >= 5 && S % 8 != 0) S = (cus - U) / U;
   if (S > tiles / least) S = tiles / least;
-  const int longest = tiles / 18 < 32 ? tiles / 18 : tiles / 32 > 32 ? tiles / 32 : 32;
+  int longest = tiles / 32;
+  if (cus / U >= 32 && longest < 32) longest = tiles / 18 < 32 ? tiles / 18 : 32;
   if (S > 16 && S > longest) S = longest > 16 ? longest : 16;
   if (S > KVD_MAX_SPLITS) S = KVD_MAX_SPLITS;
   if (S > k) S = k;

@@ -440,7 +440,7 @@ def test_rows_beyond_the_sequence_end_may_hold_anything(page, dtype, poison, mb)
     dict(ctx=64 * 16384, page=64, topk_pages=64, capacity=96, recent_pages=6, batch=1),   # the largest unit the form takes
 ], ids=["8200-pages", "8192-pages-f16-g7-lookahead", "16384-pages"])
 def test_step_parity_units_of_8192_pages_and_more(kw):
-    """Units of 8192 pages and more run the one-launch step with 1024-thread workgroups."""
+    """Units on both sides of 8192 pages, up to the largest that the one-launch step takes (32 pages a thread)."""
     w = small("wide", steps=4, **kw)
     rig = R.Rig(w, seq_lens=[w.ctx - 5, w.ctx - 3 * w.page - 1][:w.batch], micro_batches=-1)
     assert rig.kvd.step_form() == -1
