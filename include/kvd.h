@@ -500,7 +500,7 @@ int kvd_calibrate_step_form(kvd_ctx* ctx, int32_t layer, int32_t first_step, con
  * is selected — the micro-batches of SFC Disaggregation, pipelined by the order of the launch's
  * workgroups.  The context holds two shapes: multi_layer == 0 for launches of one layer (kvd_step),
  * != 0 for launches of several layers (kvd_step_layers, where consecutive layers are pipelined the
- * same way).  0 leaves a number to the library's rule.  kvd_set_step_shape waits for the device;
+ * same way; also in contexts that step a single layer as a chain of kernels).  0 leaves a number to the library's rule.  kvd_set_step_shape waits for the device;
  * KVD_ERR_SHAPE for a shape the context cannot run.  kvd_get_step_shape writes the four numbers a
  * launch would take now (host, 4 ints); for launches of several layers, one of as many as the
  * context's launches cover (its layers, at most 8).  The rule makes two passes there once the layers'
@@ -524,7 +524,8 @@ int kvd_get_step_shape(const kvd_ctx* ctx, int32_t multi_layer, int32_t* shape);
  * counts, and the fastest is kept if it beats the rule's shape by more than 1.5 %, else the rule's
  * (smaller differences are within what two timings of one shape differ by).  chosen_shape (host, 4 ints), us_chosen and us_rule (microseconds per layer-step in the
  * shape kept and in the rule's) may be NULL.  The replays count in kvd_get_stats; the outputs are
- * the step's.  Synchronous.  KVD_ERR_STATE if the step does not run as one launch or profiling is on. */
+ * the step's.  Synchronous.  KVD_ERR_STATE if kvd_step does not run as one launch (kvd_step_form() other
+ * than -1), also for the layers of such a context that would share one, or profiling is on. */
 int kvd_calibrate_step_shape(kvd_ctx* ctx, int32_t layer, int32_t n_layers, int32_t step, const void* q_layers,
                              float* out_layers, void* stream, int32_t launches_per_shape, int32_t* chosen_shape,
                              float* us_chosen, float* us_rule);
@@ -547,8 +548,8 @@ int kvd_set_wait_limit_us(kvd_ctx* ctx, int64_t microseconds);
  * of an attention split, which are there once its pages are resident), end of its work, exit; and
  * a tag: bits 0-7 the role (0 scoring, 1 selection + directory + fetch, 2 attention), bits 8-31
  * the unit (0 for scoring workgroups, which serve all units in turn), bits 32-63 the number of the
- * scoring workgroup or the attention split.  KVD_ERR_STATE if the step does not
- * run as one launch or none has run. */
+ * scoring workgroup or the attention split.  KVD_ERR_STATE if kvd_step does not run as one launch
+ * or none has run.  (With profiling on layers do not share a launch: there is none of theirs.) */
 int kvd_step_timeline(kvd_ctx* ctx, int64_t* host_records, int32_t capacity, int32_t* n_workgroups);
 int kvd_get_stats(kvd_ctx* ctx, kvd_stats* host_out);   /* synchronises the device */
 int kvd_reset_stats(kvd_ctx* ctx);

@@ -93,7 +93,9 @@ bool kvd_layers_share_launch(const kvd_ctx* c) {
 // stay those of a single layer, and with them the order of the sums.  (us per layer-step with one and with this many: 8
 // layers of 64 units x 4 splits 21.9 and 18.8, of 32 x 8 14.6 and 11.9, of 16 x 16 10.6 and 7.4, of 128 x 2 37.7 and
 // 35.5; 3 layers of 32 x 8 16.8 and 13.9, but 14.7 with 4 instead of 2; 2 of 64 x 4 25.4 and 23.4, 26.1 with 4; 4 of 8 x 8
-// 4.7 with one or two, 5.9 with 4; 6 of 40 x 5 and 4 of 56 x 4, with a workgroup for every CU and for seven of eight, 14.6 and 12.3, 17.1 and 16.5.)
+// 4.7 with one or two, 5.9 with 4; 6 of 40 x 5 and 4 of 56 x 4, with a workgroup for every CU and for seven of eight, 14.6 and 12.3, 17.1 and 16.5.
+// Where one page in five is fetched, which the host does not know, it costs up to 6 %: a launch of 8 layers of 20 units 407
+// and 430, of 8 of 28 575 and 572, 3 of 20 180 and 186, 3 of 56 440 and 450.)
 static int kvd_step_take(const kvd_ctx* c, int splits, int n_layers) {
   const int per_split = (c->k + splits - 1) / splits, held = kvd::StepSmem<kvd::kStepThreads>::splits_held(c->G);
   const int room = held < kvd::kAttnIdxCap / per_split ? held : kvd::kAttnIdxCap / per_split;

@@ -19,6 +19,7 @@
 // pages fetched), and layer l's attention streams while layer l+1 is selected.  Every layer of the
 // launch has its own directory, slots and set of per-step scratch; dependencies stay inside a layer
 // and point to lower block indices only.
+// An attention workgroup of such a launch may take several splits of its unit, but for those of the last layer.
 // The units of one layer can likewise be cut into groups that follow each other through the launch in
 // the same interleaved order (SFC Disaggregation's micro-batches, pipelined by dispatch order instead
 // of by streams): groups of one layer share the layer's scratch set, since all of it is indexed by unit.
