@@ -87,13 +87,12 @@ struct FastSmem {
   static constexpr int kMaxCapacity = BIG ? KVD_BIG_MAX_CAPACITY : KVD_FAST_MAX_CAPACITY;
   typedef std::conditional_t<BIG, u32, uint16_t> page_t;
   static constexpr page_t kNoPage = (page_t)~(page_t)0;
-  static constexpr int kCopyGroups = NT / 256;           // tiles copied at a time
   union {
     struct {
       u32 hist[kRadixBins];
       u64 cand[kListCap];
     } sel;
-    uint16_t vt[kCopyGroups][kTileTokens * kHeadDim];    // V tiles in flight during the fetch
+    uint16_t vt[NW][4 * kHeadDim];                       // V of the four tokens that a wave turns around during the fetch
   } a;
   uint16_t p2s[kMaxPages];                               // page -> slot of this unit, kAbsent = not resident
   union {
@@ -236,19 +235,22 @@ __device__ __forceinline__ u64 rank_candidates(int m, int r, FastSmem<NT, BIG>& 
   return sm.thr;
 }
 
-// Items j = 0..IPT-1 of every thread: bkt(j) in [0, 2047], or -1 for "not a candidate"; key(j)
+// Items j = 0..n_items-1 (at most IPT) of every thread: bkt(j) in [0, 2047], or -1 for "not a candidate"; key(j)
 // distinct; key1 < key2 implies bkt1 <= bkt2.  sm.a.sel.hist must be zero and sm.cand_n zero on
 // entry (with a barrier since).  Returns the need-th smallest key among the candidates
 // (1 <= need <= number of candidates).  `refine(bin, r)` is called by all threads when the
 // decisive bucket holds more than kListCap items and must return the r-th smallest key of that
 // bucket.  Ends with the block synchronised.
 template <int NT, int IPT, bool BIG, class KeyOf, class BktOf, class Refine>
-__device__ __forceinline__ u64 two_level_select(KeyOf key, BktOf bkt, int need, FastSmem<NT, BIG>& sm, int& flip,
+__device__ __forceinline__ u64 two_level_select(KeyOf key, BktOf bkt, int n_items, int need, FastSmem<NT, BIG>& sm, int& flip,
                                                 Refine refine) {
   constexpr int UNROLL = BIG ? 1 : IPT;               // (BIG: the items are read again from memory, not held in registers)
+  int held[BIG ? 1 : IPT];                             // every item's bucket
 #pragma unroll UNROLL
   for (int j = 0; j < IPT; ++j) {
+    if (j >= n_items) break;
     const int bj = bkt(j);
+    if (!BIG) held[j] = bj;
     if (bj < 0) continue;
     if (BIG) atomicAdd(&sm.a.sel.hist[bj], 1u);
     else packed_bin_add<16>(sm.a.sel.hist, bj);
@@ -264,8 +266,14 @@ __device__ __forceinline__ u64 two_level_select(KeyOf key, BktOf bkt, int need, 
   const int r = need - below;
   if (m > kListCap) return refine(bin, r);
 #pragma unroll UNROLL
-  for (int j = 0; j < IPT; ++j)
-    if (bkt(j) == bin) sm.a.sel.cand[atomicAdd(&sm.cand_n, 1)] = key(j);
+  for (int j = 0; j < IPT; ++j) {
+    if (j >= n_items) break;
+    if ((BIG ? bkt(j) : held[j]) == bin) sm.a.sel.cand[atomicAdd(&sm.cand_n, 1)] = key(j);
+  }
+  if (m <= kWave / 2) {
+    __syncthreads();
+    return kth_of_list(sm.a.sel.cand, m, r);
+  }
   return rank_candidates<NT>(m, r, sm);
 }
 
@@ -286,12 +294,15 @@ __device__ __forceinline__ u64 pooled_victim_key(bool in_pool, float s, int stam
   const u32 asc = (x & 0x80000000u) ? ~x : (x | 0x80000000u);
   return (1ull << 63) | ((u64)asc << 24) | (u64)((~(u32)page) & 0xffffffu);
 }
-__device__ __forceinline__ int victim_bucket(long long age, int page, int NP) {
+// page_scale: 32 / NP.  (A 64-bit division here, twice for each of a thread's eight slots, took 4 of the 6.2 us that the victim
+// choice of a unit of 750 pages and 340 slots took.)
+__device__ __forceinline__ int victim_bucket(int step, int stamp, int page, float page_scale) {
   // one group of 32 buckets per age (step - stamp) below 64, split by page range; everything older
   // shares bucket 0; the newest class (age <= 1) shares bucket 2047
-  if (age >= 64) return 0;
-  if (age <= 1) return 2047;
-  return (int)(2048 - 32 * age) + (int)(((long long)page * 32) / NP);
+  const long long age = (long long)step - (long long)stamp;
+  const int in_class = (int)fminf((float)page * page_scale, 31.f);   // (monotone in the page)
+  const int a = age >= 64 ? 64 : (int)(age <= 1 ? 1 : age);
+  return a >= 64 ? 0 : a <= 1 ? 2047 : 2048 - 32 * a + in_class;
 }
 
 // Top-K selection of a unit of more pages than the ordinary form holds (see select_resolve_body for
@@ -468,7 +479,7 @@ __device__ __forceinline__ void select_big(const FastArgs& a, int u, int seq, Fa
 struct ScoresAlreadyThere { __device__ bool operator()() const { return true; } };
 struct NothingToDo { __device__ void operator()() const {} };
 template <int NT, int IPT, bool DO_SELECT, bool DO_RESOLVE, bool HANDOFF, class ScoresReady = ScoresAlreadyThere,
-          bool SEL_IN_LDS = false, bool BIG = false, bool HELD = false, class ScoresTaken = NothingToDo>
+          bool SEL_IN_LDS = false, bool BIG = false, bool HELD = false, class ScoresTaken = NothingToDo, int SLOTS = -1>
 __device__ __forceinline__ bool select_resolve_body(const FastArgs& a, int u, FastSmem<NT, BIG>& sm,
                                                     ScoresReady scores_ready = ScoresReady(), ScoresTaken scores_taken = ScoresTaken()) {
   static_assert(!(BIG && HANDOFF), "the big form is a kernel of its own");
@@ -478,7 +489,6 @@ __device__ __forceinline__ bool select_resolve_body(const FastArgs& a, int u, Fa
   constexpr int UNROLL = BIG ? 1 : CPT;                 // (BIG: slots are read again where they are needed, not held in registers)
   constexpr int KPT = KVD_MAX_TOPK / NT;
   constexpr int NW = NT / kWave;
-  constexpr int kCopyGroups = FastSmem<NT, BIG>::kCopyGroups;
   const int tid = threadIdx.x, lane = tid & (kWave - 1), w = tid / kWave;
   const int b = u / a.Hkv;
   const int k = a.k;
@@ -489,14 +499,20 @@ __device__ __forceinline__ bool select_resolve_body(const FastArgs& a, int u, Fa
   int32_t* sstamp = a.slot_stamp + (size_t)u * a.Cmax;
   int sp[BIG ? 1 : CPT], ss[BIG ? 1 : CPT];           // page in slot (-1 free, -2 no such slot), stamp (BIG: read again where needed)
   int C = 0, R = 0;
-  const int cpt = BIG ? (a.Cmax + NT - 1) / NT : CPT;  // consecutive slots per thread
+  // consecutive slots per thread: as few as hold the window, or a small window would sit in one wave, which then goes through
+  // the victim choice and the hand-out alone
+  const int cpt = (a.Cmax + NT - 1) / NT;
   if (DO_RESOLVE) {
     if constexpr (!BIG) {
 #pragma unroll
       for (int j = 0; j < CPT; ++j) {
-        const int s = tid * CPT + j;
-        sp[j] = s < a.Cmax ? spage[s] : -2;
-        ss[j] = s < a.Cmax ? sstamp[s] : 0;
+        // (slots beyond the window: -2 below)
+        const int s = tid * cpt + j;
+        sp[j] = -2;
+        ss[j] = 0;
+        if (j >= cpt) continue;
+        sp[j] = spage[s < a.Cmax ? s : a.Cmax - 1];
+        ss[j] = sstamp[s < a.Cmax ? s : a.Cmax - 1];
       }
     }
     C = a.capacity[u];
@@ -552,6 +568,7 @@ __device__ __forceinline__ bool select_resolve_body(const FastArgs& a, int u, Fa
   if (tid == 0) { sm.cand_n = 0; sm.n_ev = 0; sm.late = 0; }
   __syncthreads();
   float vs[BIG ? 1 : CPT];                             // lookahead eviction: this step's score of the page in each slot
+  int vat[BIG ? 1 : CPT];                              // ... and which score that is (-1: none)
   if constexpr (DO_RESOLVE && BIG) {
     for (int sl = tid; sl < C; sl += NT) {
       const int p = spage[sl];
@@ -560,9 +577,20 @@ __device__ __forceinline__ bool select_resolve_body(const FastArgs& a, int u, Fa
   } else if constexpr (DO_RESOLVE) {
 #pragma unroll
     for (int j = 0; j < CPT; ++j) {
-      const int sl = tid * CPT + j;
-      if (sl >= C && sp[j] != -2) sp[j] = -2;          // slots beyond this unit's capacity do not exist
+      if (j >= cpt) break;
+      const int sl = tid * cpt + j;
+      if (sl >= C) sp[j] = -2;                         // slots beyond this unit's capacity do not exist
       if (sp[j] >= 0) sm.p2s[sp[j]] = (uint16_t)sl;
+    }
+    // (without branches by lane, so that no load waits for the one before: a slot without a page reads some entry)
+    if (a.lookahead) {
+#pragma unroll
+      for (int j = 0; j < CPT; ++j) {
+        vat[j] = -1;
+        if (j >= cpt) continue;
+        vat[j] = sp[j] < 0 ? 0 : sp[j];
+        if (a.page_cluster != nullptr) vat[j] = a.page_cluster[(size_t)u * a.NP + vat[j]];
+      }
     }
   }
   int32_t* sslots = a.sel_slots + (size_t)u * k;
@@ -580,10 +608,15 @@ __device__ __forceinline__ bool select_resolve_body(const FastArgs& a, int u, Fa
     }
   }
   if constexpr (DO_RESOLVE && !BIG) {
+    if (a.lookahead) {
+      const float* sc = a.scores + (size_t)u * a.score_stride;
 #pragma unroll
-    for (int j = 0; j < CPT; ++j) {
-      vs[j] = 0.f;
-      if (a.lookahead && sp[j] >= 0) vs[j] = victim_score<HANDOFF>(a, u, sp[j]);
+      for (int j = 0; j < CPT; ++j) {
+        vs[j] = 0.f;
+        if (j >= cpt) continue;
+        const int at = vat[j] < 0 ? 0 : vat[j];
+        vs[j] = HANDOFF ? load_agent(sc + at) : sc[at];
+      }
     }
   }
 
@@ -810,11 +843,12 @@ __device__ __forceinline__ bool select_resolve_body(const FastArgs& a, int u, Fa
   };
   auto score_at = [&](int j, int page) -> float {
     if constexpr (BIG) return a.lookahead ? victim_score<HANDOFF>(a, u, page) : 0.f;
-    else return vs[j];
+    else return a.lookahead && vat[j] < 0 ? -INFINITY : vs[j];   // (a page of no cluster leaves first)
   };
   u32 cand_mask = 0;
 #pragma unroll UNROLL
-  for (int j = 0; j < cpt; ++j) {
+  for (int j = 0; j < CPT; ++j) {
+    if (j >= cpt) break;
     const int sl = tid * cpt + j;
     const bool cand = page_at(j) >= 0 && !((sm.hit_bitmap[sl >> 5] >> (sl & 31)) & 1u);
     cand_mask |= cand ? (1u << j) : 0u;
@@ -824,7 +858,8 @@ __device__ __forceinline__ bool select_resolve_body(const FastArgs& a, int u, Fa
   if (a.lookahead && e > 0) {
     float lo = INFINITY, hi = -INFINITY;
 #pragma unroll UNROLL
-    for (int j = 0; j < cpt; ++j) {
+    for (int j = 0; j < CPT; ++j) {
+      if (j >= cpt) break;
       if (!((cand_mask >> j) & 1u)) continue;
       const float v = score_at(j, page_at(j));
       if (v > -INFINITY) {                             // (a page of no cluster scores -inf: bucket 0 whatever the range)
@@ -844,6 +879,7 @@ __device__ __forceinline__ bool select_resolve_body(const FastArgs& a, int u, Fa
     vmin = lo;
     vinv = hi > lo ? 2047.0f / (hi - lo) : 0.f;
   }
+  const float page_scale = 32.f / (float)a.NP;
   auto la_bucket = [&](float v) -> int { return (int)fminf(fmaxf((v - vmin) * vinv, 0.f), 2047.f); };
   // A finite look-ahead pool: the key of the pool's last member in selection order (best page first)
   // over the unit's valid pages; a resident page is in the pool iff its key is not beyond it.
@@ -888,7 +924,7 @@ __device__ __forceinline__ bool select_resolve_body(const FastArgs& a, int u, Fa
   auto la_bkt = [&](float v, int st, int page) -> int {
     if (!pooled) return la_bucket(v);
     // the halves of the bucket range: outside the pool by age, inside by score
-    return in_pool(v, page) ? 1024 + (la_bucket(v) >> 1) : (victim_bucket((long long)a.step - (long long)st, page, a.NP) >> 1);
+    return in_pool(v, page) ? 1024 + (la_bucket(v) >> 1) : (victim_bucket(a.step, st, page, page_scale) >> 1);
   };
   auto vkey_of = [&](int j) -> u64 {
     const int st = stamp_at(j), p = page_at(j);
@@ -897,7 +933,7 @@ __device__ __forceinline__ bool select_resolve_body(const FastArgs& a, int u, Fa
   auto vbkt_of = [&](int j) -> int {
     if (!((cand_mask >> j) & 1u)) return -1;
     const int st = stamp_at(j), p = page_at(j);
-    return a.lookahead ? la_bkt(score_at(j, p), st, p) : victim_bucket((long long)a.step - (long long)st, p, a.NP);
+    return a.lookahead ? la_bkt(score_at(j, p), st, p) : victim_bucket(a.step, st, p, page_scale);
   };
   u64 vthr = 0;
   if (e > 0) {
@@ -912,13 +948,13 @@ __device__ __forceinline__ bool select_resolve_body(const FastArgs& a, int u, Fa
           kk = la_key(v, st, p);
           return true;
         }
-        if (victim_bucket((long long)a.step - (long long)st, p, a.NP) != bin) return false;
+        if (victim_bucket(a.step, st, p, page_scale) != bin) return false;
         kk = ((u64)((u32)st ^ 0x80000000u) << 32) | (u32)p;
         return true;
       };
       return block_kth_smallest<NT>(fn, C, r, sm.generic, sm.a.sel.hist);
     };
-    vthr = two_level_select<NT, CPT>(vkey_of, vbkt_of, e, sm, flip, refine);
+    vthr = two_level_select<NT, CPT>(vkey_of, vbkt_of, cpt, e, sm, flip, refine);
   }
 
   // ---- hand out slots: free slots and victim slots in ascending slot order go to the misses in
@@ -926,7 +962,8 @@ __device__ __forceinline__ bool select_resolve_body(const FastArgs& a, int u, Fa
   int avail = 0;
   u32 av_mask = 0, vic_mask = 0;
 #pragma unroll UNROLL
-  for (int j = 0; j < cpt; ++j) {
+  for (int j = 0; j < CPT; ++j) {
+    if (j >= cpt) break;
     const bool vic = e > 0 && ((cand_mask >> j) & 1u) && vkey_of(j) <= vthr;
     const bool av = page_at(j) == -1 || vic;
     vic_mask |= vic ? (1u << j) : 0u;
@@ -936,7 +973,8 @@ __device__ __forceinline__ bool select_resolve_body(const FastArgs& a, int u, Fa
   int total_avail;
   int rank = fast_scan<NT>(avail, sm, flip, total_avail);
 #pragma unroll UNROLL
-  for (int j = 0; j < cpt; ++j) {
+  for (int j = 0; j < CPT; ++j) {
+    if (j >= cpt) break;
     if ((av_mask >> j) & 1u) {
       if (rank < m) {
         sm.assign[rank] = (uint16_t)(tid * cpt + j);
@@ -985,67 +1023,72 @@ __device__ __forceinline__ bool select_resolve_body(const FastArgs& a, int u, Fa
     return true;
   }
 
-  // ---- fetch the unit's missed pages: groups of 256 threads, one 16-token tile (or one or two pages
-  // in the natural layout) each per round; packed pages by waves.  Miss j is page sm.miss[j], slot sm.assign[j].
+  // ---- fetch the unit's missed pages, miss j being page sm.miss[j] for slot sm.assign[j].  Every wave for itself, without
+  // barriers, with a batch of pieces on its way while the one before is stored: four tokens' K and V a piece, or, in natural
+  // slots, 1 KiB.  Bound by the host link, which takes 150 KB on their way to be busy (read by 8 workgroups 25 GB/s with 8 KiB
+  // of each on their way, 54 with 32; 16 workgroups 56), and for few units by its latency.  (us per step with misses, with
+  // tiles of 256 threads, two barriers and 16 KiB on their way, and so, the victim choice below included: 4 units of 1024
+  // pages of 64 tokens 56.2 and 44.3, 8 of 750 of 16 46.1 and 41.1, 8 of 4096 of 4 54.8 and 49.2, 64 of 2048 of 16 236.5 and
+  // 233.6, 32 of 8192 of 16 284.8 and 277.0.)
   __syncthreads();                                     // everyone is done with sm.a.sel
-  const int grp = tid >> 8, gt = tid & 255;
   const char* store_u = a.store + (size_t)u * a.NP * a.page_bytes;
   char* pool_u = a.pool + (size_t)u * a.Cmax * a.page_bytes;
-  if (a.tiled == kLayoutPacked) {
-    // one group of four tokens per wave and round
-    const int groups = a.P >> 2, n_items = m * groups;
-    uint16_t* vt = &sm.a.vt[0][0] + w * (4 * kHeadDim);
-    for (int it = w; it < n_items; it += NW) {
-      const int jm = it / groups, tg = it % groups;
-      const int page = (int)(sm.miss[jm] & 0xffffu);
-      const int slot = sm.assign[jm] == kAbsent ? -1 : sm.assign[jm];
-      if (slot >= 0)
-        packed_copy_group<HANDOFF>(store_u + (size_t)page * a.page_bytes, a.P, tg, pool_u + (size_t)slot * a.page_bytes, vt);
+  const int layout = SLOTS >= 0 ? SLOTS : a.tiled;
+  const int pieces = layout == kLayoutNatural ? (a.P + 1) >> 1 : a.P >> 2, n_items = m * pieces;   // (a page is P half KiB)
+  // Without branches: what is no item, or has no slot, is a buffer without bytes, whose loads and stores do nothing.  (A load
+  // under a condition was waited for at once, where its register is joined with that of the other way.)
+  struct Piece { const char* src; char* dst; u32 bytes; int piece; };
+  auto item = [&](int it) -> Piece {
+    const int at = it < n_items ? it : n_items - 1;
+    const int jm = __builtin_amdgcn_readfirstlane(at / pieces);
+    const int slot = __builtin_amdgcn_readfirstlane((int)sm.assign[jm]);
+    const u32 page = (u32)__builtin_amdgcn_readfirstlane((int)(sm.miss[jm] & 0xffffu));
+    Piece x;
+    x.bytes = it < n_items && slot != kAbsent ? a.page_bytes : 0u;
+    x.src = store_u + (size_t)page * a.page_bytes;
+    x.dst = pool_u + (size_t)slot * a.page_bytes;
+    x.piece = at - jm * pieces;
+    return x;
+  };
+  // f(batch, first item): every wave's items, a batch on its way while the one before is stored
+  auto in_batches = [&](auto& x, auto& y, int size, auto fetch, auto put) {
+    fetch(x, w);
+    for (int it = w; it < n_items; it += 2 * size * NW) {
+      fetch(y, it + size * NW);
+      put(x);
+      fetch(x, it + 2 * size * NW);
+      put(y);
     }
-  } else if (a.tiled) {
-    const int tiles = a.P / kTileTokens;
-    const int n_items = m * tiles;
-    for (int it0 = 0; it0 < n_items; it0 += kCopyGroups) {
-      const int it = it0 + grp;
-      const bool on = it < n_items;
-      int page = 0, slot = -1, tile = 0;
-      if (on) {
-        const int jm = it / tiles;
-        tile = it % tiles;
-        page = (int)(sm.miss[jm] & 0xffffu);
-        slot = sm.assign[jm] == kAbsent ? -1 : sm.assign[jm];
+  };
+  if (layout == kLayoutNatural) {
+    constexpr int kBatch = NT > 512 ? 4 : 8;             // (either way 64 KiB of a workgroup)
+    struct Batch { uint4 v[kBatch]; Piece of[kBatch]; } x, y;
+    in_batches(x, y, kBatch, [&](Batch& b, int it0) {
+#pragma unroll
+      for (int i = 0; i < kBatch; ++i) {
+        b.of[i] = item(it0 + i * NW);
+        b.v[i] = buffer_load16(b.of[i].src, b.of[i].bytes, (u32)b.of[i].piece * 1024u + (u32)lane * 16u);
       }
-      char* dst_tile = pool_u + (size_t)(slot < 0 ? 0 : slot) * a.page_bytes + (size_t)tile * kTileBytes;
-      if (on && slot >= 0) tile_copy_phase_a<HANDOFF>(store_u + (size_t)page * a.page_bytes, a.P, tile, dst_tile, sm.a.vt[grp], gt);
-      __syncthreads();
-      if (on && slot >= 0) tile_copy_phase_b<HANDOFF>(dst_tile, sm.a.vt[grp], gt);
-      __syncthreads();
-    }
-  } else if constexpr (!HANDOFF) {                      // (the one-launch step has no natural slots)
-    const unsigned units = a.page_bytes / 16;
-    auto ends = [&](int jm, const uint4*& src, uint4*& dst) -> bool {
-      if (jm >= m || sm.assign[jm] == kAbsent) return false;
-      src = reinterpret_cast<const uint4*>(store_u + (size_t)(sm.miss[jm] & 0xffffu) * a.page_bytes);
-      dst = reinterpret_cast<uint4*>(pool_u + (size_t)sm.assign[jm] * a.page_bytes);
-      return true;
-    };
-    // two pages of a group in flight where one does not give each of its threads a load, that is up to 7 tokens (us per
-    // step with one and two: 8 units of 8000 pages of 1, 2 and 3 tokens 74.3, 77.8, 76.8 and 58.2, 62.1, 64.5, of 6 and
-    // 7 tokens 70.0, 56.7 and 67.7, 55.2; units of 20000 pages and more, 6, 3 and 1 tokens 83.8, 91.8, 123.2 and 73.0,
-    // 77.3, 95.2; but with pages of 20 tokens 221.7 and 225.7)
-    const int pages = units <= 256 ? 2 : 1;
-    for (int jm = grp; jm < m; jm += pages * kCopyGroups) {
-      const uint4 *s0 = nullptr, *s1 = nullptr;
-      uint4 *d0 = nullptr, *d1 = nullptr;
-      const bool on0 = ends(jm, s0, d0), on1 = pages == 2 && ends(jm + kCopyGroups, s1, d1);
-      for (unsigned o = gt; o < units; o += 256) {
-        uint4 v0, v1;
-        if (on0) v0 = s0[o];
-        if (on1) v1 = s1[o];
-        if (on0) slot_store16<HANDOFF>(d0 + o, v0);
-        if (on1) slot_store16<HANDOFF>(d1 + o, v1);
+    }, [&](const Batch& b) {
+#pragma unroll
+      for (int i = 0; i < kBatch; ++i)
+        buffer_store16<HANDOFF>(b.of[i].dst, b.of[i].bytes, (u32)b.of[i].piece * 1024u + (u32)lane * 16u, b.v[i]);
+    });
+  } else {
+    constexpr int kBatch = NT > 512 ? 2 : 4;
+    const int tile_tokens = layout == kLayoutTiles ? kTileTokens : a.P;
+    uint16_t* vt = &sm.a.vt[w][0];
+    struct Batch { PageGroup g[kBatch]; Piece of[kBatch]; } x, y;
+    in_batches(x, y, kBatch, [&](Batch& b, int it0) {
+#pragma unroll
+      for (int i = 0; i < kBatch; ++i) {
+        b.of[i] = item(it0 + i * NW);
+        page_group_load(b.of[i].src, b.of[i].bytes, a.P, b.of[i].piece, b.g[i]);
       }
-    }
+    }, [&](const Batch& b) {
+#pragma unroll
+      for (int i = 0; i < kBatch; ++i) page_group_store<HANDOFF>(b.of[i].dst, b.of[i].bytes, tile_tokens, b.of[i].piece, vt, b.g[i]);
+    });
   }
   publish_misses();
   return true;
