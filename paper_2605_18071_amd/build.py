@@ -18,7 +18,7 @@ CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libkvd.so")
 SOURCES = ["kvd_api.hip", "kvd_select.hip", "kvd_fast.hip", "kvd_cache.hip", "kvd_attn.hip", "kvd_step.hip", "kvd_centroids.hip", "kvd_tier.hip"]
-SOURCES = [f"kvd_step_{t}_{l}_{n}.hip" for t in ("bf16", "f16") for l in ("tiles", "packed") for n in ("one", "many")] + SOURCES
+SOURCES = [f"kvd_step_{t}_{l}_{n}.hip" for t in ("bf16", "f16") for l in ("tiles", "packed", "natural") for n in ("one", "many")] + SOURCES
 FLAGS = ["--offload-arch=gfx950", "-O3", "-fPIC", "-std=c++17", "-Wall", "-Wno-unused-function",
          # keep the compiler from forming packed-fp32 VALU ops
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]

@@ -31,6 +31,11 @@ static bool kvd_wants_single_launch(const kvd_ctx* c) {
   return c->cfg.micro_batches == 0 && (c->NP <= 8192 || c->U >= 8);
 }
 
+// The same choice over natural slots.
+static bool kvd_wants_natural_launch(const kvd_ctx* c) {
+  return kvd_natural_launch_ok(c) && (c->NP <= 8192 || c->U >= 8) && (c->k + c->S_natural - 1) / c->S_natural <= 512;
+}
+
 static bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
 static int validate_config(const kvd_config* c) {
@@ -199,6 +204,7 @@ static int recover_from_wait_timeout(kvd_ctx* c) {
   c->cfg.micro_batches = 1;
   c->MB = 1;
   c->single_launch = 0;
+  c->natural_launch = 0;
   return KVD_ERR_STATE;
 }
 
@@ -267,6 +273,12 @@ int kvd_create(const kvd_config* cfg, kvd_ctx** out) {
     if (S2 > c->k) S2 = c->k;
     c->S1 = S2 < 1 ? 1 : S2;
   }
+  c->S_natural = S;
+  if (c->tiled == kvd::kLayoutNatural && cfg->attn_splits == 0) {
+    int Sn = kvd_attn_splits(kNaturalLeast, c->U, c->k, c->P, c->n_cus, true, false);
+    if (Sn < (c->k + 511) / 512) Sn = (c->k + 511) / 512;
+    c->S_natural = Sn;
+  }
   // room in the partials for the splits that kvd_set_step_shape takes and a calibration of the launch shape tries: twice
   // the rule's, with its workgroups rounded to the nearest number per CU, or twice an attention workgroup per CU with two
   // tiles per wave, or, for units of more than 8192 pages, twice a split per 64 tiles (whatever the number of units: calls
@@ -283,7 +295,7 @@ int kvd_create(const kvd_config* cfg, kvd_ctx** out) {
   if (c->S1_max > KVD_MAX_SPLITS) c->S1_max = KVD_MAX_SPLITS;
   if (c->S1_max > c->k) c->S1_max = c->k;
   if (c->S1_max < c->S1) c->S1_max = c->S1;
-  const int Smax = c->S > c->S1_max ? c->S : c->S1_max;
+  const int Smax = std::max(std::max(c->S, c->S_natural), c->S1_max);
 
   const size_t LU = (size_t)c->L * c->U;
   c->h_capacity = static_cast<int32_t*>(malloc(LU * sizeof(int32_t)));
@@ -340,7 +352,7 @@ int kvd_create(const kvd_config* cfg, kvd_ctx** out) {
   if (e == hipSuccess) ok(hipMemset(c->d_score_done, 0, (size_t)c->U * 32 * sizeof(int32_t)));
   if (e == hipSuccess) ok(hipMemset(c->d_sel_entry, 0, Uk * sizeof(unsigned long long)));
   if (e == hipSuccess) *c->error_host = 0;
-  if (e == hipSuccess) c->single_launch = kvd_wants_single_launch(c);
+  if (e == hipSuccess) { c->single_launch = kvd_wants_single_launch(c); c->natural_launch = kvd_wants_natural_launch(c); }
   if (e == hipSuccess && c->Nc > 0) ok(kvd_prepare_cluster_select());
   if (e == hipSuccess && c->Nc > 0) {
     // no page belongs to a cluster until an index is built or announced (kvd_refresh_clusters)
@@ -459,6 +471,7 @@ int kvd_bind_host_store(kvd_ctx* ctx, const void* pinned_store) {
 int kvd_bind_slot_pool(kvd_ctx* ctx, void* dev_pool) {
   if (!ctx || !dev_pool || !aligned16(dev_pool)) return KVD_ERR_ARG;
   ctx->pool = static_cast<char*>(dev_pool);
+  ctx->natural_launch = kvd_wants_natural_launch(ctx);
   return KVD_OK;
 }
 
@@ -707,7 +720,7 @@ static int step_profiled(kvd_ctx* c, int layer, int step, const void* q, float* 
 static int enqueue_step(kvd_ctx* c, int layer, int step, const void* q, float* out, float* lse, hipStream_t s, bool groups) {
   ++c->n_steps;
   c->last_scores = c->d_scores;
-  if (c->single_launch) {
+  if (c->single_launch || c->natural_launch) {
     HIP_TRY(c, kvd_launch_step(c, layer, 1, step, q, out, lse, s));
     return KVD_OK;
   }
@@ -885,6 +898,7 @@ int kvd_set_step_form(kvd_ctx* ctx, int32_t form) {
   if (ctx->MB > ctx->B) ctx->MB = ctx->B;
   HIP_TRY(ctx, ensure_group_resources(ctx, ctx->MB));
   ctx->single_launch = kvd_wants_single_launch(ctx);
+  ctx->natural_launch = kvd_wants_natural_launch(ctx);
   return KVD_OK;
 }
 
@@ -899,6 +913,8 @@ int kvd_calibrate_step_form(kvd_ctx* ctx, int32_t layer, int32_t first_step, con
   const int candidates[4] = {1, 2, 4, -1};
   const size_t q_bytes = (size_t)ctx->B * ctx->Hq * ctx->D * 2;
   hipEvent_t e0 = ctx->ev_prof[10], e1 = ctx->ev_prof[11];
+  const bool natural = ctx->natural_launch;            // (what is form 1 to the caller stays the library's choice)
+  auto set_form = [&](int form) { return kvd_set_step_form(ctx, natural && form == 1 ? 0 : form); };
   bool runs[4];
   double total_ms[4] = {0.0, 0.0, 0.0, 0.0};
   for (int ci = 0; ci < 4; ++ci)
@@ -924,7 +940,7 @@ int kvd_calibrate_step_form(kvd_ctx* ctx, int32_t layer, int32_t first_step, con
         if (r != KVD_OK) return r;
       }
       first = false;
-      r = kvd_set_step_form(ctx, candidates[ci]);
+      r = set_form(candidates[ci]);
       if (r != KVD_OK) return r;
       for (int i = 0; i <= steps_per_form; ++i) {
         if (i == 1) HIP_TRY(ctx, hipEventRecord(e0, s));
@@ -948,7 +964,7 @@ int kvd_calibrate_step_form(kvd_ctx* ctx, int32_t layer, int32_t first_step, con
     if (runs[ci] && (best_ms < 0.0 || ms < best_ms)) { best_ms = ms; best = candidates[ci]; }
   }
   *chosen_form = best;
-  return kvd_set_step_form(ctx, best);
+  return set_form(best);
 }
 
 int kvd_set_step_shape(kvd_ctx* ctx, int32_t multi_layer, int32_t passes, int32_t scoring_workgroups, int32_t attn_splits,

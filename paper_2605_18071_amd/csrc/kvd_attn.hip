@@ -81,8 +81,9 @@ static bool dispatch_group(int G, int layout, const AttnArgs& a, dim3 grid, hipS
 // launch, 24 units of 2048 pages S = 11, 10 and 9 23.3, 20.2 and 19.7, 40 of 363 6, 6 and 5 18.3, 18.3 and 17.2, 56 of 2969
 // 5, 4 and 3 39.1, 33.5 and 34.8, 96 of 1250 3, 2 and 1 38.5, 33.1 and 38.2; 32 of 1001 8, 8 and 7 20.2, 20.2 and 19.8, but per layer
 // of 8 layers x 16 units of 1024 pages 7.6 with 16 and 8.5 with 15, of 3 x 32 of 2048 14.6 with 8 and 16.0 with 7 (contexts of
-// one layer keep 8 and 16 too, and lose 2 % by it); over natural slots 24 units x 53 pages of 24 tokens 25.5 with 11 and 23.6
-// with 10, 96 x 102 pages of 20 49.4 with 3 and 41.0 with 2.  But
+// one layer keep 8 and 16 too, and lose 2 % by it); over natural slots, where a workgroup takes one split also in launches of several layers, so that 8 and 16 are
+// nothing special (dealt_out false), 24 units x 53 pages of 24 tokens 25.5 with 11 and 23.6
+// with 10, 32 x 85 of 24 24.3 with 8 and 23.7 with 7, 96 x 102 pages of 20 49.4 with 3 and 41.0 with 2.  But
 //  - a split keeps at least `least` tiles of 16 tokens for its eight waves: 16 in the stand-alone kernel over tiles (where
 //    fewer made no difference), 8 in the one-launch step with pages of up to 16 tokens and at least 32 tiles (8 units
 //    of 64 pages: 16.7 us with two tiles per wave, 15.9 with one; 2 splits instead of 1 gain nothing, and with larger
@@ -96,10 +97,10 @@ static bool dispatch_group(int G, int layout, const AttnArgs& a, dim3 grid, hipS
 //    splits and with 18 tiles each where there is less room: 9 units of 320 19.8 and 20.2, of 512 22.3 and 22.1, 10 of 512 22.9
 //    and 23.2, 12 of 448 22.6 and 23.3, 14 of 576 25.7 and 26.5;
 //  - no split is left without pages.
-int kvd_attn_splits(int least, int U, int k, int P, int cus, bool beside_selection) {
+int kvd_attn_splits(int least, int U, int k, int P, int cus, bool beside_selection, bool dealt_out) {
   const int tiles = (k * P + 15) / 16;                 // of a unit's selection
   int S = cus / U;
-  if (beside_selection && S >= 5 && S % 8 != 0) S = (cus - U) / U;
+  if (beside_selection && S >= 5 && !(dealt_out && S % 8 == 0)) S = (cus - U) / U;
   if (S > tiles / least) S = tiles / least;
   int longest = tiles / 32;
   if (cus / U >= 32 && longest < 32) longest = tiles / 18 < 32 ? tiles / 18 : 32;

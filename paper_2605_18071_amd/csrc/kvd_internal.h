@@ -45,6 +45,7 @@ struct kvd_ctx {
   int L, B, Hq, Hkv, G, D, P, NP, k, Cmax, Lp, U, MB, S;
   int S1;                  // attention split-K factor of the one-launch step as kvd_create chose it (S: of the stand-alone kernel)
   int S1_max;              // the largest split factor the partials were allocated for
+  int S_natural;           // ... and over natural slots
   kvd_shape shape[2];      // launch shape of the one-launch step as set or calibrated, 0 = left to the rule:
                            // [0] launches of one layer (kvd_step), [1] launches of several layers (kvd_step_layers)
   int Nc;                  // centroids per unit of the hierarchical index, 0 = flat page index
@@ -52,7 +53,8 @@ struct kvd_ctx {
   int score_blocks;        // target number of blocks of a scoring launch
   int generic_select;      // force the size-agnostic select / resolve kernels (testing)
   int fuse_merge;          // attention: last split workgroup merges (1) or a second kernel does (0)
-  int single_launch;       // kvd_step runs as one kernel launch
+  int single_launch;       // kvd_step runs as one kernel launch (form -1)
+  int natural_launch;      // so it does over natural slots, by the library's choice (form 0)
   int tiled;               // slot layout (kvd_tile_layout.h): 0 natural, 1 16-token tiles (page size a multiple of 16), 2 packed (pages of 4 or 8 tokens)
   float scale;
   size_t page_bytes;
@@ -150,9 +152,10 @@ hipError_t kvd_launch_attend(kvd_ctx* c, int layer, const void* q, const int32_t
                              const int32_t* sel_slots, float* out, float* lse, int u0, int u1, hipStream_t s,
                              hipEvent_t between = nullptr);   // `between`: recorded after the attention kernel, before the merge
 constexpr int kNaturalLeast = 4;            // `least` of kvd_attn_splits over natural slots
-int kvd_attn_splits(int least, int U, int k, int P, int cus, bool beside_selection = false);
+int kvd_attn_splits(int least, int U, int k, int P, int cus, bool beside_selection = false, bool dealt_out = true);
 // The whole step as one launch (kvd_step.hip); usable when kvd_single_launch_ok.
 bool kvd_single_launch_ok(const kvd_ctx* c);
+bool kvd_natural_launch_ok(const kvd_ctx* c);
 bool kvd_layers_share_launch(const kvd_ctx* c);
 // The shape a launch takes: `want` (default: what the context holds for that kind of launch) with
 // its zeros filled in by the rule and the scoring workgroups capped at the number of chunks.  n_layers: layers of the

@@ -75,6 +75,19 @@ bool kvd_step_shape_ok(const kvd_ctx* c, const kvd_shape& e) {
   return true;
 }
 
+// Over natural slots (pages of a size that is neither a multiple of 16 nor 4 or 8) the library's own choice of form runs a
+// step as one launch too.  Such a context takes no form -1 and no launch shape: it goes by the rule.  Three
+// launches were three chains of latencies (us per step as a chain and so: 32 units x 2084 pages of 24 tokens, G = 7, 28.3 and 23.7,
+// 8 x 500 of 100 24.9 and 22.2, 112 x 250 of 20 36.8 and 33.5, 8 units of 10417 26.6 and 26.4; with misses 32 x 750 of 12 73.6 and
+// 70.3, 8 x 1000 of 20 51.3 and 47.1, but 8 x 2000 of 6 43.7 and 44.4; per launch of 8 layers of 16 x 375 of 24 124.7 and 81.9,
+// of 4 layers of 2 x 10417 77.9 and 25.9).
+// (Where the pool starts in the middle of a cache line two slots share one, and a slot that is being filled must not be
+// cached with its neighbour.)
+bool kvd_natural_launch_ok(const kvd_ctx* c) {
+  return c->tiled == kvd::kLayoutNatural && c->cfg.micro_batches == 0 && kvd_fast_path_ok(c) && !kvd_fast_path_big(c) &&
+         (reinterpret_cast<uintptr_t>(c->pool) & 127u) == 0;
+}
+
 bool kvd_single_launch_ok(const kvd_ctx* c) {
   return kvd_fast_path_ok(c) && !kvd_fast_path_big(c) && c->tiled &&
          (c->k + c->S1 - 1) / c->S1 <= kvd::kAttnIdxCap;   // a split's entries are staged in LDS
@@ -84,7 +97,8 @@ bool kvd_single_launch_ok(const kvd_ctx* c) {
 // the few units above, two chains of kernels in flight and one launch: 7 layers of 8 units of 10109 pages 19.3 and 11.2, 4
 // layers of 4 units of 12500 20.0 and 9.3).
 bool kvd_layers_share_launch(const kvd_ctx* c) {
-  return c->single_launch || (c->cfg.micro_batches == 0 && kvd_single_launch_ok(c) && (c->k + c->S - 1) / c->S <= kvd::kAttnIdxCap);
+  return c->single_launch || c->natural_launch ||
+         (c->cfg.micro_batches == 0 && (kvd_single_launch_ok(c) || kvd_natural_launch_ok(c)) && (c->k + c->S - 1) / c->S <= kvd::kAttnIdxCap);
 }
 
 // How many of a unit's splits an attention workgroup of a launch of several layers takes.  The layers fill each other's gaps
@@ -135,12 +149,15 @@ hipError_t kvd_launch_step(kvd_ctx* c, int layer, int n_layers, int step, const 
   a.at = kvd_attn_args(c, layer, q, c->d_sel_pages, c->d_sel_slots, out, lse, 0);
   a.at.fuse_merge = 1;
   a.at.sel_entry = c->d_sel_entry;
-  const kvd_shape shape = kvd_step_shape(c, n_layers > 1, nullptr, n_layers);
+  const bool natural = c->tiled == kLayoutNatural;
+  const kvd_shape by_rule = {0, 0, 0, 0};
+  kvd_shape shape = kvd_step_shape(c, n_layers > 1, natural ? &by_rule : nullptr, n_layers);
+  if (natural) shape.splits = c->natural_launch ? c->S_natural : c->S;   // (layers that step one by one as a chain: its splits)
   a.at.S = shape.splits;
   a.at.per_split = (c->k + shape.splits - 1) / shape.splits;
   // (the rule's number of splits, whether it was left to the rule or set: a shape that a context reports gives the same launch
   // when it is set; any other number that the caller has set stays as it is)
-  a.at.take = n_layers > 1 && shape.splits == rule_splits(c, 1) ? kvd_step_take(c, shape.splits, n_layers) : 1;
+  a.at.take = n_layers > 1 && !natural && shape.splits == rule_splits(c, 1) ? kvd_step_take(c, shape.splits, n_layers) : 1;
   a.score_done = c->d_score_done;
   a.error = c->error_dev;
   a.timeline = nullptr;
@@ -192,14 +209,16 @@ hipError_t kvd_launch_step(kvd_ctx* c, int layer, int n_layers, int step, const 
   c->tl_workgroups = n_blocks;
   if (c->profiling == 2 && n_blocks <= KVD_TIMELINE_MAX) a.timeline = c->d_timeline;
   const int ipt = (c->NP + chunk_pages - 1) / chunk_pages;
-  const bool packed = c->tiled == kLayoutPacked;
-  auto launch = [&](auto bf16, auto pk) {
-    if (n_layers > 1) launch_step<decltype(bf16)::value, decltype(pk)::value, true>(ipt, a, n_blocks, s);
-    else launch_step<decltype(bf16)::value, decltype(pk)::value, false>(ipt, a, n_blocks, s);
+  auto launch = [&](auto bf16, auto layout) {
+    if (n_layers > 1) launch_step<decltype(bf16)::value, decltype(layout)::value, true>(ipt, a, n_blocks, s);
+    else launch_step<decltype(bf16)::value, decltype(layout)::value, false>(ipt, a, n_blocks, s);
   };
-  const std::true_type yes;
-  const std::false_type no;
-  if (c->bf16) { if (packed) launch(yes, yes); else launch(yes, no); }
-  else { if (packed) launch(no, yes); else launch(no, no); }
+  auto by_layout = [&](auto bf16) {
+    if (c->tiled == kLayoutPacked) launch(bf16, std::integral_constant<int, kLayoutPacked>());
+    else if (c->tiled == kLayoutTiles) launch(bf16, std::integral_constant<int, kLayoutTiles>());
+    else launch(bf16, std::integral_constant<int, kLayoutNatural>());
+  };
+  if (c->bf16) by_layout(std::true_type());
+  else by_layout(std::false_type());
   return hipGetLastError();
 }

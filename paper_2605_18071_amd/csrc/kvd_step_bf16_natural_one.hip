@@ -1,0 +1,3 @@
+#include "kvd_step_launch.h"
+
+template void kvd::launch_step<true, kvd::kLayoutNatural, false>(int, const StepArgs&, int, hipStream_t);

@@ -1,3 +1,3 @@
 #include "kvd_step_launch.h"
 
-template void kvd::launch_step<true, true, true>(int, const StepArgs&, int, hipStream_t);
+template void kvd::launch_step<true, kvd::kLayoutPacked, true>(int, const StepArgs&, int, hipStream_t);

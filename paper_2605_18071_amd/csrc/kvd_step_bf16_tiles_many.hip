@@ -1,3 +1,3 @@
 #include "kvd_step_launch.h"
 
-template void kvd::launch_step<true, false, true>(int, const StepArgs&, int, hipStream_t);
+template void kvd::launch_step<true, kvd::kLayoutTiles, true>(int, const StepArgs&, int, hipStream_t);

@@ -160,7 +160,7 @@ __device__ __forceinline__ void step_score_role(StepArgsPtr ap, int li, int u0, 
 
 // Selection, directory update and fetch of unit u: latency-bound, so its waves go first whenever
 // they can issue.
-template <int NT, int IPT>
+template <int NT, int IPT, int LAYOUT>
 __device__ __forceinline__ void step_select_role(StepArgsPtr ap, int li, int u, unsigned char* smem_raw, int* wait_ok,
                                                            long long* ts) {
   struct { FastArgs fa; int32_t* score_done; int32_t* error; long long wait_limit; int chunks; } a;
@@ -210,10 +210,10 @@ __device__ __forceinline__ void step_select_role(StepArgsPtr ap, int li, int u, 
       __syncthreads();                                 // the selection is complete
       return true;
     };
-    done = select_resolve_body<NT, 4, false, true, true, decltype(select_clusters), true>(a.fa, u, sm, select_clusters);
+    done = select_resolve_body<NT, 4, false, true, true, decltype(select_clusters), true, false, false, NothingToDo, LAYOUT>(a.fa, u, sm, select_clusters);
   } else {
     auto scores_ready = [&]() -> bool { return wave_wait_equal(&a.score_done[u * kFlagStride], arrivals, a.wait_limit); };
-    done = select_resolve_body<NT, IPT, true, true, true, decltype(scores_ready), false, false, false, decltype(scores_taken)>(
+    done = select_resolve_body<NT, IPT, true, true, true, decltype(scores_ready), false, false, false, decltype(scores_taken), LAYOUT>(
         a.fa, u, sm, scores_ready, scores_taken);
   }
   if (!done) {
@@ -224,7 +224,7 @@ __device__ __forceinline__ void step_select_role(StepArgsPtr ap, int li, int u, 
 }
 
 // Attention workgroup (u, split): `take` splits from `split` on.
-template <bool BF16, int NT, bool PACKED, bool SEVERAL>
+template <bool BF16, int NT, int LAYOUT, bool SEVERAL>
 __device__ __forceinline__ void step_attend_role(StepArgsPtr ap, int li, int u, int split, int take, unsigned char* smem_raw, long long* ts) {
   struct { AttnArgs at; } a;
   __builtin_memcpy(&a.at, &ap->at, sizeof(AttnArgs));
@@ -240,18 +240,19 @@ __device__ __forceinline__ void step_attend_role(StepArgsPtr ap, int li, int u, 
   }
   if (ts) ts[4] = 2LL | ((long long)u << 8) | ((long long)split << 32);
   typename StepSmem<NT>::Attn& sm = *reinterpret_cast<typename StepSmem<NT>::Attn*>(smem_raw);
-  const int done = attend_mfma_body<BF16, 0, NT, true, PACKED ? kLayoutPacked : kLayoutTiles, SEVERAL>(a.at, sm, u, split, ts ? ts + 1 : nullptr);
+  const int done = attend_mfma_body<BF16, 0, NT, true, LAYOUT, SEVERAL>(a.at, sm, u, split, ts ? ts + 1 : nullptr);
   if (done < 0 && threadIdx.x == 0) __hip_atomic_store(a.at.error, 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   if (ts) ts[2] = ts[3] = wall_clock64();
 }
 
-template <bool BF16, int NT, int IPT, bool PACKED, bool MANY>
+template <bool BF16, int NT, int IPT, int LAYOUT, bool MANY>
 __device__ __forceinline__ void step_body(StepArgsPtr ap, unsigned char* smem_raw, int& wait_ok) {
   const int bid = blockIdx.x;
   long long* timeline = ap->timeline;
   long long* ts = timeline != nullptr && threadIdx.x == 0 ? timeline + (size_t)bid * 5 : nullptr;
   if (ts) { ts[0] = ts[1] = ts[2] = ts[3] = wall_clock64(); ts[4] = 3LL; }   // (role 3: a workgroup beyond its group's units, which leaves at once)
   const int n_score = ap->n_score, S = ap->at.S, groups = ap->groups, Ug = ap->group_units;
+  constexpr bool kSeveral = MANY && LAYOUT != kLayoutNatural;   // (over natural slots a workgroup takes one split)
   const int n_stages = (MANY ? ap->n_layers : 1) * groups;          // (layer, group) pairs, in order
   const int front = n_score + Ug;
   // block order: front(0) | front(1) back(0) | front(2) back(1) | ... | back(n-1), where front(i) =
@@ -260,7 +261,7 @@ __device__ __forceinline__ void step_body(StepArgsPtr ap, unsigned char* smem_ra
   bool is_back = false;
   if (bid >= front) {
     int r = bid - front, first = 0;
-    if (MANY) {
+    if (kSeveral) {
       // all stages but the last few: several splits to a workgroup
       const int whole = n_stages - ap->tail_stages, t = ap->at.take, n = (S + t - 1) / t, blocks = whole * (front + Ug * n);
       if (r < blocks) { take = t; wgs = n; } else { r -= blocks; first = whole; }
@@ -278,27 +279,27 @@ __device__ __forceinline__ void step_body(StepArgsPtr ap, unsigned char* smem_ra
   int n_units = ap->n_units - gi * Ug;                  // units of this group
   n_units = n_units < Ug ? n_units : Ug;
   if (is_back) {
-    if (o / wgs < n_units) step_attend_role<BF16, NT, PACKED, MANY>(ap, li, o / wgs + u0, (o % wgs) * take, take, smem_raw, ts);
+    if (o / wgs < n_units) step_attend_role<BF16, NT, LAYOUT, kSeveral>(ap, li, o / wgs + u0, (o % wgs) * take, take, smem_raw, ts);
   } else if (o < n_score) {
     step_score_role<BF16, NT>(ap, li, u0, n_units, o, smem_raw, ts);
   } else {
-    if (o - n_score < n_units) step_select_role<NT, IPT>(ap, li, o - n_score + u0, smem_raw, &wait_ok, ts);
+    if (o - n_score < n_units) step_select_role<NT, IPT, LAYOUT>(ap, li, o - n_score + u0, smem_raw, &wait_ok, ts);
   }
 }
 
 // PACKED: pages of 4 or 8 tokens.  MANY: a launch of
 // several layers; a kernel of its own, since what only such a launch needs (a layer's strides, attention workgroups that take
 // several splits) costs a launch of one layer 0.6 to 1 us (8 units of 256 pages 13.6 and 14.2, 128 of 2048 43.5 and 44.5).
-template <bool BF16, int NT, int IPT, bool PACKED, bool MANY>
+template <bool BF16, int NT, int IPT, int LAYOUT, bool MANY>
 __global__ __launch_bounds__(NT, 2) void step_kernel(StepArgs a) {
   __shared__ __align__(16) unsigned char smem_raw[StepSmem<NT>::bytes];
   __shared__ int wait_ok;
   // the launch arguments are the first thing in the kernel-argument segment
-  step_body<BF16, NT, IPT, PACKED, MANY>((StepArgsPtr)__builtin_amdgcn_kernarg_segment_ptr(), smem_raw, wait_ok);
+  step_body<BF16, NT, IPT, LAYOUT, MANY>((StepArgsPtr)__builtin_amdgcn_kernarg_segment_ptr(), smem_raw, wait_ok);
 }
 
 // Defined in a source file each (kvd_step_*.hip), since each takes the compiler half a minute.
-template <bool BF16, bool PACKED, bool MANY>
+template <bool BF16, int LAYOUT, bool MANY>
 void launch_step(int ipt, const StepArgs& a, int n_blocks, hipStream_t s);
 
 }  // namespace kvd

@@ -1,3 +1,3 @@
 #include "kvd_step_launch.h"
 
-template void kvd::launch_step<false, false, false>(int, const StepArgs&, int, hipStream_t);
+template void kvd::launch_step<false, kvd::kLayoutTiles, false>(int, const StepArgs&, int, hipStream_t);

@@ -1,0 +1,97 @@
+"""Pages kept in natural order (sizes that are neither 4, 8 nor a multiple of 16): with the choice of form left to the library
+the step is one launch.  It is compared with the chain of kernels, whose stages the oracle checks."""
+import pytest
+import torch
+
+from paper_2605_18071_amd import kvd as K
+from paper_2605_18071_amd import workloads as W
+from tests.test_gpu_parity import small
+
+pytestmark = pytest.mark.gpu
+
+if torch.cuda.is_available():
+    from tests import gpu_rig as R
+
+
+def fresh(w, seq, mb):
+    return R.Rig(w, seq_lens=seq, micro_batches=mb)
+
+
+@pytest.mark.parametrize("page,pages,k,kw", [
+    (1, 700, 520, dict()),                                             # more entries than one split stages
+    (2, 2049, 60, dict(dtype="f16")),                                  # two pages to a KiB piece of the copy
+    (3, 300, 17, dict(sink_pages=1, recent_pages=2)),                  # a page ends in half a piece
+    (12, 513, 33, dict(n_q_heads=14, policy="lookahead")),
+    (24, 400, 85, dict(dtype="f16", n_q_heads=14, sink_pages=2, recent_pages=4)),
+    (33, 90, 20, dict(policy="lookahead", lookahead_pool=25)),
+    (20, 600, 40, dict(index_centroids=70)),
+    (255, 40, 5, dict()),
+    (6, 8200, 30, dict(batch=5)),                                      # 10 units of more than 8192 pages
+])
+def test_equals_the_chain(page, pages, k, kw):
+    w = small("natural-launch", **{**dict(ctx=page * pages, page=page, topk_pages=k, capacity=k + k // 2 + 2, batch=3, n_kv_heads=2, n_q_heads=4,
+                                          heavy_count=3, steps=5, rho=0.5), **kw})
+    seq = [max(1, w.ctx - page // 2 - b * (w.ctx // 3)) for b in range(w.batch)]
+    one, chain = fresh(w, seq, 0), fresh(w, seq, 1)
+    misses = 0
+    for t, q in enumerate(W.query_stream(w, one.q0, w.steps, R.DEV)):
+        one.out.fill_(float("nan"))
+        one.step(0, t, q[0])
+        chain.step(0, t, q[0])
+        misses += int(chain.n_counts[:, 1].sum())
+        for what in ("sel_pages", "sel_slots", "hit_mask", "counts"):
+            assert torch.equal(getattr(one, what), getattr(chain, what)), (what, t)
+        # 24 bits of P and fp32 sums in both, in another order where the splits differ
+        assert float((one.out - chain.out).norm() / chain.out.norm()) < 1e-6
+        assert float((one.lse - chain.lse).abs().max()) < 1e-4
+    assert misses > 0 and torch.equal(one.pool, chain.pool)
+    one.close()
+    chain.close()
+
+
+@pytest.mark.parametrize("layers,pages,kw", [(5, 300, dict()), (3, 8300, dict(batch=1, n_kv_heads=2)), (10, 60, dict(dtype="f16", page=12))])
+def test_layers_in_a_launch_equal_layers_one_by_one(layers, pages, kw):
+    """Bit for bit; 3 layers of two units of 8300 pages step one by one as a chain, whose splits the shared launch has."""
+    w = small("natural-layers", **{**dict(page=6, topk_pages=25, capacity=37, batch=3, n_kv_heads=2, n_q_heads=4, heavy_count=3, steps=4,
+                                          n_layers=layers, physical_layers=2, rho=0.5), **kw})
+    w = w.replace(ctx=w.page * pages)
+    seq = [w.ctx - 5 * b for b in range(w.batch)]
+    one, together = fresh(w, seq, 0), fresh(w, seq, 0)
+    shape = (layers, w.batch, w.n_q_heads, w.head_dim)
+    a, b = (torch.empty(shape, dtype=torch.float32, device=R.DEV) for _ in range(2))
+    for t, q in enumerate(W.query_stream(w, one.q0, w.steps, R.DEV)):
+        b.fill_(float("nan"))
+        for l in range(layers):
+            one.kvd.step(l, t, q[l], a[l])
+        together.kvd.step_layers(0, layers, t, q, b)
+        torch.cuda.synchronize()
+        assert torch.equal(a, b), t
+    assert torch.equal(one.pool, together.pool)
+    one.close()
+    together.close()
+
+
+def test_a_pool_that_starts_inside_a_cache_line_and_a_wait_that_runs_out():
+    """Slots that share cache lines take the chain, which has no waits; elsewhere a wait that runs out is reported once and
+    the context goes on as a chain."""
+    w = small("natural-limits", page=12, ctx=12 * 300, topk_pages=40, capacity=60, batch=2, n_kv_heads=2, n_q_heads=4, steps=3)
+    rig, shifted, chain = fresh(w, [w.ctx] * 2, 0), fresh(w, [w.ctx] * 2, 0), fresh(w, [w.ctx] * 2, 1)
+    room = torch.zeros(rig.pool.numel() + 64, dtype=w.torch_dtype, device=R.DEV)
+    shifted.kvd.bind_slot_pool(room[8:8 + rig.pool.numel()].view(rig.pool.shape))
+    for r in (rig, shifted, chain):
+        r.kvd.set_wait_limit_us(0)
+    qs = list(W.query_stream(w, rig.q0, w.steps, R.DEV))
+    for t, q in enumerate(qs):
+        shifted.step(0, t, q[0])
+        chain.step(0, t, q[0])
+        assert torch.equal(shifted.sel_slots, chain.sel_slots) and torch.equal(shifted.out, chain.out)
+    rig.kvd.step(0, 0, qs[0][0], rig.out, rig.lse)
+    torch.cuda.synchronize()
+    with pytest.raises(K.KvdError):
+        rig.kvd.step(0, 0, qs[0][0], rig.out, rig.lse)
+    for t, q in enumerate(qs):
+        rig.step(0, t, q[0])
+        chain.step(0, t + 3, q[0])
+        assert torch.equal(rig.sel_pages, chain.sel_pages) and torch.equal(rig.out, chain.out)
+    for r in (rig, shifted, chain):
+        r.close()
