@@ -106,7 +106,7 @@ struct FastSmem {
   float2 red[NW];                                        // extremes over the waves
   int red_cnt[NW];
   u64 thr;
-  int cand_n, bin, below, n_ev, late;
+  int cand_n, tied_n, bin, below, n_ev, late;
   SelectSmem generic;
 };
 
@@ -459,6 +459,205 @@ __device__ __forceinline__ void select_big(const FastArgs& a, int u, int seq, Fa
   }
 }
 
+// The same for units whose scores the registers hold (NP <= 32 NT), by quads of four consecutive pages: as many quads as pages
+// are wanted have their best page at or before some bucket, so that the decisive bucket is no later; the quads that reach it,
+// hardly more than pages are wanted, are listed and dealt out to the threads again, and only their pages are counted, compared and
+// ranked.  Bound by instruction issue (16 waves on one CU: 100 instructions a thread are 0.7 us), of which the three passes of
+// select_big need about 30 a page and this 3 a page and 20 a quad.  The selected pages are written from a map with four bits to
+// a quad's byte, 32 pages a thread, in one block scan instead of a wave scan per load.  False, with nothing done but
+// sm.a.sel.hist and sm.cand_n used, where more quads than the list holds reach the bucket (many pages alike): select_big then.
+template <int NT>
+__device__ __forceinline__ void select_held_load(const FastArgs& a, int u, int seq, float4 (&s)[8]) {
+  const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
+  int n_valid = (seq + a.P - 1) / a.P;
+  n_valid = n_valid < a.NP ? n_valid : a.NP;
+  const float* sc = a.scores + (size_t)u * a.NP;
+  const int nq = (n_valid + 4 * NT - 1) / (4 * NT);
+  const int p0 = w * (4 * kWave) * nq + 4 * lane;
+  if ((a.NP & 3) == 0) {
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(sc), 0, a.NP * 4, 0x00020000);
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      const u32x4_t v = __builtin_amdgcn_raw_buffer_load_b128(rs, q < nq ? (p0 + q * (4 * kWave)) * 4 : 0, 0, 0);
+      s[q] = make_float4(as_f32(v.x), as_f32(v.y), as_f32(v.z), as_f32(v.w));
+    }
+  } else {
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      float x[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int p = p0 + q * (4 * kWave) + e;
+        x[e] = sc[q < nq && p < a.NP ? p : a.NP - 1];
+      }
+      s[q] = make_float4(x[0], x[1], x[2], x[3]);
+    }
+  }
+}
+template <int NT>
+__device__ __forceinline__ bool select_held(const FastArgs& a, int u, int seq, const float4 (&s)[8], FastSmem<NT, true>& sm, int& flip) {
+  typedef FastSmem<NT, true> Smem;
+  constexpr int NW = NT / kWave, Q = 8, kQuads = 2 * NT;   // quads of a lane, quads of the list
+  constexpr int kHeldPages = 4 * Q * NT;
+  // the upper half of the page -> slot map is not in use: the list and the map of the selection
+  struct Lists { float4 score[kQuads]; int quad[kQuads]; unsigned char picked[kHeldPages / 4]; };
+  static_assert(sizeof(Lists) <= sizeof(uint16_t) * (Smem::kMaxPages - kHeldPages), "room behind the map of this many pages");
+  Lists& ls = *reinterpret_cast<Lists*>(sm.p2s + kHeldPages);
+  u32* hist_quads = sm.a.sel.hist;
+  u32* hist_pages = sm.a.sel.hist + kRadixBins / 2;
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), w = tid / kWave, k = a.k;
+  int n_valid = (seq + a.P - 1) / a.P;
+  n_valid = n_valid < a.NP ? n_valid : a.NP;
+  const int k_eff = k < n_valid ? k : n_valid;
+  const int recent_from = n_valid - a.recent;
+  const int n_free = recent_from > a.sink ? recent_from - a.sink : 0;
+  const int k_free = k_eff - (n_valid - n_free);
+  const int free_quads = n_free > 0 ? (recent_from + 3) / 4 - a.sink / 4 : 0;   // with a free page
+  const float* sc = a.scores + (size_t)u * a.NP;
+  const int nq = (n_valid + 4 * NT - 1) / (4 * NT);
+  const int wave_p0 = w * (4 * kWave) * nq;
+  // bits of the four pages from p on below `bound`
+  auto upto = [&](int p, int bound) -> u32 {
+    const int n = bound - p;
+    return (1u << (n < 0 ? 0 : (n > 4 ? 4 : n))) - 1u;
+  };
+  auto free_of = [&](int p) -> u32 { return upto(p, recent_from) & ~upto(p, a.sink); };
+  auto page_of = [&](int q) -> int { return wave_p0 + q * (4 * kWave) + 4 * lane; };
+  float best[Q], fmin = INFINITY, fmax = -INFINITY;
+  u32 first = 0;                                         // bit q: in the first bucket
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    const u32 fr = q < nq ? free_of(page_of(q)) : 0u;
+    const float x0 = fr & 1u ? s[q].x : -INFINITY, x1 = fr & 2u ? s[q].y : -INFINITY, x2 = fr & 4u ? s[q].z : -INFINITY,
+                x3 = fr & 8u ? s[q].w : -INFINITY;
+    const float sum = (x0 + x1) + (x2 + x3);
+    best[q] = fmaxf(fmaxf(x0, x1), fmaxf(x2, x3));
+    fmax = fmaxf(fmax, best[q]);
+    fmin = fminf(fmin, best[q] > -INFINITY ? best[q] : INFINITY);
+    // (a page that is no number is in the first bucket, and so is its quad; where the sum is none because of two infinities
+    // all pages are in the first bucket)
+    first |= sum != sum ? 1u << q : 0u;
+    if (q < nq) ls.picked[page_of(q) >> 2] = (unsigned char)(upto(page_of(q), n_valid) & ~fr);   // the forced pages
+  }
+  fmin = wave_allreduce_min(fmin);
+  fmax = wave_allreduce_max(fmax);
+  if (lane == 0) sm.red[w] = make_float2(fmin, fmax);
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < NW; ++i) {
+    fmin = fminf(fmin, sm.red[i].x);
+    fmax = fmaxf(fmax, sm.red[i].y);
+  }
+  if (k_free > 0) {
+    const float range = fmax - fmin;
+    const float inv = range > 0.f ? 2047.0f / range : 0.f;
+    auto bucket_of = [&](float v) -> int { return (int)fminf(fmaxf((fmax - v) * inv, 0.f), 2047.f); };
+    int bk[Q];
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      bk[q] = q < nq && free_of(page_of(q)) ? ((first >> q) & 1u ? 0 : bucket_of(best[q])) : 2048;
+      if (bk[q] < 2048) packed_bin_add<16>(hist_quads, bk[q]);
+    }
+    __syncthreads();
+    int last = 2047, n_listed = free_quads;              // the quads up to bucket `last` are listed
+    if (k_free <= free_quads) {
+      int before, in_last;
+      packed_bin_find<16>(hist_quads, k_free, last, before, in_last);
+      n_listed = before + in_last;
+    }
+    if (n_listed > kQuads) return false;
+    int mine = 0;
+#pragma unroll
+    for (int q = 0; q < Q; ++q) mine += bk[q] <= last ? 1 : 0;
+    const int inc = wave_inclusive_scan(mine);
+    int at = 0;
+    if (lane == kWave - 1) at = atomicAdd(&sm.cand_n, inc);
+    at = __builtin_amdgcn_readlane(at, kWave - 1) + inc - mine;
+#pragma unroll
+    for (int q = 0; q < Q; ++q)
+      if (bk[q] <= last) {
+        ls.score[at] = s[q];
+        ls.quad[at++] = page_of(q) >> 2;
+      }
+    __syncthreads();
+    // the listed quads, up to two a thread
+    float v[8];
+    int quad[2], pb[8];                                  // pages' buckets, 2048 = takes no part
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const bool on = tid + i * NT < n_listed;
+      quad[i] = on ? ls.quad[tid + i * NT] : -1;
+      const float4 x = on ? ls.score[tid + i * NT] : make_float4(0.f, 0.f, 0.f, 0.f);
+      const u32 fr = on ? free_of(4 * quad[i]) : 0u;
+      v[4 * i] = x.x; v[4 * i + 1] = x.y; v[4 * i + 2] = x.z; v[4 * i + 3] = x.w;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int j = 4 * i + e, bj = (fr >> e) & 1u ? bucket_of(v[j]) : 2048;
+        pb[j] = bj <= last ? bj : 2048;
+        if (pb[j] < 2048) packed_bin_add<16>(hist_pages, pb[j]);
+      }
+    }
+    __syncthreads();
+    int bin, below, m;
+    packed_bin_find<16>(hist_pages, k_free, bin, below, m);
+    const int r = k_free - below;                        // of the m pages of the decisive bucket r are in
+    auto key_of = [&](int j) -> u64 { return selection_order_key(v[j], 4 * quad[j >> 2] + (j & 3)); };
+    u64 thr = ~0ull;
+    if (r < m) {
+      if (m <= kListCap) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+          if (pb[j] == bin) sm.a.sel.cand[atomicAdd(&sm.tied_n, 1)] = key_of(j);
+        if (m <= kWave / 2) {
+          __syncthreads();
+          thr = kth_of_list(sm.a.sel.cand, m, r);
+        } else {
+          thr = rank_candidates<NT>(m, r, sm);
+        }
+      } else {
+        auto fn = [&](int i, u64& kk) -> bool {
+          if (i < a.sink || i >= recent_from) return false;
+          const float x = sc[i];
+          if (bucket_of(x) != bin) return false;
+          kk = selection_order_key(x, i);
+          return true;
+        };
+        thr = block_kth_smallest<NT>(fn, n_valid, r, sm.generic, sm.a.sel.hist);
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      if (quad[i] < 0) continue;
+      u32 in = upto(4 * quad[i], n_valid) & ~free_of(4 * quad[i]);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int j = 4 * i + e;
+        in |= pb[j] < bin || (pb[j] == bin && key_of(j) <= thr) ? 1u << e : 0u;
+      }
+      ls.picked[quad[i]] = (unsigned char)in;
+    }
+  }
+  __syncthreads();
+  // output in ascending page order: 32 pages a thread
+  static_assert(kHeldPages == 32 * NT, "a thread's 32 pages are eight bytes of the map");
+  u64 bits = 32 * tid < n_valid ? reinterpret_cast<const u64*>(ls.picked)[tid] : 0ull;
+  int total;
+  int pos = fast_scan<NT>((int)__popcll(bits), sm, flip, total);
+  int32_t* out = a.sel_pages + (size_t)u * k;
+  while (bits) {
+    const int bit = __ffsll((unsigned long long)bits) - 1;
+    bits &= bits - 1;
+    const int p = 32 * tid + 4 * (bit >> 3) + (bit & 7);
+    if (pos < k) { sm.sel[pos] = (u32)p; out[pos] = p; }
+    ++pos;
+  }
+  for (int i = k_eff + tid; i < k; i += NT) {
+    sm.sel[i] = Smem::kNoPage;
+    out[i] = -1;
+  }
+  return true;
+}
+
 // All NT threads of a workgroup, for unit u.  DO_SELECT: scores -> sel_pages (Top-K, ties to the
 // lower page, sink/recent pages forced, ascending page order, -1 padding).  DO_RESOLVE: sel_pages
 // -> directory update, slots, hit mask, evicted list, counts, the (page, slot) miss list and,
@@ -525,6 +724,8 @@ __device__ __forceinline__ bool select_resolve_body(const FastArgs& a, int u, Fa
   auto page_of = [&](int j) -> int { return wave_p0 + (j >> 2) * (4 * kWave) + 4 * lane + (j & 3); };
   float s[BIG ? 4 : IPT];
   int seq = 0;
+  bool try_held = false;
+  float4 held[HELD ? 8 : 1];
   auto load_scores = [&]() {
     const float* sc = a.scores + (size_t)u * a.NP;
     if ((a.NP & 3) == 0) {
@@ -549,6 +750,12 @@ __device__ __forceinline__ bool select_resolve_body(const FastArgs& a, int u, Fa
   if (DO_SELECT) {
     if (!HANDOFF && !BIG) load_scores();                       // (with HANDOFF the scores may not be complete yet)
     seq = a.seq_len[b];
+    if constexpr (HELD) {
+      // (not where select_big's passes are few, nor for selections of which the list might not hold the quads: 16 units of 7500
+      // pages 31.9 us a step with it and 33.3 with this, 2048 of 17500 pages 47.8 and 52.1)
+      try_held = seq > KVD_FAST_MAX_PAGES * a.P && k <= NT;
+      if (try_held) select_held_load<NT>(a, u, seq, held);
+    }
   } else if (!SEL_IN_LDS) {
     for (int i = tid; i < k; i += NT) {
       const int p = a.sel_pages[(size_t)u * k + i];
@@ -565,14 +772,19 @@ __device__ __forceinline__ bool select_resolve_body(const FastArgs& a, int u, Fa
     for (int i = tid; i < FastSmem<NT, BIG>::kMaxCapacity / 32; i += NT) sm.hit_bitmap[i] = 0;
     for (int i = tid; i < k; i += NT) sm.assign[i] = kAbsent;
   }
-  if (tid == 0) { sm.cand_n = 0; sm.n_ev = 0; sm.late = 0; }
+  if (tid == 0) { sm.cand_n = 0; sm.tied_n = 0; sm.n_ev = 0; sm.late = 0; }
   __syncthreads();
   float vs[BIG ? 1 : CPT];                             // lookahead eviction: this step's score of the page in each slot
   int vat[BIG ? 1 : CPT];                              // ... and which score that is (-1: none)
   if constexpr (DO_RESOLVE && BIG) {
-    for (int sl = tid; sl < C; sl += NT) {
-      const int p = spage[sl];
-      if (p >= 0) sm.p2s[p] = (uint16_t)sl;
+    // (four loads on their way at a time)
+    for (int sl0 = tid; sl0 < C; sl0 += 4 * NT) {
+      int p[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) p[i] = spage[sl0 + i * NT < C ? sl0 + i * NT : C - 1];
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        if (sl0 + i * NT < C && p[i] >= 0) sm.p2s[p[i]] = (uint16_t)(sl0 + i * NT);
     }
   } else if constexpr (DO_RESOLVE) {
 #pragma unroll
@@ -622,7 +834,17 @@ __device__ __forceinline__ bool select_resolve_body(const FastArgs& a, int u, Fa
 
   // ---- selection
   if constexpr (DO_SELECT && BIG) {
-    select_big<NT, HELD>(a, u, seq, sm, flip);
+    bool done = false;
+    if constexpr (HELD) {
+      if (try_held) done = select_held<NT>(a, u, seq, held, sm, flip);
+      if (try_held && !done) {
+        __syncthreads();                                 // (the histogram has been read)
+        for (int i = tid; i < kHistWords; i += NT) sm.a.sel.hist[i] = 0;
+        if (tid == 0) sm.cand_n = 0;
+        __syncthreads();
+      }
+    }
+    if (!done) select_big<NT, HELD>(a, u, seq, sm, flip);
     if (!DO_RESOLVE) return true;
   } else if constexpr (DO_SELECT) {
     constexpr int kBinWords = IPT == 4 ? 8 : 16;       // 1024 or 2048 buckets
