@@ -61,10 +61,10 @@ __device__ __forceinline__ void page_group_load(const char* src_page, u32 bytes,
   x.k = buffer_load16(src_page, bytes, at);
   x.v = buffer_load16(src_page, bytes, at + (u32)P * kRowBytes);
 }
-// T: tokens of a tile (16, or those of a packed page)
+// T: tokens of a tile (16, or the 4 or 8 of a packed page)
 template <bool HANDOFF>
 __device__ __forceinline__ void page_group_store(char* slot, u32 bytes, int T, int group, uint16_t* vt, const PageGroup& x) {
-  const u32 lane = threadIdx.x & (kWave - 1), tile = (u32)(4 * group / T) * (u32)T * 2 * kRowBytes, t0 = (u32)(4 * group % T);
+  const u32 lane = threadIdx.x & (kWave - 1), t0 = 4u * (u32)group & (u32)(T - 1), tile = (4u * (u32)group - t0) * 2 * kRowBytes;
   buffer_store16<HANDOFF>(slot, bytes, tile + ((lane & 15) * (u32)T + t0 + (lane >> 4)) * 16, x.k);
   wave_lds_fence();                                    // (the group before this one has been read)
   *reinterpret_cast<uint4*>(vt + (lane >> 4) * kHeadDim + (lane & 15) * 8) = x.v;

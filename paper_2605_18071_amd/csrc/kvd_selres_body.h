@@ -1246,12 +1246,12 @@ __device__ __forceinline__ bool select_resolve_body(const FastArgs& a, int u, Fa
   }
 
   // ---- fetch the unit's missed pages, miss j being page sm.miss[j] for slot sm.assign[j].  Every wave for itself, without
-  // barriers, with a batch of pieces on its way while the one before is stored: four tokens' K and V a piece, or, in natural
-  // slots, 1 KiB.  Bound by the host link, which takes 150 KB on their way to be busy (read by 8 workgroups 25 GB/s with 8 KiB
+  // barriers, a batch of pieces on its way at a time: four tokens' K and V a piece, or, in natural slots, 1 KiB.  Bound by the host link, which takes 150 KB on their way to be busy (read by 8 workgroups 25 GB/s with 8 KiB
   // of each on their way, 54 with 32; 16 workgroups 56), and for few units by its latency.  (us per step with misses, with
-  // tiles of 256 threads, two barriers and 16 KiB on their way, and so, the victim choice below included: 4 units of 1024
-  // pages of 64 tokens 56.2 and 44.3, 8 of 750 of 16 46.1 and 41.1, 8 of 4096 of 4 54.8 and 49.2, 64 of 2048 of 16 236.5 and
-  // 233.6, 32 of 8192 of 16 284.8 and 277.0.)
+  // tiles of 256 threads, two barriers and 16 KiB on their way, and so, the victim choice above included: 4 units of 1024
+  // pages of 64 tokens 56.2 and 43.3, 8 of 750 of 16 46.1 and 38.4, 8 of 4096 of 4 54.8 and 47.0, 64 of 2048 of 16 236.5 and
+  // 229.8, 32 of 8192 of 16 284.8 and 274.1.  The code is met cold, so less of it is faster: with a second batch on its way while the
+  // first is stored, which is five copies of the unrolled loops instead of two, these were 44.6, 41.0, 49.2, 233.3 and 277.5.)
   __syncthreads();                                     // everyone is done with sm.a.sel
   const char* store_u = a.store + (size_t)u * a.NP * a.page_bytes;
   char* pool_u = a.pool + (size_t)u * a.Cmax * a.page_bytes;
@@ -1259,10 +1259,12 @@ __device__ __forceinline__ bool select_resolve_body(const FastArgs& a, int u, Fa
   const int pieces = layout == kLayoutNatural ? (a.P + 1) >> 1 : a.P >> 2, n_items = m * pieces;   // (a page is P half KiB)
   // Without branches: what is no item, or has no slot, is a buffer without bytes, whose loads and stores do nothing.  (A load
   // under a condition was waited for at once, where its register is joined with that of the other way.)
+  // (at / pieces by the reciprocal rounded up: exact below 2^32 / pieces^2, and at most 2048 pages have 128 pieces each)
+  const u32 recip = 0xffffffffu / (u32)pieces + 1u;    // (0 for one piece)
   struct Piece { const char* src; char* dst; u32 bytes; int piece; };
   auto item = [&](int it) -> Piece {
     const int at = it < n_items ? it : n_items - 1;
-    const int jm = __builtin_amdgcn_readfirstlane(at / pieces);
+    const int jm = __builtin_amdgcn_readfirstlane(pieces == 1 ? at : (int)(((u64)(u32)at * recip) >> 32));
     const int slot = __builtin_amdgcn_readfirstlane((int)sm.assign[jm]);
     const u32 page = (u32)__builtin_amdgcn_readfirstlane((int)(sm.miss[jm] & 0xffffu));
     Piece x;
@@ -1272,45 +1274,34 @@ __device__ __forceinline__ bool select_resolve_body(const FastArgs& a, int u, Fa
     x.piece = at - jm * pieces;
     return x;
   };
-  // f(batch, first item): every wave's items, a batch on its way while the one before is stored
-  auto in_batches = [&](auto& x, auto& y, int size, auto fetch, auto put) {
-    fetch(x, w);
-    for (int it = w; it < n_items; it += 2 * size * NW) {
-      fetch(y, it + size * NW);
-      put(x);
-      fetch(x, it + 2 * size * NW);
-      put(y);
-    }
-  };
   if (layout == kLayoutNatural) {
     constexpr int kBatch = NT > 512 ? 4 : 8;             // (either way 64 KiB of a workgroup)
-    struct Batch { uint4 v[kBatch]; Piece of[kBatch]; } x, y;
-    in_batches(x, y, kBatch, [&](Batch& b, int it0) {
+    for (int it = w; it < n_items; it += kBatch * NW) {
+      uint4 v[kBatch];
+      Piece of[kBatch];
 #pragma unroll
       for (int i = 0; i < kBatch; ++i) {
-        b.of[i] = item(it0 + i * NW);
-        b.v[i] = buffer_load16(b.of[i].src, b.of[i].bytes, (u32)b.of[i].piece * 1024u + (u32)lane * 16u);
+        of[i] = item(it + i * NW);
+        v[i] = buffer_load16(of[i].src, of[i].bytes, (u32)of[i].piece * 1024u + (u32)lane * 16u);
       }
-    }, [&](const Batch& b) {
 #pragma unroll
-      for (int i = 0; i < kBatch; ++i)
-        buffer_store16<HANDOFF>(b.of[i].dst, b.of[i].bytes, (u32)b.of[i].piece * 1024u + (u32)lane * 16u, b.v[i]);
-    });
+      for (int i = 0; i < kBatch; ++i) buffer_store16<HANDOFF>(of[i].dst, of[i].bytes, (u32)of[i].piece * 1024u + (u32)lane * 16u, v[i]);
+    }
   } else {
     constexpr int kBatch = NT > 512 ? 2 : 4;
     const int tile_tokens = layout == kLayoutTiles ? kTileTokens : a.P;
     uint16_t* vt = &sm.a.vt[w][0];
-    struct Batch { PageGroup g[kBatch]; Piece of[kBatch]; } x, y;
-    in_batches(x, y, kBatch, [&](Batch& b, int it0) {
+    for (int it = w; it < n_items; it += kBatch * NW) {
+      PageGroup g[kBatch];
+      Piece of[kBatch];
 #pragma unroll
       for (int i = 0; i < kBatch; ++i) {
-        b.of[i] = item(it0 + i * NW);
-        page_group_load(b.of[i].src, b.of[i].bytes, a.P, b.of[i].piece, b.g[i]);
+        of[i] = item(it + i * NW);
+        page_group_load(of[i].src, of[i].bytes, a.P, of[i].piece, g[i]);
       }
-    }, [&](const Batch& b) {
 #pragma unroll
-      for (int i = 0; i < kBatch; ++i) page_group_store<HANDOFF>(b.of[i].dst, b.of[i].bytes, tile_tokens, b.of[i].piece, vt, b.g[i]);
-    });
+      for (int i = 0; i < kBatch; ++i) page_group_store<HANDOFF>(of[i].dst, of[i].bytes, tile_tokens, of[i].piece, vt, g[i]);
+    }
   }
   publish_misses();
   return true;
