@@ -39,7 +39,7 @@ __global__ __launch_bounds__(kMergeThreads) void combine_kernel(AttnArgs a) {
 constexpr int kAttnMfmaThreads = 512;
 template <bool BF16, int G, int LAYOUT>
 __global__ __launch_bounds__(kAttnMfmaThreads, 2) void attend_mfma_kernel(AttnArgs a) {
-  __shared__ AttnSmem<G, kAttnMfmaThreads / kWave> sm;
+  __shared__ AttnSmem<G, kAttnMfmaThreads / kWave, LAYOUT == kLayoutNatural ? KVD_MAX_TOPK : kAttnIdxCap> sm;
   attend_mfma_body<BF16, G, kAttnMfmaThreads, false, LAYOUT>(a, sm, blockIdx.y + a.u0, blockIdx.x);
 }
 

@@ -41,9 +41,9 @@ struct AttnArgs {
 // floats: the accumulators, then maximum and sum.  `part` holds one split of the waves; a caller with more LDS behind it may
 // have a workgroup take several splits (part_of).
 constexpr int kPartStride = kHeadDim + 4;   // (a multiple of 16 bytes)
-template <int GMAX, int NW>
+template <int GMAX, int NW, int CAP = kAttnIdxCap>
 struct AttnSmem {
-  int32_t page[kAttnIdxCap], slot[kAttnIdxCap];
+  int32_t page[CAP], slot[CAP];
   int is_last;
   __align__(16) float part[NW * GMAX * kPartStride];
   __device__ __forceinline__ float* part_of(int v, int w, int g, int G) { return part + ((v * NW + w) * G + g) * kPartStride; }
@@ -170,9 +170,8 @@ __device__ __forceinline__ void merge_splits(const AttnArgs& a, int u, float* ld
 // Returns true in the workgroup that completed the unit's output (with a separate merge kernel:
 // never).
 // SEVERAL: a workgroup may have taken more than one split.
-template <int GT, int NT, bool SEVERAL>
-__device__ __forceinline__ bool finish_splits(const AttnArgs& a, AttnSmem<GroupMax<GT>::value, NT / kWave>& sm, int u,
-                                              int split, int n_taken) {
+template <int GT, int NT, bool SEVERAL, class Smem>
+__device__ __forceinline__ bool finish_splits(const AttnArgs& a, Smem& sm, int u, int split, int n_taken) {
   const int n = SEVERAL ? n_taken : 1;
   constexpr int NW = NT / kWave;
   const int G = group_size<GT>(a);
@@ -317,9 +316,8 @@ __device__ __forceinline__ f32x4 mfma_pv(const uint2& vfrag, const uint2& pfrag,
 // Returns 1 in the workgroup that completed the unit's output, 0 in the others, -1 (from all
 // threads, no output) when a HANDOFF wait ran out.  inputs_ready_tick (one thread passes it)
 // receives the wall clock at which the split's entries were all there.
-template <bool BF16, int GT, int NT, bool HANDOFF, int LAYOUT = kLayoutTiles, bool SEVERAL = false>
-__device__ __forceinline__ int attend_mfma_body(const AttnArgs& a, AttnSmem<GroupMax<GT>::value, NT / kWave>& sm, int u,
-                                                int split, long long* inputs_ready_tick = nullptr) {
+template <bool BF16, int GT, int NT, bool HANDOFF, int LAYOUT = kLayoutTiles, bool SEVERAL = false, class Smem>
+__device__ __forceinline__ int attend_mfma_body(const AttnArgs& a, Smem& sm, int u, int split, long long* inputs_ready_tick = nullptr) {
   constexpr int NW = NT / kWave;
   constexpr bool PACKED = LAYOUT == kLayoutPacked, NATURAL = LAYOUT == kLayoutNatural;
   constexpr float kPScale = NATURAL && !BF16 ? 32768.f : 1.f;   // of the probabilities that multiply V
@@ -365,7 +363,8 @@ __device__ __forceinline__ int attend_mfma_body(const AttnArgs& a, AttnSmem<Grou
   // one 64-bit word each, and a thread polls its word until it has been published (a word is
   // published when the page is in its slot); the wait is bounded and its verdict shared.
   const int n_entries = last - first;
-  const bool idx_in_lds = HANDOFF || n_entries <= kAttnIdxCap;   // (HANDOFF callers keep splits within kAttnIdxCap)
+  // (HANDOFF callers keep splits within kAttnIdxCap, and over natural slots there is room for any)
+  const bool idx_in_lds = HANDOFF || NATURAL || n_entries <= kAttnIdxCap;
   if (HANDOFF) {
     const u64* ent = a.sel_entry + (size_t)u * a.k + first;
     if (tid == 0) sm.is_last = 0;                      // (here: -1 once some thread's wait has run out)
@@ -401,7 +400,7 @@ __device__ __forceinline__ int attend_mfma_body(const AttnArgs& a, AttnSmem<Grou
   // software pipeline: three tile buffers rotate, so the operands of the next two tiles of this
   // wave (16 KiB) are in flight while one tile is computed
   struct Tile { uint4 k[4], v[4]; u32 valid; int split; };   // valid: bit i = token i of the tile takes part
-  auto issue_tile = [&](Tile& tl, int split_v, int t) {
+  auto issue_tile = [&](Tile& tl, int split_v, int t, bool there = true) {   // (there: looked at over natural slots)
     // the split's entries in LDS, and behind `first`
     const int e_base = SEVERAL ? split_v * a.per_split : 0;
     const int e_end = SEVERAL && e_base + a.per_split < n_entries ? e_base + a.per_split : n_entries;
@@ -443,22 +442,24 @@ __device__ __forceinline__ int attend_mfma_body(const AttnArgs& a, AttnSmem<Grou
       }
       return;
     }
-    if (NATURAL) {
+    if constexpr (NATURAL) {
       // token d of the tile: row (16 t + d) % P of entry (16 t + d) / P.  Each lane looks up the token of its K row, and
       // learns where its V rows are from the lanes 4g .. 4g+3, which have looked up their tokens.  (us per step with five
       // lookups per lane and so: 160 units x 85 pages of 12 tokens, G = 2 and 7, 49.7, 52.0 and 37.5, 40.0; 40 x 300
       // pages of 6 34.8 and 31.4; 96 x 102 pages of 20 41.0 and 40.4; 16 x 26 pages of 20 20.0 and 20.3.  Ways of their own
       // for pages of more and of up to 16 tokens: the last gained nothing, large ones lost 10 % to the longer code.)
-      const int t_u = __builtin_amdgcn_readfirstlane(t);
+      // The loads have no branch around them, a token that is not there an address that is: where one path loads a register
+      // and another does not, the compiler has all loads waited for before the next ones, and one tile is in flight instead of
+      // three (32 units x 2084 pages of 24 tokens, G = 7, 24.3 us a step and 23.6 so).
+      const int t_u = there ? __builtin_amdgcn_readfirstlane(t) : 0, end = there ? e_end : 0;
       const int e0_v = (int)((u32)(((u64)(16 * t_u) * recip) >> 32)) + (a.P == 1 ? 16 * t_u : 0), row0 = 16 * t_u - e0_v * a.P;
       const int e0 = e_base + e0_v;
       auto entry = [&](int e, int& page, int& slot) {
-        page = -1; slot = -1;
-        if (e < e_end) {
-          if (idx_in_lds) { page = sm.page[e]; slot = sm.slot[e]; }
-          else { page = sel[first + e]; slot = slots[first + e]; }
-        }
-        if (slot >= a.Cmax) slot = -1;
+        const int at = e < end ? e : 0;
+        page = sm.page[at];
+        slot = sm.slot[at];
+        slot = e >= end || slot >= a.Cmax ? -1 : slot;
+        page = e >= end ? -1 : page;
       };
       int page, slot, row = row0 + 4 * (j & 3) + (j >> 2);
       if (a.P > 16) {                                    // the tile lies in entries e0 and e0 + 1
@@ -479,23 +480,20 @@ __device__ __forceinline__ int attend_mfma_body(const AttnArgs& a, AttnSmem<Grou
       const bool kok = page >= 0 && slot >= 0 && page * a.P + row < seq;
       const u32 valid = (u32)(__ballot(kok) & 0xffffull);   // bit i: the token of row i takes part
       tl.valid = valid;
-      if (valid == 0) return;
       const int krow = slot * 2 * a.P + row;             // of the unit's slots, in rows of 256 bytes (below 2^25)
       int vrow[4];
 #pragma unroll
       for (int m = 0; m < 4; ++m) vrow[m] = __shfl(krow, 4 * g + m, kWave) + a.P;
+      // a token that takes no part reads the query's first row, which is there and in no slot (its logit is not used, and its V is blanked)
+      const char* nowhere = reinterpret_cast<const char*>(a.q + ((size_t)b * a.Hq + (size_t)h * G) * kHeadDim);
+      // (each 128-byte line is the business of two of the K loads: no streaming hint)
+      const char* kb = (kok ? pool_u + (size_t)krow * kRowBytes : nowhere) + g * 16;
 #pragma unroll
-      for (int c = 0; c < 4; ++c) { tl.k[c] = make_uint4(0u, 0u, 0u, 0u); tl.v[c] = make_uint4(0u, 0u, 0u, 0u); }
-      if (kok) {
-        // (each 128-byte line is the business of two of these loads: no streaming hint)
-        const char* kb = pool_u + (size_t)krow * kRowBytes + g * 16;
-#pragma unroll
-        for (int c = 0; c < 4; ++c) tl.k[c] = *reinterpret_cast<const uint4*>(kb + c * 64);
-      }
+      for (int c = 0; c < 4; ++c) tl.k[c] = *reinterpret_cast<const uint4*>(kb + c * 64);
       const u32 mine = (valid >> (4 * g)) & 15u;
 #pragma unroll
-      for (int m = 0; m < 4; ++m)                        // (a token that takes no part may hold anything: its V stays zero)
-        if ((mine >> m) & 1u) tl.v[m] = load_stream16(pool_u + (size_t)vrow[m] * kRowBytes + j * 16);
+      for (int m = 0; m < 4; ++m)
+        tl.v[m] = load_stream16(((mine >> m) & 1u ? pool_u + (size_t)vrow[m] * kRowBytes : nowhere) + j * 16);
       return;
     }
     const int e = e_base + t / tiles_per_page, tile = t % tiles_per_page;
@@ -523,7 +521,12 @@ __device__ __forceinline__ int attend_mfma_body(const AttnArgs& a, AttnSmem<Grou
   // exact: P.V in fp32 whatever the probabilities
   auto compute = [&](Tile& tl, auto exact) {
     const u32 valid = tl.valid;
-    if (valid == 0) return;
+    if (!NATURAL && valid == 0) return;
+    if (NATURAL && valid != 0xffffu) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (!((valid >> (4 * g + e)) & 1u)) tl.v[e] = make_uint4(0u, 0u, 0u, 0u);
+    }
     const u32 mine = (valid >> (4 * g)) & 15u;          // this lane's four tokens 4g..4g+3
     if (!NATURAL && valid != 0xffffu) {
       // a tile with tokens that take no part (the ragged end of a sequence, whose slot holds whatever
@@ -703,6 +706,25 @@ __device__ __forceinline__ int attend_mfma_body(const AttnArgs& a, AttnSmem<Grou
       }
     } else {
       const int n_tiles = tiles_of(0);
+      if constexpr (NATURAL) {
+        auto issue = [&](Tile& tl, int t) { issue_tile(tl, 0, t, t < n_tiles); };
+        if (w >= n_tiles) return;
+        Tile ta, tb2, tc;
+        issue(ta, w);
+        issue(tb2, w + NW);
+        for (int t = w;; t += 3 * NW) {
+          issue(tc, t + 2 * NW);
+          compute(ta, exact);
+          if (t + NW >= n_tiles) break;
+          issue(ta, t + 3 * NW);
+          compute(tb2, exact);
+          if (t + 2 * NW >= n_tiles) break;
+          issue(tb2, t + 4 * NW);
+          compute(tc, exact);
+          if (t + 3 * NW >= n_tiles) break;
+        }
+        return;
+      }
       auto issue = [&](Tile& tl, int t) {
         tl.valid = 0;
         if (t < n_tiles) issue_tile(tl, 0, t);

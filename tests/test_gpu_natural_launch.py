@@ -26,6 +26,9 @@ def fresh(w, seq, mb):
     (33, 90, 20, dict(policy="lookahead", lookahead_pool=25)),
     (20, 600, 40, dict(index_centroids=70)),
     (255, 40, 5, dict()),
+    (3, 4000, 150, dict(n_q_heads=6, dtype="f16")),                    # each number of pages that a thread holds, and what it holds them in
+    (20, 8000, 40, dict(n_q_heads=10, heavy_count=3, steps=3)),
+    (20, 7000, 40, dict(n_q_heads=16, heavy_count=3, steps=3, dtype="f16")),
     (6, 8200, 30, dict(batch=5)),                                      # 10 units of more than 8192 pages
 ])
 def test_equals_the_chain(page, pages, k, kw):
