@@ -4,7 +4,7 @@
 // The splits that the rule leaves a launch with.  Where the library takes one layer as a chain of kernels and several in a
 // launch, these have that chain's splits, for the same order of the sums.
 static int rule_splits(const kvd_ctx* c, int multi_layer) {
-  return multi_layer && !c->single_launch && kvd_layers_share_launch(c) ? c->S : c->S1;
+  return multi_layer && !c->single_launch && c->tiled && kvd_layers_share_launch(c) ? c->S : c->S1;   // (natural slots: kvd_launch_step has theirs)
 }
 
 // The launch shape of the one-launch step.  What kvd_set_step_shape / kvd_calibrate_step_shape fixed
