@@ -287,7 +287,7 @@ __device__ __forceinline__ void step_body(StepArgsPtr ap, unsigned char* smem_ra
   }
 }
 
-// PACKED: pages of 4 or 8 tokens.  MANY: a launch of
+// LAYOUT: how the pages are kept in their slots (kvd_tile_layout.h).  MANY: a launch of
 // several layers; a kernel of its own, since what only such a launch needs (a layer's strides, attention workgroups that take
 // several splits) costs a launch of one layer 0.6 to 1 us (8 units of 256 pages 13.6 and 14.2, 128 of 2048 43.5 and 44.5).
 template <bool BF16, int NT, int IPT, int LAYOUT, bool MANY>
