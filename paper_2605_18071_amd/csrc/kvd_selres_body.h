@@ -530,13 +530,13 @@ __device__ __forceinline__ bool select_held(const FastArgs& a, int u, int seq, c
     const u32 fr = q < nq ? free_of(page_of(q)) : 0u;
     const float x0 = fr & 1u ? s[q].x : -INFINITY, x1 = fr & 2u ? s[q].y : -INFINITY, x2 = fr & 4u ? s[q].z : -INFINITY,
                 x3 = fr & 8u ? s[q].w : -INFINITY;
-    const float sum = (x0 + x1) + (x2 + x3);
     best[q] = fmaxf(fmaxf(x0, x1), fmaxf(x2, x3));
     fmax = fmaxf(fmax, best[q]);
     fmin = fminf(fmin, best[q] > -INFINITY ? best[q] : INFINITY);
-    // (a page that is no number is in the first bucket, and so is its quad; where the sum is none because of two infinities
-    // all pages are in the first bucket)
-    first |= sum != sum ? 1u << q : 0u;
+    // (a page that is no number is in the first bucket, and so is its quad.  The pages are looked at one by one: a sum of theirs may
+    // be none where all are numbers, as of pairs that overflow to the two infinities, and a quad in an earlier bucket than any
+    // of its pages would leave fewer pages than are wanted in the list)
+    first |= __builtin_isunordered(x0, x1) || __builtin_isunordered(x2, x3) ? 1u << q : 0u;
     if (q < nq) ls.picked[page_of(q) >> 2] = (unsigned char)(upto(page_of(q), n_valid) & ~fr);   // the forced pages
   }
   fmin = wave_allreduce_min(fmin);

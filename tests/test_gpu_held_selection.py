@@ -1,5 +1,7 @@
 """Selection of units of 16385 to 32768 pages, of which only the quads that can hold a selected page are looked at closely: the
 result of the size-agnostic kernels at the edges of what the list of quads holds."""
+import functools
+
 import numpy as np
 import pytest
 import torch
@@ -10,6 +12,7 @@ from tests.test_gpu_parity import small
 pytestmark = pytest.mark.gpu
 
 if torch.cuda.is_available():
+    from paper_2605_18071_amd import kvd as K
     from tests import gpu_rig as R
 
 
@@ -54,3 +57,41 @@ def test_equals_the_size_agnostic_kernels(pages, same, k, kw, monkeypatch):
             assert np.array_equal(getattr(fused, what), getattr(plain, what)), (what, t)
     fused.close()
     plain.close()
+
+
+@pytest.mark.parametrize("pages,k,kw,at", [
+    (20000, 2, dict(), {5000: 3e38, 8000: 2e38, 8001: 2e38, 8002: -2e38, 8003: -2e38}),     # pairs that overflow to both infinities
+    (20000, 2, dict(), {5000: 3e38, 8000: -2e38, 8001: -2e38, 8002: 2e38, 8003: 2e38}),
+    (20000, 2, dict(), {5000: 3e38, 8000: 2e38, 8001: 2e38, 8002: -np.inf}),                # one pair does, beside a page of minus infinity
+    (20000, 4, dict(sink_pages=2), {5000: 3e38, 2: 2e38, 3: 2e38}),                         # ... beside forced pages
+    (20000, 4, dict(recent_pages=2), {5000: 3e38, -4: 2e38, -3: 2e38}),
+    (20002, 2, dict(), {5000: 3e38, -2: 2e38, -1: 2e38}),                                   # ... at the end of the sequence
+    (16385, 3, dict(), {5000: -1e38, 16384: 3e38, 8000: 3e38, 8001: 3.2e38, 8002: -3e38, 8003: -3e38}),   # the range overflows
+])
+def test_scores_whose_sums_overflow(pages, k, kw, at, monkeypatch):
+    """Scores near the largest number: the best k pages in the order of (score, page), as a step's stage and alone."""
+    monkeypatch.setattr(K, "Kvd", functools.partial(K.Kvd, softmax_scale=1.0))
+    w = small("held-overflow", **{**dict(ctx=4 * pages, page=4, topk_pages=k, capacity=k + 5, batch=1, n_kv_heads=2, n_q_heads=4,
+                                         heavy_count=0, steps=1), **kw})
+    rig = R.Rig(w, build_index=False)
+    gen = np.random.default_rng(pages + k)
+    values = torch.from_numpy(gen.random((w.units, pages), dtype=np.float32) * np.float32(9e37)).to(w.torch_dtype)
+    for page, v in at.items():
+        values[:, page] = v
+    rig.summaries.zero_()
+    rig.summaries.view(w.units, pages, 128)[:, :, 0] = values.to(R.DEV)
+    q = torch.zeros((w.batch, w.n_q_heads, 128), dtype=w.torch_dtype, device=R.DEV)
+    q[:, :, 0] = 1.0                                        # a page's score is the first element of its summary
+    scores = values.float().numpy()
+    want = np.empty((w.units, k), np.int32)
+    for u in range(w.units):
+        forced = list(range(w.sink_pages)) + list(range(pages - w.recent_pages, pages))
+        free = np.arange(w.sink_pages, pages - w.recent_pages)
+        best = free[np.lexsort((free, -scores[u, free]))][:k - len(forced)]
+        want[u] = np.sort(np.concatenate([np.array(forced, int), best]))
+    rig.step(0, 0, q)
+    assert np.array_equal(rig.n_scores, scores) and np.array_equal(rig.n_sel_pages, want)
+    alone = torch.full((w.units, k), -7, dtype=torch.int32, device=R.DEV)
+    rig.kvd.score_select(0, q, alone)
+    assert np.array_equal(alone.cpu().numpy(), want)
+    rig.close()
