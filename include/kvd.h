@@ -85,8 +85,8 @@ typedef struct {
                               -1 = the whole step as one launch in which every (sequence, KV head) unit
                                    moves through the stages on its own, synchronised by counters and
                                    published words in device memory (needs a page size that is a multiple of
-                                   16, or 4, or 8; max_pages <= 16384; capacity_max <= 4096; other shapes run
-                                   as for 1).  A workgroup of that
+                                   16, or 4, or 8; max_pages <= 16384; capacity_max <= 4096; and a slot pool
+                                   that starts on a 128-byte line; others run as for 1).  A workgroup of that
                                    launch only ever waits for workgroups with a lower index, and the form
                                    relies on the GPU starting the workgroups of a one-dimensional grid in
                                    index order (what a waiting workgroup waits for has then started and
@@ -159,7 +159,10 @@ int kvd_bind_summaries(kvd_ctx* ctx, void* dev_summaries);
 /* Paged KV store in pinned host memory, [Lp][B][Hkv][NP][2][P][D] kv_dtype (K page, then V
  * page).  KVD_ERR_ARG if the GPU cannot address the pointer. */
 int kvd_bind_host_store(kvd_ctx* ctx, const void* pinned_store);
-/* GPU cache tier, dev, [L][B][Hkv][Cmax] slots of page_bytes each, 16-byte aligned.  Contents are
+/* GPU cache tier, dev, [L][B][Hkv][Cmax] slots of page_bytes each, 16-byte aligned.  Where it does not
+ * start on a 128-byte line two slots share a line, which a launch that fills and reads slots cannot
+ * have: steps and layers then run as a chain of kernels whatever form -1 or 0 asks for (kvd_step_form
+ * says so), until a pool that starts on a line is bound.  Contents are
  * managed by the library: which page sits in which slot is the directory's business, and inside a
  * slot the page is stored in the order the attention kernel reads it (pages of a multiple of 16
  * tokens: 16-token tiles of MFMA-operand-ready K and transposed V; pages of 4 or 8 tokens: the same
@@ -471,7 +474,8 @@ int kvd_set_profiling(kvd_ctx* ctx, int32_t mode);
  * many groups on the library's streams. */
 int kvd_step_form(const kvd_ctx* ctx);
 /* Changes the form of kvd_step (same values as kvd_config.micro_batches).  Waits for the device.
- * KVD_ERR_SHAPE if the context's shapes cannot run that form. */
+ * KVD_ERR_SHAPE if the context's shapes cannot run that form.  (-1 also says what is wanted of slot
+ * pools bound later: with one that starts inside a 128-byte line the step stays a chain.) */
 int kvd_set_step_form(kvd_ctx* ctx, int32_t form);
 /* Pre-run calibration (Pipeline Optimization: the micro-batch size is found by a short calibration
  * before inference begins).  Runs real decode steps of `layer` — step indices first_step ..

@@ -471,6 +471,7 @@ int kvd_bind_host_store(kvd_ctx* ctx, const void* pinned_store) {
 int kvd_bind_slot_pool(kvd_ctx* ctx, void* dev_pool) {
   if (!ctx || !dev_pool || !aligned16(dev_pool)) return KVD_ERR_ARG;
   ctx->pool = static_cast<char*>(dev_pool);
+  ctx->single_launch = kvd_wants_single_launch(ctx);
   ctx->natural_launch = kvd_wants_natural_launch(ctx);
   return KVD_OK;
 }
@@ -891,7 +892,7 @@ int kvd_set_profiling(kvd_ctx* ctx, int32_t on) {
 int kvd_set_step_form(kvd_ctx* ctx, int32_t form) {
   if (!ctx) return KVD_ERR_ARG;
   if (form < -1 || form > KVD_MAX_MICRO) return KVD_ERR_SHAPE;
-  if (form == -1 && !kvd_single_launch_ok(ctx)) return KVD_ERR_SHAPE;
+  if (form == -1 && !kvd_single_launch_fits(ctx)) return KVD_ERR_SHAPE;   // (a pool on a cache line may still be bound)
   HIP_TRY(ctx, hipDeviceSynchronize());
   ctx->cfg.micro_batches = form;
   ctx->MB = form < 1 ? 1 : form;

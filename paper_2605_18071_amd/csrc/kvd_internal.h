@@ -153,7 +153,9 @@ hipError_t kvd_launch_attend(kvd_ctx* c, int layer, const void* q, const int32_t
                              hipEvent_t between = nullptr);   // `between`: recorded after the attention kernel, before the merge
 constexpr int kNaturalLeast = 4;            // `least` of kvd_attn_splits over natural slots
 int kvd_attn_splits(int least, int U, int k, int P, int cus, bool beside_selection = false, bool dealt_out = true);
-// The whole step as one launch (kvd_step.hip); usable when kvd_single_launch_ok.
+// The whole step as one launch (kvd_step.hip); usable when kvd_single_launch_ok: the sizes fit, and the pool starts on a
+// cache line.
+bool kvd_single_launch_fits(const kvd_ctx* c);
 bool kvd_single_launch_ok(const kvd_ctx* c);
 bool kvd_natural_launch_ok(const kvd_ctx* c);
 bool kvd_layers_share_launch(const kvd_ctx* c);

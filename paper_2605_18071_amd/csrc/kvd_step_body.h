@@ -38,7 +38,7 @@
 // or an entry published only after those stores have been acknowledged; counters, scores, the
 // entries and the partials are read with device-scope loads.  Fetched pages are read with
 // ordinary loads: no workgroup of the launch touches a slot before the page's entry has been
-// published, so no cache can hold an older copy.
+// published, and no two slots share a cache line (kvd_single_launch_ok), so no cache can hold an older copy.
 #pragma once
 #include <stddef.h>
 
