@@ -388,7 +388,7 @@ def brief_config(cfg_id, args, torch, K, W):
     b.calibrate_shape(qs[0], multi_layer=multi)
     e2e = b.end_to_end(qs, warmup, steps)
     res = {"workload": describe(w1), "layers_of_state": 1, "steps": steps, "warmup": warmup,
-           "step_form": "one launch (step_kernel)" if b.ctx.step_form() == -1 else f"chain of kernels x {b.ctx.step_form()} group(s)",
+           "step_form": "one launch (step_kernel)" if b.ctx.step_form() <= 0 else f"chain of kernels x {b.ctx.step_form()} group(s)",
            "layer_steps_per_s": steps / e2e["elapsed"], "ms_per_step": e2e["ms_per_step"], "hit_rate": e2e["hit_rate"],
            "host_bytes_per_step": e2e["host_bytes_per_step"], "host_link_GBps": e2e["host_link_GBps"],
            "setup_s": round(b.setup_s, 1)}
@@ -770,7 +770,7 @@ def main() -> int:
         result["config"]["calibration"] = calibration
     if b.calibration is not None:
         result["config"]["launch_shape"] = b.calibration
-    single = ctx.step_form() == -1
+    single = ctx.step_form() <= 0
     result["config"]["step_form"] = "one launch (step_kernel)" if single else f"chain of kernels x {ctx.step_form()} group(s)"
     q_last = queries[used - 1][0]
     if not args.no_profile_pass:

@@ -97,9 +97,8 @@ typedef struct {
                                    library recovers by itself as described there;
                               0  = chosen by the library: the one launch where it can run (for one layer with units
                                    of more than 8192 pages only from 8 units on), else as for 1; pages of other
-                                   sizes run their chain's stages in one launch too, within the same limits and
-                                   where the slot pool starts on a 128-byte line, though kvd_step_form calls
-                                   them 1 and they take neither form -1 nor a launch shape;
+                                   sizes are stepped as one launch by this choice alone, within the same limits
+                                   (kvd_step_form then says 0; they take neither form -1 nor a launch shape);
                               1  = one chain of kernels on the caller's stream, no overlap;
                               n >= 2 = the B sequences are split into n groups, each running
                                    select -> fetch -> attend as its own chain on one of the library's
@@ -470,8 +469,8 @@ int kvd_step_tiered(kvd_ctx* ctx, int32_t layer, int32_t step, const void* q, fl
  *         wall clock (see kvd_step_timeline); the step stays asynchronous. */
 int kvd_set_profiling(kvd_ctx* ctx, int32_t mode);
 /* The form kvd_step takes for this context, in the terms of kvd_config.micro_batches: -1 one launch,
- * 1 a chain of kernels (also where 0 puts the chain's stages into one launch, see there), n >= 2 that
- * many groups on the library's streams. */
+ * 0 one launch of pages of a size that only the library's own choice takes there, 1 a chain of kernels,
+ * n >= 2 that many groups on the library's streams.  kvd_set_step_form of this value changes nothing. */
 int kvd_step_form(const kvd_ctx* ctx);
 /* Changes the form of kvd_step (same values as kvd_config.micro_batches).  Waits for the device.
  * KVD_ERR_SHAPE if the context's shapes cannot run that form.  (-1 also says what is wanted of slot
@@ -480,8 +479,8 @@ int kvd_set_step_form(kvd_ctx* ctx, int32_t form);
 /* Pre-run calibration (Pipeline Optimization: the micro-batch size is found by a short calibration
  * before inference begins).  Runs real decode steps of `layer` — step indices first_step ..
  * first_step + steps_per_form with the queries q_steps [n_queries][B][Hq][D] (device) taken in
- * turn — in each form the context can run (chain of kernels, as the library's choice runs it if that was the
- * form; 2 groups, 4 groups, one launch).
+ * turn — in each form the context can run (chain of kernels, 2 groups, 4 groups, one launch: -1, or 0
+ * for the page sizes that only the library's choice runs so).
  * Every form replays the same 1 untimed + steps_per_form timed steps from the same cache: the
  * layer's directory is kept on the host when the call starts and put back before each replay (its
  * slots refilled from the host store), so that all forms see the same misses — a step's time

@@ -31,10 +31,11 @@ static bool kvd_wants_single_launch(const kvd_ctx* c) {
   return c->cfg.micro_batches == 0 && (c->NP <= 8192 || c->U >= 8);
 }
 
-// The same choice over natural slots.
-static bool kvd_wants_natural_launch(const kvd_ctx* c) {
+// The same choice over natural slots: whether form 0 is one launch there, and whether the context is to run it.
+static bool kvd_natural_launch_is_choice(const kvd_ctx* c) {
   return kvd_natural_launch_ok(c) && (c->NP <= 8192 || c->U >= 8) && (c->k + c->S_natural - 1) / c->S_natural <= 512;
 }
+static bool kvd_wants_natural_launch(const kvd_ctx* c) { return c->cfg.micro_batches == 0 && kvd_natural_launch_is_choice(c); }
 
 static bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
@@ -911,15 +912,14 @@ int kvd_calibrate_step_form(kvd_ctx* ctx, int32_t layer, int32_t first_step, con
     return KVD_ERR_ARG;
   if (!ctx->summaries || !ctx->pool || !ctx->store_dev || ctx->profiling != 0) return KVD_ERR_STATE;   // (profiled steps all run as one chain)
   hipStream_t s = static_cast<hipStream_t>(stream);
-  const int candidates[4] = {1, 2, 4, -1};
+  const bool natural = ctx->tiled == kvd::kLayoutNatural;
+  const int candidates[4] = {1, 2, 4, natural ? 0 : -1};
   const size_t q_bytes = (size_t)ctx->B * ctx->Hq * ctx->D * 2;
   hipEvent_t e0 = ctx->ev_prof[10], e1 = ctx->ev_prof[11];
-  const bool natural = ctx->natural_launch;            // (what is form 1 to the caller stays the library's choice)
-  auto set_form = [&](int form) { return kvd_set_step_form(ctx, natural && form == 1 ? 0 : form); };
   bool runs[4];
   double total_ms[4] = {0.0, 0.0, 0.0, 0.0};
-  for (int ci = 0; ci < 4; ++ci)
-    runs[ci] = !((candidates[ci] == -1 && !kvd_single_launch_ok(ctx)) || candidates[ci] > ctx->B);
+  for (int ci = 0; ci < 3; ++ci) runs[ci] = candidates[ci] <= ctx->B;
+  runs[3] = natural ? kvd_natural_launch_is_choice(ctx) : kvd_single_launch_ok(ctx);
   // Every form replays the same steps from the same cache: the directory as it is now is kept on
   // the host and put back (slots refilled from the host store) before each replay, so that all
   // forms see the same misses — the time of a step follows its misses, which vary more from step
@@ -941,7 +941,7 @@ int kvd_calibrate_step_form(kvd_ctx* ctx, int32_t layer, int32_t first_step, con
         if (r != KVD_OK) return r;
       }
       first = false;
-      r = set_form(candidates[ci]);
+      r = kvd_set_step_form(ctx, candidates[ci]);
       if (r != KVD_OK) return r;
       for (int i = 0; i <= steps_per_form; ++i) {
         if (i == 1) HIP_TRY(ctx, hipEventRecord(e0, s));
@@ -965,7 +965,7 @@ int kvd_calibrate_step_form(kvd_ctx* ctx, int32_t layer, int32_t first_step, con
     if (runs[ci] && (best_ms < 0.0 || ms < best_ms)) { best_ms = ms; best = candidates[ci]; }
   }
   *chosen_form = best;
-  return set_form(best);
+  return kvd_set_step_form(ctx, best);
 }
 
 int kvd_set_step_shape(kvd_ctx* ctx, int32_t multi_layer, int32_t passes, int32_t scoring_workgroups, int32_t attn_splits,
@@ -1090,7 +1090,7 @@ int kvd_calibrate_step_shape(kvd_ctx* ctx, int32_t layer, int32_t n_layers, int3
 
 int kvd_step_form(const kvd_ctx* ctx) {
   if (!ctx) return KVD_ERR_ARG;
-  return ctx->single_launch ? -1 : ctx->MB;
+  return ctx->single_launch ? -1 : ctx->natural_launch ? 0 : ctx->MB;
 }
 
 int kvd_set_wait_limit_us(kvd_ctx* ctx, int64_t microseconds) {
@@ -1101,7 +1101,7 @@ int kvd_set_wait_limit_us(kvd_ctx* ctx, int64_t microseconds) {
 
 int kvd_step_timeline(kvd_ctx* ctx, int64_t* host_records, int32_t capacity, int32_t* n_workgroups) {
   if (!ctx || !host_records || !n_workgroups || capacity < 0) return KVD_ERR_ARG;
-  if (!ctx->single_launch || ctx->tl_workgroups == 0) return KVD_ERR_STATE;
+  if (!(ctx->single_launch || ctx->natural_launch) || ctx->tl_workgroups == 0) return KVD_ERR_STATE;
   HIP_TRY(ctx, hipDeviceSynchronize());
   *n_workgroups = ctx->tl_workgroups;
   int n = ctx->tl_workgroups < capacity ? ctx->tl_workgroups : capacity;

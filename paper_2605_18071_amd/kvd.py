@@ -356,7 +356,9 @@ class Kvd:
         self._check(self.lib.kvd_calibrate_step_form(self.ctx, layer, first_step, q_steps.data_ptr(), q_steps.shape[0],
                                                      steps_per_form, out.data_ptr(), _stream_handle(stream),
                                                      C.byref(chosen), ms), "kvd_calibrate_step_form")
-        return chosen.value, {f: ms[i] for i, f in enumerate((1, 2, 4, -1)) if ms[i] >= 0}
+        P = self.cfg.page_size
+        one_launch = -1 if P % 16 == 0 or P in (4, 8) else 0           # (other sizes: by the library's choice only)
+        return chosen.value, {f: ms[i] for i, f in enumerate((1, 2, 4, one_launch)) if ms[i] >= 0}
 
     def set_step_shape(self, passes: int = 0, scoring_workgroups: int = 0, attn_splits: int = 0, groups: int = 0,
                        multi_layer: bool = False):

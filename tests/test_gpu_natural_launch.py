@@ -98,3 +98,48 @@ def test_a_pool_that_starts_inside_a_cache_line_and_a_wait_that_runs_out():
         assert torch.equal(rig.sel_pages, chain.sel_pages) and torch.equal(rig.out, chain.out)
     for r in (rig, shifted, chain):
         r.close()
+
+
+def test_the_form_that_runs_is_the_one_reported():
+    """Form 0 where the library's choice is one launch: setting what is reported changes nothing, a calibration times the chain
+    and the launch apart and leaves the form that it names, and a launch's timeline can be had."""
+    w = small("natural-form", page=12, ctx=12 * 300, topk_pages=40, capacity=60, batch=3, n_kv_heads=2, n_q_heads=4, heavy_count=3, steps=4)
+    seq = [w.ctx] * w.batch
+    rig, same, chain = fresh(w, seq, 0), fresh(w, seq, 0), fresh(w, seq, 1)
+    assert rig.kvd.step_form() == 0 and chain.kvd.step_form() == 1
+    qs = [q[0] for q in W.query_stream(w, rig.q0, w.steps, R.DEV)]
+    for t, q in enumerate(qs):
+        same.kvd.set_step_form(same.kvd.step_form())
+        assert same.kvd.step_form() == 0
+        rig.step(0, t, q)
+        same.step(0, t, q)
+        chain.step(0, t, q)
+        assert torch.equal(rig.out, same.out) and torch.equal(rig.sel_slots, chain.sel_slots)
+    with pytest.raises(K.KvdError):
+        rig.kvd.set_step_form(-1)
+    # the timeline of the launch
+    with pytest.raises(K.KvdError):
+        chain.kvd.step_timeline()
+    rig.kvd.set_profiling(2)
+    rig.step(0, w.steps, qs[0])
+    rec = rig.kvd.step_timeline()
+    rig.kvd.set_profiling(0)
+    role = rec[:, 4] & 0xff
+    assert int((role == 1).sum()) == w.units and bool((rec[:, 3] >= rec[:, 0]).all()) and int((role == 2).sum()) % w.units == 0
+    # the calibration
+    for r in (rig, chain):
+        chosen, ms = r.kvd.calibrate_step_form(0, w.steps + 1, torch.stack(qs).contiguous(), 5, r.out)
+        assert set(ms) == {0, 1, 2} and all(v > 0 for v in ms.values())
+        assert chosen == min(ms, key=ms.get) and r.kvd.step_form() == chosen
+    rig.kvd.set_step_form(0)
+    same.kvd.set_step_form(1)
+    assert rig.kvd.step_form() == 0 and same.kvd.step_form() == 1
+    for r in (rig, same, chain):
+        r.close()
+    # what the library's choice takes as a chain is one
+    few = small("natural-few", page=6, ctx=6 * 8300, topk_pages=25, capacity=37, batch=1, n_kv_heads=2, n_q_heads=4, steps=2)
+    rig = fresh(few, [few.ctx], 0)
+    assert rig.kvd.step_form() == 1
+    q = torch.stack([q[0] for q in W.query_stream(few, rig.q0, 2, R.DEV)]).contiguous()
+    assert set(rig.kvd.calibrate_step_form(0, 0, q, 2, rig.out)[1]) == {1}
+    rig.close()
