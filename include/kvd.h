@@ -98,7 +98,7 @@ typedef struct {
                               0  = chosen by the library: the one launch where it can run (for one layer with units
                                    of more than 8192 pages only from 8 units on), else as for 1; pages of other
                                    sizes are stepped as one launch by this choice alone, within the same limits
-                                   (kvd_step_form then says 0; they take neither form -1 nor a launch shape);
+                                   (kvd_step_form then says 0; they do not take form -1);
                               1  = one chain of kernels on the caller's stream, no overlap;
                               n >= 2 = the B sequences are split into n groups, each running
                                    select -> fetch -> attend as its own chain on one of the library's
@@ -515,7 +515,7 @@ int kvd_calibrate_step_form(kvd_ctx* ctx, int32_t layer, int32_t first_step, con
  * chunks fill most of the compute units: a launch of fewer layers, whose chunks would not, makes
  * one, and takes more scoring workgroups if there are chunks for them.  With the rule's number of splits,
  * left to it or set, an attention workgroup of a launch of several layers may take several of a unit's
- * splits; splits of any other number have a workgroup each.  Results do not depend on the shape. */
+ * splits (not with kvd_step_form() 0); splits of any other number have a workgroup each.  Results do not depend on the shape. */
 int kvd_set_step_shape(kvd_ctx* ctx, int32_t multi_layer, int32_t passes, int32_t scoring_workgroups, int32_t attn_splits,
                        int32_t groups);
 int kvd_get_step_shape(const kvd_ctx* ctx, int32_t multi_layer, int32_t* shape);
@@ -532,8 +532,8 @@ int kvd_get_step_shape(const kvd_ctx* ctx, int32_t multi_layer, int32_t* shape);
  * counts, and the fastest is kept if it beats the rule's shape by more than 1.5 %, else the rule's
  * (smaller differences are within what two timings of one shape differ by).  chosen_shape (host, 4 ints), us_chosen and us_rule (microseconds per layer-step in the
  * shape kept and in the rule's) may be NULL.  The replays count in kvd_get_stats; the outputs are
- * the step's.  Synchronous.  KVD_ERR_STATE if kvd_step does not run as one launch (kvd_step_form() other
- * than -1), also for the layers of such a context that would share one, or profiling is on. */
+ * the step's.  Synchronous.  KVD_ERR_STATE if kvd_step_form() is not -1, also for the layers of such a
+ * context that would share a launch, or profiling is on. */
 int kvd_calibrate_step_shape(kvd_ctx* ctx, int32_t layer, int32_t n_layers, int32_t step, const void* q_layers,
                              float* out_layers, void* stream, int32_t launches_per_shape, int32_t* chosen_shape,
                              float* us_chosen, float* us_rule);

@@ -37,6 +37,8 @@ static bool kvd_natural_launch_is_choice(const kvd_ctx* c) {
 }
 static bool kvd_wants_natural_launch(const kvd_ctx* c) { return c->cfg.micro_batches == 0 && kvd_natural_launch_is_choice(c); }
 
+int kvd_most_splits(const kvd_ctx* c) { return std::max(std::max(c->S, c->S_natural), c->S1_max); }
+
 static bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
 static int validate_config(const kvd_config* c) {
@@ -296,7 +298,7 @@ int kvd_create(const kvd_config* cfg, kvd_ctx** out) {
   if (c->S1_max > KVD_MAX_SPLITS) c->S1_max = KVD_MAX_SPLITS;
   if (c->S1_max > c->k) c->S1_max = c->k;
   if (c->S1_max < c->S1) c->S1_max = c->S1;
-  const int Smax = std::max(std::max(c->S, c->S_natural), c->S1_max);
+  const int Smax = kvd_most_splits(c);
 
   const size_t LU = (size_t)c->L * c->U;
   c->h_capacity = static_cast<int32_t*>(malloc(LU * sizeof(int32_t)));

@@ -44,8 +44,8 @@ struct kvd_ctx {
   kvd_config cfg;
   int L, B, Hq, Hkv, G, D, P, NP, k, Cmax, Lp, U, MB, S;
   int S1;                  // attention split-K factor of the one-launch step as kvd_create chose it (S: of the stand-alone kernel)
-  int S1_max;              // the largest split factor the partials were allocated for
-  int S_natural;           // ... and over natural slots
+  int S1_max;              // the largest that the partials have room for beside S and S_natural
+  int S_natural;           // attention split-K factor of the one-launch step over natural slots
   kvd_shape shape[2];      // launch shape of the one-launch step as set or calibrated, 0 = left to the rule:
                            // [0] launches of one layer (kvd_step), [1] launches of several layers (kvd_step_layers)
   int Nc;                  // centroids per unit of the hierarchical index, 0 = flat page index
@@ -164,6 +164,7 @@ bool kvd_layers_share_launch(const kvd_ctx* c);
 // launch (0 = the most that one covers).
 kvd_shape kvd_step_shape(const kvd_ctx* c, int multi_layer, const kvd_shape* want = nullptr, int n_layers = 0);
 bool kvd_step_shape_ok(const kvd_ctx* c, const kvd_shape& effective);
+int kvd_most_splits(const kvd_ctx* c);      // that the partials were allocated for
 // Layers [layer, layer + n_layers) of one decode step in one launch, layer `layer + i` in scratch set i
 // (q / out / lse: the layers one after another); n_layers == 1: the context's current set.
 hipError_t kvd_launch_step(kvd_ctx* c, int layer, int n_layers, int step, const void* q, float* out, float* lse, hipStream_t s);

@@ -4,7 +4,8 @@
 // The splits that the rule leaves a launch with.  Where the library takes one layer as a chain of kernels and several in a
 // launch, these have that chain's splits, for the same order of the sums.
 static int rule_splits(const kvd_ctx* c, int multi_layer) {
-  return multi_layer && !c->single_launch && c->tiled && kvd_layers_share_launch(c) ? c->S : c->S1;   // (natural slots: kvd_launch_step has theirs)
+  if (c->natural_launch) return c->S_natural;
+  return multi_layer && !c->single_launch && kvd_layers_share_launch(c) ? c->S : c->S1;
 }
 
 // The launch shape of the one-launch step.  What kvd_set_step_shape / kvd_calibrate_step_shape fixed
@@ -69,7 +70,7 @@ kvd_shape kvd_step_shape(const kvd_ctx* c, int multi_layer, const kvd_shape* wan
 // area; 1..8 groups.
 bool kvd_step_shape_ok(const kvd_ctx* c, const kvd_shape& e) {
   if (e.passes < 1 || e.passes > 8 || e.n_score < 1 || e.n_score > c->n_cus) return false;
-  if (e.splits < 1 || e.splits > (c->S > c->S1_max ? c->S : c->S1_max) || e.splits > c->k) return false;
+  if (e.splits < 1 || e.splits > kvd_most_splits(c) || e.splits > c->k) return false;
   if ((c->k + e.splits - 1) / e.splits > kvd::kAttnIdxCap) return false;
   if (e.groups < 1 || e.groups > 8) return false;
   return true;
@@ -81,7 +82,7 @@ bool kvd_step_shape_ok(const kvd_ctx* c, const kvd_shape& e) {
 static bool slots_have_own_lines(const kvd_ctx* c) { return (reinterpret_cast<uintptr_t>(c->pool) & 127u) == 0; }
 
 // Over natural slots (pages of a size that is neither a multiple of 16 nor 4 or 8) the library's own choice of form runs a
-// step as one launch too (kvd_step_form says 0; such a context takes no form -1 and no launch shape: it goes by the rule).  Three
+// step as one launch too (kvd_step_form says 0; such a context takes no form -1).  Three
 // launches were three chains of latencies (us per step as a chain and so: 32 units x 2084 pages of 24 tokens, G = 7, 28.3 and 23.7,
 // 8 x 500 of 100 24.9 and 22.2, 112 x 250 of 20 36.8 and 33.5, 8 units of 10417 26.6 and 26.4; with misses 32 x 750 of 12 73.6 and
 // 70.3, 8 x 1000 of 20 51.3 and 47.1, but 8 x 2000 of 6 43.7 and 44.4; per launch of 8 layers of 16 x 375 of 24 124.7 and 81.9,
@@ -154,9 +155,7 @@ hipError_t kvd_launch_step(kvd_ctx* c, int layer, int n_layers, int step, const 
   a.at.fuse_merge = 1;
   a.at.sel_entry = c->d_sel_entry;
   const bool natural = c->tiled == kLayoutNatural;
-  const kvd_shape by_rule = {0, 0, 0, 0};
-  kvd_shape shape = kvd_step_shape(c, n_layers > 1, natural ? &by_rule : nullptr, n_layers);
-  if (natural) shape.splits = c->natural_launch ? c->S_natural : c->S;   // (layers that step one by one as a chain: its splits)
+  const kvd_shape shape = kvd_step_shape(c, n_layers > 1, nullptr, n_layers);
   a.at.S = shape.splits;
   a.at.per_split = (c->k + shape.splits - 1) / shape.splits;
   // (the rule's number of splits, whether it was left to the rule or set: a shape that a context reports gives the same launch

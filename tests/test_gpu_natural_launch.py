@@ -143,3 +143,38 @@ def test_the_form_that_runs_is_the_one_reported():
     q = torch.stack([q[0] for q in W.query_stream(few, rig.q0, 2, R.DEV)]).contiguous()
     assert set(rig.kvd.calibrate_step_form(0, 0, q, 2, rig.out)[1]) == {1}
     rig.close()
+
+
+@pytest.mark.parametrize("shape", [(1, 5, 2, 1), (2, 7, 3, 2), (0, 0, 8, 0), (3, 200, 1, 4), (0, 0, 0, 0)])
+def test_the_launch_shape_that_is_reported_runs(shape):
+    w = small("natural-shape", page=20, ctx=20 * 1100, topk_pages=35, capacity=50, batch=3, n_kv_heads=2, n_q_heads=4, heavy_count=3,
+              n_layers=3, steps=3, rho=0.5)
+    seq = [w.ctx - 5 * b for b in range(w.batch)]
+    rig, one, chain = fresh(w, seq, 0), fresh(w, seq, 0), fresh(w, seq, 1)
+    for r in (rig, one):
+        r.kvd.set_step_shape(*shape)
+    rig.kvd.set_step_shape(*shape, multi_layer=True)
+    for multi in (False, True):
+        got = rig.kvd.step_shape(multi_layer=multi)
+        assert all(a == b for a, b in zip(got, shape) if b > 0) or shape[1] > got[1], got
+    out = torch.empty((w.n_layers, w.batch, w.n_q_heads, w.head_dim), dtype=torch.float32, device=R.DEV)
+    for t, q in enumerate(W.query_stream(w, rig.q0, w.steps, R.DEV)):
+        out.fill_(float("nan"))
+        rig.kvd.step_layers(0, w.n_layers, t, q, out)
+        for l in range(w.n_layers):
+            one.step(l, t, q[l])
+            chain.step(l, t, q[l])
+            assert torch.equal(out[l], one.out) and torch.equal(one.sel_slots, chain.sel_slots), (t, l)
+            assert float((one.out - chain.out).norm() / chain.out.norm()) < 1e-6
+    assert torch.equal(rig.pool, chain.pool)
+    one.kvd.set_profiling(2)
+    one.step(0, w.steps, q[0])
+    role = one.kvd.step_timeline()[:, 4] & 0xff
+    passes, n_score, splits, groups = one.kvd.step_shape()
+    assert int((role == 2).sum()) == splits * w.units and int((role == 0).sum()) == n_score * groups
+    with pytest.raises(K.KvdError):
+        rig.kvd.set_step_shape(passes=9)
+    with pytest.raises(K.KvdError):                       # shapes are calibrated in form -1 only
+        rig.kvd.calibrate_step_shape(0, w.steps, q[0], rig.out)
+    for r in (rig, one, chain):
+        r.close()
