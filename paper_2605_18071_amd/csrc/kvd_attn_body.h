@@ -711,6 +711,12 @@ __device__ __forceinline__ int attend_mfma_body(const AttnArgs& a, Smem& sm, int
         if (w >= n_tiles) return;
         Tile ta, tb2, tc;
         issue(ta, w);
+        // a tile to a wave, where the loads of two more that are not there cost their time (us per step with and without them:
+        // 4 units x 500 pages of 40 tokens 15.1 and 14.3, 2 x 170 of 12 14.2 and 13.4, 16 x 1000 of 20 16.2 and 15.3)
+        if (!decltype(exact)::value && n_tiles <= NW) {
+          compute(ta, exact);
+          return;
+        }
         issue(tb2, w + NW);
         for (int t = w;; t += 3 * NW) {
           issue(tc, t + 2 * NW);

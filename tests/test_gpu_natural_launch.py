@@ -178,3 +178,34 @@ def test_the_launch_shape_that_is_reported_runs(shape):
         rig.kvd.calibrate_step_shape(0, w.steps, q[0], rig.out)
     for r in (rig, one, chain):
         r.close()
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("k", [1, 10, 11, 21, 22, 43, 70])
+def test_tiles_of_a_split_and_of_its_waves(k, dtype):
+    """One split of k pages of 12 tokens: 1, 8, 9, 16, 17, 33 and 53 tiles for 8 waves; sequences that fill the selection, end in
+    its first tiles, and are a token long."""
+    w = small("natural-tiles", page=12, ctx=12 * 120, topk_pages=k, capacity=k + 9, batch=4, n_kv_heads=2, n_q_heads=6, heavy_count=0, steps=3,
+              dtype=dtype, rho=0.5)
+    seq = [w.ctx, 12 * max(1, k - 2) - 5, 12 * (k // 3) + 1, 1]
+    one, chain = (R.Rig(w, seq_lens=seq, micro_batches=mb, attn_splits=1) for mb in (0, 1))
+    assert one.kvd.step_form() == 0 and one.kvd.step_shape()[2] == 1
+    for t, q in enumerate(W.query_stream(w, one.q0, w.steps, R.DEV)):
+        one.out.fill_(float("nan"))
+        one.step(0, t, q[0])
+        chain.step(0, t, q[0])
+        assert torch.equal(one.sel_slots, chain.sel_slots)
+        assert float((one.out - chain.out).norm() / chain.out.norm()) < 1e-6 and float((one.lse - chain.lse).abs().max()) < 1e-4
+        # a selection that is all of its sequence: attention over it in fp64
+        for b in range(w.batch):
+            if -(-seq[b] // w.page) > k:
+                continue
+            kv = one.store[0, b].double()
+            K_, V_ = (kv[:, :, i].reshape(w.n_kv_heads, -1, 128)[:, :seq[b]] for i in (0, 1))
+            qb = q[0][b].double().cpu().view(w.n_kv_heads, w.group, 128)
+            logits = qb @ K_.transpose(1, 2) / 128 ** 0.5
+            want = (torch.softmax(logits, -1) @ V_).reshape(w.n_q_heads, 128)
+            got = one.out[b].double().cpu()
+            assert float((got - want).norm() / want.norm()) < 1e-5, (t, b)
+    one.close()
+    chain.close()
