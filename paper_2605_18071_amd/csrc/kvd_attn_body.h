@@ -708,6 +708,11 @@ __device__ __forceinline__ int attend_mfma_body(const AttnArgs& a, Smem& sm, int
       const int n_tiles = tiles_of(0);
       if constexpr (NATURAL) {
         auto issue = [&](Tile& tl, int t) { issue_tile(tl, 0, t, t < n_tiles); };
+        // Behind a tile without a valid token a launch's own selection, which is in the pages' order, has padding only: the wave
+        // is done.  (us per step of sequences with fewer pages than are selected, without and with it: 64 units, 50 of 300 pages of
+        // 12 tokens 28.1 and 25.6, 16 x 150 of 1000 of 20 31.3 and 31.0; full selections 0 to 0.4 % slower.  The tiles counted to the
+        // sequence's end beforehand instead 26.0 and 30.8, but 0.5 % slower where they are full, and 2 % in launches of 8 layers.)
+        auto none = [&](const Tile& next, int t) { return t >= n_tiles || (HANDOFF && next.valid == 0); };
         if (w >= n_tiles) return;
         Tile ta, tb2, tc;
         issue(ta, w);
@@ -721,13 +726,13 @@ __device__ __forceinline__ int attend_mfma_body(const AttnArgs& a, Smem& sm, int
         for (int t = w;; t += 3 * NW) {
           issue(tc, t + 2 * NW);
           compute(ta, exact);
-          if (t + NW >= n_tiles) break;
+          if (none(tb2, t + NW)) break;
           issue(ta, t + 3 * NW);
           compute(tb2, exact);
-          if (t + 2 * NW >= n_tiles) break;
+          if (none(tc, t + 2 * NW)) break;
           issue(tb2, t + 4 * NW);
           compute(tc, exact);
-          if (t + 3 * NW >= n_tiles) break;
+          if (none(ta, t + 3 * NW)) break;
         }
         return;
       }

@@ -181,13 +181,13 @@ def test_the_launch_shape_that_is_reported_runs(shape):
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
-@pytest.mark.parametrize("k", [1, 10, 11, 21, 22, 43, 70])
+@pytest.mark.parametrize("k", [1, 10, 11, 21, 22, 43, 70, 115])
 def test_tiles_of_a_split_and_of_its_waves(k, dtype):
-    """One split of k pages of 12 tokens: 1, 8, 9, 16, 17, 33 and 53 tiles for 8 waves; sequences that fill the selection, end in
+    """One split of k pages of 12 tokens: 1, 8, 9, 16, 17, 33, 53 and 87 tiles for 8 waves; sequences that fill the selection, end in
     its first tiles, and are a token long."""
     w = small("natural-tiles", page=12, ctx=12 * 120, topk_pages=k, capacity=k + 9, batch=4, n_kv_heads=2, n_q_heads=6, heavy_count=0, steps=3,
               dtype=dtype, rho=0.5)
-    seq = [w.ctx, 12 * max(1, k - 2) - 5, 12 * (k // 3) + 1, 1]
+    seq = [w.ctx, 12 * max(1, k - 2) - 5, 12 * (k // 3) + 1, 1]   # (waves that end before the split does)
     one, chain = (R.Rig(w, seq_lens=seq, micro_batches=mb, attn_splits=1) for mb in (0, 1))
     assert one.kvd.step_form() == 0 and one.kvd.step_shape()[2] == 1
     for t, q in enumerate(W.query_stream(w, one.q0, w.steps, R.DEV)):
