@@ -240,7 +240,7 @@ __device__ __forceinline__ u64 rank_candidates(int m, int r, FastSmem<NT, BIG>& 
 // entry (with a barrier since).  Returns the need-th smallest key among the candidates
 // (1 <= need <= number of candidates).  `refine(bin, r)` is called by all threads when the
 // decisive bucket holds more than kListCap items and must return the r-th smallest key of that
-// bucket.  Ends with the block synchronised.
+// bucket.  Other waves may still be reading the list on return: a barrier comes before sm.a is written again.
 template <int NT, int IPT, bool BIG, class KeyOf, class BktOf, class Refine>
 __device__ __forceinline__ u64 two_level_select(KeyOf key, BktOf bkt, int n_items, int need, FastSmem<NT, BIG>& sm, int& flip,
                                                 Refine refine) {
