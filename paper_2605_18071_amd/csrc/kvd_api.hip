@@ -33,7 +33,7 @@ static bool kvd_wants_single_launch(const kvd_ctx* c) {
 
 // The same choice over natural slots: whether form 0 is one launch there, and whether the context is to run it.
 static bool kvd_natural_launch_is_choice(const kvd_ctx* c) {
-  return kvd_natural_launch_ok(c) && (c->NP <= 8192 || c->U >= 8) && (c->k + c->S_natural - 1) / c->S_natural <= 512;
+  return kvd_natural_launch_ok(c) && (c->NP <= 8192 || c->U >= 8) && (c->k + c->S_natural - 1) / c->S_natural <= kvd::kAttnIdxCap;
 }
 static bool kvd_wants_natural_launch(const kvd_ctx* c) { return c->cfg.micro_batches == 0 && kvd_natural_launch_is_choice(c); }
 
@@ -266,20 +266,21 @@ int kvd_create(const kvd_config* cfg, kvd_ctx** out) {
   // The one-launch step runs one workgroup of 512 threads per CU, with 256 registers per lane (three
   // tile buffers in the attention role); its attention splits follow the rule of the stand-alone kernel, with the units'
   // selection workgroups beside them.
+  const int least_splits = (c->k + kvd::kAttnIdxCap - 1) / kvd::kAttnIdxCap;   // a split's entries are staged in LDS
   c->S1 = S;
   if (cfg->attn_splits == 0) {
     const int sel_tiles = (c->k * c->P + 15) / 16;      // 16-token tiles of a unit's selection
     const int least = c->P <= 16 && sel_tiles >= 32 ? 8 : 16;
     int S2 = kvd_attn_splits(least, c->U, c->k, c->P, c->n_cus, true);
     if (S2 > KVD_MAX_SPLITS) S2 = KVD_MAX_SPLITS;
-    if (S2 < (c->k + 511) / 512) S2 = (c->k + 511) / 512;   // a split's entries are staged in LDS, 512 at most
+    if (S2 < least_splits) S2 = least_splits;
     if (S2 > c->k) S2 = c->k;
     c->S1 = S2 < 1 ? 1 : S2;
   }
   c->S_natural = S;
   if (c->tiled == kvd::kLayoutNatural && cfg->attn_splits == 0) {
     int Sn = kvd_attn_splits(kNaturalLeast, c->U, c->k, c->P, c->n_cus, true, false);
-    if (Sn < (c->k + 511) / 512) Sn = (c->k + 511) / 512;
+    if (Sn < least_splits) Sn = least_splits;
     c->S_natural = Sn;
   }
   // room in the partials for the splits that kvd_set_step_shape takes and a calibration of the launch shape tries: twice

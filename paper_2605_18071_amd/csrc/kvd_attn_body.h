@@ -13,7 +13,6 @@
 
 namespace kvd {
 
-constexpr int kAttnIdxCap = 512;          // (page, slot) entries of a split kept in LDS
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
 

@@ -22,6 +22,7 @@ constexpr int KVD_MAX_CENTROIDS = 8192;   // centroids per unit of the hierarchi
 constexpr int KVD_TIMELINE_MAX = 1 << 16; // workgroups of a single-launch step whose times can be recorded
 
 namespace kvd {
+constexpr int kAttnIdxCap = 512;          // (page, slot) entries of a split kept in LDS
 struct FastArgs;
 struct AttnArgs;
 }  // namespace kvd
