@@ -61,6 +61,9 @@ def test_pages_of_any_number_of_pieces(page, ks, mb):
     (1536, 20, dict()),
     (1537, 2**31 - 200, dict()),                          # the last steps there are
     (2500, 0, dict(policy="lookahead", lookahead_pool=2600)),
+    (3076, 3, dict()),                                    # slots in loads of four: in the chain from 3073 on, in the launch from 3585
+    (3588, 8, dict(policy="lookahead")),
+    (3590, 8, dict()),                                    # a number of slots that is no multiple of four
     (4095, 30, dict()),
     (4096, 0, dict()),                                    # more pages of one class than a list holds
     (4096, 100, dict(policy="lookahead")),
