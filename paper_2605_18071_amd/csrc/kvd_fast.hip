@@ -15,19 +15,21 @@ __global__ __launch_bounds__(kFastThreads) void select_resolve_kernel(FastArgs a
   select_resolve_body<kFastThreads, IPT, DO_SELECT, DO_RESOLVE, false>(a, blockIdx.x + a.u0, sm);
 }
 
-template <bool DO_SELECT, bool DO_RESOLVE, bool HELD>
+template <bool DO_SELECT, bool DO_RESOLVE, int HELD>
 __global__ __launch_bounds__(kFastThreads) void select_resolve_big_kernel(FastArgs a) {
   __shared__ FastSmem<kFastThreads, true> sm;
   select_resolve_body<kFastThreads, 4, DO_SELECT, DO_RESOLVE, false, ScoresAlreadyThere, false, true, HELD>(a, blockIdx.x + a.u0, sm);
 }
 
 template <bool SEL, bool RES>
-static void launch_fast(bool big, int ipt, const FastArgs& a, int n_units, hipStream_t s) {
+static void launch_fast(bool big, bool by_quads, int ipt, const FastArgs& a, int n_units, hipStream_t s) {
   dim3 grid(n_units), block(kFastThreads);
-  if (big && SEL && ipt <= 32)
-    hipLaunchKernelGGL((select_resolve_big_kernel<SEL, RES, SEL>), grid, block, 0, s, a);
+  if (big && SEL && ipt <= 32 && by_quads)
+    hipLaunchKernelGGL((select_resolve_big_kernel<SEL, RES, SEL ? 2 : 0>), grid, block, 0, s, a);
+  else if (big && SEL && ipt <= 32)
+    hipLaunchKernelGGL((select_resolve_big_kernel<SEL, RES, SEL ? 1 : 0>), grid, block, 0, s, a);
   else if (big)
-    hipLaunchKernelGGL((select_resolve_big_kernel<SEL, RES, false>), grid, block, 0, s, a);
+    hipLaunchKernelGGL((select_resolve_big_kernel<SEL, RES, 0>), grid, block, 0, s, a);
   else if (ipt <= 4)
     hipLaunchKernelGGL((select_resolve_kernel<4, SEL, RES>), grid, block, 0, s, a);
   else if (ipt <= 8)
@@ -85,8 +87,14 @@ hipError_t kvd_launch_select_resolve(kvd_ctx* c, int layer, int step, bool do_se
   const FastArgs a = kvd_fast_args(c, layer, step, do_gather, scores, sel_pages, sel_slots, hit_mask, evicted, counts, u0);
   const int ipt = (c->NP + kFastThreads - 1) / kFastThreads;
   const bool big = kvd_fast_path_big(c);
-  if (do_select && do_resolve) launch_fast<true, true>(big, ipt, a, u1 - u0, s);
-  else if (do_select) launch_fast<true, false>(big, ipt, a, u1 - u0, s);
-  else launch_fast<false, true>(big, 4, a, u1 - u0, s);
+  // the selection by quads is a kernel of its own, since its code costs steps that do not take it up to 1 us (8 units of 16400
+  // pages, sequences of 10000, 29.4 and 28.7, of 15000 with 5000 slots 30.0 and 29.4).  It takes sequences of more pages than the
+  // ordinary form holds, as they are now: a captured launch selects the same when they have grown or been cut.
+  bool by_quads = false;
+  for (int b = u0 / c->Hkv; do_select && big && c->k <= kFastThreads && b * c->Hkv < u1; ++b)
+    by_quads |= c->h_seq_len[b] > KVD_FAST_MAX_PAGES * c->P;
+  if (do_select && do_resolve) launch_fast<true, true>(big, by_quads, ipt, a, u1 - u0, s);
+  else if (do_select) launch_fast<true, false>(big, by_quads, ipt, a, u1 - u0, s);
+  else launch_fast<false, true>(big, false, 4, a, u1 - u0, s);
   return hipGetLastError();
 }

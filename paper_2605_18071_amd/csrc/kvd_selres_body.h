@@ -28,6 +28,8 @@
 
 namespace kvd {
 
+struct NothingToDo { __device__ void operator()() const {} };
+
 constexpr int kListCap = 1024;
 constexpr uint16_t kAbsent = 0xffffu;
 
@@ -464,8 +466,10 @@ __device__ __forceinline__ void select_big(const FastArgs& a, int u, int seq, Fa
 // hardly more than pages are wanted, are listed and dealt out to the threads again, and only their pages are counted, compared and
 // ranked.  Bound by instruction issue (16 waves on one CU: 100 instructions a thread are 0.7 us), of which the three passes of
 // select_big need about 30 a page and this 3 a page and 20 a quad.  The selected pages are written from a map with four bits to
-// a quad's byte, 32 pages a thread, in one block scan instead of a wave scan per load.  False, with nothing done but
-// sm.a.sel.hist and sm.cand_n used, where more quads than the list holds reach the bucket (many pages alike): select_big then.
+// a quad's byte, 32 pages a thread, in one block scan instead of a wave scan per load.  Where more quads than the list holds reach
+// the bucket (many pages alike) the threads go through them where they are, in the registers.  (us per step, 8 units of 30000 pages of
+// 4 tokens, k = 500, with select_big, with select_big after the quads had been tried, and so: 1200 pages alike 125, 119 and
+// 118, 2500 131, 136 and 130, 9000 77.4, 85.9 and 76.9, all 99.6, 108.9 and 106.6, none 39.0, 35.6 and 35.6.)
 template <int NT>
 __device__ __forceinline__ void select_held_load(const FastArgs& a, int u, int seq, float4 (&s)[8]) {
   const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
@@ -495,7 +499,7 @@ __device__ __forceinline__ void select_held_load(const FastArgs& a, int u, int s
   }
 }
 template <int NT>
-__device__ __forceinline__ bool select_held(const FastArgs& a, int u, int seq, const float4 (&s)[8], FastSmem<NT, true>& sm, int& flip) {
+__device__ __forceinline__ void select_held(const FastArgs& a, int u, int seq, const float4 (&s)[8], FastSmem<NT, true>& sm, int& flip) {
   typedef FastSmem<NT, true> Smem;
   constexpr int NW = NT / kWave, Q = 8, kQuads = 2 * NT;   // quads of a lane, quads of the list
   constexpr int kHeldPages = 4 * Q * NT;
@@ -565,49 +569,19 @@ __device__ __forceinline__ bool select_held(const FastArgs& a, int u, int seq, c
       packed_bin_find<16>(hist_quads, k_free, last, before, in_last);
       n_listed = before + in_last;
     }
-    if (n_listed > kQuads) return false;
-    int mine = 0;
-#pragma unroll
-    for (int q = 0; q < Q; ++q) mine += bk[q] <= last ? 1 : 0;
-    const int inc = wave_inclusive_scan(mine);
-    int at = 0;
-    if (lane == kWave - 1) at = atomicAdd(&sm.cand_n, inc);
-    at = __builtin_amdgcn_readlane(at, kWave - 1) + inc - mine;
-#pragma unroll
-    for (int q = 0; q < Q; ++q)
-      if (bk[q] <= last) {
-        ls.score[at] = s[q];
-        ls.quad[at++] = page_of(q) >> 2;
-      }
-    __syncthreads();
-    // the listed quads, up to two a thread
-    float v[8];
-    int quad[2], pb[8];                                  // pages' buckets, 2048 = takes no part
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const bool on = tid + i * NT < n_listed;
-      quad[i] = on ? ls.quad[tid + i * NT] : -1;
-      const float4 x = on ? ls.score[tid + i * NT] : make_float4(0.f, 0.f, 0.f, 0.f);
-      const u32 fr = on ? free_of(4 * quad[i]) : 0u;
-      v[4 * i] = x.x; v[4 * i + 1] = x.y; v[4 * i + 2] = x.z; v[4 * i + 3] = x.w;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int j = 4 * i + e, bj = (fr >> e) & 1u ? bucket_of(v[j]) : 2048;
-        pb[j] = bj <= last ? bj : 2048;
-        if (pb[j] < 2048) packed_bin_add<16>(hist_pages, pb[j]);
-      }
-    }
-    __syncthreads();
-    int bin, below, m;
-    packed_bin_find<16>(hist_pages, k_free, bin, below, m);
-    const int r = k_free - below;                        // of the m pages of the decisive bucket r are in
-    auto key_of = [&](int j) -> u64 { return selection_order_key(v[j], 4 * quad[j >> 2] + (j & 3)); };
+    int bin, r;
     u64 thr = ~0ull;
-    if (r < m) {
+    // the pages up to bucket `last` are counted: the decisive bucket, and which of its pages are in; found() is told that `bin` is
+    // known, put_tied() puts the keys of this thread's pages there into the list
+    auto decide = [&](auto put_tied, auto found) {
+      __syncthreads();
+      int below, m;
+      packed_bin_find<16>(hist_pages, k_free, bin, below, m);
+      r = k_free - below;                                // of the m pages of the decisive bucket r are in
+      found();
+      if (r == m) return;
       if (m <= kListCap) {
-#pragma unroll
-        for (int j = 0; j < 8; ++j)
-          if (pb[j] == bin) sm.a.sel.cand[atomicAdd(&sm.tied_n, 1)] = key_of(j);
+        put_tied();
         if (m <= kWave / 2) {
           __syncthreads();
           thr = kth_of_list(sm.a.sel.cand, m, r);
@@ -624,17 +598,97 @@ __device__ __forceinline__ bool select_held(const FastArgs& a, int u, int seq, c
         };
         thr = block_kth_smallest<NT>(fn, n_valid, r, sm.generic, sm.a.sel.hist);
       }
-    }
+    };
+    if (n_listed <= kQuads) {
+      int mine = 0;
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      if (quad[i] < 0) continue;
-      u32 in = upto(4 * quad[i], n_valid) & ~free_of(4 * quad[i]);
+      for (int q = 0; q < Q; ++q) mine += bk[q] <= last ? 1 : 0;
+      const int inc = wave_inclusive_scan(mine);
+      int at = 0;
+      if (lane == kWave - 1) at = atomicAdd(&sm.cand_n, inc);
+      at = __builtin_amdgcn_readlane(at, kWave - 1) + inc - mine;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int j = 4 * i + e;
-        in |= pb[j] < bin || (pb[j] == bin && key_of(j) <= thr) ? 1u << e : 0u;
+      for (int q = 0; q < Q; ++q)
+        if (bk[q] <= last) {
+          ls.score[at] = s[q];
+          ls.quad[at++] = page_of(q) >> 2;
+        }
+      __syncthreads();
+      // the listed quads, up to two a thread
+      float v[8];
+      int quad[2], pb[8];                                // pages' buckets, 2048 = takes no part
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const bool on = tid + i * NT < n_listed;
+        quad[i] = on ? ls.quad[tid + i * NT] : -1;
+        const float4 x = on ? ls.score[tid + i * NT] : make_float4(0.f, 0.f, 0.f, 0.f);
+        const u32 fr = on ? free_of(4 * quad[i]) : 0u;
+        v[4 * i] = x.x; v[4 * i + 1] = x.y; v[4 * i + 2] = x.z; v[4 * i + 3] = x.w;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int j = 4 * i + e, bj = (fr >> e) & 1u ? bucket_of(v[j]) : 2048;
+          pb[j] = bj <= last ? bj : 2048;
+          if (pb[j] < 2048) packed_bin_add<16>(hist_pages, pb[j]);
+        }
       }
-      ls.picked[quad[i]] = (unsigned char)in;
+      auto key_of = [&](int j) -> u64 { return selection_order_key(v[j], 4 * quad[j >> 2] + (j & 3)); };
+      decide([&]() {
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+          if (pb[j] == bin) sm.a.sel.cand[atomicAdd(&sm.tied_n, 1)] = key_of(j);
+      }, NothingToDo());
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        if (quad[i] < 0) continue;
+        u32 in = upto(4 * quad[i], n_valid) & ~free_of(4 * quad[i]);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int j = 4 * i + e;
+          in |= pb[j] < bin || (pb[j] == bin && key_of(j) <= thr) ? 1u << e : 0u;
+        }
+        ls.picked[quad[i]] = (unsigned char)in;
+      }
+    } else {
+      // this thread's pages up to bucket `last`
+#pragma unroll
+      for (int q = 0; q < Q; ++q) {
+        if (bk[q] > last) continue;
+        const u32 fr = free_of(page_of(q));
+        const float x[4] = {s[q].x, s[q].y, s[q].z, s[q].w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int b = bucket_of(x[e]);
+          if (((fr >> e) & 1u) && b <= last) packed_bin_add<16>(hist_pages, b);
+        }
+      }
+      u32 in = 0, tied = 0;                              // bit 4q + e: page_of(q) + e lies before the decisive bucket, or in it
+      auto pages_of = [&](u32 bits, auto f) {            // (their scores come from memory again)
+        while (bits) {
+          const int bit = __ffs((int)bits) - 1;
+          bits &= bits - 1;
+          const int p = page_of(bit >> 2) + (bit & 3);
+          f(bit, selection_order_key(sc[p], p));
+        }
+      };
+      decide([&]() { pages_of(tied, [&](int, u64 key) { sm.a.sel.cand[atomicAdd(&sm.tied_n, 1)] = key; }); },
+             [&]() {
+#pragma unroll
+               for (int q = 0; q < Q; ++q) {
+                 const u32 fr = bk[q] <= last ? free_of(page_of(q)) : 0u;
+                 const float x[4] = {s[q].x, s[q].y, s[q].z, s[q].w};
+#pragma unroll
+                 for (int e = 0; e < 4; ++e) {
+                   const int b = (fr >> e) & 1u ? bucket_of(x[e]) : 2048;
+                   in |= b < bin ? 1u << (4 * q + e) : 0u;
+                   tied |= b == bin ? 1u << (4 * q + e) : 0u;
+                 }
+               }
+             });
+      if (thr == ~0ull) in |= tied;
+      else pages_of(tied, [&](int bit, u64 key) { in |= key <= thr ? 1u << bit : 0u; });
+#pragma unroll
+      for (int q = 0; q < Q; ++q)
+        if (bk[q] <= last) ls.picked[page_of(q) >> 2] |= (unsigned char)((in >> (4 * q)) & 15u);   // (beside its forced pages)
     }
   }
   __syncthreads();
@@ -655,7 +709,6 @@ __device__ __forceinline__ bool select_held(const FastArgs& a, int u, int seq, c
     sm.sel[i] = Smem::kNoPage;
     out[i] = -1;
   }
-  return true;
 }
 
 // All NT threads of a workgroup, for unit u.  DO_SELECT: scores -> sel_pages (Top-K, ties to the
@@ -674,11 +727,11 @@ __device__ __forceinline__ bool select_held(const FastArgs& a, int u, int seq, c
 // the hierarchical index's cluster selection, by the same workgroup — and leaves it in sm.sel
 // (16-bit pages, kAbsent = padding) and in a.sel_pages; nothing is read back from global memory.
 // BIG: more pages than the registers hold (NP <= KVD_BIG_MAX_PAGES whatever IPT, Cmax <= KVD_BIG_MAX_CAPACITY;
-// without HANDOFF): select_big takes the pages, slots are read again where they are needed.
+// without HANDOFF): select_big takes the pages, slots are read again where they are needed.  HELD: 1 the registers hold the
+// scores (NP <= 32 NT), 2 and k <= NT: sequences of more pages than the ordinary form holds are selected by quads.
 struct ScoresAlreadyThere { __device__ bool operator()() const { return true; } };
-struct NothingToDo { __device__ void operator()() const {} };
 template <int NT, int IPT, bool DO_SELECT, bool DO_RESOLVE, bool HANDOFF, class ScoresReady = ScoresAlreadyThere,
-          bool SEL_IN_LDS = false, bool BIG = false, bool HELD = false, class ScoresTaken = NothingToDo, int SLOTS = -1>
+          bool SEL_IN_LDS = false, bool BIG = false, int HELD = 0, class ScoresTaken = NothingToDo, int SLOTS = -1>
 __device__ __forceinline__ bool select_resolve_body(const FastArgs& a, int u, FastSmem<NT, BIG>& sm,
                                                     ScoresReady scores_ready = ScoresReady(), ScoresTaken scores_taken = ScoresTaken()) {
   static_assert(!(BIG && HANDOFF), "the big form is a kernel of its own");
@@ -736,8 +789,8 @@ __device__ __forceinline__ bool select_resolve_body(const FastArgs& a, int u, Fa
   auto page_of = [&](int j) -> int { return wave_p0 + (j >> 2) * (4 * kWave) + 4 * lane + (j & 3); };
   float s[BIG ? 4 : IPT];
   int seq = 0;
-  bool try_held = false;
-  float4 held[HELD ? 8 : 1];
+  bool by_quads = false;
+  float4 held[HELD == 2 ? 8 : 1];
   auto load_scores = [&]() {
     const float* sc = a.scores + (size_t)u * a.NP;
     if ((a.NP & 3) == 0) {
@@ -762,11 +815,11 @@ __device__ __forceinline__ bool select_resolve_body(const FastArgs& a, int u, Fa
   if (DO_SELECT) {
     if (!HANDOFF && !BIG) load_scores();                       // (with HANDOFF the scores may not be complete yet)
     seq = a.seq_len[b];
-    if constexpr (HELD) {
+    if constexpr (HELD == 2) {
       // (not where select_big's passes are few, nor for selections of which the list might not hold the quads: 16 units of 7500
       // pages 31.9 us a step with it and 33.3 with this, 2048 of 17500 pages 47.8 and 52.1)
-      try_held = seq > KVD_FAST_MAX_PAGES * a.P && k <= NT;
-      if (try_held) select_held_load<NT>(a, u, seq, held);
+      by_quads = seq > KVD_FAST_MAX_PAGES * a.P;
+      if (by_quads) select_held_load<NT>(a, u, seq, held);
     }
   } else if (!SEL_IN_LDS) {
     for (int i = tid; i < k; i += NT) {
@@ -846,17 +899,11 @@ __device__ __forceinline__ bool select_resolve_body(const FastArgs& a, int u, Fa
 
   // ---- selection
   if constexpr (DO_SELECT && BIG) {
-    bool done = false;
-    if constexpr (HELD) {
-      if (try_held) done = select_held<NT>(a, u, seq, held, sm, flip);
-      if (try_held && !done) {
-        __syncthreads();                                 // (the histogram has been read)
-        for (int i = tid; i < kHistWords; i += NT) sm.a.sel.hist[i] = 0;
-        if (tid == 0) sm.cand_n = 0;
-        __syncthreads();
-      }
+    if (HELD == 2 && by_quads) {
+      if constexpr (HELD == 2) select_held<NT>(a, u, seq, held, sm, flip);
+    } else {
+      select_big<NT, HELD != 0>(a, u, seq, sm, flip);
     }
-    if (!done) select_big<NT, HELD>(a, u, seq, sm, flip);
     if (!DO_RESOLVE) return true;
   } else if constexpr (DO_SELECT) {
     constexpr int kBinWords = IPT == 4 ? 8 : 16;       // 1024 or 2048 buckets

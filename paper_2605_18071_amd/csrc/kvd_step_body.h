@@ -210,10 +210,10 @@ __device__ __forceinline__ void step_select_role(StepArgsPtr ap, int li, int u, 
       __syncthreads();                                 // the selection is complete
       return true;
     };
-    done = select_resolve_body<NT, 4, false, true, true, decltype(select_clusters), true, false, false, NothingToDo, LAYOUT>(a.fa, u, sm, select_clusters);
+    done = select_resolve_body<NT, 4, false, true, true, decltype(select_clusters), true, false, 0, NothingToDo, LAYOUT>(a.fa, u, sm, select_clusters);
   } else {
     auto scores_ready = [&]() -> bool { return wave_wait_equal(&a.score_done[u * kFlagStride], arrivals, a.wait_limit); };
-    done = select_resolve_body<NT, IPT, true, true, true, decltype(scores_ready), false, false, false, decltype(scores_taken), LAYOUT>(
+    done = select_resolve_body<NT, IPT, true, true, true, decltype(scores_ready), false, false, 0, decltype(scores_taken), LAYOUT>(
         a.fa, u, sm, scores_ready, scores_taken);
   }
   if (!done) {

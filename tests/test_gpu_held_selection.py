@@ -66,6 +66,9 @@ def test_equals_the_size_agnostic_kernels(pages, same, k, kw, monkeypatch):
     (20000, 4, dict(sink_pages=2), {5000: 3e38, 2: 2e38, 3: 2e38}),                         # ... beside forced pages
     (20000, 4, dict(recent_pages=2), {5000: 3e38, -4: 2e38, -3: 2e38}),
     (20002, 2, dict(), {5000: 3e38, -2: 2e38, -1: 2e38}),                                   # ... at the end of the sequence
+    (20000, 40, dict(sink_pages=3), {p: np.inf for p in range(3001, 15000)}),               # more quads than are listed, all in the first bucket
+    (32767, 1024, dict(recent_pages=9), {**{p: 2e38 for p in range(5, 9500)}, 9000: 3e38}),  # ... in a later one
+    (30000, 700, dict(sink_pages=1), {p: 1e38 + 1e36 * (p % 300) for p in range(1, 30000, 3)}),   # ... of which few are in doubt
     (16385, 3, dict(), {5000: -1e38, 16384: 3e38, 8000: 3e38, 8001: 3.2e38, 8002: -3e38, 8003: -3e38}),   # the range overflows
 ])
 def test_scores_whose_sums_overflow(pages, k, kw, at, monkeypatch):
@@ -77,7 +80,7 @@ def test_scores_whose_sums_overflow(pages, k, kw, at, monkeypatch):
     gen = np.random.default_rng(pages + k)
     values = torch.from_numpy(gen.random((w.units, pages), dtype=np.float32) * np.float32(9e37)).to(w.torch_dtype)
     for page, v in at.items():
-        values[:, page] = v
+        values[:, page] = float(v)
     rig.summaries.zero_()
     rig.summaries.view(w.units, pages, 128)[:, :, 0] = values.to(R.DEV)
     q = torch.zeros((w.batch, w.n_q_heads, 128), dtype=w.torch_dtype, device=R.DEV)
@@ -95,3 +98,31 @@ def test_scores_whose_sums_overflow(pages, k, kw, at, monkeypatch):
     rig.kvd.score_select(0, q, alone)
     assert np.array_equal(alone.cpu().numpy(), want)
     rig.close()
+
+
+@pytest.mark.parametrize("lens", [(9000, 60001), (68000, 40000), (65536, 65537)])
+def test_a_captured_selection_of_sequences_that_grow_and_are_cut(lens):
+    """The kernel that a capture records is that of the lengths at that time; it selects the same of others."""
+    w = small("held-captured", ctx=4 * 17001, page=4, topk_pages=200, capacity=240, batch=2, n_kv_heads=1, n_q_heads=4, heavy_count=0, steps=3)
+    rig, eager = R.Rig(w, seq_lens=[lens[0]] * 2), R.Rig(w, seq_lens=[lens[0]] * 2)
+    q = torch.zeros((w.batch, w.n_q_heads, 128), dtype=w.torch_dtype, device=R.DEV)
+    s = torch.cuda.Stream()
+    rig.kvd.score_select(0, q, rig.sel_pages, rig.scores, stream=s)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=s):
+        rig.kvd.score_select(0, q, rig.sel_pages, rig.scores, stream=s)
+    for t, query in enumerate(W.query_stream(w, rig.q0, w.steps, R.DEV)):
+        for n in (lens[0], lens[1], lens):
+            n = list(n) if isinstance(n, tuple) else [n, n]
+            for r in (rig, eager):
+                r.kvd.set_seq_lens(n)
+            q.copy_(query[0])
+            rig.sel_pages.fill_(-7)
+            torch.cuda.synchronize()
+            graph.replay()
+            eager.kvd.score_select(0, query[0], eager.sel_pages, eager.scores)
+            torch.cuda.synchronize()
+            assert torch.equal(rig.scores, eager.scores) and torch.equal(rig.sel_pages, eager.sel_pages), (t, n)
+    rig.close()
+    eager.close()
