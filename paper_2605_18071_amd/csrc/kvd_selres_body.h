@@ -731,7 +731,7 @@ __device__ __forceinline__ void select_held(const FastArgs& a, int u, int seq, c
 // scores (NP <= 32 NT), 2 and k <= NT: sequences of more pages than the ordinary form holds are selected by quads.
 struct ScoresAlreadyThere { __device__ bool operator()() const { return true; } };
 template <int NT, int IPT, bool DO_SELECT, bool DO_RESOLVE, bool HANDOFF, class ScoresReady = ScoresAlreadyThere,
-          bool SEL_IN_LDS = false, bool BIG = false, int HELD = 0, class ScoresTaken = NothingToDo, int SLOTS = -1>
+          bool SEL_IN_LDS = false, bool BIG = false, int HELD = 0, class ScoresTaken = NothingToDo, int SLOTS = -1, bool SLOT_QUADS = true>
 __device__ __forceinline__ bool select_resolve_body(const FastArgs& a, int u, FastSmem<NT, BIG>& sm,
                                                     ScoresReady scores_ready = ScoresReady(), ScoresTaken scores_taken = ScoresTaken()) {
   static_assert(!(BIG && HANDOFF), "the big form is a kernel of its own");
@@ -758,8 +758,9 @@ __device__ __forceinline__ bool select_resolve_body(const FastArgs& a, int u, Fa
     if constexpr (!BIG) {
       // (slots beyond the window: -2 below.  As many slots as a thread holds come in loads of four, where every unit's start on 16 bytes: loads
       // of one word ask for the same 16 lines again each time.  us per step, all resident, 8 units of 4100 pages, windows of 3600
-      // and 4000 slots 17.8 and 18.3 a word at a time, 17.1 and 17.1 so; lookahead eviction 19.9 and 18.6.)
-      if (cpt == CPT && (a.Cmax & 3) == 0) {
+      // and 4000 slots 17.8 and 18.3 a word at a time, 17.1 and 17.1 so; lookahead eviction 19.9 and 18.6.  Not
+      // in launches of several layers, which hide those loads and lose up to 0.7 % by the code: 6 layers of 16 units 61.5 and 61.9.)
+      if (SLOT_QUADS && cpt == CPT && (a.Cmax & 3) == 0) {
 #pragma unroll
         for (int j = 0; j < CPT; j += 4) {
           const int s = tid * CPT + j, at = s < a.Cmax ? s : a.Cmax - 4;

@@ -160,7 +160,7 @@ __device__ __forceinline__ void step_score_role(StepArgsPtr ap, int li, int u0, 
 
 // Selection, directory update and fetch of unit u: latency-bound, so its waves go first whenever
 // they can issue.
-template <int NT, int IPT, int LAYOUT>
+template <int NT, int IPT, int LAYOUT, bool MANY>
 __device__ __forceinline__ void step_select_role(StepArgsPtr ap, int li, int u, unsigned char* smem_raw, int* wait_ok,
                                                            long long* ts) {
   struct { FastArgs fa; int32_t* score_done; int32_t* error; long long wait_limit; int chunks; } a;
@@ -210,10 +210,10 @@ __device__ __forceinline__ void step_select_role(StepArgsPtr ap, int li, int u, 
       __syncthreads();                                 // the selection is complete
       return true;
     };
-    done = select_resolve_body<NT, 4, false, true, true, decltype(select_clusters), true, false, 0, NothingToDo, LAYOUT>(a.fa, u, sm, select_clusters);
+    done = select_resolve_body<NT, 4, false, true, true, decltype(select_clusters), true, false, 0, NothingToDo, LAYOUT, !MANY>(a.fa, u, sm, select_clusters);
   } else {
     auto scores_ready = [&]() -> bool { return wave_wait_equal(&a.score_done[u * kFlagStride], arrivals, a.wait_limit); };
-    done = select_resolve_body<NT, IPT, true, true, true, decltype(scores_ready), false, false, 0, decltype(scores_taken), LAYOUT>(
+    done = select_resolve_body<NT, IPT, true, true, true, decltype(scores_ready), false, false, 0, decltype(scores_taken), LAYOUT, !MANY>(
         a.fa, u, sm, scores_ready, scores_taken);
   }
   if (!done) {
@@ -283,7 +283,7 @@ __device__ __forceinline__ void step_body(StepArgsPtr ap, unsigned char* smem_ra
   } else if (o < n_score) {
     step_score_role<BF16, NT>(ap, li, u0, n_units, o, smem_raw, ts);
   } else {
-    if (o - n_score < n_units) step_select_role<NT, IPT, LAYOUT>(ap, li, o - n_score + u0, smem_raw, &wait_ok, ts);
+    if (o - n_score < n_units) step_select_role<NT, IPT, LAYOUT, MANY>(ap, li, o - n_score + u0, smem_raw, &wait_ok, ts);
   }
 }
 
