@@ -83,10 +83,10 @@ static bool slots_have_own_lines(const kvd_ctx* c) { return (reinterpret_cast<ui
 
 // Over natural slots (pages of a size that is neither a multiple of 16 nor 4 or 8) the library's own choice of form runs a
 // step as one launch too (kvd_step_form says 0; such a context takes no form -1).  Three
-// launches were three chains of latencies (us per step as a chain and so: 32 units x 2084 pages of 24 tokens, G = 7, 28.3 and 23.7,
-// 8 x 500 of 100 24.9 and 22.2, 112 x 250 of 20 36.8 and 33.5, 8 units of 10417 26.6 and 26.4; with misses 32 x 750 of 12 73.6 and
-// 70.3, 8 x 1000 of 20 51.3 and 47.1, but 8 x 2000 of 6 43.7 and 44.4; per launch of 8 layers of 16 x 375 of 24 124.7 and 81.9,
-// of 4 layers of 2 x 10417 77.9 and 25.9).
+// launches were three chains of latencies (us per step as a chain and so: 32 units x 2084 pages of 24 tokens, G = 7, 26.4 and 23.0,
+// 16 x 500 of 100 23.8 and 21.4, 112 x 250 of 20 35.8 and 32.5, 8 units of 10417 25.9 and 25.0; with misses 32 x 750 of 12 70.9 and
+// 67.2, 8 x 1000 of 20 46.9 and 44.4, 8 x 2000 of 6 42.4 and 40.7; per launch of 8 layers of 16 x 375 of 24 127.6 and 77.3,
+// of 4 layers of 2 x 10417 85.0 and 24.5).
 bool kvd_natural_launch_ok(const kvd_ctx* c) {
   return c->tiled == kvd::kLayoutNatural && kvd_fast_path_ok(c) && !kvd_fast_path_big(c) && slots_have_own_lines(c);
 }
