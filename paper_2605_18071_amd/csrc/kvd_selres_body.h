@@ -469,7 +469,7 @@ __device__ __forceinline__ void select_big(const FastArgs& a, int u, int seq, Fa
 // a quad's byte, 32 pages a thread, in one block scan instead of a wave scan per load.  Where more quads than the list holds reach
 // the bucket (many pages alike) the threads go through them where they are, in the registers.  (us per step, 8 units of 30000 pages of
 // 4 tokens, k = 500, with select_big, with select_big after the quads had been tried, and so: 1200 pages alike 125, 119 and
-// 118, 2500 131, 136 and 130, 9000 77.4, 85.9 and 76.9, all 99.6, 108.9 and 106.6, none 39.0, 35.6 and 35.6.)
+// 118, 2500 131, 136 and 131, 9000 77.1, 86.2 and 77.7, half of them 78.9, 89.2 and 83.5, all 99.5, 110 and 79.0, none 39.0, 35.7 and 35.5.)
 template <int NT>
 __device__ __forceinline__ void select_held_load(const FastArgs& a, int u, int seq, float4 (&s)[8]) {
   const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
@@ -556,15 +556,16 @@ __device__ __forceinline__ void select_held(const FastArgs& a, int u, int seq, c
     const float range = fmax - fmin;
     const float inv = range > 0.f ? 2047.0f / range : 0.f;
     auto bucket_of = [&](float v) -> int { return (int)fminf(fmaxf((fmax - v) * inv, 0.f), 2047.f); };
+    const bool one_bucket = inv == 0.f;                  // (one score for all, or infinities: nothing to count)
     int bk[Q];
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
       bk[q] = q < nq && free_of(page_of(q)) ? ((first >> q) & 1u ? 0 : bucket_of(best[q])) : 2048;
-      if (bk[q] < 2048) packed_bin_add<16>(hist_quads, bk[q]);
+      if (bk[q] < 2048 && !one_bucket) packed_bin_add<16>(hist_quads, bk[q]);
     }
     __syncthreads();
     int last = 2047, n_listed = free_quads;              // the quads up to bucket `last` are listed
-    if (k_free <= free_quads) {
+    if (k_free <= free_quads && !one_bucket) {
       int before, in_last;
       packed_bin_find<16>(hist_quads, k_free, last, before, in_last);
       n_listed = before + in_last;
@@ -576,7 +577,8 @@ __device__ __forceinline__ void select_held(const FastArgs& a, int u, int seq, c
     auto decide = [&](auto put_tied, auto found) {
       __syncthreads();
       int below, m;
-      packed_bin_find<16>(hist_pages, k_free, bin, below, m);
+      bin = 0; below = 0; m = n_free;
+      if (!one_bucket) packed_bin_find<16>(hist_pages, k_free, bin, below, m);
       r = k_free - below;                                // of the m pages of the decisive bucket r are in
       found();
       if (r == m) return;
@@ -658,7 +660,7 @@ __device__ __forceinline__ void select_held(const FastArgs& a, int u, int seq, c
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           const int b = bucket_of(x[e]);
-          if (((fr >> e) & 1u) && b <= last) packed_bin_add<16>(hist_pages, b);
+          if (((fr >> e) & 1u) && b <= last && !one_bucket) packed_bin_add<16>(hist_pages, b);
         }
       }
       u32 in = 0, tied = 0;                              // bit 4q + e: page_of(q) + e lies before the decisive bucket, or in it
