@@ -171,7 +171,7 @@ __device__ __forceinline__ void find_bucket(int need, FastSmem<NT, BIG>& sm, int
   __syncthreads();
 }
 
-// A histogram of 128 * W buckets, two 16-bit counts to a word (a unit of the ordinary form has at most 16384 items): lane l
+// A histogram of 128 * W buckets, two 16-bit counts to a word (of at most 32768 items): lane l
 // of a wave reads the 2 W buckets from 2 W l on with W / 4 16-byte loads without bank conflicts.
 template <int W>
 __device__ __forceinline__ int packed_bin_word(int bucket) {
@@ -179,8 +179,8 @@ __device__ __forceinline__ int packed_bin_word(int bucket) {
   return (((word >> 2) * kWave + l) << 2) | (word & 3);
 }
 template <int W>
-__device__ __forceinline__ void packed_bin_add(u32* hist, int bucket) {
-  atomicAdd(&hist[packed_bin_word<W>(bucket)], 1u << (16 * (bucket & 1)));
+__device__ __forceinline__ void packed_bin_add(u32* hist, int bucket, u32 n = 1u) {
+  atomicAdd(&hist[packed_bin_word<W>(bucket)], n << (16 * (bucket & 1)));
 }
 // The bucket that holds the need-th smallest item, the items before it and those in it, the same in every lane.  Each
 // wave finds out for itself: no barrier and nothing handed around.  The histogram is complete (a barrier before).
@@ -468,8 +468,8 @@ __device__ __forceinline__ void select_big(const FastArgs& a, int u, int seq, Fa
 // select_big need about 30 a page and this 3 a page and 20 a quad.  The selected pages are written from a map with four bits to
 // a quad's byte, 32 pages a thread, in one block scan instead of a wave scan per load.  Where more quads than the list holds reach
 // the bucket (many pages alike) the threads go through them where they are, in the registers.  (us per step, 8 units of 30000 pages of
-// 4 tokens, k = 500, with select_big, with select_big after the quads had been tried, and so: 1200 pages alike 125, 119 and
-// 118, 2500 131, 136 and 131, 9000 77.1, 86.2 and 77.7, half of them 78.9, 89.2 and 83.5, all 99.5, 110 and 79.0, none 39.0, 35.7 and 35.5.)
+// 4 tokens, k = 500, with select_big and so: 1200 pages alike 65.5 and 60.4, 2500 67.8 and 66.5, 9000 74.5 and 71.3, half
+// of them 77.8 and 73.7 (83.7 with the pages of the last bucket counted one by one), all 100.0 and 79.3, none 38.6 and 35.1.)
 template <int NT>
 __device__ __forceinline__ void select_held_load(const FastArgs& a, int u, int seq, float4 (&s)[8]) {
   const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
@@ -651,7 +651,9 @@ __device__ __forceinline__ void select_held(const FastArgs& a, int u, int seq, c
         ls.picked[quad[i]] = (unsigned char)in;
       }
     } else {
-      // this thread's pages up to bucket `last`
+      // this thread's pages up to bucket `last`; those in it, which are most of them, are counted by the wave (one by one they wait for
+      // each other at one word)
+      int at_last = 0;
 #pragma unroll
       for (int q = 0; q < Q; ++q) {
         if (bk[q] > last) continue;
@@ -659,10 +661,13 @@ __device__ __forceinline__ void select_held(const FastArgs& a, int u, int seq, c
         const float x[4] = {s[q].x, s[q].y, s[q].z, s[q].w};
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          const int b = bucket_of(x[e]);
-          if (((fr >> e) & 1u) && b <= last && !one_bucket) packed_bin_add<16>(hist_pages, b);
+          const int b = (fr >> e) & 1u ? bucket_of(x[e]) : 2048;
+          at_last += b == last ? 1 : 0;
+          if (b < last && !one_bucket) packed_bin_add<16>(hist_pages, b);
         }
       }
+      at_last = wave_inclusive_scan(at_last);
+      if (lane == kWave - 1 && at_last > 0 && !one_bucket) packed_bin_add<16>(hist_pages, last, (u32)at_last);
       u32 in = 0, tied = 0;                              // bit 4q + e: page_of(q) + e lies before the decisive bucket, or in it
       auto pages_of = [&](u32 bits, auto f) {            // (their scores come from memory again)
         while (bits) {

@@ -25,6 +25,7 @@ if torch.cuda.is_available():
     (20000, 600, 333, dict(sink_pages=2, recent_pages=330, dtype="f16")),
     (24576, 2500, 64, dict()),                            # 2500 pages alike: the list of tied pages is too short for them
     (28672, 9000, 500, dict()),                           # more quads alike than are listed
+    (29999, 15000, 1000, dict(sink_pages=3, recent_pages=5)),    # two scores
     (30001, 30001, 90, dict()),                           # one score for all
     (25000, 1, 300, dict(values=True)),                   # scores of both infinities and none
     (25000, 1, 300, dict(none=True)),                     # scores that are no numbers
