@@ -88,8 +88,8 @@ hipError_t kvd_launch_select_resolve(kvd_ctx* c, int layer, int step, bool do_se
   const int ipt = (c->NP + kFastThreads - 1) / kFastThreads;
   const bool big = kvd_fast_path_big(c);
   // the selection by quads is a kernel of its own, since its code costs steps that do not take it up to 1 us (8 units of 16400
-  // pages, sequences of 10000, 29.4 and 28.7, of 15000 with 5000 slots 30.0 and 29.4).  It takes sequences of more pages than the
-  // ordinary form holds, as they are now: a captured launch selects the same when they have grown or been cut.
+  // pages, sequences of 10000, 29.4 and 28.7, of 15000 with 5000 slots 30.0 and 29.4).  It is launched for sequences of more pages
+  // than the ordinary form holds, as they are now: a captured launch selects the same when they have grown or been cut.
   bool by_quads = false;
   for (int b = u0 / c->Hkv; do_select && big && c->k <= kFastThreads && b * c->Hkv < u1; ++b)
     by_quads |= c->h_seq_len[b] > KVD_FAST_MAX_PAGES * c->P;

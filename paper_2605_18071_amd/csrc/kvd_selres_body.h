@@ -735,7 +735,7 @@ __device__ __forceinline__ void select_held(const FastArgs& a, int u, int seq, c
 // (16-bit pages, kAbsent = padding) and in a.sel_pages; nothing is read back from global memory.
 // BIG: more pages than the registers hold (NP <= KVD_BIG_MAX_PAGES whatever IPT, Cmax <= KVD_BIG_MAX_CAPACITY;
 // without HANDOFF): select_big takes the pages, slots are read again where they are needed.  HELD: 1 the registers hold the
-// scores (NP <= 32 NT), 2 and k <= NT: sequences of more pages than the ordinary form holds are selected by quads.
+// scores (NP <= 32 NT), 2 and k <= NT: sequences of more than 12 NT pages are selected by quads.
 struct ScoresAlreadyThere { __device__ bool operator()() const { return true; } };
 template <int NT, int IPT, bool DO_SELECT, bool DO_RESOLVE, bool HANDOFF, class ScoresReady = ScoresAlreadyThere,
           bool SEL_IN_LDS = false, bool BIG = false, int HELD = 0, class ScoresTaken = NothingToDo, int SLOTS = -1, bool SLOT_QUADS = true>
@@ -825,8 +825,10 @@ __device__ __forceinline__ bool select_resolve_body(const FastArgs& a, int u, Fa
     seq = a.seq_len[b];
     if constexpr (HELD == 2) {
       // (not where select_big's passes are few, nor for selections of which the list might not hold the quads: 16 units of 7500
-      // pages 31.9 us a step with it and 33.3 with this, 2048 of 17500 pages 47.8 and 52.1)
-      by_quads = seq > KVD_FAST_MAX_PAGES * a.P;
+      // pages 31.9 us a step with it and 33.3 with this, 2048 of 17500 pages 47.8 and 52.1.  Sequences that fill four loads of every
+      // thread are not left to it beside a longer one, or the launch ends with them: one of 17000 pages and seven of 11000 pages
+      // 34.6 either way, of 13000 35.6 with it and 34.7 with this, of 16300 35.8 and 34.7; all with the three passes alone 36.0.)
+      by_quads = seq > 12 * NT * a.P;
       if (by_quads) select_held_load<NT>(a, u, seq, held);
     }
   } else if (!SEL_IN_LDS) {

@@ -127,3 +127,29 @@ def test_a_captured_selection_of_sequences_that_grow_and_are_cut(lens):
             assert torch.equal(rig.scores, eager.scores) and torch.equal(rig.sel_pages, eager.sel_pages), (t, n)
     rig.close()
     eager.close()
+
+
+@pytest.mark.parametrize("same,k,kw", [(1, 1024, dict()), (40, 300, dict(sink_pages=2, recent_pages=7)), (9000, 64, dict())])
+def test_shorter_sequences_beside_a_long_one(same, k, kw, monkeypatch):
+    """Sequences on both sides of the number of pages from which they are selected by quads too."""
+    monkeypatch.delenv("KVD_GENERIC_SELECT", raising=False)
+    w = small("held-mixed", **{**dict(ctx=4 * 16386, page=4, topk_pages=k, capacity=k + 9, batch=6, n_kv_heads=1, n_q_heads=4, heavy_count=0,
+                                      steps=2), **kw})
+    seq = [w.ctx, 4 * 12288, 4 * 12288 + 1, 4 * 12289, 4 * 15000 - 1, 4 * 700]
+    fused = R.Rig(w, seq_lens=seq, build_index=False)
+    monkeypatch.setenv("KVD_GENERIC_SELECT", "1")
+    plain = R.Rig(w, seq_lens=seq, micro_batches=1, build_index=False)
+    gen = torch.Generator(device=R.DEV)
+    gen.manual_seed(same + k)
+    rows = max(1, w.n_pages // same)
+    base = torch.randn(w.units, rows, 128, device=R.DEV, generator=gen)
+    summ = base[:, torch.randperm(w.n_pages, device=R.DEV, generator=gen) % rows].to(w.torch_dtype)
+    for r in (fused, plain):
+        r.summaries.copy_(summ.view(r.summaries.shape))
+    for t, q in enumerate(W.query_stream(w, fused.q0, w.steps, R.DEV)):
+        fused.step(0, t, q[0])
+        plain.step(0, t, q[0])
+        for what in ("n_scores", "n_sel_pages", "n_hit_mask", "n_sel_slots", "n_counts"):
+            assert np.array_equal(getattr(fused, what), getattr(plain, what), equal_nan=what == "n_scores"), (what, t)
+    fused.close()
+    plain.close()
