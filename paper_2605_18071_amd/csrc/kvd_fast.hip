@@ -47,7 +47,7 @@ bool kvd_fast_path_ok(const kvd_ctx* c) {
 bool kvd_fast_path_big(const kvd_ctx* c) { return c->NP > KVD_FAST_MAX_PAGES || c->Cmax > KVD_FAST_MAX_CAPACITY; }
 
 kvd::FastArgs kvd_fast_args(kvd_ctx* c, int layer, int step, bool do_gather, const float* scores, int32_t* sel_pages,
-                            int32_t* sel_slots, int32_t* hit_mask, int32_t* evicted, int32_t* counts, int u0) {
+                            int32_t* sel_slots, int32_t* hit_mask, int32_t* evicted, int32_t* counts, int u0, int n_layers) {
   kvd::FastArgs a;
   const size_t lu = (size_t)layer * c->U;
   a.scores = scores;
@@ -76,6 +76,7 @@ kvd::FastArgs kvd_fast_args(kvd_ctx* c, int layer, int step, bool do_gather, con
   a.page_cluster = c->Nc > 0 ? c->d_page_cluster + lu * c->NP : nullptr;
   a.score_stride = c->Nc > 0 ? c->Nc : c->NP;
   a.page_bytes = (unsigned)c->page_bytes;
+  a.shallow_fetch = n_layers * c->U >= 48 ? 1 : 0;
   return a;
 }
 

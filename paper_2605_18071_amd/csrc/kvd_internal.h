@@ -139,7 +139,7 @@ hipError_t kvd_launch_select_resolve(kvd_ctx* c, int layer, int step, bool do_se
                                      const float* scores, int32_t* sel_pages, int32_t* sel_slots, int32_t* hit_mask,
                                      int32_t* evicted, int32_t* counts, int u0, int u1, hipStream_t s);
 kvd::FastArgs kvd_fast_args(kvd_ctx* c, int layer, int step, bool do_gather, const float* scores, int32_t* sel_pages,
-                            int32_t* sel_slots, int32_t* hit_mask, int32_t* evicted, int32_t* counts, int u0);
+                            int32_t* sel_slots, int32_t* hit_mask, int32_t* evicted, int32_t* counts, int u0, int n_layers = 1);
 kvd::AttnArgs kvd_attn_args(kvd_ctx* c, int layer, const void* q, const int32_t* sel_pages, const int32_t* sel_slots,
                             float* out, float* lse, int u0);
 // Copies the missed pages of units [u0, u1) into their slots: from the pinned host store, or, with

@@ -58,6 +58,7 @@ struct FastArgs {
   const int32_t* page_cluster;  // [U][NP] or null: the victims' scores are those of the pages' clusters
   int score_stride;           // scores of unit u start at scores + u * score_stride (NP, or the number of centroids)
   unsigned page_bytes;
+  int shallow_fetch;          // many units fetch at the same time: each with less on its way
 };
 
 // What the attention workgroups of the same launch read instead of sel_pages / sel_slots: one
@@ -1331,46 +1332,64 @@ __device__ __forceinline__ bool select_resolve_body(const FastArgs& a, int u, Fa
   // under a condition was waited for at once, where its register is joined with that of the other way.)
   // (at / pieces by the reciprocal rounded up: exact below 2^32 / pieces^2, and at most 2048 pages have 128 pieces each)
   const u32 recip = 0xffffffffu / (u32)pieces + 1u;    // (0 for one piece)
+  const int w0 = __builtin_amdgcn_readfirstlane(w);      // (the compiler does not see that it is one number to a wave, and would load lane by lane)
   struct Piece { const char* src; char* dst; u32 bytes; int piece; };
-  auto item = [&](int it) -> Piece {
+  auto item = [&](int it, int end) -> Piece {
     const int at = it < n_items ? it : n_items - 1;
     const int jm = __builtin_amdgcn_readfirstlane(pieces == 1 ? at : (int)(((u64)(u32)at * recip) >> 32));
     const int slot = __builtin_amdgcn_readfirstlane((int)sm.assign[jm]);
     const u32 page = (u32)__builtin_amdgcn_readfirstlane((int)(sm.miss[jm] & 0xffffu));
     Piece x;
-    x.bytes = it < n_items && slot != kAbsent ? a.page_bytes : 0u;
+    x.bytes = it < end && slot != kAbsent ? a.page_bytes : 0u;
     x.src = store_u + (size_t)page * a.page_bytes;
     x.dst = pool_u + (size_t)slot * a.page_bytes;
     x.piece = at - jm * pieces;
     return x;
   };
+  // 64 KiB of a workgroup are on their way at a time; with 48 units and more in a launch 16 (24 over natural slots; in the chain's
+  // workgroups of 1024 threads 32 and 16).  So many workgroups keep the link busy with less, and with more it is a queue of
+  // megabytes, at whose end they all come at once.  (us per step with misses before the copies by waves, with 64 KiB, and so: 128 units
+  // of 175 pages of 32 tokens, k = 4, 154, 170 and 149, k = 12 344, 354 and 337, 96 of 700 of 8 in two layers 238, 258 and
+  // 231, natural slots, 64 of 300 of 12 in two layers 350, 326 and 316.  With 64 and 16 KiB 4 units of 175 of 32 33.5 and 34.9, 32
+  // 99.0 and 99.0, 64 178 and 176.)  What is beyond is asked for of a buffer without bytes and not stored: loops of their own
+  // for fewer pieces cost the steps without misses 1 % through the code.
   if (layout == kLayoutNatural) {
-    constexpr int kBatch = NT > 512 ? 4 : 8;             // (either way 64 KiB of a workgroup)
-    for (int it = w; it < n_items; it += kBatch * NW) {
+    constexpr int kBatch = NT > 512 ? 4 : 8;
+    const int depth = !a.shallow_fetch ? kBatch : NT > 512 ? 1 : 3;
+    for (int it = w0; it < n_items; it += depth * NW) {
+      const int end = it + depth * NW < n_items ? it + depth * NW : n_items;
       uint4 v[kBatch];
       Piece of[kBatch];
 #pragma unroll
       for (int i = 0; i < kBatch; ++i) {
-        of[i] = item(it + i * NW);
+        of[i] = item(it + i * NW, end);
         v[i] = buffer_load16(of[i].src, of[i].bytes, (u32)of[i].piece * 1024u + (u32)lane * 16u);
       }
 #pragma unroll
-      for (int i = 0; i < kBatch; ++i) buffer_store16<HANDOFF>(of[i].dst, of[i].bytes, (u32)of[i].piece * 1024u + (u32)lane * 16u, v[i]);
+      for (int i = 0; i < kBatch; ++i) {
+        if (it + i * NW >= end) break;
+        buffer_store16<HANDOFF>(of[i].dst, of[i].bytes, (u32)of[i].piece * 1024u + (u32)lane * 16u, v[i]);
+      }
     }
   } else {
     constexpr int kBatch = NT > 512 ? 2 : 4;
+    const int depth = !a.shallow_fetch ? kBatch : 1;
     const int tile_tokens = layout == kLayoutTiles ? kTileTokens : a.P;
     uint16_t* vt = &sm.a.vt[w][0];
-    for (int it = w; it < n_items; it += kBatch * NW) {
+    for (int it = w0; it < n_items; it += depth * NW) {
+      const int end = it + depth * NW < n_items ? it + depth * NW : n_items;
       PageGroup g[kBatch];
       Piece of[kBatch];
 #pragma unroll
       for (int i = 0; i < kBatch; ++i) {
-        of[i] = item(it + i * NW);
+        of[i] = item(it + i * NW, end);
         page_group_load(of[i].src, of[i].bytes, a.P, of[i].piece, g[i]);
       }
 #pragma unroll
-      for (int i = 0; i < kBatch; ++i) page_group_store<HANDOFF>(of[i].dst, of[i].bytes, tile_tokens, of[i].piece, vt, g[i]);
+      for (int i = 0; i < kBatch; ++i) {
+        if (it + i * NW >= end) break;
+        page_group_store<HANDOFF>(of[i].dst, of[i].bytes, tile_tokens, of[i].piece, vt, g[i]);
+      }
     }
   }
   publish_misses();

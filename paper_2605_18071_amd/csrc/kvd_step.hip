@@ -150,7 +150,7 @@ hipError_t kvd_launch_step(kvd_ctx* c, int layer, int n_layers, int step, const 
   a.q = reinterpret_cast<const uint16_t*>(q);
   a.scores = c->d_scores;
   a.fa = kvd_fast_args(c, layer, step, true, c->d_scores, c->d_sel_pages, c->d_sel_slots, c->d_hit_mask, c->d_evicted,
-                       c->d_counts, 0);
+                       c->d_counts, 0, n_layers);
   a.at = kvd_attn_args(c, layer, q, c->d_sel_pages, c->d_sel_slots, out, lse, 0);
   a.at.fuse_merge = 1;
   a.at.sel_entry = c->d_sel_entry;

@@ -15,21 +15,25 @@ if torch.cuda.is_available():
 
 
 # Pieces of a page: half its tokens, rounded up, in natural order (1 KiB each), else a quarter.  A workgroup has 64 (natural) or 32
-# of them on their way at a time.
+# of them on their way at a time; with 48 units and more 24 (in the chain 16) and 8 (16).
+@pytest.mark.parametrize("batch", [1, 23, 24])
 @pytest.mark.parametrize("mb", [0, 1], ids=["one-launch", "chain"])
 @pytest.mark.parametrize("page,ks", [
     (1, [1, 7, 8, 9, 63, 64, 65, 129]),                   # a piece that is half there
     (2, [64, 65]),
     (3, [4, 31, 32, 33]),                                 # ... behind one that is
+    (15, [1, 2, 3, 4]),                                   # 8 pieces a page
     (254, [1]), (255, [1, 2]),
     (4, [1, 7, 8, 9, 31, 32, 33, 65]),
     (8, [16, 17]),
     (16, [1, 7, 8, 9, 17]),
     (48, [2, 3]), (256, [1, 2]),
 ])
-def test_pages_of_any_number_of_pieces(page, ks, mb):
+def test_pages_of_any_number_of_pieces(page, ks, mb, batch):
     for k in ks:
-        w = small("pieces", page=page, ctx=page * (k + 3), topk_pages=k, capacity=k + 2, batch=1, n_kv_heads=2, n_q_heads=4, heavy_count=0,
+        if batch * 2 * (k + 3) * page > 60_000:
+            continue
+        w = small("pieces", page=page, ctx=page * (k + 3), topk_pages=k, capacity=k + 2, batch=batch, n_kv_heads=2, n_q_heads=4, heavy_count=0,
                   steps=1, seed=10 * page + k)
         rig = R.Rig(w, micro_batches=mb)
         rig.pool.view(torch.int16).fill_(0x2a55)
@@ -39,10 +43,11 @@ def test_pages_of_any_number_of_pieces(page, ks, mb):
         for u in range(w.units):
             pages, slots = rig.n_sel_pages[u], rig.n_sel_slots[u]
             assert sorted(slots.tolist()) == list(range(k))
+            pool, store = rig.pool[0].flatten(0, 1)[u].cpu(), rig.store[0].flatten(0, 1)[u]
             for s in range(w.capacity):
-                got = rig.pool[0, 0, u, s].cpu().view(torch.int16).reshape(-1)
+                got = pool[s].view(torch.int16).reshape(-1)
                 if s in slots:
-                    assert torch.equal(got, H.slot_image(rig.store[0, 0, u, int(pages[list(slots).index(s)])])), (k, u, s)
+                    assert torch.equal(got, H.slot_image(store[int(pages[list(slots).index(s)])])), (k, u, s)
                 else:                                     # a slot that no page went to
                     assert bool((got == 0x2a55).all()), (k, u, s)
         rig.close()
