@@ -1346,48 +1346,50 @@ __device__ __forceinline__ bool select_resolve_body(const FastArgs& a, int u, Fa
     x.piece = at - jm * pieces;
     return x;
   };
-  // 64 KiB of a workgroup are on their way at a time; with 48 units and more in a launch 16 (24 over natural slots; in the chain's
-  // workgroups of 1024 threads 32 and 16).  So many workgroups keep the link busy with less, and with more it is a queue of
-  // megabytes, at whose end they all come at once.  (us per step with misses before the copies by waves, with 64 KiB, and so: 128 units
-  // of 175 pages of 32 tokens, k = 4, 154, 170 and 149, k = 12 344, 354 and 337, 96 of 700 of 8 in two layers 238, 258 and
-  // 231, natural slots, 64 of 300 of 12 in two layers 350, 326 and 316.  With 64 and 16 KiB 4 units of 175 of 32 33.5 and 34.9, 32
-  // 99.0 and 99.0, 64 178 and 176.)  What is beyond is asked for of a buffer without bytes and not stored: loops of their own
-  // for fewer pieces cost the steps without misses 1 % through the code.
+  // 64 KiB of a workgroup are on their way at a time; with 48 units and more in a launch 16 (24 over natural slots).  So many
+  // workgroups keep the link busy with less, and with more it is a queue of megabytes, at whose end they all come at once.  (us per step
+  // with misses before the copies by waves, with 64 KiB, and so: 128 units of 175 pages of 32 tokens, k = 4, 154, 170 and 149,
+  // k = 12 344, 354 and 337, 96 of 700 of 8 in two layers 238, 258 and 231, natural slots, 64 of 300 of 12 in two layers 350,
+  // 326 and 316; as a chain 128 of 175, k = 12, of 16 192, 201 and 183, of 12 146, 163 and 143.  With 64 and 16 KiB 4 units of 175
+  // of 32 33.5 and 34.9, 32 99.0 and 99.0, 64 178 and 176.)  With 512 threads every wave has fewer pieces, and those beyond are
+  // asked for of a buffer without bytes and not stored (loops of their own cost the steps without misses 1 % through the code); with 1024
+  // every fourth wave has all of its pieces, which is faster there (183 above with the other way 190).
+  const int waves = NT > 512 && a.shallow_fetch ? NW / 4 : NW;
   if (layout == kLayoutNatural) {
     constexpr int kBatch = NT > 512 ? 4 : 8;
-    const int depth = !a.shallow_fetch ? kBatch : NT > 512 ? 1 : 3;
-    for (int it = w0; it < n_items; it += depth * NW) {
-      const int end = it + depth * NW < n_items ? it + depth * NW : n_items;
+    const int depth = NT <= 512 && a.shallow_fetch ? 3 : kBatch;
+    for (int it = w0 < waves ? w0 : n_items; it < n_items; it += depth * waves) {
+      const int end = NT <= 512 && it + depth * NW < n_items ? it + depth * NW : n_items;
       uint4 v[kBatch];
       Piece of[kBatch];
 #pragma unroll
       for (int i = 0; i < kBatch; ++i) {
-        of[i] = item(it + i * NW, end);
+        of[i] = item(it + i * waves, end);
         v[i] = buffer_load16(of[i].src, of[i].bytes, (u32)of[i].piece * 1024u + (u32)lane * 16u);
       }
 #pragma unroll
       for (int i = 0; i < kBatch; ++i) {
-        if (it + i * NW >= end) break;
+        if (NT <= 512 && it + i * NW >= end) break;
         buffer_store16<HANDOFF>(of[i].dst, of[i].bytes, (u32)of[i].piece * 1024u + (u32)lane * 16u, v[i]);
       }
     }
   } else {
     constexpr int kBatch = NT > 512 ? 2 : 4;
-    const int depth = !a.shallow_fetch ? kBatch : 1;
+    const int depth = NT <= 512 && a.shallow_fetch ? 1 : kBatch;
     const int tile_tokens = layout == kLayoutTiles ? kTileTokens : a.P;
     uint16_t* vt = &sm.a.vt[w][0];
-    for (int it = w0; it < n_items; it += depth * NW) {
-      const int end = it + depth * NW < n_items ? it + depth * NW : n_items;
+    for (int it = w0 < waves ? w0 : n_items; it < n_items; it += depth * waves) {
+      const int end = NT <= 512 && it + depth * NW < n_items ? it + depth * NW : n_items;
       PageGroup g[kBatch];
       Piece of[kBatch];
 #pragma unroll
       for (int i = 0; i < kBatch; ++i) {
-        of[i] = item(it + i * NW, end);
+        of[i] = item(it + i * waves, end);
         page_group_load(of[i].src, of[i].bytes, a.P, of[i].piece, g[i]);
       }
 #pragma unroll
       for (int i = 0; i < kBatch; ++i) {
-        if (it + i * NW >= end) break;
+        if (NT <= 512 && it + i * NW >= end) break;
         page_group_store<HANDOFF>(of[i].dst, of[i].bytes, tile_tokens, of[i].piece, vt, g[i]);
       }
     }
