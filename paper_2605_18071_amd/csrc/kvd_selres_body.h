@@ -1320,9 +1320,9 @@ __device__ __forceinline__ bool select_resolve_body(const FastArgs& a, int u, Fa
   // link, which takes 150 KB on their way to be busy (read by 8 workgroups 25 GB/s with 8 KiB of each on their way, 54 with
   // 32; 16 workgroups 56), and for few units by its latency.  (us per step with misses, with tiles of 256 threads, two
   // barriers and 16 KiB on their way, and so, the victim choice above included: 4 units of 1024 pages of 64 tokens 56.2 and 43.3,
-  // 8 of 750 of 16 46.1 and 38.4, 8 of 4096 of 4 54.8 and 47.0, 64 of 2048 of 16 236.5 and 229.8, 32 of 8192 of 16 284.8 and
-  // 274.1.  The code is met cold, so less of it is faster: with a second batch on its way while the first is stored, which is
-  // five copies of the unrolled loops instead of two, these were 44.6, 41.0, 49.2, 233.3 and 277.5.)
+  // 8 of 750 of 16 46.1 and 38.4, 8 of 4096 of 4 54.8 and 47.0, 32 of 8192 of 16 284.8 and 274.1.  The code is met cold, so less
+  // of it is faster: with a second batch on its way while the first is stored, which is five copies of the unrolled loops instead of
+  // two, these were 44.6, 41.0, 49.2 and 277.5.)
   __syncthreads();                                     // everyone is done with sm.a.sel
   const char* store_u = a.store + (size_t)u * a.NP * a.page_bytes;
   char* pool_u = a.pool + (size_t)u * a.Cmax * a.page_bytes;
